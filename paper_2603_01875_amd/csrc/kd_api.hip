@@ -95,17 +95,24 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   q.prep_ht = q.prep_hs = 1;
   q.T_pad = (int)round_up(q.T, kd::kTileN);
   q.n_tt = q.T_pad / kd::kTileN;
-  q.n_vt = (int)((q.V + kd::kTileM - 1) / kd::kTileM);
+  // The strip loop takes bf16 operands with [V][K] heads (in place or re-packed) and more than one token tile.  It
+  // reads the hidden states from a packed copy, so they are re-packed whether a mask is given or not.  With a single
+  // token tile the heads stream through once, nothing is shared, and the smaller tiles of the eight-wave loop spread
+  // better over the CUs: a step at T = 256 takes 1.16 ms there, 1.24 ms with strips; at T = 512 strips are ahead.
+  q.strip = !q.t_fp8 && !q.w_hv_inplace && q.n_tt > 1;
+  q.parts = q.strip ? 1 : 4;
+  q.n_vt = (q.V + kd::kTileM - 1) / kd::kTileM;
   // Vocabulary splits of the statistics passes.  The device picks the actual number once it knows
-  // how many token tiles survive the mask (about n_cu / tiles, at least 8 so that the 32 workgroups
-  // co-resident on an XCD form a 4 x 8 block); this is the upper bound the buffers are sized for:
-  // enough to keep every CU busy with up to half of the tokens masked.
+  // how many token tiles survive the mask; this is the upper bound the buffers are sized for:
+  // enough to keep every CU busy with up to half of the tokens masked, and to even out the rounds
+  // of workgroups where there are many token tiles.
   int ns = 2 * ((q.n_cu + q.n_tt - 1) / q.n_tt);
-  if (ns < 8) ns = 8;
+  if (ns < 32) ns = 32;
   if (ns > q.n_cu) ns = q.n_cu;          // a single token tile is split over all CUs
-  if (ns > q.n_vt) ns = q.n_vt;
-  if (ns < 1) ns = 1;
-  q.n_split = ns;
+  const int tiles_8w = (q.V + kd::kTileM - 1) / kd::kTileM, strips = (q.V + 63) / 64;   // shortest worthwhile ranges
+  const int split_room = ns < tiles_8w ? ns : tiles_8w;   // in fours of parts: covers the strip loop's ranges, too
+  q.n_split = !q.strip ? split_room : ns < strips ? ns : strips;
+  q.g_split = q.n_split;        // (bounded by the chunk's rows where it is used)
 
   // vocabulary chunk of the backward pass: a power of two.  The [T_pad, V_c] bf16 staging buffer of
   // dL/dz_s is written by the gradient kernel and read back by both products, so it should stay within
@@ -140,12 +147,14 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   L.rowmap = take((size_t)q.T_pad * 4);
   L.inv = take((size_t)q.T * 4);
   L.row_loss = take((size_t)q.T_pad * 4);
-  // partial sums per (vocabulary split, quarter of a workgroup, token): 5 statistics, 6 for AKL, whose
-  // search passes keep one sum per threshold
+  // partial sums per (vocabulary split, part of a workgroup, token): 5 statistics, 6 for AKL, whose
+  // search passes keep one sum per threshold.  Sized for the loop with more parts and longer copies, so that the
+  // workspace does not depend on the order in which the heads are stored
   const int part_vals = q.kind == KD_AKL ? kd::kAklThresholds : 5;
-  L.partials = take((size_t)q.n_split * 4 * part_vals * q.T_pad * 4);
+  L.partials = take((size_t)split_room * 4 * part_vals * q.T_pad * 4);
   L.prep_h_t = L.prep_W_t = L.prep_h_s = L.prep_W_s = 0;
-  if (q.prep_hs) L.prep_h_s = take((size_t)q.T * q.K_s * 2);
+  const size_t h_rows = q.T_pad;
+  if (q.prep_hs) L.prep_h_s = take(h_rows * q.K_s * 2);
   if (q.prep_Ws) L.prep_W_s = take((size_t)q.V * q.K_s * 2);
   if (with_backward) {
     L.h_sT = take((size_t)q.H_s * q.T_pad * 2);
@@ -161,7 +170,7 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   L.rowinfo = take((size_t)q.T_pad * 16);
   L.akl = q.kind == KD_AKL ? take((size_t)q.T_pad * 6 * 4) : 0;
   const size_t t_es = q.t_fp8 ? 1 : 2;
-  if (q.prep_ht) L.prep_h_t = take((size_t)q.T * q.K_t * t_es);
+  if (q.prep_ht) L.prep_h_t = take(h_rows * q.K_t * t_es);
   if (q.prep_Wt) L.prep_W_t = take((size_t)q.V * q.K_t * t_es);
   L.total = off;
 }
@@ -179,8 +188,8 @@ void carve(Problem& q, const Layout& L, void* ws) {
   q.dz = b + L.dz;
   q.gh32 = reinterpret_cast<float*>(b + L.gh32);
   q.user_h_t = q.h_t; q.user_W_t = q.W_t; q.user_h_s = q.h_s; q.user_W_s = q.W_s;
-  // without a mask the hidden states are used in place unless they need re-packing anyway
-  if (!q.mask) {
+  // without a mask the eight-wave loop uses the hidden states in place unless they need re-packing anyway
+  if (!q.mask && !q.strip) {
     q.prep_ht = q.prep_Wt;
     q.prep_hs = q.prep_Ws;
   }
@@ -239,16 +248,21 @@ struct ProfileScope {
 // Re-pack the operands that need it (fp32 split / K padding / compaction) into the workspace.
 kd_status prepare_operands(const Problem& q, hipStream_t st, bool student, bool teacher) {
   const int* map = q.mask ? q.rowmap : nullptr;     // gather valid tokens to the front
-  if (teacher && q.prep_ht && q.t_fp8)     // rows of H_t bytes are gathered as rows of H_t / 2 two-byte words
-    KD_TRY(kd::launch_prepare(q.user_h_t, 0, q.T, q.H_t / 2, const_cast<void*>(q.h_t), q.K_t / 2, 2, map, q.meta, 0, st));
-  else if (teacher && q.prep_ht)
-    KD_TRY(kd::launch_prepare(q.user_h_t, q.in_f32, q.T, q.H_t, const_cast<void*>(q.h_t), q.K_t, 2, map, q.meta, 0, st));
+  if (q.strip) {
+    if (teacher) KD_TRY(kd::launch_pack_rows(q, q.user_h_t, q.H_t, const_cast<void*>(q.h_t), q.K_t, st));
+    if (student) KD_TRY(kd::launch_pack_rows(q, q.user_h_s, q.H_s, const_cast<void*>(q.h_s), q.K_s, st));
+  } else {
+    if (teacher && q.prep_ht && q.t_fp8)     // rows of H_t bytes are gathered as rows of H_t / 2 two-byte words
+      KD_TRY(kd::launch_prepare(q.user_h_t, 0, q.T, q.H_t / 2, const_cast<void*>(q.h_t), q.K_t / 2, 2, map, q.meta, 0, st));
+    else if (teacher && q.prep_ht)
+      KD_TRY(kd::launch_prepare(q.user_h_t, q.in_f32, q.T, q.H_t, const_cast<void*>(q.h_t), q.K_t, 2, map, q.meta, 0, st));
+    if (student && q.prep_hs)
+      KD_TRY(kd::launch_prepare(q.user_h_s, q.in_f32, q.T, q.H_s, const_cast<void*>(q.h_s), q.K_s, 2, map, q.meta, 0, st));
+  }
   if (teacher && q.prep_Wt && q.t_fp8)      // only ever an [H][V] head of e4m3 bytes: transposed copy
-    KD_TRY(kd::launch_transpose(q.user_W_t, q.V, q.H_t, q.V, const_cast<void*>(q.W_t), q.K_t, q.K_t, 1, st));
+    KD_TRY(kd::launch_transpose_bytes(q.user_W_t, q.V, q.H_t, q.V, const_cast<void*>(q.W_t), q.K_t, q.K_t, st));
   else if (teacher && q.prep_Wt)
     KD_TRY(kd::launch_prepare(q.user_W_t, q.in_f32, q.V, q.H_t, const_cast<void*>(q.W_t), q.K_t, 1, nullptr, q.meta, q.w_hv, st));
-  if (student && q.prep_hs)
-    KD_TRY(kd::launch_prepare(q.user_h_s, q.in_f32, q.T, q.H_s, const_cast<void*>(q.h_s), q.K_s, 2, map, q.meta, 0, st));
   if (student && q.prep_Ws)
     KD_TRY(kd::launch_prepare(q.user_W_s, q.in_f32, q.V, q.H_s, const_cast<void*>(q.W_s), q.K_s, 1, nullptr, q.meta, q.w_hv, st));
   return KD_OK;
@@ -294,7 +308,7 @@ kd_status run_forward(const Problem& q, hipStream_t st, bool first_teacher = tru
 kd_status run_backward(const Problem* qs, int n_teachers, hipStream_t st) {
   const Problem& q = qs[0];          // everything on the student side is the same for all teachers
   // h_s^T [H_s][T_pad] once (token axis zero-padded): the K-contiguous operand of grad_W_s
-  KD_TRY(kd::launch_transpose(q.h_s, q.K_s, q.T, q.H_s, q.h_sT, q.T_pad, q.T_pad, 2, st));
+  KD_TRY(kd::launch_transpose_rows(q, st));
 
   const size_t gsz = q.grad_f32 ? 4 : 2;
   bool first = true;

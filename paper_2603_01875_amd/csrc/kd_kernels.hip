@@ -14,6 +14,7 @@
 //   gradh_finish : fp32 partial sums -> grad_h_s
 // All logarithms inside the kernels are base 2: a = z * log2(e)/tau.
 #include "kd_mfma.hpp"
+#include "kd_strip.hpp"
 #include "kd_launch.h"
 
 #include <atomic>
@@ -67,7 +68,10 @@ __device__ __forceinline__ int xcd_logical_id(int b, int G) {
 
 // Device-side plan, written by rowmap_kernel once the mask has been counted (the host never
 // learns how many tokens are valid, so everything that depends on it is decided on the device).
-enum { META_N_VALID = 0, META_N_TT = 1, META_N_SPLIT = 2, META_BA = 3, META_BB = 4, META_T_EFF = 5, META_WORDS = 8 };
+// META_N_SPLIT: vocabulary ranges per token tile in the statistics passes; META_G_SPLIT, META_G_SPLIT_LAST: in the
+// gradient kernel, for a full chunk and for the last one (strip loop).
+enum { META_N_VALID = 0, META_N_TT = 1, META_N_SPLIT = 2, META_T_EFF = 3, META_G_SPLIT = 4, META_G_SPLIT_LAST = 5,
+       META_WORDS = 6 };
 __device__ __forceinline__ int meta_get(const int* meta, int i) { return uniform(meta[i]); }
 
 // Index q over an (na x nb) grid walked in (ba x bb) blocks, a fastest inside a block.
@@ -79,13 +83,28 @@ __device__ __forceinline__ void block_decode(int q, int na, int ba, int bb, int&
   b = (blk / nblk_a) * bb + w / ba;
 }
 
+// Index q over n_tt token tiles x n_split vocabulary splits: the token tiles in groups of at most four (of sizes
+// that differ by one where four does not divide them), a group's splits one after the other.  32 consecutive
+// indices, the workgroups of an XCD, then cover 4 x 8: the shape that streams the fewest rows into one L2.
+__device__ __forceinline__ void group_decode(int q, int n_tt, int n_split, int& tt, int& split) {
+  const int ng = (n_tt + 3) / 4, small = n_tt / ng, n_big = n_tt - small * ng;
+  const int big_units = n_big * (small + 1) * n_split;
+  int g = small, base = 0;
+  if (q < big_units) g = small + 1;
+  else { q -= big_units; base = n_big * (small + 1); }
+  const int grp = q / (g * n_split), w = q - grp * g * n_split;
+  tt = base + grp * g + w % g;
+  split = w / g;
+}
+
 struct LogitArgs {
   const bf16_t* W_s; const bf16_t* h_s; const bf16_t* W_t; const bf16_t* h_t;
   int T, V, H_s, H_t;  // H_*: contraction length and row stride of the (re-packed) operands
                        // (heads in [H][V] order: their row stride is V)
-  const int* meta;     // device-side plan: valid tokens, token tiles, vocabulary splits, block shape
-  int vt0, n_vt;       // vocabulary tiles [vt0, vt0 + n_vt) of BM rows handled by this launch
-  int bb;              // grad kernel: block width of the work map along the vocabulary (bb | n_vt).
+  const int* meta;     // device-side plan: valid tokens, token tiles, vocabulary splits
+  int v0, v_end;       // vocabulary rows [v0, v_end) handled by this launch
+  int n_vt;            // ... in this many tiles
+  int bb;              // grad kernel, eight-wave loop: block width of the work map along the vocabulary (bb | n_vt).
                        // An XCD's 32 workgroups cover 2 token tiles x 16 vocabulary tiles where the
                        // counts allow: measured 2-3 % faster than 4 x 8 for this kernel (1 x 32 and
                        // 8 x 4 are slower), while the statistics kernels do not care
@@ -93,11 +112,12 @@ struct LogitArgs {
   float beta;
   float t_scale;       // fp8 teacher: z_t = t_scale * (product of the e4m3 codes); 1 otherwise
   int T_pad;
-  float* partials;     // stats: [n_split*4][5][T_pad];  jsd: [n_split*4][2][T_pad]
+  float* partials;     // stats: [parts][5][T_pad];  jsd: [parts][2][T_pad]
   const f32x4* rowinfo;// [T_pad]: {lse2_t, lse2_s, mask/(n tau), row term}
   const float* akl;    // AKL only: [AKL_ROWS][T_pad] per-token values (see the AKL_* indices)
   bf16_t* dz;          // [T_pad][ldz]   chunk of dL/dz_s, vocabulary contiguous
   int ldz;
+  int last_chunk;      // this launch handles the last chunk of the vocabulary
   int dz_accumulate;   // add to dz instead of overwriting it (further teachers of a multi-teacher call)
   long long* clock_out;// measurement aid (may be null): workgroup 0 of the statistics kernel stores the shader
                        // cycles and the 100 MHz ticks its tile loop took
@@ -108,18 +128,19 @@ struct LogitArgs {
 template <bool TF8, bool WHV>
 __device__ __forceinline__ WorkItem logit_item(const LogitArgs& a, int vt, int tt) {
   WorkItem it;
+  const int m0 = a.v0 + vt * BM;
   it.B0 = a.h_s + (int64_t)tt * BN * a.H_s;
   if (WHV) {
-    it.A0 = a.W_s + vt * BM;
-    it.A1 = a.W_t + vt * BM;
+    it.A0 = a.W_s + m0;
+    it.A1 = a.W_t + m0;
     it.B1 = a.h_t + (int64_t)tt * BN * a.H_t;
   } else if (TF8) {
-    it.A0 = a.W_s + (int64_t)vt * BM * a.H_s;
-    it.A1 = (const bf16_t*)((const char*)a.W_t + (int64_t)vt * BM * a.H_t);
+    it.A0 = a.W_s + (int64_t)m0 * a.H_s;
+    it.A1 = (const bf16_t*)((const char*)a.W_t + (int64_t)m0 * a.H_t);
     it.B1 = (const bf16_t*)((const char*)a.h_t + (int64_t)tt * BN * a.H_t);
   } else {
-    it.A0 = a.W_s + (int64_t)vt * BM * a.H_s;
-    it.A1 = a.W_t + (int64_t)vt * BM * a.H_t;
+    it.A0 = a.W_s + (int64_t)m0 * a.H_s;
+    it.A1 = a.W_t + (int64_t)m0 * a.H_t;
     it.B1 = a.h_t + (int64_t)tt * BN * a.H_t;
   }
 #if KD_ABLATE & 1
@@ -129,55 +150,97 @@ __device__ __forceinline__ WorkItem logit_item(const LogitArgs& a, int vt, int t
   }
 #endif
   it.ka_rows = it.kb_rows = 1 << 30;       // hidden sizes are whole k-steps: no k-row is ever missing
-  it.a_rows = min(BM, a.V - vt * BM);
+  it.a_rows = min(BM, a.v_end - m0);
   it.b_rows = min(BN, a.T - tt * BN);
   it.nk0 = a.H_s / BK;
   it.nk1 = a.H_t / (TF8 ? 2 * BK : BK);
-  it.m0 = vt * BM;
+  it.m0 = m0;
   it.n0 = tt * BN;
   it.aux = 0;
   return it;
 }
 
 // One workgroup = one (token tile, vocabulary split); it walks the split's tiles in order.
-template <bool TF8, bool WHV>
-struct SplitWork {
+struct SplitMap {
   const LogitArgs& a;
   int tt, split, lo, cnt;
-  __device__ SplitWork(const LogitArgs& a_) : a(a_) {
+  __device__ SplitMap(const LogitArgs& a_) : a(a_) {
     const int n_tt = meta_get(a.meta, META_N_TT), n_split = meta_get(a.meta, META_N_SPLIT);
     const int active = n_tt * n_split;               // the grid is sized for the unmasked worst case
     tt = split = lo = cnt = 0;
     if ((int)blockIdx.x >= active) return;
-    const int L = xcd_logical_id(blockIdx.x, active);
-    block_decode(L, n_tt, meta_get(a.meta, META_BA), meta_get(a.meta, META_BB), tt, split);
+    group_decode(xcd_logical_id(blockIdx.x, active), n_tt, n_split, tt, split);
     lo = (int)(((int64_t)split * a.n_vt) / n_split);
     const int hi = (int)(((int64_t)(split + 1) * a.n_vt) / n_split);
     cnt = hi - lo;
   }
   __device__ int n_items() const { return cnt; }
-  __device__ WorkItem item(int i) const { return logit_item<TF8, WHV>(a, a.vt0 + lo + i, tt); }
+};
+template <bool TF8, bool WHV>
+struct SplitWork : SplitMap {
+  using SplitMap::SplitMap;
+  __device__ WorkItem item(int i) const { return logit_item<TF8, WHV>(a, lo + i, tt); }
 };
 
-// The same split of the work, teacher product only (one accumulator): the AKL threshold search.
-template <bool WHV>
-struct TeacherSplitWork {
+// The strip loop's share of a workgroup.  With n_split > 0: one (token tile, vocabulary range), the ranges in units
+// of 64 rows, walked in tiles of three units and a rest.  With n_split == 0: the (token tile x 192-row tile) grid,
+// four token tiles at a time, strided over kNumCU persistent workgroups (which evens out better where few tiles per
+// workgroup meet an awkward number of token tiles: 29 x 43 tiles in five rounds, not six).
+struct StripWork {
   const LogitArgs& a;
-  int tt, split, lo, cnt;
-  __device__ TeacherSplitWork(const LogitArgs& a_) : a(a_) {
-    const int n_tt = meta_get(a.meta, META_N_TT), n_split = meta_get(a.meta, META_N_SPLIT);
-    const int active = n_tt * n_split;
-    tt = split = lo = cnt = 0;
+  int n_tt, tt, split, row0, row1, cnt, L, G, n_vt;
+  __device__ StripWork(const LogitArgs& a_, int n_split) : a(a_) {
+    n_tt = meta_get(a.meta, META_N_TT);
+    tt = split = row0 = row1 = cnt = L = n_vt = 0;
+    G = 1;
+    if (n_split == 0) {
+      G = min((int)gridDim.x, kNumCU);
+      n_vt = (a.v_end - a.v0 + StripCfg::BM - 1) / StripCfg::BM;
+      if ((int)blockIdx.x >= G) return;
+      L = xcd_logical_id(blockIdx.x, G);
+      cnt = L < n_tt * n_vt ? (n_tt * n_vt - L + G - 1) / G : 0;
+      return;
+    }
+    const int active = n_tt * n_split;               // the grid is sized for the unmasked worst case
     if ((int)blockIdx.x >= active) return;
-    const int L = xcd_logical_id(blockIdx.x, active);
-    block_decode(L, n_tt, meta_get(a.meta, META_BA), meta_get(a.meta, META_BB), tt, split);
-    lo = (int)(((int64_t)split * a.n_vt) / n_split);
-    const int hi = (int)(((int64_t)(split + 1) * a.n_vt) / n_split);
-    cnt = hi - lo;
+    group_decode(xcd_logical_id(blockIdx.x, active), n_tt, n_split, tt, split);
+    const int units = (a.v_end - a.v0 + 63) / 64;
+    row0 = a.v0 + 64 * (int)(((int64_t)split * units) / n_split);
+    row1 = min(a.v_end, a.v0 + 64 * (int)(((int64_t)(split + 1) * units) / n_split));
+    cnt = (row1 - row0 + StripCfg::BM - 1) / StripCfg::BM;
   }
   __device__ int n_items() const { return cnt; }
+  __device__ StripItem item(int i) const {
+    StripItem it;
+    int m0 = row0 + i * StripCfg::BM, n0 = tt * BN, end = row1;
+    if (n_vt > 0) {
+      const int q = i * G + L, n_four = n_tt / 4, grp = q / (4 * n_vt), w = q - grp * 4 * n_vt;
+      const int g = grp < n_four ? 4 : n_tt - 4 * n_four;
+      const int vt = w / g;
+      n0 = (4 * grp + w - vt * g) * BN;
+      m0 = a.v0 + vt * StripCfg::BM;
+      end = a.v_end;
+    }
+    it.a_rows = min(StripCfg::BM, end - m0);
+    it.out_rows = (it.a_rows + 63) / 64 * 64;        // zeros behind the chunk's last row: the k-steps of grad_h_s are whole
+    it.m0 = m0;
+    it.n0 = n0;
+#if KD_ABLATE & 1
+    m0 = n0 = 0;       // same operand rows for every tile (the tile's coordinates stay its own)
+#endif
+    it.A0 = (const char*)(a.W_s + (int64_t)m0 * a.H_s);
+    it.A1 = (const char*)(a.W_t + (int64_t)m0 * a.H_t);
+    it.B0 = (const char*)(a.h_s + (int64_t)n0 * a.H_s);
+    it.B1 = (const char*)(a.h_t + (int64_t)n0 * a.H_t);
+    return it;
+  }
+};
+// Teacher product only (one accumulator): the AKL threshold search.
+template <bool WHV>
+struct TeacherSplitWork : SplitMap {
+  using SplitMap::SplitMap;
   __device__ WorkItem item(int i) const {
-    WorkItem it = logit_item<false, WHV>(a, a.vt0 + lo + i, tt);
+    WorkItem it = logit_item<false, WHV>(a, lo + i, tt);
     it.A0 = it.A1; it.B0 = it.B1;       // phase 0 is the teacher product
     it.nk0 = it.nk1;
     return it;
@@ -185,11 +248,10 @@ struct TeacherSplitWork {
 };
 
 // Persistent workgroups striding over the (token tile x vocabulary tile) grid of a chunk.
-template <bool TF8, bool WHV>
-struct ChunkWork {
+struct ChunkMap {
   const LogitArgs& a;
   int L, G, n_tiles, n_tt, ba;
-  __device__ ChunkWork(const LogitArgs& a_) : a(a_) {
+  __device__ ChunkMap(const LogitArgs& a_) : a(a_) {
     G = gridDim.x;
     L = xcd_logical_id(blockIdx.x, G);
     n_tt = meta_get(a.meta, META_N_TT);
@@ -198,13 +260,17 @@ struct ChunkWork {
     n_tiles = n_tt * a.n_vt;
   }
   __device__ int n_items() const { return L < n_tiles ? (n_tiles - L + G - 1) / G : 0; }
+  __device__ void tile(int i, int& tt, int& vt) const { block_decode(i * G + L, n_tt, ba, a.bb, tt, vt); }
+};
+template <bool TF8, bool WHV>
+struct ChunkWork : ChunkMap {
+  using ChunkMap::ChunkMap;
   __device__ WorkItem item(int i) const {
     int tt, vt;
-    block_decode(i * G + L, n_tt, ba, a.bb, tt, vt);
-    return logit_item<TF8, WHV>(a, a.vt0 + vt, tt);
+    tile(i, tt, vt);
+    return logit_item<TF8, WHV>(a, vt, tt);
   }
 };
-
 // ------------------------------------------------------------------------------------------
 // epilogues of the logit tiles
 // ------------------------------------------------------------------------------------------
@@ -228,110 +294,201 @@ constexpr float AKL_TOP_EPS = 1.0e-4f;   // entries this close (base-2 log) to t
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float flog2(float x) { return __builtin_amdgcn_logf(x); }
 
-// fp8 teacher: the accumulator holds the product of the e4m3 codes; bring it to logits.
-__device__ __forceinline__ void scale_teacher(AccTile& accT, float ts) {
-  if (ts == 1.f) return;
-#pragma unroll
-  for (int mt = 0; mt < MI; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NI; ++nt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) accT[mt][nt][r] *= ts;
-}
-
-// Rows of A beyond the vocabulary (last tile only) must not contribute: give them a
-// huge negative logit in both accumulators (their exp is 0, their difference is 0).
-__device__ __forceinline__ void mask_tail_rows(const WorkItem& it, AccTile& accS, AccTile& accT,
-                                               int wm, int lane) {
-  if (it.a_rows == BM) return;
-#pragma unroll
-  for (int mt = 0; mt < MI; ++mt)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const bool ok = acc_m(wm, mt, r, lane) < it.a_rows;
-#pragma unroll
-      for (int nt = 0; nt < NI; ++nt) {
-        accS[mt][nt][r] = ok ? accS[mt][nt][r] : NEG_BIG;
-        accT[mt][nt][r] = ok ? accT[mt][nt][r] : NEG_BIG;
-      }
-    }
-}
-
-// Online log-sum-exp of both models plus the cross term of FKL / RKL.
-//   FKL: X = sum_v 2^(a_t - m_t) (z_t - z_s)      RKL: X = sum_v 2^(a_s - m_s) (z_s - z_t)
-template <int KIND>
-struct StatsEpi {
-  static constexpr int NV = KIND == 6 ? 6 : 5;     // values per token and part (AKL keeps both cross terms)
-  float m_t[NI], S_t[NI], m_s[NI], S_s[NI], X[NI], X2[NI];
-  float c, ts;
+// How a lane sees a finished tile: NC token columns of (up to) NE vocabulary entries each, entry e of the lane's
+// share lying at vocabulary row m(e) of the tile (four consecutive e are four consecutive rows), column j at
+// token n(j).  PARTS partial results per token and vocabulary split leave a workgroup; this lane's is part().
+struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
+  static constexpr int NC = NI, NE = MI * 16, PARTS = 4;
   int wm, wn, lane;
-  __device__ StatsEpi(float c_, float ts_) : c(c_), ts(ts_) {
+  __device__ TileGeo() {
     lane = threadIdx.x & 63;
     wm = (threadIdx.x >> 6) & 1;
     wn = threadIdx.x >> 7;
+  }
+  __device__ __forceinline__ int m(int e) const { return acc_m(wm, e >> 4, e & 15, lane); }
+  __device__ __forceinline__ int n(int j) const { return acc_n(wn, j, lane); }
+  __device__ __forceinline__ int part() const { return wm * 2 + (lane >> 5); }
+  static constexpr int MERGE = 64;                   // lanes of one token merged before they leave: none
+  // o: entries 16 p .. 16 p + 15 of the lane's column; row: the token's row at the tile's first vocabulary entry
+  __device__ __forceinline__ void store(bf16_t* row, int p, bf16x4 (&o)[4], int) const {
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      m_t[nt] = M_FLOOR; m_s[nt] = M_FLOOR; S_t[nt] = 0.f; S_s[nt] = 0.f; X[nt] = 0.f; X2[nt] = 0.f;
+    for (int q = 0; q < 4; ++q) *(bf16x4*)(row + m(16 * p + 4 * q)) = o[q];
+  }
+};
+struct StripGeo {        // 192 x 256 tile of four waves (kd_strip.hpp)
+  static constexpr int NC = StripCfg::NB, NE = StripCfg::MB * 4, PARTS = 1;
+  int wave, lane;
+  __device__ StripGeo() {
+    lane = threadIdx.x & 63;
+    wave = threadIdx.x >> 6;
+  }
+  __device__ __forceinline__ int m(int e) const { return StripCfg::acc_m(e >> 2, e & 3, lane); }
+  __device__ __forceinline__ int n(int j) const { return StripCfg::acc_n(j, lane, wave); }
+  __device__ __forceinline__ int part() const { return 0; }
+  static constexpr int MERGE = 16;                   // lanes 16 and 32 apart hold the same token
+  // Four lanes share a token, each with four rows of every 16-row block: a 4 x 4 transposition of these 8-byte
+  // pieces between them gives each lane 16 rows of one block, so that the wave's stores fill whole 128-byte
+  // lines instead of 32-byte pieces.  rows: those that may be stored, a multiple of 64.
+  __device__ __forceinline__ void store(bf16_t* row, int p, bf16x4 (&o)[4], int rows) const {
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    uint32_t x[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u32x2 w = __builtin_bit_cast(u32x2, o[i]);
+      x[i][0] = w[0]; x[i][1] = w[1];
+    }
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      // (x0, x2), (x1, x3): the upper 32 lanes of the first against the lower 32 of the second; then
+      // (x0, x1), (x2, x3) in the same way by rows of 16 lanes
+      auto r0 = __builtin_amdgcn_permlane32_swap(x[0][d], x[2][d], false, false);
+      auto r1 = __builtin_amdgcn_permlane32_swap(x[1][d], x[3][d], false, false);
+      auto s0 = __builtin_amdgcn_permlane16_swap(r0[0], r1[0], false, false);
+      auto s1 = __builtin_amdgcn_permlane16_swap(r0[1], r1[1], false, false);
+      x[0][d] = s0[0]; x[1][d] = s0[1]; x[2][d] = s1[0]; x[3][d] = s1[1];
+    }
+    if (64 * p < rows) {
+      u32x4* const dst = (u32x4*)(row + 64 * p + 16 * (lane >> 4));
+      dst[0] = u32x4{x[0][0], x[0][1], x[1][0], x[1][1]};
+      dst[1] = u32x4{x[2][0], x[2][1], x[3][0], x[3][1]};
+    }
+    __builtin_amdgcn_sched_barrier(0);       // (or all of a column is computed before anything is stored: spills)
+  }
+};
+
+// Drives an epilogue (template on the geometry, one column at a time) from tile_loop.
+template <class Epi>
+struct TileEpi {
+  Epi& epi;
+  float ts;
+  __device__ TileEpi(Epi& e, float t_scale) : epi(e), ts(t_scale) {}
+  __device__ void begin_item(const WorkItem& it) { epi.begin_item(it.m0, it.n0, BM); }
+  __device__ void end_item(const WorkItem& it, AccTile& accS, AccTile& accT) {
+    if (ts != 1.f) {     // fp8 teacher: the accumulator holds the product of the e4m3 codes; bring it to logits
+#pragma unroll
+      for (int mt = 0; mt < MI; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NI; ++nt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) accT[mt][nt][r] *= ts;
+    }
+    // Rows of A beyond the vocabulary (last tile only) must not contribute: give them a huge negative logit in
+    // both accumulators (their exp is 0, their difference is 0).
+    if (it.a_rows != BM) {
+#pragma unroll
+      for (int mt = 0; mt < MI; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool ok = epi.geo.m(16 * mt + r) < it.a_rows;
+#pragma unroll
+          for (int nt = 0; nt < NI; ++nt) {
+            accS[mt][nt][r] = ok ? accS[mt][nt][r] : NEG_BIG;
+            accT[mt][nt][r] = ok ? accT[mt][nt][r] : NEG_BIG;
+          }
+        }
+    }
+    static_for<0, NI>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      float S[TileGeo::NE], T[TileGeo::NE];
+#pragma unroll
+      for (int mt = 0; mt < MI; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { S[16 * mt + r] = accS[mt][j][r]; T[16 * mt + r] = accT[mt][j][r]; }
+      epi.column(jc, S, T);
+    });
+  }
+};
+// ... and from strip_loop.
+template <class Epi>
+struct StripEpi {
+  Epi& epi;
+  __device__ StripEpi(Epi& e) : epi(e) {}
+  __device__ void begin_item(const StripItem& it) { epi.begin_item(it.m0, it.n0, it.out_rows); }
+  __device__ float pad(int) const { return NEG_BIG; }
+  template <class J, int NM>
+  __device__ __forceinline__ void column(const StripItem&, J jc, f32x4 (&S4)[NM], f32x4 (&T4)[NM]) {
+    float S[4 * NM], T[4 * NM];
+#pragma unroll
+    for (int e = 0; e < 4 * NM; ++e) { S[e] = S4[e >> 2][e & 3]; T[e] = T4[e >> 2][e & 3]; }
+    epi.column(jc, S, T);
+  }
+};
+
+// Online log-sum-exp of both models plus the cross term of FKL / RKL.
+//   FKL: X = sum_v 2^(a_t - m_t) (z_t - z_s)      RKL: X = sum_v 2^(a_s - m_s) (z_s - z_t)
+template <int KIND, class Geo>
+struct StatsEpi {
+  static constexpr int NV = KIND == 6 ? 6 : 5;     // values per token and part (AKL keeps both cross terms)
+  static constexpr int NC = Geo::NC;
+  Geo geo;
+  float m_t[NC], S_t[NC], m_s[NC], S_s[NC], X[NC], X2[NC];
+  float c;
+  __device__ StatsEpi(float c_) : c(c_) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      m_t[j] = M_FLOOR; m_s[j] = M_FLOOR; S_t[j] = 0.f; S_s[j] = 0.f; X[j] = 0.f; X2[j] = 0.f;
     }
   }
-  __device__ void begin_item(const WorkItem&) {}
-  __device__ void end_item(const WorkItem& it, AccTile& accS, AccTile& accT) {
+  __device__ void begin_item(int, int, int) {}
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
 #if KD_ABLATE & 2
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt)
-#pragma unroll
-      for (int mt = 0; mt < MI; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { S_t[nt] += accT[mt][nt][r]; S_s[nt] += accS[mt][nt][r]; }
+    for (int e = 0; e < NE; ++e) { S_t[j] += T[e]; S_s[j] += S[e]; }
     return;
 #endif
-    scale_teacher(accT, ts);
-    mask_tail_rows(it, accS, accT, wm, lane);
+    float tmax = NEG_BIG, smax = NEG_BIG;
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      float tmax = NEG_BIG, smax = NEG_BIG;
-#pragma unroll
-      for (int mt = 0; mt < MI; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          tmax = fmaxf(tmax, accT[mt][nt][r]);
-          smax = fmaxf(smax, accS[mt][nt][r]);
-        }
-      const float nmt = fmaxf(m_t[nt], tmax * c);
-      const float nms = fmaxf(m_s[nt], smax * c);
-      const float sct = fexp2(m_t[nt] - nmt);
-      const float scs = fexp2(m_s[nt] - nms);
-      float st = S_t[nt] * sct, ss = S_s[nt] * scs;
-      float x = X[nt] * ((KIND == 0 || KIND == 6) ? sct : scs);
-      float x2 = X2[nt] * scs;
-#pragma unroll
-      for (int mt = 0; mt < MI; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float zt = accT[mt][nt][r], zs = accS[mt][nt][r];
-          const float et = fexp2(fmaf(zt, c, -nmt));
-          const float es = fexp2(fmaf(zs, c, -nms));
-          st += et;
-          ss += es;
-          if (KIND == 0 || KIND == 6) x = fmaf(et, zt - zs, x);
-          if (KIND == 1) x = fmaf(es, zs - zt, x);
-          if (KIND == 6) x2 = fmaf(es, zs - zt, x2);
-        }
-      m_t[nt] = nmt; m_s[nt] = nms; S_t[nt] = st; S_s[nt] = ss; X[nt] = x; X2[nt] = x2;
+    for (int e = 0; e < NE; ++e) {
+      tmax = fmaxf(tmax, T[e]);
+      smax = fmaxf(smax, S[e]);
     }
-  }
-  __device__ void write(const LogitArgs& a, int tt, int split) const {
-    const int part = split * 4 + wm * 2 + (lane >> 5);
-    float* p = a.partials + (int64_t)part * NV * a.T_pad;
+    const float nmt = fmaxf(m_t[j], tmax * c);
+    const float nms = fmaxf(m_s[j], smax * c);
+    const float sct = fexp2(m_t[j] - nmt);
+    const float scs = fexp2(m_s[j] - nms);
+    float st = S_t[j] * sct, ss = S_s[j] * scs;
+    float x = X[j] * ((KIND == 0 || KIND == 6) ? sct : scs);
+    float x2 = X2[j] * scs;
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      const int t = tt * BN + acc_n(wn, nt, lane);
-      p[0 * a.T_pad + t] = m_t[nt];
-      p[1 * a.T_pad + t] = S_t[nt];
-      p[2 * a.T_pad + t] = m_s[nt];
-      p[3 * a.T_pad + t] = S_s[nt];
-      p[4 * a.T_pad + t] = X[nt];
-      if (KIND == 6) p[5 * a.T_pad + t] = X2[nt];
+    for (int e = 0; e < NE; ++e) {
+      const float zt = T[e], zs = S[e];
+      const float et = fexp2(fmaf(zt, c, -nmt));
+      const float es = fexp2(fmaf(zs, c, -nms));
+      st += et;
+      ss += es;
+      if (KIND == 0 || KIND == 6) x = fmaf(et, zt - zs, x);
+      if (KIND == 1) x = fmaf(es, zs - zt, x);
+      if (KIND == 6) x2 = fmaf(es, zs - zt, x2);
+    }
+    m_t[j] = nmt; m_s[j] = nms; S_t[j] = st; S_s[j] = ss; X[j] = x; X2[j] = x2;
+  }
+  __device__ void write(const LogitArgs& a, int tt, int split) {
+    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * NV * a.T_pad;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+#pragma unroll
+      for (int off = Geo::MERGE; off < 64; off <<= 1) {      // lanes that hold the same token
+        const float omt = __shfl_xor(m_t[j], off, 64), oms = __shfl_xor(m_s[j], off, 64);
+        const float nmt = fmaxf(m_t[j], omt), nms = fmaxf(m_s[j], oms);
+        const float wt = fexp2(m_t[j] - nmt), ws = fexp2(m_s[j] - nms);
+        const float owt = fexp2(omt - nmt), ows = fexp2(oms - nms);
+        const bool by_t = KIND == 0 || KIND == 6;
+        S_t[j] = fmaf(__shfl_xor(S_t[j], off, 64), owt, S_t[j] * wt);
+        S_s[j] = fmaf(__shfl_xor(S_s[j], off, 64), ows, S_s[j] * ws);
+        X[j] = fmaf(__shfl_xor(X[j], off, 64), by_t ? owt : ows, X[j] * (by_t ? wt : ws));
+        if (KIND == 6) X2[j] = fmaf(__shfl_xor(X2[j], off, 64), ows, X2[j] * ws);
+        m_t[j] = nmt; m_s[j] = nms;
+      }
+      if (geo.lane >= Geo::MERGE) continue;
+      const int t = tt * BN + geo.n(j);
+      p[0 * a.T_pad + t] = m_t[j];
+      p[1 * a.T_pad + t] = S_t[j];
+      p[2 * a.T_pad + t] = m_s[j];
+      p[3 * a.T_pad + t] = S_s[j];
+      p[4 * a.T_pad + t] = X[j];
+      if (KIND == 6) p[5 * a.T_pad + t] = X2[j];
     }
   }
 };
@@ -394,58 +551,56 @@ struct RowTerm {
 
 // AKL (KIND 6) uses the same pass for its gaps:  a1 = sum over the head of |p_t - p_s|,  a2 = the same over
 // the tail, the head being the entries whose teacher log-probability reaches the token's threshold.
-template <int KIND>
+template <int KIND, class Geo>
 struct RowsEpi {
-  float A1[NI], A2[NI], Lt[NI], Ls[NI], Thr[NI];
-  float c, w, ts;
-  int wm, wn, lane;
-  __device__ RowsEpi(const LogitArgs& a, int tt) : c(a.c), w(a.beta), ts(a.t_scale) {
-    lane = threadIdx.x & 63;
-    wm = (threadIdx.x >> 6) & 1;
-    wn = threadIdx.x >> 7;
+  static constexpr int NC = Geo::NC;
+  Geo geo;
+  float A1[NC], A2[NC], Lt[NC], Ls[NC], Thr[NC];
+  float c, w;
+  __device__ RowsEpi(const LogitArgs& a, int tt) : c(a.c), w(a.beta) {
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      const int t = tt * BN + acc_n(wn, nt, lane);
+    for (int j = 0; j < NC; ++j) {
+      const int t = tt * BN + geo.n(j);
       const f32x4 ri = a.rowinfo[t];
-      Lt[nt] = ri[0]; Ls[nt] = ri[1]; A1[nt] = 0.f; A2[nt] = 0.f;
-      Thr[nt] = 0.f;
+      Lt[j] = ri[0]; Ls[j] = ri[1]; A1[j] = 0.f; A2[j] = 0.f;
+      Thr[j] = 0.f;
       if (KIND == 6)    // the top entry is head whatever its mass
-        Thr[nt] = fminf(a.akl[AKL_HI * a.T_pad + t], a.akl[AKL_LTMAX * a.T_pad + t] - AKL_TOP_EPS);
+        Thr[j] = fminf(a.akl[AKL_HI * a.T_pad + t], a.akl[AKL_LTMAX * a.T_pad + t] - AKL_TOP_EPS);
     }
   }
-  __device__ void begin_item(const WorkItem&) {}
-  __device__ void end_item(const WorkItem& it, AccTile& accS, AccTile& accT) {
-    scale_teacher(accT, ts);
-    mask_tail_rows(it, accS, accT, wm, lane);
+  __device__ void begin_item(int, int, int) {}
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+    float a1 = A1[j], a2 = A2[j];
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      float a1 = A1[nt], a2 = A2[nt];
-#pragma unroll
-      for (int mt = 0; mt < MI; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float lt = fmaf(accT[mt][nt][r], c, -Lt[nt]);
-          const float ls = fmaf(accS[mt][nt][r], c, -Ls[nt]);
-          if constexpr (KIND == 6) {
-            const float gap = fabsf(fexp2(lt) - fexp2(ls));
-            const bool head = lt >= Thr[nt];
-            a1 += head ? gap : 0.f;
-            a2 += head ? 0.f : gap;
-          } else {
-            (void)RowTerm<KIND>::template eval<true>(lt, ls, w, a1, a2);
-          }
-        }
-      A1[nt] = a1; A2[nt] = a2;
+    for (int e = 0; e < NE; ++e) {
+      const float lt = fmaf(T[e], c, -Lt[j]);
+      const float ls = fmaf(S[e], c, -Ls[j]);
+      if constexpr (KIND == 6) {
+        const float gap = fabsf(fexp2(lt) - fexp2(ls));
+        const bool head = lt >= Thr[j];
+        a1 += head ? gap : 0.f;
+        a2 += head ? 0.f : gap;
+      } else {
+        (void)RowTerm<KIND>::template eval<true>(lt, ls, w, a1, a2);
+      }
     }
+    A1[j] = a1; A2[j] = a2;
   }
-  __device__ void write(const LogitArgs& a, int tt, int split) const {
-    const int part = split * 4 + wm * 2 + (lane >> 5);
-    float* p = a.partials + (int64_t)part * 2 * a.T_pad;
+  __device__ void write(const LogitArgs& a, int tt, int split) {
+    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * 2 * a.T_pad;
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      const int t = tt * BN + acc_n(wn, nt, lane);
-      p[0 * a.T_pad + t] = A1[nt];
-      p[1 * a.T_pad + t] = A2[nt];
+    for (int j = 0; j < NC; ++j) {
+#pragma unroll
+      for (int off = Geo::MERGE; off < 64; off <<= 1) {
+        A1[j] += __shfl_xor(A1[j], off, 64);
+        A2[j] += __shfl_xor(A2[j], off, 64);
+      }
+      if (geo.lane >= Geo::MERGE) continue;
+      const int t = tt * BN + geo.n(j);
+      p[0 * a.T_pad + t] = A1[j];
+      p[1 * a.T_pad + t] = A2[j];
     }
   }
 };
@@ -456,85 +611,193 @@ struct RowsEpi {
 //   JSD, TVD, skewed KL: dz = s p_s (c - R)  (RowTerm above)
 //   AKL: dz = s (w_f (p_s - p_t) + w_r p_s (ln2 (l_s - l_t) - RKL)) = s (p_s (w_r ln2 (l_s - l_t) + R) - w_f p_t),
 //        R = w_f - w_r RKL, the weights being constants for the gradient
-template <int KIND>
+// Vocabulary entries that do not exist carry the logit NEG_BIG in both models: their dz comes out 0 in every
+// kind, and that is what the chunk buffer holds from its last valid column to the end of a 64-column step.
+template <int KIND, class Geo>
 struct GradEpi {
+  static constexpr int NC = Geo::NC;
+  Geo geo;
   const LogitArgs& a;
-  float Lt[NI], Ls[NI], sc[NI], R[NI], Wr[NI];
-  int wm, wn, lane;
-  __device__ GradEpi(const LogitArgs& a_) : a(a_) {
-    lane = threadIdx.x & 63;
-    wm = (threadIdx.x >> 6) & 1;
-    wn = threadIdx.x >> 7;
-  }
-  __device__ void begin_item(const WorkItem& it) {
+  float Lt[NC], Ls[NC], sc[NC], R[NC], Wr[NC];
+  int m0, n0, out_rows;
+  __device__ GradEpi(const LogitArgs& a_) : a(a_) {}
+  __device__ void begin_item(int m0_, int n0_, int out_rows_) {
+    out_rows = out_rows_;
+    m0 = m0_ - a.v0;                           // vocabulary offset inside the chunk
+    n0 = n0_;
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      const f32x4 ri = a.rowinfo[it.n0 + acc_n(wn, nt, lane)];
-      Lt[nt] = ri[0]; Ls[nt] = ri[1]; sc[nt] = ri[2]; R[nt] = ri[3];
-      Wr[nt] = 0.f;
-      if (KIND == 6) Wr[nt] = a.akl[AKL_WR * a.T_pad + it.n0 + acc_n(wn, nt, lane)];
+    for (int j = 0; j < NC; ++j) {
+      const f32x4 ri = a.rowinfo[n0 + geo.n(j)];
+      Lt[j] = ri[0]; Ls[j] = ri[1]; sc[j] = ri[2]; R[j] = ri[3];
+      Wr[j] = 0.f;
+      if (KIND == 6) Wr[j] = a.akl[AKL_WR * a.T_pad + n0 + geo.n(j)];
     }
   }
-  __device__ void end_item(const WorkItem& it, AccTile& accS, AccTile& accT) {
-    scale_teacher(accT, a.t_scale);
-    const float c = a.c, w = a.beta;
-    const int mloc0 = it.m0 - a.vt0 * BM;      // vocabulary offset inside the chunk
+  template <bool ADD, class J, int NE>
+  __device__ __forceinline__ void emit(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+    const float c = a.c, w = a.beta, s = sc[j];
+    bf16_t* const row = a.dz + (int64_t)(n0 + geo.n(j)) * a.ldz + m0;
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      const int n = it.n0 + acc_n(wn, nt, lane);
-      const float s = sc[nt];
-#pragma unroll
-      for (int mt = 0; mt < MI; ++mt)
+    for (int p = 0; p < NE / 16; ++p) {
+      bf16x4 o[4];
+      if (ADD)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int m = acc_m(wm, mt, 4 * q, lane);
-          const bool ok = m < it.a_rows;
-          bf16x4* const dst = (bf16x4*)(a.dz + (int64_t)n * a.ldz + mloc0 + m);
-          bf16x4 o;
-          if (a.dz_accumulate) o = *dst;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float lt = fmaf(accT[mt][nt][4 * q + i], c, -Lt[nt]);
-            const float ls = fmaf(accS[mt][nt][4 * q + i], c, -Ls[nt]);
-            const float ps = fexp2(ls);
-            float g;
-            if (KIND == 0) {
-              g = ps - fexp2(lt);
-            } else if (KIND == 1) {
-              g = ps * fmaf(LN2, ls - lt, -R[nt]);
-            } else if (KIND == 6) {
-              g = fmaf(ps, fmaf(Wr[nt] * LN2, ls - lt, R[nt]), -(1.f - Wr[nt]) * fexp2(lt));
-            } else {
-              float u1, u2;
-              g = ps * (RowTerm<KIND>::template eval<false>(lt, ls, w, u1, u2) - R[nt]);
-            }
-            const float d = ok ? s * g : 0.f;
-            o[i] = (bf16_t)(a.dz_accumulate ? (float)o[i] + d : d);
-          }
-          *dst = o;
+          const int m = geo.m(16 * p + 4 * q);
+          o[q] = *(const bf16x4*)(row + (m < out_rows ? m : 0));       // (rows that are not stored: any valid address)
         }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float lt = fmaf(T[16 * p + e], c, -Lt[j]);
+        const float ls = fmaf(S[16 * p + e], c, -Ls[j]);
+        const float ps = fexp2(ls);
+        float g;
+        if (KIND == 0) {
+          g = ps - fexp2(lt);
+        } else if (KIND == 1) {
+          g = ps * fmaf(LN2, ls - lt, -R[j]);
+        } else if (KIND == 6) {
+          g = fmaf(ps, fmaf(Wr[j] * LN2, ls - lt, R[j]), -(1.f - Wr[j]) * fexp2(lt));
+        } else {
+          float u1, u2;
+          g = ps * (RowTerm<KIND>::template eval<false>(lt, ls, w, u1, u2) - R[j]);
+        }
+        const float d = s * g;
+        o[e >> 2][e & 3] = (bf16_t)(ADD ? (float)o[e >> 2][e & 3] + d : d);
+      }
+      geo.store(row, p, o, out_rows);
+    }
+  }
+  // (two bodies: a shared one would wait for the loads of the adding one, and for everything older, on both paths)
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J jc, const float (&S)[NE], const float (&T)[NE]) {
+    if (a.dz_accumulate) emit<true>(jc, S, T);
+    else emit<false>(jc, S, T);
+  }
+};
+
+// AKL threshold search, one pass: for AKL_K thresholds spread evenly inside the token's current interval
+// (LO, HI), the teacher mass of the entries at or above each threshold.
+template <class Geo>
+struct SearchEpi {
+  static constexpr int NC = Geo::NC;
+  Geo geo;
+  float Lt[NC], th0[NC], step[NC];
+  float mass[NC][AKL_K];
+  float c;
+  __device__ SearchEpi(const LogitArgs& a, int tt) : c(a.c) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = tt * BN + geo.n(j);
+      Lt[j] = a.rowinfo[t][0];
+      const float lo = a.akl[AKL_LO * a.T_pad + t], hi = a.akl[AKL_HI * a.T_pad + t];
+      step[j] = (hi - lo) * (1.f / (AKL_K + 1));
+      th0[j] = lo + step[j];
+#pragma unroll
+      for (int k = 0; k < AKL_K; ++k) mass[j][k] = 0.f;
+    }
+  }
+  __device__ void begin_item(int, int, int) {}
+  // T alone: the teacher's logits (entries that do not exist are NEG_BIG: below every threshold)
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const float lt = fmaf(T[e], c, -Lt[j]);
+      const float p = fexp2(lt);
+#pragma unroll
+      for (int k = 0; k < AKL_K; ++k) mass[j][k] += (lt >= fmaf((float)k, step[j], th0[j])) ? p : 0.f;
+    }
+  }
+  __device__ void write(const LogitArgs& a, int tt, int split) {
+    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * AKL_K * a.T_pad;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = tt * BN + geo.n(j);
+#pragma unroll
+      for (int k = 0; k < AKL_K; ++k) {
+#pragma unroll
+        for (int off = Geo::MERGE; off < 64; off <<= 1) mass[j][k] += __shfl_xor(mass[j][k], off, 64);
+        if (geo.lane < Geo::MERGE) p[k * a.T_pad + t] = mass[j][k];
+      }
     }
   }
 };
 
 // ------------------------------------------------------------------------------------------
-// logit kernels
+// logit kernels: the strip loop for bf16 operands with [V][H] heads and more than one token tile; the eight-wave tile
+// loop where the heads are read in place as [H][V] (k-major fragments come from LDS by transposing reads), the
+// teacher is fp8, or there is one token tile
 // ------------------------------------------------------------------------------------------
 #define KD_LOGIT_KERNEL __global__ __launch_bounds__(LCfg::NT)
 #define KD_GEMM_KERNEL __global__ __launch_bounds__(GCfg::NT)
+#define KD_STRIP_KERNEL __global__ __launch_bounds__(StripCfg::NT, 1) __attribute__((amdgpu_waves_per_eu(1, 1)))
+
+// measurement aid, off unless asked for
+struct LoopClock {
+  long long c0 = 0, r0 = 0;
+  __device__ LoopClock(const LogitArgs& a) {
+    if (a.clock_out) { c0 = clock64(); r0 = wall_clock64(); }
+  }
+  __device__ void stop(const LogitArgs& a) {
+    if (a.clock_out && blockIdx.x == 0 && threadIdx.x == 0) {
+      a.clock_out[0] = clock64() - c0;
+      a.clock_out[1] = wall_clock64() - r0;
+    }
+  }
+};
+
+template <int KIND>
+KD_STRIP_KERNEL void stats_strip_kernel(const LogitArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  StripWork work(a, meta_get(a.meta, META_N_SPLIT));
+  StatsEpi<KIND, StripGeo> epi(a.c);
+  StripEpi<StatsEpi<KIND, StripGeo>> drive(epi);
+  LoopClock clk(a);
+  strip_loop<2, true>(work, drive, 2 * a.H_s, 2 * a.H_t, smem);
+  clk.stop(a);
+  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+}
+
+template <int KIND>
+KD_STRIP_KERNEL void rows_strip_kernel(const LogitArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  StripWork work(a, meta_get(a.meta, META_N_SPLIT));
+  RowsEpi<KIND, StripGeo> epi(a, work.tt);
+  StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
+  strip_loop<2, true>(work, drive, 2 * a.H_s, 2 * a.H_t, smem);
+  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+}
+
+KD_STRIP_KERNEL void akl_search_strip_kernel(const LogitArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  StripWork work(a, meta_get(a.meta, META_N_SPLIT));
+  SearchEpi<StripGeo> epi(a, work.tt);
+  StripEpi<SearchEpi<StripGeo>> drive(epi);
+  strip_loop<1, true>(work, drive, 0, 2 * a.H_t, smem);
+  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+}
+
+template <int KIND>
+KD_STRIP_KERNEL void grad_strip_kernel(const LogitArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  StripWork work(a, meta_get(a.meta, a.last_chunk ? META_G_SPLIT_LAST : META_G_SPLIT));
+  GradEpi<KIND, StripGeo> epi(a);
+  StripEpi<GradEpi<KIND, StripGeo>> drive(epi);
+  strip_loop<2, false>(work, drive, 2 * a.H_s, 2 * a.H_t, smem);
+}
 
 template <int KIND, bool TF8, bool WHV>
 KD_LOGIT_KERNEL void stats_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   SplitWork<TF8, WHV> work(a);
-  StatsEpi<KIND> epi(a.c, a.t_scale);
-  long long c0 = 0, r0 = 0;
-  if (a.clock_out) { c0 = clock64(); r0 = wall_clock64(); }     // measurement aid, off unless asked for
-  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, epi, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
-  if (a.clock_out && blockIdx.x == 0 && threadIdx.x == 0) {
-    a.clock_out[0] = clock64() - c0;
-    a.clock_out[1] = wall_clock64() - r0;
-  }
+  StatsEpi<KIND, TileGeo> epi(a.c);
+  TileEpi<StatsEpi<KIND, TileGeo>> drive(epi, a.t_scale);
+  LoopClock clk(a);
+  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  clk.stop(a);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
 
@@ -542,66 +805,25 @@ template <int KIND, bool TF8, bool WHV>
 KD_LOGIT_KERNEL void rows_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   SplitWork<TF8, WHV> work(a);
-  RowsEpi<KIND> epi(a, work.tt);
-  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, epi, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  RowsEpi<KIND, TileGeo> epi(a, work.tt);
+  TileEpi<RowsEpi<KIND, TileGeo>> drive(epi, a.t_scale);
+  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
 
-// AKL threshold search, one pass: for AKL_K thresholds spread evenly inside the token's current interval
-// (LO, HI), the teacher mass of the entries at or above each threshold.
-struct SearchEpi {
-  float Lt[NI], th0[NI], step[NI];
-  float mass[NI][AKL_K];
-  float c;
-  int wm, wn, lane;
-  __device__ SearchEpi(const LogitArgs& a, int tt) : c(a.c) {
-    lane = threadIdx.x & 63;
-    wm = (threadIdx.x >> 6) & 1;
-    wn = threadIdx.x >> 7;
-#pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      const int t = tt * BN + acc_n(wn, nt, lane);
-      Lt[nt] = a.rowinfo[t][0];
-      const float lo = a.akl[AKL_LO * a.T_pad + t], hi = a.akl[AKL_HI * a.T_pad + t];
-      step[nt] = (hi - lo) * (1.f / (AKL_K + 1));
-      th0[nt] = lo + step[nt];
-#pragma unroll
-      for (int k = 0; k < AKL_K; ++k) mass[nt][k] = 0.f;
-    }
-  }
-  __device__ void begin_item(const WorkItem&) {}
-  __device__ void end_item(const WorkItem& it, AccTile& accT, AccTile&) {
-#pragma unroll
-    for (int nt = 0; nt < NI; ++nt)
-#pragma unroll
-      for (int mt = 0; mt < MI; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const bool ok = acc_m(wm, mt, r, lane) < it.a_rows;      // rows beyond the vocabulary hold nothing
-          const float lt = ok ? fmaf(accT[mt][nt][r], c, -Lt[nt]) : NEG_BIG;
-          const float p = fexp2(lt);
-#pragma unroll
-          for (int k = 0; k < AKL_K; ++k) mass[nt][k] += (lt >= fmaf((float)k, step[nt], th0[nt])) ? p : 0.f;
-        }
-  }
-  __device__ void write(const LogitArgs& a, int tt, int split) const {
-    const int part = split * 4 + wm * 2 + (lane >> 5);
-    float* p = a.partials + (int64_t)part * AKL_K * a.T_pad;
-#pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      const int t = tt * BN + acc_n(wn, nt, lane);
-#pragma unroll
-      for (int k = 0; k < AKL_K; ++k) p[k * a.T_pad + t] = mass[nt][k];
-    }
-  }
+// (one accumulator: the driver gets the teacher's tile as the first one)
+template <class Epi>
+struct SearchTileEpi : TileEpi<Epi> {
+  using TileEpi<Epi>::TileEpi;
+  __device__ void end_item(const WorkItem& it, AccTile& accT, AccTile&) { TileEpi<Epi>::end_item(it, accT, accT); }
 };
-
 template <bool WHV>
 KD_LOGIT_KERNEL void akl_search_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   TeacherSplitWork<WHV> work(a);
-  SearchEpi epi(a, work.tt);
-  tile_loop<1, LCfg, WHV ? 1 : 0, false>(work, epi, WHV ? a.V : a.H_t, WHV ? a.V : a.H_t, a.H_t, a.H_t, smem);
+  SearchEpi<TileGeo> epi(a, work.tt);
+  SearchTileEpi<SearchEpi<TileGeo>> drive(epi, 1.f);
+  tile_loop<1, LCfg, WHV ? 1 : 0, false>(work, drive, WHV ? a.V : a.H_t, WHV ? a.V : a.H_t, a.H_t, a.H_t, smem);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
 
@@ -609,8 +831,9 @@ template <int KIND, bool TF8, bool WHV>
 KD_LOGIT_KERNEL void grad_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   ChunkWork<TF8, WHV> work(a);
-  GradEpi<KIND> epi(a);
-  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, epi, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  GradEpi<KIND, TileGeo> epi(a);
+  TileEpi<GradEpi<KIND, TileGeo>> drive(epi, a.t_scale);
+  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -732,12 +955,23 @@ KD_GEMM_KERNEL void gemm_kernel(const GemmArgs a) {
 // rowmap[j] = index of the j-th valid token, inv[t] = its compacted index or -1, and writes the
 // device-side plan that depends on how many there are.  Every later kernel works on the compacted
 // token axis, so masked tokens cost nothing.
-__global__ void rowmap_kernel(const uint8_t* mask, int T, int T_pad, int n_split_max, int n_cu,
-                              int* rowmap, int* inv, int* meta) {
+//
+// Vocabulary ranges per token tile: the number s that finishes soonest when ceil(n_tt s / n_cu) rounds of workgroups
+// walk ceil(units / s) units each, in tiles of `per_tile` units and a rest.  A rest of at most `short_units` costs
+// 0.45 of a tile, a workgroup 0.33 of one to fill and drain its pipeline; the fewest ranges among equals, and at
+// least eight (the blocks of group_decode) where there are that many; 0 where striding over whole tiles
+// (StripWork) is better.  29 token tiles x 128256 rows: 26 ranges in
+// three rounds, where eight leave 24 of 256 CUs idle; one token tile x 151936 rows: 256 ranges of three tiles and at most
+// a short one, where whole tiles would take four.
+struct SplitChoice { int units, per_tile, short_units, most, strided; };
+__global__ void rowmap_kernel(const uint8_t* mask, int T, int T_pad, int n_cu, SplitChoice stats, SplitChoice grad,
+                              SplitChoice grad_last, int* rowmap, int* inv, int* meta) {
   __shared__ int s_scan[1024];
   __shared__ int s_running;
+  __shared__ unsigned long long s_best[3];
   const int tid = threadIdx.x;
   if (tid == 0) s_running = 0;
+  if (tid < 3) s_best[tid] = ~0ull;
   __syncthreads();
   for (int base = 0; base < T; base += 1024) {
     const int t = base + tid;
@@ -764,21 +998,28 @@ __global__ void rowmap_kernel(const uint8_t* mask, int T, int T_pad, int n_split
   const int last = n > 0 ? rowmap[n - 1] : 0;
   __syncthreads();
   for (int j = n + tid; j < T_pad; j += 1024) rowmap[j] = last;   // never dereferenced for results
+  const int n_tt = max((n + BN - 1) / BN, 1);
+  if (const int k = tid >> 8; k < 3) {               // 256 threads per choice
+    const SplitChoice c = k == 0 ? stats : k == 1 ? grad : grad_last;
+    for (int sp = (tid & 255) + 1; sp <= c.most; sp += 256) {
+      if (c.strided && sp == 1) {                    // (n_split 0; dearer by a hair: 2 % slower at equal counts)
+        const int r = (n_tt * ((c.units + c.per_tile - 1) / c.per_tile) + n_cu - 1) / n_cu;
+        atomicMin(&s_best[k], ((unsigned long long)(((float)r + 0.4f) * 16.f) << 16));
+      }
+      if (sp < 8 && sp < c.most) continue;
+      const int rounds = (n_tt * sp + n_cu - 1) / n_cu, u = (c.units + sp - 1) / sp, rest = u % c.per_tile;
+      const float tiles = (float)(u / c.per_tile) + (rest == 0 ? 0.f : rest <= c.short_units ? 0.45f : 1.f) + 0.33f;
+      atomicMin(&s_best[k], ((unsigned long long)((float)rounds * tiles * 16.f) << 16) | (unsigned)sp);
+    }
+  }
+  __syncthreads();
   if (tid == 0) {
-    int n_tt = (n + BN - 1) / BN;
-    if (n_tt < 1) n_tt = 1;
-    int n_split = n_cu / n_tt;                     // as many splits as keep one workgroup per CU
-    if (n_split < 8) n_split = 8;
-    if (n_split > n_split_max) n_split = n_split_max;
-    int ba = 1, bb = 1;
-    for (int d = 2; d <= 4; ++d) if (n_tt % d == 0) ba = d;
-    for (int d = 2; d <= 8; ++d) if (n_split % d == 0) bb = d;
     meta[META_N_VALID] = n;
     meta[META_N_TT] = n_tt;
-    meta[META_N_SPLIT] = n_split;
-    meta[META_BA] = ba;
-    meta[META_BB] = bb;
     meta[META_T_EFF] = n_tt * BN;
+    meta[META_N_SPLIT] = (int)(s_best[0] & 0xffff);
+    meta[META_G_SPLIT] = (int)(s_best[1] & 0xffff);
+    meta[META_G_SPLIT_LAST] = (int)(s_best[2] & 0xffff);
   }
 }
 
@@ -821,11 +1062,11 @@ __device__ __forceinline__ void merge_parts(float (&v)[NV], float* lds) {
 // Merge the partial statistics of one (compacted) token; write log-sum-exps and, for FKL / RKL, the
 // row loss.
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int T_pad, int kind, float c,
+__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind, float c,
                                                      f32x4* rowinfo, float* row_loss, float* akl) {
   __shared__ float lds[NT / 64 * 4 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = 4 * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
   const int nv = kind == 6 ? 6 : 5;
   if ((int)(blockIdx.x * TX) >= n_valid && g > 0) return;     // a whole workgroup of padding rows
   if (t >= n_valid && g == 0) {   // padding rows: probabilities evaluate to 0, gradient scale 0
@@ -882,11 +1123,11 @@ __global__ __launch_bounds__(NT) void combine_kernel(const float* partials, cons
 // AKL: merge one search pass.  mass_k = teacher mass at or above threshold k (decreasing in k); the new
 // interval is the pair of neighbouring thresholds between which the mass drops to mu or below.
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void akl_search_combine_kernel(const float* partials, const int* meta, int T_pad,
+__global__ __launch_bounds__(NT) void akl_search_combine_kernel(const float* partials, const int* meta, int per_split, int T_pad,
                                                                 float mu, float* akl) {
   __shared__ float lds[NT / 64 * AKL_K * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = 4 * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
   if ((int)(blockIdx.x * TX) >= n_valid) return;
   float m[AKL_K];
 #pragma unroll
@@ -930,11 +1171,11 @@ __device__ __forceinline__ void merge_row_sums(const float* partials, int n_part
 
 // AKL: gaps -> weights, row loss and the row term of the gradient (see GradEpi).
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, const int* meta, int T_pad,
+__global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, const int* meta, int per_split, int T_pad,
                                                          f32x4* rowinfo, float* row_loss, float* akl) {
   __shared__ float lds[NT / 64 * 2 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = 4 * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
   if ((int)(blockIdx.x * TX) >= n_valid) return;
   float a[2];
   merge_row_sums<TX, NT>(partials, n_parts, T_pad, t, g, lds, a);
@@ -951,11 +1192,11 @@ __global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, 
 
 // JSD / TVD / skewed KL: merge the row sums into the row loss and R (see RowTerm).
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void combine_rows_kernel(const float* partials, const int* meta, int T_pad, int kind,
+__global__ __launch_bounds__(NT) void combine_rows_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind,
                                                           float w, f32x4* rowinfo, float* row_loss) {
   __shared__ float lds[NT / 64 * 2 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = 4 * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
   if ((int)(blockIdx.x * TX) >= n_valid) return;
   float a[2];
   merge_row_sums<TX, NT>(partials, n_parts, T_pad, t, g, lds, a);
@@ -1019,6 +1260,57 @@ __global__ void transpose_kernel(const E* src, int64_t ld_src, int R, int C, E* 
     const int c = c0 + i, r = r0 + tx;
     if (c < C && r < R_pad) dst[(int64_t)c * ld_dst + r] = tile[tx][i];
   }
+}
+
+// h_s^T of the compacted tokens: dst[c][j] = src[rowmap[j]][c] in bf16 for j < n_valid, zero up to R_pad.
+template <class E>
+__global__ void transpose_rows_kernel(const E* src, int C, bf16_t* dst, int R_pad, const int* rowmap, const int* meta) {
+  __shared__ bf16_t tile[64][66];
+  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const int n_valid = meta[META_N_VALID];
+  const int c = c0 + tx, cc = min(c, C - 1);
+  E v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i)           // (rowmap holds a valid row for every r < R_pad: the loads need no test)
+    v[i] = src[(int64_t)rowmap[r0 + ty + 4 * i] * C + cc];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) tile[ty + 4 * i][tx] = r0 + ty + 4 * i < n_valid && c < C ? (bf16_t)v[i] : (bf16_t)0.f;
+  __syncthreads();
+  for (int i = ty; i < 64; i += 4) {
+    const int c = c0 + i, r = r0 + tx;
+    if (c < C && r < R_pad) dst[(int64_t)c * R_pad + r] = tile[tx][i];
+  }
+}
+
+// The token operand of the strip loop: the compacted rows (row j = row rowmap[j] of src for j < n_valid, zero
+// beyond) in the order in which its waves load them: [64-token panel][32-element sub-step][16-token block][lane][8],
+// lane l holding elements 8 (l / 16) .. + 7 of token l mod 16.  fp32 rows become [hi | lo | hi] (see
+// prepare_kernel).  A workgroup writes 4 KiB; bound by its reads of 64-byte pieces, 20 us for 30 MB.
+__global__ void pack_rows_kernel(const void* src, int src_f32, int H, bf16_t* dst, int K, const int* rowmap,
+                                 const int* meta) {
+  const int lane = threadIdx.x & 63, blk = threadIdx.x >> 6;
+  const int kb = blockIdx.x, panel = blockIdx.y;
+  const int j = panel * 64 + 16 * blk + (lane & 15), k0 = 32 * kb + 8 * (lane >> 4);
+  bf16x8 v;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = (bf16_t)0.f;
+  if (j < meta[META_N_VALID]) {
+    const int64_t row = (int64_t)rowmap[j] * H;
+    if (!src_f32) {
+      if (k0 < H) v = *(const bf16x8*)((const bf16_t*)src + row + k0);
+    } else if (k0 < 3 * H) {
+      const int part = k0 / H;                     // H is a multiple of 8: the eight values are of one part
+      const f32x4* x = (const f32x4*)((const float*)src + row + (k0 - part * H));
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float f = x[i >> 2][i & 3];
+        const bf16_t hi = (bf16_t)f;
+        v[i] = part == 1 ? (bf16_t)(f - (float)hi) : hi;
+      }
+    }
+  }
+  *(bf16x8*)(dst + ((((int64_t)panel * (K / 32) + kb) * 4 + blk) * 64 + lane) * 8) = v;
 }
 
 // Re-pack one operand as bf16 [R][K]: plain copy (bf16 source) or the high / low bf16 parts of an
@@ -1210,17 +1502,21 @@ static LogitArgs make_logit_args(const Problem& p) {
 
 hipError_t launch_stats(const Problem& p, hipStream_t st) {
   LogitArgs a = make_logit_args(p);
-  a.vt0 = 0; a.n_vt = p.n_vt;
+  a.v0 = 0; a.v_end = p.V; a.n_vt = p.n_vt;
   a.partials = p.partials;
   a.clock_out = p.clock_out;
   const int grid = p.n_tt * p.n_split;      // worst case; workgroups beyond the device-side plan exit
-#define KD_STATS(K) (p.t_fp8 ? launch_big<stats_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
+#define KD_STATS(K) (p.strip ? launch_big<stats_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a) \
+                     : p.t_fp8 ? launch_big<stats_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                      : p.w_hv_inplace ? launch_big<stats_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
-                              : launch_big<stats_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
+                               : launch_big<stats_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
   switch (p.kind) {
     case 0: return KD_STATS(0);
     case 1: return KD_STATS(1);
-    case 6: return KD_STATS(6);    // both cross terms (AKL)
+    case 6:                        // both cross terms (AKL; never with the fp8 teacher)
+      return p.strip ? launch_big<stats_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+             : p.w_hv_inplace ? launch_big<stats_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
+                              : launch_big<stats_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
     default: return KD_STATS(2);   // log-sum-exps only
   }
 #undef KD_STATS
@@ -1228,17 +1524,21 @@ hipError_t launch_stats(const Problem& p, hipStream_t st) {
 
 hipError_t launch_rows(const Problem& p, hipStream_t st) {
   LogitArgs a = make_logit_args(p);
-  a.vt0 = 0; a.n_vt = p.n_vt;
+  a.v0 = 0; a.v_end = p.V; a.n_vt = p.n_vt;
   a.partials = p.partials;
   const int grid = p.n_tt * p.n_split;
-#define KD_ROWS(K) (p.t_fp8 ? launch_big<rows_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
-                    : p.w_hv_inplace ? launch_big<rows_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
-                             : launch_big<rows_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
+#define KD_ROWS(K) (p.strip ? launch_big<rows_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a) \
+                     : p.t_fp8 ? launch_big<rows_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
+                     : p.w_hv_inplace ? launch_big<rows_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
+                               : launch_big<rows_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
   switch (p.kind) {
     case 2: return KD_ROWS(2);
     case 3: return KD_ROWS(3);
     case 4: return KD_ROWS(4);
-    case 6: return KD_ROWS(6);
+    case 6:
+      return p.strip ? launch_big<rows_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+             : p.w_hv_inplace ? launch_big<rows_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
+                              : launch_big<rows_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
     default: return KD_ROWS(5);
   }
 #undef KD_ROWS
@@ -1246,48 +1546,66 @@ hipError_t launch_rows(const Problem& p, hipStream_t st) {
 
 // Shape of the merges: 8 tokens x 128 threads each where a token may have more than 128 parts, else 32 tokens x 8
 // threads each (see merge_parts).
-static bool many_parts(const Problem& p) { return 4 * p.n_split > 128; }
+static bool many_parts(const Problem& p) { return p.parts * p.n_split > 128; }
 
 // AKL: one pass of the threshold search (teacher logit tiles only) and its merge.
 hipError_t launch_akl_search(const Problem& p, hipStream_t st) {
   LogitArgs a = make_logit_args(p);
-  a.vt0 = 0; a.n_vt = p.n_vt;
+  a.v0 = 0; a.v_end = p.V; a.n_vt = p.n_vt;
   a.partials = p.partials;
   const int grid = p.n_tt * p.n_split;
-  hipError_t e = p.w_hv_inplace ? launch_big<akl_search_kernel<true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
-                                : launch_big<akl_search_kernel<false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
+  hipError_t e = p.strip ? launch_big<akl_search_strip_kernel>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+           : p.w_hv_inplace ? launch_big<akl_search_kernel<true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
+                            : launch_big<akl_search_kernel<false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
   if (e != hipSuccess) return e;
   if (many_parts(p))
     hipLaunchKernelGGL((akl_search_combine_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
-                       p.T_pad, p.beta, p.akl);
+                       p.parts, p.T_pad, p.beta, p.akl);
   else
     hipLaunchKernelGGL((akl_search_combine_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
-                       p.T_pad, p.beta, p.akl);
+                       p.parts, p.T_pad, p.beta, p.akl);
   return hipGetLastError();
 }
 
 hipError_t launch_akl_weights(const Problem& p, hipStream_t st) {
   if (many_parts(p))
-    hipLaunchKernelGGL((akl_weights_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta, p.T_pad,
+    hipLaunchKernelGGL((akl_weights_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
+                       p.parts, p.T_pad,
                        (f32x4*)p.rowinfo, p.row_loss, p.akl);
   else
-    hipLaunchKernelGGL((akl_weights_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta, p.T_pad,
+    hipLaunchKernelGGL((akl_weights_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
+                       p.parts, p.T_pad,
                        (f32x4*)p.rowinfo, p.row_loss, p.akl);
   return hipGetLastError();
 }
 
 hipError_t launch_rowmap(const Problem& p, hipStream_t st) {
-  hipLaunchKernelGGL(rowmap_kernel, dim3(1), dim3(1024), 0, st, p.mask, p.T, p.T_pad, p.n_split, p.n_cu, p.rowmap,
-                     p.inv, p.meta);
+  // units: 64 vocabulary rows for the strip loop, tiles for the eight-wave one (whose gradient kernel strides)
+  const int last = p.V - (p.V - 1) / p.V_c * p.V_c;      // width of the last chunk
+  SplitChoice stats{p.n_vt, 1, 0, p.n_split, 0}, grad{1, 1, 0, 1, 0}, grad_last = grad;
+  if (p.strip) {
+    const int per = StripCfg::BM / 64, sh = StripCfg::SHORT / 64, full = p.V < p.V_c ? p.V : p.V_c;
+    auto choice = [&](int rows, int most, int short_units, int strided) {
+      const int units = (rows + 63) / 64;
+      return SplitChoice{units, per, short_units, most < units ? most : units, strided};
+    };
+    stats = choice(p.V, p.n_split, sh, 0);
+    grad = choice(full, p.g_split, 0, 1);
+    grad_last = choice(last, p.g_split, 0, 1);
+  }
+  hipLaunchKernelGGL(rowmap_kernel, dim3(1), dim3(1024), 0, st, p.mask, p.T, p.T_pad, p.n_cu, stats, grad, grad_last,
+                     p.rowmap, p.inv, p.meta);
   return hipGetLastError();
 }
 
 hipError_t launch_combine(const Problem& p, hipStream_t st) {
   if (many_parts(p))
-    hipLaunchKernelGGL((combine_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta, p.T_pad,
+    hipLaunchKernelGGL((combine_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
+                       p.parts, p.T_pad,
                        p.kind, 1.4426950408889634f / p.tau, (f32x4*)p.rowinfo, p.row_loss, p.akl);
   else
-    hipLaunchKernelGGL((combine_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta, p.T_pad,
+    hipLaunchKernelGGL((combine_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
+                       p.parts, p.T_pad,
                        p.kind, 1.4426950408889634f / p.tau, (f32x4*)p.rowinfo, p.row_loss, p.akl);
   return hipGetLastError();
 }
@@ -1295,10 +1613,10 @@ hipError_t launch_combine(const Problem& p, hipStream_t st) {
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st) {
   if (many_parts(p))
     hipLaunchKernelGGL((combine_rows_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
-                       p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
+                       p.parts, p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
   else
     hipLaunchKernelGGL((combine_rows_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
-                       p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
+                       p.parts, p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
   return hipGetLastError();
 }
 
@@ -1311,36 +1629,55 @@ hipError_t launch_finalize(const Problem& p, hipStream_t st) {
 hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulate, hipStream_t st) {
   LogitArgs a = make_logit_args(p);
   a.dz_accumulate = accumulate ? 1 : 0;
-  a.vt0 = v0 / BM;
+  a.v0 = v0; a.v_end = v0 + width;
   a.n_vt = (width + BM - 1) / BM;
   a.bb = largest_divisor_le(a.n_vt, 16);
+  a.last_chunk = v0 + width >= p.V;
   a.dz = (bf16_t*)p.dz; a.ldz = p.V_c;
   const int tiles = p.n_tt * a.n_vt;
-  int grid = tiles < p.n_cu ? tiles : p.n_cu;
-#define KD_GRAD(K) (p.t_fp8 ? launch_big<grad_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
-                    : p.w_hv_inplace ? launch_big<grad_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
-                             : launch_big<grad_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
+  // strip loop: one workgroup per (token tile, range), surplus ones exit; eight-wave loop: persistent workgroups
+  const int grid = p.strip ? p.n_tt * p.g_split : tiles < p.n_cu ? tiles : p.n_cu;
+#define KD_GRAD(K) (p.strip ? launch_big<grad_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a) \
+                     : p.t_fp8 ? launch_big<grad_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
+                     : p.w_hv_inplace ? launch_big<grad_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
+                               : launch_big<grad_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
   switch (p.kind) {
     case 0: return KD_GRAD(0);
     case 1: return KD_GRAD(1);
     case 2: return KD_GRAD(2);
     case 3: return KD_GRAD(3);
     case 4: return KD_GRAD(4);
-    case 6: return KD_GRAD(6);
+    case 6:
+      return p.strip ? launch_big<grad_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+             : p.w_hv_inplace ? launch_big<grad_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
+                              : launch_big<grad_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
     default: return KD_GRAD(5);
   }
 #undef KD_GRAD
 }
 
-hipError_t launch_transpose(const void* src, int64_t ld_src, int R, int C, void* dst, int64_t ld_dst, int R_pad,
-                            int elem_bytes, hipStream_t st) {
+hipError_t launch_transpose_bytes(const void* src, int64_t ld_src, int R, int C, void* dst, int64_t ld_dst, int R_pad,
+                                  hipStream_t st) {
   dim3 grid((R_pad + 63) / 64, (C + 63) / 64);
-  if (elem_bytes == 1)
-    hipLaunchKernelGGL(transpose_kernel<uint8_t>, grid, dim3(256), 0, st, (const uint8_t*)src, ld_src, R, C,
-                       (uint8_t*)dst, ld_dst, R_pad);
+  hipLaunchKernelGGL(transpose_kernel<uint8_t>, grid, dim3(256), 0, st, (const uint8_t*)src, ld_src, R, C, (uint8_t*)dst,
+                     ld_dst, R_pad);
+  return hipGetLastError();
+}
+
+hipError_t launch_transpose_rows(const Problem& p, hipStream_t st) {
+  dim3 grid(p.T_pad / 64, (p.H_s + 63) / 64);
+  if (p.in_f32)
+    hipLaunchKernelGGL(transpose_rows_kernel<float>, grid, dim3(256), 0, st, (const float*)p.user_h_s, p.H_s,
+                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
   else
-    hipLaunchKernelGGL(transpose_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)src, ld_src, R, C,
-                       (bf16_t*)dst, ld_dst, R_pad);
+    hipLaunchKernelGGL(transpose_rows_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)p.user_h_s, p.H_s,
+                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
+  return hipGetLastError();
+}
+
+hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst, int K, hipStream_t st) {
+  hipLaunchKernelGGL(pack_rows_kernel, dim3(K / 32, p.T_pad / 64), dim3(256), 0, st, src, p.in_f32, H, (bf16_t*)dst, K,
+                     p.rowmap, p.meta);
   return hipGetLastError();
 }
 

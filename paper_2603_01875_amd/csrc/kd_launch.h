@@ -7,7 +7,7 @@
 namespace kd {
 
 constexpr int kNumCU = 256;            // MI355X: 8 XCDs x 32 CUs; persistent grids are sized for it
-constexpr int kTileM = 128;            // vocabulary rows per logit tile
+constexpr int kTileM = 128;            // vocabulary rows per logit tile of the eight-wave loop
 constexpr int kTileN = 256;            // token rows per logit tile
 #ifndef KD_GEMM_TILE_M
 #define KD_GEMM_TILE_M 128
@@ -39,6 +39,9 @@ struct Problem {
   float* per_token_loss;
   void *grad_h_s, *grad_W_s;
   // plan
+  int strip;                    // bf16 logit operands, [V][K] heads: strip loop on packed hidden states
+  int parts;                    // partial results per token and vocabulary split
+  int g_split;                  // strip loop: most vocabulary ranges per token tile in the gradient kernel
   int T_pad, n_tt, n_vt, n_split, V_c, n_ksplit_h, ksteps_h, n_cu;
   // workspace carve-up
   int* meta;           // device-side plan written by the row-map kernel
@@ -47,7 +50,7 @@ struct Problem {
   float* rowinfo;      // [T_pad][4]
   float* akl;          // AKL only: [6][T_pad] per-token values between its passes (null otherwise)
   float* row_loss;     // [T_pad]
-  float* partials;     // [n_split*4][5][T_pad]
+  float* partials;     // [n_split*parts][5][T_pad]
   void* h_sT;          // bf16 [H_s][T_pad]
   void* dz;            // bf16 [T_pad][V_c]
   float* gh32;         // [n_ksplit_h][T][H_s]
@@ -86,9 +89,13 @@ constexpr int kAklThresholds = 16;     // per pass (the kernels' AKL_K)
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st);
 hipError_t launch_finalize(const Problem& p, hipStream_t st);
 hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulate, hipStream_t st);
-// dst[c][r] = src[r][c] (zero for R <= r < R_pad); elements of 1 or 2 bytes
-hipError_t launch_transpose(const void* src, int64_t ld_src, int R, int C, void* dst, int64_t ld_dst, int R_pad,
-                            int elem_bytes, hipStream_t st);
+// dst[c][r] = src[r][c] (zero for R <= r < R_pad), one-byte elements
+hipError_t launch_transpose_bytes(const void* src, int64_t ld_src, int R, int C, void* dst, int64_t ld_dst, int R_pad,
+                                  hipStream_t st);
+// h_s^T of the compacted tokens (bf16 [H_s][T_pad]), from the caller's array
+hipError_t launch_transpose_rows(const Problem& p, hipStream_t st);
+// hidden states [T][H] -> compacted, packed for the strip loop (T_pad rows of K elements)
+hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst, int K, hipStream_t st);
 hipError_t launch_gemm(const GemmDesc& d, int n_cu, hipStream_t st);
 hipError_t launch_gradh_finish(const Problem& p, hipStream_t st);
 const char* build_info();     // compile-time configuration of the kernels (tile shapes, ablation switch)
