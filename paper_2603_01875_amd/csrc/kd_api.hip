@@ -59,6 +59,51 @@ kd_status check_params(const kd_loss_params* p) {
   return KD_OK;
 }
 
+// Vocabulary chunk of the backward pass.  The [T_pad, V_c] bf16 staging buffer of dL/dz_s is written by the gradient
+// kernel and read back by both products, so it should stay in the 256 MB last-level cache together with the operands;
+// but every chunk also re-reads and re-writes the fp32 sums of grad_h_s, so with many tokens a chunk of at least 8192
+// columns wins as long as the staging buffer stays within 512 MiB.
+//  - From 4096 tokens on a power of two within 128 MiB (16384 columns at T = 4096: the workspace stays far from a
+//    [T, V] tensor), at least 8192 columns.
+//  - Below, up to 208 MiB (201 MB still stays in the cache), and the width decides how full the last rounds of
+//    workgroups are: the candidates (multiples of the tile heights) are priced by the rounds of the gradient kernel,
+//    with all tokens and with an eighth of them masked, and of the grad_W_s product.  Measured steps: T = 3584 10.60 ms
+//    with 24576 columns against 10.78 with 16384; T = 2048 6.03 with 49152 against 6.25 with 32768; T = 1024 3.28 with
+//    98304 against 3.34 with 65536.
+int64_t choose_chunk(const Problem& q, int64_t v_all) {
+  if (q.T_pad >= 4096) {
+    int64_t vc = 1 << 20;
+    while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (128ll << 20)) vc >>= 1;
+    if (vc < 8192) {
+      vc = 8192;
+      while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (512ll << 20)) vc >>= 1;
+    }
+    return vc;
+  }
+  const int64_t step = 1536, most = (208ll << 20) / (2 * q.T_pad);      // a multiple of 192, 256 and 128
+  if (most >= v_all) return v_all;
+  const int tile_m = q.strip ? 192 : kd::kTileM, masked_tt = (q.n_tt * 7 + 7) / 8;
+  const int64_t m_tiles = (q.H_s + kd::kGemmTileM - 1) / kd::kGemmTileM;
+  // multiply-adds of one workgroup: a logit tile, a grad_W_s tile, and what a chunk costs besides (three launches
+  // and the sums of grad_h_s: 20 us and 8 bytes per element at 5 TB/s, at 2.6e12 a second)
+  const double logit = (double)tile_m * kd::kTileN * (q.K_s + (q.t_fp8 ? q.K_t / 2 : q.K_t));
+  const double gw = (double)kd::kGemmTileM * kd::kTileN * q.T_pad;
+  const double fixed = 52e6 + (double)q.T * q.H_s * 4.2;
+  auto cost = [&](int64_t width) {
+    const int64_t n = (width + tile_m - 1) / tile_m;
+    auto rounds = [&](int64_t tiles) { return (double)((tiles + q.n_cu - 1) / q.n_cu); };
+    return logit * 0.5 * (rounds(n * q.n_tt) + rounds(n * masked_tt)) + gw * rounds((width + 255) / 256 * m_tiles) + fixed;
+  };
+  int64_t best = step;
+  double best_cost = 1e300;
+  for (int64_t vc = step; vc <= most; vc += step) {
+    const int64_t full = q.V / vc, rest = q.V - full * vc;
+    const double c = (double)full * cost(vc) + (rest > 0 ? cost(rest) : 0.);
+    if (c <= best_cost) { best_cost = c; best = vc; }
+  }
+  return best;
+}
+
 // Tile counts, vocabulary chunk and split factors.  Depends on the params only.  The per-teacher
 // block is placed at `teacher_base` (default: right after the common part).  `repack_hv` makes
 // [H][V] heads go through the re-packing path even where they could be read in place (a
@@ -114,21 +159,9 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   q.n_split = !q.strip ? split_room : ns < strips ? ns : strips;
   q.g_split = q.n_split;        // (bounded by the chunk's rows where it is used)
 
-  // vocabulary chunk of the backward pass: a power of two.  The [T_pad, V_c] bf16 staging buffer of
-  // dL/dz_s is written by the gradient kernel and read back by both products, so it should stay within
-  // the 256 MB last-level cache together with the operands (128 MiB: measured best from T = 256 to 4096);
-  // but every chunk also re-reads and re-writes the fp32 sums of grad_h_s, so with many tokens a chunk
-  // of at least 8192 columns wins as long as the staging buffer stays within 512 MiB.
-  int64_t vc = 1 << 20;
-  while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (128ll << 20)) vc >>= 1;
-  if (vc < 8192) {
-    vc = 8192;
-    while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (512ll << 20)) vc >>= 1;
-  }
-  if (p->vocab_chunk > 0) vc = p->vocab_chunk;       // the caller's choice (checked: a multiple of 256)
   const int64_t v_all = round_up(q.V, 256);
-  if (vc > v_all) vc = v_all;
-  q.V_c = (int)vc;
+  const int64_t vc = p->vocab_chunk > 0 ? p->vocab_chunk : choose_chunk(q, v_all);   // (the caller's: a multiple of 256)
+  q.V_c = (int)(vc < v_all ? vc : v_all);
 
   // split-K of the grad_h_s product so that a chunk offers about one tile per CU
   const int tiles_h = ((q.H_s + kd::kGemmTileM - 1) / kd::kGemmTileM) * q.n_tt;
