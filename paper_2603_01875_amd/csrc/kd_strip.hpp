@@ -37,7 +37,7 @@ struct StripCfg {
   static constexpr int SMEM_BYTES = NST * STAGE_BYTES + PARK_BYTES;
   static_assert(SMEM_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
   // A workgroup's last tile, if it has at most SHORT rows, is multiplied as four blocks (its loads stay as they are:
-  // rows that do not exist repeat the last one).  Measured: 0.4 of the time of a full tile.
+  // rows that do not exist repeat the last one).  Priced at 0.45 of a full tile by the choice of ranges.
   static constexpr int SHORT = 64;                   // (rows behind those that exist are stored up to 64: see out_rows)
   static_assert(MB >= 2 * A_LOADS && MB % 4 == 0, "places of the loads in a sub-step");
   // Sub-step of NM vocabulary blocks.  B load j goes out after block b_place(j); in the first sub-step A load j
