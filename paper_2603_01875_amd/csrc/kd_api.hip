@@ -70,7 +70,8 @@ kd_status check_params(const kd_loss_params* p) {
 //    with all tokens and with an eighth of them masked, and of the grad_W_s product.  Measured steps: T = 3584 10.60 ms
 //    with 24576 columns against 10.78 with 16384; T = 2048 6.03 with 49152 against 6.25 with 32768; T = 1024 3.28 with
 //    98304 against 3.34 with 65536.
-int64_t choose_chunk(const Problem& q, int64_t v_all) {
+// `logit_k`: elements contracted for one logit of every model of the call (each teacher with the student again).
+int64_t choose_chunk(const Problem& q, int64_t v_all, int64_t logit_k) {
   if (q.T_pad >= 4096) {
     int64_t vc = 1 << 20;
     while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (128ll << 20)) vc >>= 1;
@@ -86,7 +87,7 @@ int64_t choose_chunk(const Problem& q, int64_t v_all) {
   const int64_t m_tiles = (q.H_s + kd::kGemmTileM - 1) / kd::kGemmTileM;
   // multiply-adds of one workgroup: a logit tile, a grad_W_s tile, and what a chunk costs besides (three launches
   // and the sums of grad_h_s: 20 us and 8 bytes per element at 5 TB/s, at 2.6e12 a second)
-  const double logit = (double)tile_m * kd::kTileN * (q.K_s + (q.t_fp8 ? q.K_t / 2 : q.K_t));
+  const double logit = (double)tile_m * kd::kTileN * (double)logit_k;
   const double gw = (double)kd::kGemmTileM * kd::kTileN * q.T_pad;
   const double fixed = 52e6 + (double)q.T * q.H_s * 4.2;
   auto cost = [&](int64_t width) {
@@ -104,12 +105,20 @@ int64_t choose_chunk(const Problem& q, int64_t v_all) {
   return best;
 }
 
-// Tile counts, vocabulary chunk and split factors.  Depends on the params only.  The per-teacher
-// block is placed at `teacher_base` (default: right after the common part).  `repack_hv` makes
-// [H][V] heads go through the re-packing path even where they could be read in place (a
-// multi-teacher call takes that decision once for all its teachers).
-void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, size_t teacher_base = 0,
-          bool repack_hv = false) {
+// What a plan depends on besides the params.  The backward pass and the student's buffers are shared by all teachers of
+// a call, so whatever decides about them looks at the whole call and never at one teacher's hidden size.
+struct CallPlan {
+  const int64_t* H_t = nullptr;    // hidden sizes of the call's teachers (null: the one of the params)
+  int n_teachers = 1;
+  size_t teacher_base = 0;         // where this teacher's block lies (0: right after the common part)
+  bool repack_hv = false;          // [H][V] heads are re-packed even where they could be read in place
+};
+
+// Contraction length of one operand as the kernels read it: fp32 is three bf16 products side by side.
+inline int64_t contraction(bool f32, int64_t H) { return round_up(f32 ? 3 * H : H, 64); }
+
+// Tile counts, vocabulary chunk and split factors.  Depends on the params and on `call` only.
+void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, const CallPlan& call = CallPlan{}) {
   q.T = (int)p->T; q.V = (int)p->V; q.H_s = (int)p->H_s; q.H_t = (int)p->H_t;
   q.kind = p->kind; q.tau = p->tau; q.beta = p->beta;
   q.grad_f32 = p->grad_dtype == KD_F32;
@@ -124,8 +133,8 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   q.w_hv = p->w_layout == KD_W_HV;
   q.t_fp8 = (p->flags & KD_FLAG_TEACHER_FP8) ? 1 : 0;
   q.t_scale = q.t_fp8 ? p->teacher_scale : 1.f;
-  q.K_t = (int)round_up(q.in_f32 ? 3 * q.H_t : q.H_t, 64);      // fp8: H_t % 128 == 0, used as it is
-  q.K_s = (int)round_up(q.in_f32 ? 3 * q.H_s : q.H_s, 64);
+  q.K_t = (int)contraction(q.in_f32, q.H_t);                    // fp8: H_t % 128 == 0, used as it is
+  q.K_s = (int)contraction(q.in_f32, q.H_s);
   q.prep_Wt = q.in_f32 || q.K_t != q.H_t;
   q.prep_Ws = q.in_f32 || q.K_s != q.H_s;
   // [H][V] heads are read in place as k-major operands when they are bf16 with whole k-steps and a
@@ -133,7 +142,7 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   // steps; otherwise both are re-packed (transposing) and the kernels see [V][K] copies
   // (an fp8 teacher head kept as [H][V] bytes is transposed into a [V][H] copy: the fp8 phase of the tile
   // loop reads K-contiguous rows only)
-  q.w_hv_inplace = q.w_hv && !repack_hv && !q.t_fp8 && !q.prep_Wt && !q.prep_Ws && q.V % 64 == 0;
+  q.w_hv_inplace = q.w_hv && !call.repack_hv && !q.t_fp8 && !q.prep_Wt && !q.prep_Ws && q.V % 64 == 0;
   if (q.w_hv && !q.w_hv_inplace) q.prep_Wt = q.prep_Ws = 1;
   // hidden states are also re-packed when a mask is given: valid tokens are compacted to the front
   // (the workspace is sized as if it were, since the size query does not see the mask)
@@ -159,8 +168,13 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   q.n_split = !q.strip ? split_room : ns < strips ? ns : strips;
   q.g_split = q.n_split;        // (bounded by the chunk's rows where it is used)
 
+  int64_t logit_k = 0;
+  for (int i = 0; i < call.n_teachers; ++i) {
+    const int64_t K_t = contraction(q.in_f32, call.H_t ? call.H_t[i] : p->H_t);
+    logit_k += q.K_s + (q.t_fp8 ? K_t / 2 : K_t);        // (an e4m3 element costs half a bf16 one)
+  }
   const int64_t v_all = round_up(q.V, 256);
-  const int64_t vc = p->vocab_chunk > 0 ? p->vocab_chunk : choose_chunk(q, v_all);   // (the caller's: a multiple of 256)
+  const int64_t vc = p->vocab_chunk > 0 ? p->vocab_chunk : choose_chunk(q, v_all, logit_k);  // (the caller's: a multiple of 256)
   q.V_c = (int)(vc < v_all ? vc : v_all);
 
   // split-K of the grad_h_s product so that a chunk offers about one tile per CU
@@ -199,7 +213,7 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, si
   // what belongs to one teacher comes last, so that everything above sits at the same offsets for
   // every teacher of a multi-teacher call and the teachers' blocks can lie side by side
   L.common = off;
-  if (teacher_base > off) off = teacher_base;
+  if (call.teacher_base > off) off = call.teacher_base;
   L.rowinfo = take((size_t)q.T_pad * 16);
   L.akl = q.kind == KD_AKL ? take((size_t)q.T_pad * 6 * 4) : 0;
   const size_t t_es = q.t_fp8 ? 1 : 2;
@@ -403,7 +417,7 @@ kd_status run_backward(const Problem* qs, int n_teachers, hipStream_t st) {
 kd_status check_buffers(const kd_loss_params* params, const void* h_t, const void* W_t, const void* h_s,
                         const void* W_s, const uint8_t* mask, float* loss, void* workspace,
                         size_t workspace_bytes, bool backward, void* grad_h_s, void* grad_W_s,
-                        Problem& q, Layout& L, size_t teacher_base = 0, bool repack_hv = false) {
+                        Problem& q, Layout& L, const CallPlan& call = CallPlan{}) {
   kd_status s = check_params(params);
   if (s != KD_OK) return s;
   if (!h_t || !W_t || !h_s || !W_s || !loss || !workspace) return KD_ERR_NULL;
@@ -411,7 +425,7 @@ kd_status check_buffers(const kd_loss_params* params, const void* h_t, const voi
   if (!aligned16(h_t) || !aligned16(W_t) || !aligned16(h_s) || !aligned16(W_s)) return KD_ERR_ALIGN;
   if (backward && (!aligned16(grad_h_s) || !aligned16(grad_W_s))) return KD_ERR_ALIGN;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return KD_ERR_ALIGN;
-  plan(params, q, L, backward, teacher_base, repack_hv);
+  plan(params, q, L, backward, call);
   if (workspace_bytes < L.total) return KD_ERR_WORKSPACE;
   q.h_t = h_t; q.W_t = W_t; q.h_s = h_s; q.W_s = W_s; q.mask = mask;
   q.clock_out = g_clock_out;
@@ -426,8 +440,9 @@ kd_status check_buffers(const kd_loss_params* params, const void* h_t, const voi
 // be read in place depends on each teacher's hidden size, so the decision is taken here once: if any
 // teacher needs the re-packing path, all of them (and the student head) take it.  Also runs the parameter
 // checks of every teacher.
-kd_status multi_student_plan(const kd_loss_params* params, int n_teachers, const int64_t* H_t, bool& repack_hv) {
-  repack_hv = false;
+kd_status multi_call_plan(const kd_loss_params* params, int n_teachers, const int64_t* H_t, CallPlan& call) {
+  call.H_t = H_t;
+  call.n_teachers = n_teachers;
   for (int k = 0; k < n_teachers; ++k) {
     kd_loss_params pk = *params;
     pk.H_t = H_t[k];
@@ -437,9 +452,17 @@ kd_status multi_student_plan(const kd_loss_params* params, int n_teachers, const
     Problem q{};
     Layout L{};
     plan(&pk, q, L, true);
-    if (q.w_hv && !q.w_hv_inplace) repack_hv = true;
+    if (q.w_hv && !q.w_hv_inplace) call.repack_hv = true;
   }
   return KD_OK;
+}
+
+// The backward pass and the student operands are laid out by teacher 0's plan: every teacher's must agree with it.
+// (By construction they do; the size query and the call both ask.)
+bool same_student_plan(const Problem& a, const Layout& A, const Problem& b, const Layout& B) {
+  return A.common == B.common && A.dz == B.dz && A.h_sT == B.h_sT && A.gh32 == B.gh32 && A.prep_h_s == B.prep_h_s &&
+         A.prep_W_s == B.prep_W_s && a.w_hv_inplace == b.w_hv_inplace && a.prep_Ws == b.prep_Ws &&
+         a.prep_hs == b.prep_hs && a.V_c == b.V_c && a.strip == b.strip && a.n_split == b.n_split;
 }
 
 }  // namespace
@@ -554,20 +577,23 @@ kd_status kd_loss_workspace_size_multi(const kd_loss_params* params, int n_teach
                                        size_t* bytes) {
   if (!bytes || !params || !H_t) return KD_ERR_NULL;
   if (n_teachers < 1 || n_teachers > 16) return KD_ERR_PARAM;
-  bool repack_hv = false;
-  kd_status s = multi_student_plan(params, n_teachers, H_t, repack_hv);
+  CallPlan call;
+  kd_status s = multi_call_plan(params, n_teachers, H_t, call);
   if (s != KD_OK) return s;
-  size_t base = 0;                       // teacher blocks lie side by side after the common part
-  for (int k = 0; k < n_teachers; ++k) {
+  Problem q0{};
+  Layout L0{};
+  for (int k = 0; k < n_teachers; ++k) {  // teacher blocks lie side by side after the common part
     kd_loss_params pk = *params;
     pk.H_t = H_t[k];
     if (pk.flags & KD_FLAG_TEACHER_FP8) pk.teacher_scale = 1.f;   // the size does not depend on the scales
     Problem q{};
     Layout L{};
-    plan(&pk, q, L, true, base, repack_hv);
-    base = L.total;
+    plan(&pk, q, L, true, call);
+    if (k == 0) { q0 = q; L0 = L; }
+    if (!same_student_plan(q0, L0, q, L)) return KD_ERR_UNSUPPORTED;
+    call.teacher_base = L.total;
   }
-  *bytes = base;
+  *bytes = call.teacher_base;
   return KD_OK;
 }
 
@@ -584,12 +610,11 @@ kd_status kd_loss_fwd_bwd_multi(const kd_loss_params* params, int n_teachers, co
   // all checks for all teachers before the first launch
   Problem q[16];
   Layout L[16];
-  bool repack_hv = false;
+  CallPlan call;
   {
-    kd_status s = multi_student_plan(params, n_teachers, H_t, repack_hv);
+    kd_status s = multi_call_plan(params, n_teachers, H_t, call);
     if (s != KD_OK) return s;
   }
-  size_t base = 0;
   for (int k = 0; k < n_teachers; ++k) {
     if (!std::isfinite(weights[k])) return KD_ERR_PARAM;
     kd_loss_params pk = *params;
@@ -597,14 +622,10 @@ kd_status kd_loss_fwd_bwd_multi(const kd_loss_params* params, int n_teachers, co
     if (fp8) pk.teacher_scale = teacher_scales[k];
     q[k] = Problem{};
     kd_status s = check_buffers(&pk, h_t[k], W_t[k], h_s, W_s, mask, loss, workspace, workspace_bytes, true,
-                                grad_h_s, grad_W_s, q[k], L[k], base, repack_hv);
+                                grad_h_s, grad_W_s, q[k], L[k], call);
     if (s != KD_OK) return s;
-    // the backward pass and the student operands are laid out by teacher 0's plan: every teacher must agree
-    if (L[k].common != L[0].common || L[k].dz != L[0].dz || L[k].h_sT != L[0].h_sT || L[k].gh32 != L[0].gh32 ||
-        L[k].prep_h_s != L[0].prep_h_s || L[k].prep_W_s != L[0].prep_W_s || q[k].w_hv_inplace != q[0].w_hv_inplace ||
-        q[k].prep_Ws != q[0].prep_Ws || q[k].prep_hs != q[0].prep_hs || q[k].V_c != q[0].V_c)
-      return KD_ERR_UNSUPPORTED;
-    base = L[k].total;
+    if (!same_student_plan(q[0], L[0], q[k], L[k])) return KD_ERR_UNSUPPORTED;
+    call.teacher_base = L[k].total;
     q[k].per_token_loss = per_token_loss;
     q[k].out_weight *= weights[k];     // scales this teacher's loss and its share of dL/dz_s
     q[k].accumulate_loss = k > 0;
