@@ -112,6 +112,7 @@ struct CallPlan {
   int n_teachers = 1;
   size_t teacher_base = 0;         // where this teacher's block lies (0: right after the common part)
   bool repack_hv = false;          // [H][V] heads are re-packed even where they could be read in place
+  bool lean = false;               // the smallest workspace: the eight-wave loop with the fewest ranges of the vocabulary
 };
 
 // Contraction length of one operand as the kernels read it: fp32 is three bf16 products side by side.
@@ -153,19 +154,23 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   // reads the hidden states from a packed copy, so they are re-packed whether a mask is given or not.  With a single
   // token tile the heads stream through once, nothing is shared, and the smaller tiles of the eight-wave loop spread
   // better over the CUs: a step at T = 256 takes 1.16 ms there, 1.24 ms with strips; at T = 512 strips are ahead.
-  q.strip = !q.t_fp8 && !q.w_hv_inplace && q.n_tt > 1;
+  q.strip = !q.t_fp8 && !q.w_hv_inplace && q.n_tt > 1 && !call.lean;
   q.parts = q.strip ? 1 : 4;
   q.n_vt = (q.V + kd::kTileM - 1) / kd::kTileM;
-  // Vocabulary splits of the statistics passes.  The device picks the actual number once it knows
+  // Vocabulary ranges of the statistics passes.  The device picks the actual number once it knows
   // how many token tiles survive the mask; this is the upper bound the buffers are sized for:
   // enough to keep every CU busy with up to half of the tokens masked, and to even out the rounds
-  // of workgroups where there are many token tiles.
-  int ns = 2 * ((q.n_cu + q.n_tt - 1) / q.n_tt);
-  if (ns < 32) ns = 32;
-  if (ns > q.n_cu) ns = q.n_cu;          // a single token tile is split over all CUs
-  const int tiles_8w = (q.V + kd::kTileM - 1) / kd::kTileM, strips = (q.V + 63) / 64;   // shortest worthwhile ranges
-  const int split_room = ns < tiles_8w ? ns : tiles_8w;   // in fours of parts: covers the strip loop's ranges, too
-  q.n_split = !q.strip ? split_room : ns < strips ? ns : strips;
+  // of workgroups where there are many token tiles (65 of them: 31 ranges in eight full rounds, where eight ranges
+  // leave the last of three rounds nearly empty).  A lean plan leaves that last point out.
+  auto ranges = [&](int least) {
+    int ns = 2 * ((q.n_cu + q.n_tt - 1) / q.n_tt);
+    if (ns < least) ns = least;
+    return ns > q.n_cu ? q.n_cu : ns;      // a single token tile is split over all CUs
+  };
+  const int strips = (q.V + 63) / 64;      // shortest worthwhile ranges: 64 rows, or a tile of the eight-wave loop
+  const int lean_split = ranges(8) < q.n_vt ? ranges(8) : q.n_vt;
+  const int full_split = ranges(32) < q.n_vt ? ranges(32) : q.n_vt;
+  q.n_split = q.strip ? (ranges(32) < strips ? ranges(32) : strips) : call.lean ? lean_split : full_split;
   q.g_split = q.n_split;        // (bounded by the chunk's rows where it is used)
 
   int64_t logit_k = 0;
@@ -194,13 +199,14 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   L.rowmap = take((size_t)q.T_pad * 4);
   L.inv = take((size_t)q.T * 4);
   L.row_loss = take((size_t)q.T_pad * 4);
-  // partial sums per (vocabulary split, part of a workgroup, token): 5 statistics, 6 for AKL, whose
-  // search passes keep one sum per threshold.  Sized for the loop with more parts and longer copies, so that the
-  // workspace does not depend on the order in which the heads are stored
+  // partial sums per (vocabulary range, part of a workgroup, token): 5 statistics, 6 for AKL, whose
+  // search passes keep one sum per threshold.  A strip range leaves one part, an eight-wave one four: what a lean plan
+  // needs (at least 32 parts, four for every two strips) holds the strip loop's up to 32 ranges and more, too.
   const int part_vals = q.kind == KD_AKL ? kd::kAklThresholds : 5;
-  L.partials = take((size_t)split_room * 4 * part_vals * q.T_pad * 4);
+  const int parts = 4 * (q.strip ? lean_split : q.n_split);
+  L.partials = take((size_t)parts * part_vals * q.T_pad * 4);
   L.prep_h_t = L.prep_W_t = L.prep_h_s = L.prep_W_s = 0;
-  const size_t h_rows = q.T_pad;
+  const size_t h_rows = q.strip ? q.T_pad : q.T;         // the strip loop reads whole token tiles of packed rows
   if (q.prep_hs) L.prep_h_s = take(h_rows * q.K_s * 2);
   if (q.prep_Ws) L.prep_W_s = take((size_t)q.V * q.K_s * 2);
   if (with_backward) {
@@ -530,23 +536,37 @@ kd_status kd_loss_fwd_bwd_static(const kd_loss_params* params, const void* h_t, 
                                  void* grad_h_s, void* grad_W_s, void* hip_stream) {
   kd_status s = check_params(params);
   if (s != KD_OK) return s;
-  // the plan: the caller's chunk, else the widest one that fits the array
+  // the plan: the caller's chunk, else the widest one that fits the array; at each width a lean plan before the next
+  // narrower one
   kd_loss_params pp = *params;
-  Problem q{};
-  Layout L{};
-  plan(&pp, q, L, true);
-  if (L.total > KD_STATIC_SCRATCH_BYTES && params->vocab_chunk == 0) {
-    for (int vc = 1 << 19; vc >= 256 && L.total > KD_STATIC_SCRATCH_BYTES; vc >>= 1) {
+  CallPlan call;
+  auto fits = [&]() {
+    for (int lean = 0; lean < 2; ++lean) {
+      Problem q{};
+      Layout L{};
+      call.lean = lean != 0;
+      plan(&pp, q, L, true, call);
+      if (L.total <= KD_STATIC_SCRATCH_BYTES) return true;
+    }
+    return false;
+  };
+  bool fit = fits();
+  if (!fit && params->vocab_chunk == 0) {
+    Problem q{};
+    Layout L{};
+    plan(params, q, L, true);
+    for (int vc = 1 << 19; vc >= 256 && !fit; vc >>= 1) {
       if (vc >= q.V_c) continue;
       pp.vocab_chunk = vc;
-      plan(&pp, q, L, true);
+      fit = fits();
     }
   }
-  if (L.total > KD_STATIC_SCRATCH_BYTES) return KD_ERR_TOO_LARGE;
+  if (!fit) return KD_ERR_TOO_LARGE;
   // every remaining host-side check, with a stand-in for the scratch address (nothing is dereferenced)
-  q = Problem{};
+  Problem q{};
+  Layout L{};
   s = check_buffers(&pp, h_t, W_t, h_s, W_s, mask, loss, reinterpret_cast<void*>(uintptr_t{256}),
-                    KD_STATIC_SCRATCH_BYTES, true, grad_h_s, grad_W_s, q, L);
+                    KD_STATIC_SCRATCH_BYTES, true, grad_h_s, grad_W_s, q, L, call);
   if (s != KD_OK) return s;
   // device address of this GPU's copy of the array, looked up once per device
   static void* ptr_of_device[64];
@@ -564,7 +584,8 @@ kd_status kd_loss_fwd_bwd_static(const kd_loss_params* params, const void* h_t, 
   }
   void* const ptr = ptr_of_device[dev];
   q = Problem{};
-  s = check_buffers(&pp, h_t, W_t, h_s, W_s, mask, loss, ptr, KD_STATIC_SCRATCH_BYTES, true, grad_h_s, grad_W_s, q, L);
+  s = check_buffers(&pp, h_t, W_t, h_s, W_s, mask, loss, ptr, KD_STATIC_SCRATCH_BYTES, true, grad_h_s, grad_W_s, q, L,
+                    call);
   if (s != KD_OK) return s;
   q.per_token_loss = per_token_loss;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);

@@ -52,6 +52,26 @@ def run_oracle(cfg, data):
     return ref
 
 
+def few_tokens(cfg, keep):
+    """Inputs with `keep` tokens that count, the first and the last among them; the same with those tokens alone, as the
+    oracle can take them where T is large; and their indices."""
+    data = I.generate(cfg)
+    data["mask"] = np.zeros(cfg.T, dtype=np.uint8)
+    rng = np.random.default_rng(cfg.T)
+    idx = np.sort(np.concatenate([[0, cfg.T - 1], 1 + rng.permutation(cfg.T - 2)[:keep - 2]]))
+    data["mask"][idx] = 1
+    return data, dict(data, h_t=data["h_t"][idx], h_s=data["h_s"][idx], mask=np.ones(keep, dtype=np.uint8)), idx
+
+
+def spread_tokens(ref, idx, T):
+    """The oracle's per-token outputs for the tokens `idx`, with zeros for all others."""
+    out = dict(ref)
+    for k in ("per_token_loss", "grad_h_s"):
+        out[k] = np.zeros((T,) + np.shape(ref[k])[1:])
+        out[k][idx] = ref[k]
+    return out
+
+
 def tvd_tie_allowance(cfg, data, rel_gap=2e-5):
     """TVD's gradient carries sign(p_s - p_t): where the two probabilities agree to within fp32
     rounding of the logits, either sign is a valid subgradient and the two sides may pick different

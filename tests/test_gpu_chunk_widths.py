@@ -11,23 +11,6 @@ from tests import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 
-def _masked(cfg, keep):
-    """Inputs with `keep` tokens that count, the first and the last among them, and the oracle's view of those alone."""
-    data = I.generate(cfg)
-    data["mask"] = np.zeros(cfg.T, dtype=np.uint8)
-    rng = np.random.default_rng(cfg.T)
-    idx = np.sort(np.concatenate([[0, cfg.T - 1], 1 + rng.permutation(cfg.T - 2)[:keep - 2]]))
-    data["mask"][idx] = 1
-    few = dict(data, h_t=data["h_t"][idx], h_s=data["h_s"][idx], mask=np.ones(keep, dtype=np.uint8))
-    return data, few, idx
-
-
-def _spread(ref, idx, T):
-    full = lambda x: np.concatenate([x, np.zeros((T - len(idx),) + x.shape[1:])])[np.argsort(
-        np.concatenate([idx, np.setdiff1d(np.arange(T), idx)]))]
-    return dict(ref, per_token_loss=full(ref["per_token_loss"]), grad_h_s=full(ref["grad_h_s"]))
-
-
 def _chunks(cfg):
     from paper_2603_01875_amd import kdloss as K
     vc, _ = K.kd_loss_plan_info(K.make_params(cfg.T, cfg.H_t, cfg.H_s, cfg.V, cfg.kind, cfg.tau, cfg.beta))
@@ -42,8 +25,8 @@ def _chunks(cfg):
 def test_chosen_widths(T, H_t, H_s, V, keep, kind):
     cfg = I.scaled(I.workload("fkl_bf16"), batch=1, seq=T, H_t=H_t, H_s=H_s, V=V, kind=kind, w_t_std=0.1)
     assert _chunks(cfg) > 1
-    data, few, idx = _masked(cfg, keep)
-    ref = _spread(G.run_oracle(cfg, few), idx, T)
+    data, few, idx = G.few_tokens(cfg, keep)
+    ref = G.spread_tokens(G.run_oracle(cfg, few), idx, T)
     G.check(G.run_gpu(cfg, data), ref, f"T={T} H={H_t},{H_s} V={V}")
 
 
@@ -56,7 +39,7 @@ def test_teachers_of_different_width_in_chosen_chunks(T, V, H_s, H_ts):
     base = I.scaled(I.workload("fkl_bf16"), batch=1, seq=T, H_t=H_ts[0], H_s=H_s, V=V, w_t_std=0.1)
     weights = [0.5, 0.3, 0.2][:len(H_ts)]
     weights[-1] = 1.0 - sum(weights[:-1])
-    data, few, idx = _masked(base, 90)
+    data, few, idx = G.few_tokens(base, 90)
     h_t, W_t, ref = [], [], None
     for k, H in enumerate(H_ts):
         cfg = I.scaled(I.workload("fkl_bf16"), batch=1, seq=T, H_t=H, H_s=H_s, V=V, w_t_std=0.1)
@@ -68,7 +51,7 @@ def test_teachers_of_different_width_in_chosen_chunks(T, V, H_s, H_ts):
         part = {n: weights[k] * r[n] for n in ("loss", "per_token_loss", "grad_h_s", "grad_W_s")}
         ref = part if ref is None else {n: ref[n] + part[n] for n in part}
     dev = lambda k: G.to_device(data[k], I.BF16)
-    ref = _spread(ref, idx, T)
+    ref = G.spread_tokens(ref, idx, T)
     mask = torch.from_numpy(data["mask"]).cuda()
     h_s, W_s = dev("h_s"), dev("W_s")
     for order in (slice(None), slice(None, None, -1)):

@@ -47,3 +47,35 @@ def test_one_teacher_plans_as_the_plain_call():
     for T, V in ((100, 4096), (700, 50264), (2048, 151936), (8192, 32000)):
         p = K.make_params(T, 2048, 512, V)
         assert _multi_size(p, (2048,))[1] == K.kd_loss_workspace_size(p)
+
+
+# T, H_t, H_s, V, kind, [H,V] heads, fp32, fp8 teacher, the caller's chunk
+FIT_THE_STATIC_ARRAY = [
+    (6144, 3584, 768, 32000, 6, 0, 0, 0, 0), (8192, 2048, 512, 128256, 6, 0, 0, 0, 0), (10934, 2176, 704, 115968, 0, 0, 0, 0, 0),
+    (32768, 256, 256, 32000, 0, 0, 0, 0, 0), (32768, 64, 64, 32000, 6, 0, 0, 0, 0), (257, 65536, 24576, 256, 0, 0, 0, 0, 0),
+    (31234, 128, 16, 89272, 4, 1, 0, 0, 256), (28889, 192, 128, 7144, 2, 0, 0, 0, 1024), (1060, 44216, 64, 240, 1, 1, 0, 0, 0),
+    (61676, 24, 24, 6560, 5, 1, 0, 0, 256), (41261, 64, 48, 26536, 0, 0, 1, 0, 0), (28652, 640, 192, 114192, 0, 0, 0, 0, 256),
+    (17295, 2048, 232, 13808, 2, 0, 0, 1, 1024), (11477, 768, 1024, 145928, 0, 0, 0, 1, 256), (52484, 256, 24, 11480, 5, 0, 0, 1, 0),
+    (59165, 384, 24, 11168, 1, 1, 0, 1, 0), (31648, 256, 128, 28064, 1, 1, 0, 0, 0), (1429, 32, 10768, 296, 3, 0, 0, 0, 256),
+    (28, 52408, 96, 224, 3, 0, 1, 0, 0), (1, 56368, 128, 1112, 0, 0, 0, 0, 0), (7, 62568, 3344, 784, 4, 0, 0, 0, 0),
+    (20, 1536, 192, 66672, 0, 1, 0, 1, 1024), (9137, 128, 1088, 6696, 1, 1, 0, 1, 1024), (3775, 1832, 1920, 80, 5, 1, 1, 0, 0),
+    (612, 160, 12048, 416, 1, 0, 1, 0, 256), (12687, 576, 448, 11520, 6, 1, 0, 0, 0), (19162, 32, 16, 33128, 6, 0, 1, 0, 256),
+]
+
+
+@pytest.mark.parametrize("T, H_t, H_s, V, kind, hv, f32, fp8, chunk", FIT_THE_STATIC_ARRAY)
+def test_calls_that_fit_the_static_array(T, H_t, H_s, V, kind, hv, f32, fp8, chunk):
+    """Sizes near the limit of the static array, where only the smallest partial sums and copies fit: many tokens, or
+    few tokens of wide hidden states; every layout and type."""
+    p = K.make_params(T, H_t, H_s, V, kind, beta=0.5, w_layout=K.W_HV if hv else K.W_VH, in_dtype=K.F32 if f32 else K.BF16,
+                      flags=K.FLAG_TEACHER_FP8 if fp8 else 0, teacher_scale=1.0 if fp8 else 0.0, vocab_chunk=chunk)
+    args = [None] + FAKE
+    assert K.lib().kd_loss_fwd_bwd_static(ctypes.byref(p), *args, None) == NULL
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(kind=K.AKL), dict(w_layout=K.W_HV), dict(flags=K.FLAG_TEACHER_FP8, teacher_scale=1.0)])
+def test_few_tokens_need_few_rows(kw):
+    """Below a token tile the copies of the hidden states have the rows that there are, not a tile's."""
+    n = [K.kd_loss_workspace_size(K.make_params(T, 65536, 64, 256, beta=0.5, **kw)) for T in (1, 101, 201)]
+    es = 1 if "flags" in kw else 2
+    assert n[1] - n[0] >= 100 * 65536 * es and n[2] - n[1] >= 100 * 65536 * es and n[0] < 4 << 20
