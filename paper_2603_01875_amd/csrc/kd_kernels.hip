@@ -1290,7 +1290,7 @@ __global__ void transpose_rows_kernel(const E* src, int C, bf16_t* dst, int R_pa
 __global__ void pack_rows_kernel(const void* src, int src_f32, int H, bf16_t* dst, int K, const int* rowmap,
                                  const int* meta) {
   const int lane = threadIdx.x & 63, blk = threadIdx.x >> 6;
-  const int kb = blockIdx.x, panel = blockIdx.y;
+  const int kb = blockIdx.x, panel = blockIdx.z * gridDim.y + blockIdx.y;
   const int j = panel * 64 + 16 * blk + (lane & 15), k0 = 32 * kb + 8 * (lane >> 4);
   bf16x8 v;
 #pragma unroll
@@ -1718,7 +1718,10 @@ hipError_t launch_transpose_rows(const Problem& p, hipStream_t st) {
 }
 
 hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst, int K, hipStream_t st) {
-  hipLaunchKernelGGL(pack_rows_kernel, dim3(K / 32, p.T_pad / 64), dim3(256), 0, st, src, p.in_f32, H, (bf16_t*)dst, K,
+  // (neighbouring workgroups share rows, so the panels stay on the slow axis; 2^22 tokens are 65536 of them, one more
+  // than an axis other than the first takes, and a multiple of 4 always)
+  const int panels = p.T_pad / 64, z = panels > 32768 ? 2 : 1;
+  hipLaunchKernelGGL(pack_rows_kernel, dim3(K / 32, panels / z, z), dim3(256), 0, st, src, p.in_f32, H, (bf16_t*)dst, K,
                      p.rowmap, p.meta);
   return hipGetLastError();
 }
