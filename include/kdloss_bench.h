@@ -38,6 +38,10 @@ int kd_loss_profile_count(void);
  * nominal 2.4 GHz for these kernels).  Host only. */
 kd_status kd_loss_profile_clock(void* two_int64_device);
 
+/* Which loop makes the logit tiles of a call with these params: 0 = the eight-wave loop (stats_kernel, rows_kernel,
+ * grad_kernel), 1 = the strip loop (stats_strip_kernel, ...).  Host only. */
+kd_status kd_loss_plan_loop(const kd_loss_params* params, int32_t* loop);
+
 /* Benchmark aid, not part of the method: what the bf16 matrix pipe sustains on this GPU with nothing
  * else going on.  One launch of 256 workgroups x 8 waves (the occupancy of the logit kernels), each wave
  * issuing `iters` x 8 independent MFMA 32x32x16 on operands taken from `operands` (device, 128 KiB of

@@ -115,6 +115,35 @@ struct CallPlan {
   bool lean = false;               // the smallest workspace: the eight-wave loop with the fewest ranges of the vocabulary
 };
 
+// Whether the strip loop (192-row tiles) or the eight-wave loop (128-row tiles) makes the logit tiles.
+//  - A contracted element costs the strip loop 0.91 of what it costs the other, but its one wave per SIMD has nothing to
+//    hide a tile's epilogue behind: that costs as much as 100 more elements (FKL, RKL), 200 (the row pass of JSD, TVD and
+//    the skewed KLs) or 300 (AKL, whose four search passes contract the teacher's elements alone).
+//  - The gradient kernel walks whole tiles in rounds of n_cu workgroups; the passes before it even out over ranges of the
+//    vocabulary, down to a tile each.
+// Measured over 1178 sizes, T = 257 .. 16384 and V = 256 .. 151936 (steps, eight waves against strips): T = 512, H_t = 8192,
+// H_s = 512, V = 512 189 against 250 us; T = 4096, H = 2048 / 1024, V = 4096 292 against 323 us and V = 100000 6.00 against
+// 5.86 ms; T = 4096, H = 256 / 128, V = 151936 2.28 against 2.40 ms; T = 2048, H = 4096 / 1024, V = 151936 6.74 against
+// 6.23 ms.  Where the two are close the rule may take the slower one: 0.2 % is lost on average over these sizes, 7 % at
+// most.  A forward pass alone takes the same loop (0.5 % on average; the few calls with more than 10 % run one or two rounds
+// of workgroups, which its ranges fill unevenly).
+// One token tile: the heads stream through once, nothing is shared, and the smaller tiles spread better over the CUs
+// (T = 256, V = 151936 1.16 against 1.24 ms).
+// `logit_k`: the contraction of one logit of all models, summed over the call's teachers.
+bool strips_ahead(const Problem& q, int n_teachers, int64_t logit_k) {
+  if (q.n_tt < 2) return false;
+  double k = (double)logit_k / n_teachers;
+  if (q.kind == KD_AKL) k -= q.K_s * 4. / 7.;                 // mean over its seven passes
+  const double epilogue = q.kind == KD_AKL ? 300. : q.kind >= KD_JSD ? 200. : 100.;
+  const int spread = q.kind == KD_AKL ? 6 : q.kind >= KD_JSD ? 2 : 1;
+  auto rounds = [&](int rows) {
+    const int64_t tiles = (int64_t)q.n_tt * ((q.V + rows - 1) / rows);
+    const double even = (double)tiles / q.n_cu;
+    return (double)((tiles + q.n_cu - 1) / q.n_cu) + spread * (even > 1. ? even : 1.);
+  };
+  return rounds(192) * 192. * (0.91 * k + epilogue) < rounds(kd::kTileM) * kd::kTileM * k;
+}
+
 // Contraction length of one operand as the kernels read it: fp32 is three bf16 products side by side.
 inline int64_t contraction(bool f32, int64_t H) { return round_up(f32 ? 3 * H : H, 64); }
 
@@ -150,11 +179,14 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   q.prep_ht = q.prep_hs = 1;
   q.T_pad = (int)round_up(q.T, kd::kTileN);
   q.n_tt = q.T_pad / kd::kTileN;
-  // The strip loop takes bf16 operands with [V][K] heads (in place or re-packed) and more than one token tile.  It
-  // reads the hidden states from a packed copy, so they are re-packed whether a mask is given or not.  With a single
-  // token tile the heads stream through once, nothing is shared, and the smaller tiles of the eight-wave loop spread
-  // better over the CUs: a step at T = 256 takes 1.16 ms there, 1.24 ms with strips; at T = 512 strips are ahead.
-  q.strip = !q.t_fp8 && !q.w_hv_inplace && q.n_tt > 1 && !call.lean;
+  int64_t logit_k = 0;       // elements contracted for one logit of every model of the call
+  for (int i = 0; i < call.n_teachers; ++i) {
+    const int64_t K_t = contraction(q.in_f32, call.H_t ? call.H_t[i] : p->H_t);
+    logit_k += q.K_s + (q.t_fp8 ? K_t / 2 : K_t);        // (an e4m3 element costs half a bf16 one)
+  }
+  // The strip loop takes bf16 operands with [V][K] heads (in place or re-packed).  It reads the hidden states from a
+  // packed copy, so they are re-packed whether a mask is given or not.
+  q.strip = !q.t_fp8 && !q.w_hv_inplace && !call.lean && strips_ahead(q, call.n_teachers, logit_k);
   q.parts = q.strip ? 1 : 4;
   q.n_vt = (q.V + kd::kTileM - 1) / kd::kTileM;
   // Vocabulary ranges of the statistics passes.  The device picks the actual number once it knows
@@ -173,11 +205,6 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   q.n_split = q.strip ? (ranges(32) < strips ? ranges(32) : strips) : call.lean ? lean_split : full_split;
   q.g_split = q.n_split;        // (bounded by the chunk's rows where it is used)
 
-  int64_t logit_k = 0;
-  for (int i = 0; i < call.n_teachers; ++i) {
-    const int64_t K_t = contraction(q.in_f32, call.H_t ? call.H_t[i] : p->H_t);
-    logit_k += q.K_s + (q.t_fp8 ? K_t / 2 : K_t);        // (an e4m3 element costs half a bf16 one)
-  }
   const int64_t v_all = round_up(q.V, 256);
   const int64_t vc = p->vocab_chunk > 0 ? p->vocab_chunk : choose_chunk(q, v_all, logit_k);  // (the caller's: a multiple of 256)
   q.V_c = (int)(vc < v_all ? vc : v_all);
@@ -499,6 +526,17 @@ kd_status kd_loss_plan_info(const kd_loss_params* params, int64_t* vocab_chunk, 
   if (n_launches)
     *n_launches = 1 + (q.prep_ht + q.prep_Wt + q.prep_hs + q.prep_Ws) + 2 + (q.kind >= KD_JSD ? 2 : 0) +
                   (q.kind == KD_AKL ? 2 * kd::kAklSearchPasses : 0) + 1 + 1 + chunks * 3 + 1;
+  return KD_OK;
+}
+
+kd_status kd_loss_plan_loop(const kd_loss_params* params, int32_t* loop) {
+  if (!loop) return KD_ERR_NULL;
+  kd_status s = check_params(params);
+  if (s != KD_OK) return s;
+  Problem q{};
+  Layout L{};
+  plan(params, q, L, true);
+  *loop = q.strip;
   return KD_OK;
 }
 

@@ -62,6 +62,8 @@ def lib():
         L.kd_loss_workspace_size.restype = ctypes.c_int
         L.kd_loss_plan_info.argtypes = [P, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int64)]
         L.kd_loss_plan_info.restype = ctypes.c_int
+        L.kd_loss_plan_loop.argtypes = [P, ctypes.POINTER(ctypes.c_int32)]
+        L.kd_loss_plan_loop.restype = ctypes.c_int
         L.kd_loss_fwd_bwd.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.kd_loss_fwd_bwd.restype = ctypes.c_int
         L.kd_loss_fwd_bwd_static.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
@@ -141,6 +143,15 @@ def kd_loss_plan_info(params: KdLossParams):
     if st != KD_OK:
         raise KdLossError(st)
     return int(vc.value), int(nl.value)
+
+
+def kd_loss_plan_loop(params: KdLossParams):
+    """0: the eight-wave loop makes the logit tiles of such a call; 1: the strip loop."""
+    loop = ctypes.c_int32(0)
+    st = lib().kd_loss_plan_loop(ctypes.byref(params), ctypes.byref(loop))
+    if st != KD_OK:
+        raise KdLossError(st)
+    return int(loop.value)
 
 
 PROF_STATS, PROF_ROWS, PROF_GRAD, PROF_GEMM_GRAD_W, PROF_GEMM_GRAD_H = range(5)

@@ -1,6 +1,7 @@
-"""The strip loop (192 x 256 logit tiles on packed hidden states) where it can go wrong: one k-step and odd numbers
-of k-steps per phase, last vocabulary tiles of 8 .. 192 rows, chunks that 192 does not divide, one row more or less
-than a token tile, token tiles that fours do not divide, fewer vocabulary tiles than splits, fp32 and padded operands.
+"""Small sizes at the edges of the strip loop's tiles (192 x 256 logit tiles): one k-step and odd numbers of k-steps
+per phase, last vocabulary tiles of 8 .. 192 rows, chunks that 192 does not divide, one row more or less than a token tile,
+token tiles that fours do not divide, fewer vocabulary tiles than splits, fp32 and padded operands.  As small as they are,
+the library gives them to the eight-wave loop; test_gpu_strip_reach.py has the same edges at sizes that reach the strip loop.
 Against the fp64 oracle with the tolerances of the other parity tests."""
 import numpy as np
 import pytest
@@ -30,7 +31,7 @@ def test_strip_loop_edges(T, H_t, H_s, V, kind, chunk, dtype):
 
 
 def test_strip_loop_adds_the_teachers_of_a_call():
-    """The gradient kernel's adding form, on a chunk that 192 does not divide: two equal halves of one teacher."""
+    """The gradient kernel's adding form, on chunks that 192 does not divide: two equal halves of one teacher."""
     from paper_2603_01875_amd import kdloss as K
     cfg = I.scaled(I.workload("fkl_bf16"), batch=1, seq=300, H_t=128, H_s=64, V=1096, w_t_std=0.1)
     data = I.generate(cfg)
