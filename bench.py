@@ -267,11 +267,12 @@ def main():
 
     # HBM-side traffic of one statistics launch: NOT measured in this run (it needs rocprofv3 --pmc); the value
     # stored with its command under profiles/ is passed through and labelled as such
+    stats_kernel = "stats_strip_kernel" if K.kd_loss_plan_loop(p) else "stats_kernel"
     traffic, traffic_source = None, None
     if os.path.exists(args.traffic_file) and not args.teacher_fp8 and not hv:
         try:
             rec = json.load(open(args.traffic_file)).get(args.workload, {})
-            traffic = rec.get("stats_kernel_bytes")
+            traffic = rec.get(stats_kernel + "_bytes")
             traffic_source = "stored: " + rec.get("source", os.path.relpath(args.traffic_file, ROOT))
         except Exception:
             traffic = None
@@ -286,7 +287,7 @@ def main():
         "config": {"workload": args.workload, "T": T, "H_t": H_t, "H_s": H_s, "V": V,
                    "kind": {0: "fkl", 1: "rkl", 2: "jsd", 3: "tvd", 4: "skew_fkl", 5: "skew_rkl"}[cfg.kind], "tau": cfg.tau, "beta": cfg.beta,
                    "valid_tokens": n_valid, "computed_token_rows": T_comp, "w_layout": args.w_layout.upper(), "teacher_fp8": bool(args.teacher_fp8), "vocab_chunk": vc, "launches_per_step": n_launch},
-        "roofline": {"bound": "mfma", "kernel": "stats_kernel", "achieved": stats_tflops,
+        "roofline": {"bound": "mfma", "kernel": stats_kernel, "achieved": stats_tflops,
                      "peak": peak, "unit": "TFLOP/s", "frac": stats_tflops / peak,
                      "traffic": traffic, "traffic_source": traffic_source,
                      "launch_ms": stats_avg, "flop_per_launch": logit_flop,
