@@ -83,7 +83,7 @@ typedef enum { KD_BF16 = 0, KD_F32 = 1 } kd_dtype;
  * The same order applies to W_t, W_s and grad_W_s.  KD_W_VH is the faster one (both logit operands
  * contiguous along the contraction; about 5 % ahead).  KD_W_HV heads are read in place when they are
  * bf16 with H_t, H_s and V multiples of 64; otherwise they are re-packed into the workspace (which then
- * holds copies of both heads) by a slow strided pass, a fallback for small problems.  grad_W_s is written
+ * holds copies of both heads) by a transposing pass on every call.  grad_W_s is written
  * in the caller's order either way.  With the fp8 teacher, KD_W_HV heads always take the re-packing path
  * (better: quantise the frozen head from a [V,H] copy once and pass KD_W_VH). */
 typedef enum { KD_W_HV = 0, KD_W_VH = 1 } kd_wlayout;
@@ -136,10 +136,12 @@ typedef struct {
  * (Footnote of Sec. 1: shipping full logits would take about 160 GB per global
  * batch, 2 T V bytes per T tokens; this is what the recomputation needs instead.)
  * Host only.  The size is O(T * V_c + H_s * V_c + T * (H_t + H_s)) for a vocabulary
- * chunk V_c chosen by the library (a few thousand columns) - staging of dL/dz_s,
- * fp32 sums of grad_h_s, compacted copies of the hidden states - plus copies of
- * the heads only when they must be re-packed (fp32 inputs, hidden sizes that are
- * not multiples of 64).  It never grows like T * V.  Returns KD_OK or the status kd_loss_fwd_bwd would return for
+ * chunk V_c chosen by the library - staging of dL/dz_s, fp32 sums of grad_h_s,
+ * compacted copies of the hidden states - plus copies of the heads only when they
+ * must be re-packed (fp32 inputs, hidden sizes that are not multiples of 64).  The
+ * staging buffer (2 T V_c bytes, T rounded up to 256) takes at most 208 MiB below
+ * 4096 tokens, which may be the whole vocabulary; from there on at most 16384
+ * columns and 512 MiB, or 1024 columns.  It never grows like T * V.  Returns KD_OK or the status kd_loss_fwd_bwd would return for
  * the same params. */
 kd_status kd_loss_workspace_size(const kd_loss_params* params, size_t* bytes);
 
@@ -177,7 +179,8 @@ kd_status kd_loss_fwd_bwd(const kd_loss_params* params,
  * is a static device array of KD_STATIC_SCRATCH_BYTES inside the library (each GPU the library runs on
  * holds its own copy until the process ends).  The call allocates and frees nothing.
  *  - With params->vocab_chunk == 0 the library picks the widest vocabulary chunk whose plan fits the
- *    array; with a chunk given, that plan must fit.  A problem that does not fit returns
+ *    array; with a chunk given, that plan must fit.  Near the limit it takes a lean plan (fewer partial
+ *    sums, the logit loop with the smaller copies) before a narrower chunk.  A problem that does not fit returns
  *    KD_ERR_TOO_LARGE and enqueues nothing (the headline workload, T = 4096, H_t = 4096, H_s = 1024,
  *    V = 151936, fits; T = 32768 with H_s = 4096 does not).
  *  - The array's address is looked up on the first call on each device (current device = the stream's);

@@ -63,8 +63,9 @@ kd_status check_params(const kd_loss_params* p) {
 // kernel and read back by both products, so it should stay in the 256 MB last-level cache together with the operands;
 // but every chunk also re-reads and re-writes the fp32 sums of grad_h_s, so with many tokens a chunk of at least 8192
 // columns wins as long as the staging buffer stays within 512 MiB.
-//  - From 4096 tokens on a power of two within 128 MiB (16384 columns at T = 4096: the workspace stays far from a
-//    [T, V] tensor), at least 8192 columns.
+//  - From 4096 tokens on a power of two within 128 MiB, at least 8192 columns.  (Nothing in the kernels asks for the line
+//    to lie at 4096: 24576 columns there, 201 MB, measured 11.72 against 12.25 ms without a mask.  What holds the width at
+//    16384 is the bound on the workspace of that size in tests/test_abi_host.py.)
 //  - Below, up to 208 MiB (201 MB still stays in the cache), and the width decides how full the last rounds of
 //    workgroups are: the candidates (multiples of the tile heights) are priced by the rounds of the gradient kernel,
 //    with all tokens and with an eighth of them masked, and of the grad_W_s product.  Measured steps: T = 3584 10.60 ms
@@ -424,7 +425,7 @@ kd_status run_backward(const Problem* qs, int n_teachers, hipStream_t st) {
     }
     if (!q.w_hv_inplace) {
       // grad_h_s[t][h] += sum_v W_s[v][h] dz[t][v]   (the [V][K] head read vocabulary-major as it lies; dz is
-      // zero from the chunk's last valid column to the end of its 128-column tile)
+      // zero from the chunk's last valid column to the next multiple of 64, where the product's last k-step ends)
       gh.A = static_cast<const char*>(q.W_s) + (size_t)v0 * q.K_s * 2; gh.lda = q.K_s; gh.M = q.H_s;
       gh.k_major = 1; gh.k_rows = width;
     } else {

@@ -727,9 +727,9 @@ struct SearchEpi {
 };
 
 // ------------------------------------------------------------------------------------------
-// logit kernels: the strip loop for bf16 operands with [V][H] heads and more than one token tile; the eight-wave tile
-// loop where the heads are read in place as [H][V] (k-major fragments come from LDS by transposing reads), the
-// teacher is fp8, or there is one token tile
+// logit kernels: the strip loop for bf16 operands with [V][H] heads where it is ahead (strips_ahead in kd_api.hip); the
+// eight-wave tile loop for the others, where the heads are read in place as [H][V] (k-major fragments come from LDS by
+// transposing reads), and where the teacher is fp8
 // ------------------------------------------------------------------------------------------
 #define KD_LOGIT_KERNEL __global__ __launch_bounds__(LCfg::NT)
 #define KD_GEMM_KERNEL __global__ __launch_bounds__(GCfg::NT)
@@ -1023,12 +1023,12 @@ __global__ void rowmap_kernel(const uint8_t* mask, int T, int T_pad, int n_cu, S
   }
 }
 
-// Merging the partial sums.  Every (vocabulary split, quarter workgroup) leaves its values as [part][value][T_pad],
-// and with few tokens there are many parts (up to 1024 at T <= 256).  A merge is bound by the latency of its loads:
+// Merging the partial sums.  Every part (one per vocabulary range in the strip loop, four in the eight-wave loop) leaves
+// its values as [part][value][T_pad], and with few tokens there are many parts (up to 1024 at T <= 256).  A merge is bound by the latency of its loads:
 // one thread walking all the parts of a token took 658 us at T = 256 and 47 us at T = 4096.  So a workgroup owns TX
 // tokens and NT / TX threads share the parts of each: lanes run along the tokens (TX = 8: 32-byte runs, TX = 32:
 // whole lines), the rest of the lanes and the waves along the parts; partial results meet by shuffles, then through
-// LDS, in a fixed order.  Measured: combine_kernel 658 -> 23 us at T = 256, 47 -> 10 us at 128 parts and fewer,
+// LDS, in a fixed order.  Measured: combine_kernel 658 -> 23 us at T = 256, 47 -> 9 us at 128 parts, 6 us at the strip loop's 32 (T = 4096),
 // one search merge of AKL 536 -> 15 us at T = 2048.
 struct MergeSum {
   static __device__ __forceinline__ float op(float a, float b) { return a + b; }
@@ -1787,8 +1787,9 @@ hipError_t launch_quantize_e4m3(const void* src, int src_f32, int64_t n, float i
 #define KD_STR2(...) #__VA_ARGS__
 #define KD_STR(...) KD_STR2(__VA_ARGS__)
 const char* build_info() {
-  return "logit tile cfg (MI,NI,WN,BK,NST) = " KD_STR(KD_LOGIT_CFG) "; product tile cfg = " KD_STR(KD_GEMM_CFG)
-         "; ablation = " KD_STR(KD_ABLATE);
+  static_assert(StripCfg::BM == 192 && StripCfg::NT == 256 && StripCfg::NST == 3, "as named below");
+  return "logit tile cfg (MI,NI,WN,BK,NST) = " KD_STR(KD_LOGIT_CFG) "; strip loop = 192 x 256 tiles, 4 waves, 3 stages"
+         "; product tile cfg = " KD_STR(KD_GEMM_CFG) "; ablation = " KD_STR(KD_ABLATE);
 }
 int build_ablation() { return KD_ABLATE; }
 

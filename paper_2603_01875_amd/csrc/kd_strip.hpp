@@ -13,8 +13,11 @@
 //
 // Two such accumulators are 384 registers.  The student's tile is built first and set aside while the teacher's is
 // built: 16 of its 48 blocks are accumulated in vector registers, 12 in accumulation registers, and stay there; the
-// other 20 are accumulated in accumulation registers and parked in LDS.  MFMAs are inline assembly so that each accumulator stays in the register file
-// it was given; the compiler's own choice copies them around inside the loop.
+// other 20 are accumulated in accumulation registers and parked in LDS.  MFMAs are inline assembly so that each
+// accumulator stays in the register file it was given; the compiler's own choice copies them around inside the loop.
+// With the B ring and the fragments the 512 registers do not quite hold what an epilogue needs: 1 to 33 of them are
+// spilled between tiles and in epilogues (up to 132 bytes of scratch per lane, under a hundred scratch instructions in a
+// kernel), none inside a k-loop.
 //
 // Operands are described in bytes per row: a sub-step is 64 bytes of every row (32 bf16), a k-step two sub-steps.
 #pragma once
@@ -224,8 +227,9 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, const int
         for (int j = 0; j < NB; ++j) { const u32x4 t = B[s][j]; B[s][j] = B[2 + s][j]; B[2 + s][j] = t; }
     }
   };
-  // Rows that a tile does not have start at `pad`, a huge negative logit that the finite product of
-  // the clamped row cannot move: their exponentials are 0 and their dL/dz comes out 0, with no test per element.
+  // Rows that a tile does not have start at `pad`, a huge negative logit: they end that far below the row that their
+  // clamped loads repeat, which is one of the same range, so that beside it their exponentials are 0 and their dL/dz comes
+  // out 0, with no test per element (up to logits of 1e30 in size, where the two can no longer be told apart).
   auto first = [&](auto nmc, int rows, float pad, auto&& set) {
     constexpr int NM = decltype(nmc)::value;
     if (rows == 16 * NM) {
