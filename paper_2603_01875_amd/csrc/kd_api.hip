@@ -85,11 +85,11 @@ int64_t choose_chunk(const Problem& q, int64_t v_all, int64_t logit_k) {
   const int64_t step = 1536, most = (208ll << 20) / (2 * q.T_pad);      // a multiple of 192, 256 and 128
   if (most >= v_all) return v_all;
   const int tile_m = q.strip ? 192 : kd::kTileM, masked_tt = (q.n_tt * 7 + 7) / 8;
-  const int64_t m_tiles = (q.H_s + kd::kGemmTileM - 1) / kd::kGemmTileM;
+  const int64_t gw_rows = kd::grad_W_tile(q.H_s), m_tiles = (q.H_s + gw_rows - 1) / gw_rows;
   // multiply-adds of one workgroup: a logit tile, a grad_W_s tile, and what a chunk costs besides (three launches
   // and the sums of grad_h_s: 20 us and 8 bytes per element at 5 TB/s, at 2.6e12 a second)
   const double logit = (double)tile_m * kd::kTileN * (double)logit_k;
-  const double gw = (double)kd::kGemmTileM * kd::kTileN * q.T_pad;
+  const double gw = (double)gw_rows * 256. * q.T_pad;
   const double fixed = 52e6 + (double)q.T * q.H_s * 4.2;
   auto cost = [&](int64_t width) {
     const int64_t n = (width + tile_m - 1) / tile_m;
@@ -210,14 +210,26 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   const int64_t vc = p->vocab_chunk > 0 ? p->vocab_chunk : choose_chunk(q, v_all, logit_k);  // (the caller's: a multiple of 256)
   q.V_c = (int)(vc < v_all ? vc : v_all);
 
-  // split-K of the grad_h_s product so that a chunk offers about one tile per CU
-  const int tiles_h = ((q.H_s + kd::kGemmTileM - 1) / kd::kGemmTileM) * q.n_tt;
-  int sk = q.n_cu / tiles_h;
-  if (sk < 1) sk = 1;
-  if (sk > 32) sk = 32;
-  while (sk > 1 && q.V_c / sk < 512) --sk;
+  // Tile and split-K of the grad_h_s product: a chunk's tiles are rounds of n_cu workgroups, each of so many k-steps of 64
+  // columns; 1.48, 1.15, 0.85, 0.6 us a k-step for 256, 192, 128, 64 hidden rows (1.41 PFLOP/s down to 0.9), and 4 us a
+  // tile to start and 11 us per 256 rows to write its sums, as much again to read them where there are several chunks;
+  // and every part is read once more at the end of the call (4 TB/s).  Measured: T = 256, one chunk of 151936 columns,
+  // H_s = 1024 112 us with 128 rows x 32 parts, 167 us with 256 x 32, which is half of the workgroups.
   const int steps_first = (int)(round_up(q.V < q.V_c ? q.V : q.V_c, 64) / 64);
-  if (sk > steps_first) sk = steps_first;
+  double least = 1e300;
+  int sk = 1;
+  for (int rows = call.lean ? 128 : 256; rows >= 64; rows -= 64) {
+    if (q.w_hv_inplace && q.V > (1 << 23) && rows > 128) continue;              // (32-bit offsets: rows of 2 V bytes)
+    const double step = rows == 256 ? 1.48 : rows == 192 ? 1.15 : rows == 128 ? 0.85 : 0.6;
+    const double ends = 4. + rows / 256. * (q.V > q.V_c ? 22. : 11.);
+    const int64_t tiles = (int64_t)((q.H_s + rows - 1) / rows) * q.n_tt;
+    for (int s = 1; s <= 32 && (s == 1 || q.V_c / s >= 512) && s <= steps_first; ++s) {
+      if (call.lean && s > 1 && s * tiles > q.n_cu) break;
+      const double t = (double)((tiles * s + q.n_cu - 1) / q.n_cu) * ((steps_first + s - 1) / s * step + ends) +
+                       (double)s * q.T * q.H_s * 1e-6 * q.V_c / q.V;
+      if (t < least) { least = t; q.gh_rows = rows; sk = s; }
+    }
+  }
   q.ksteps_h = (steps_first + sk - 1) / sk;
   q.n_ksplit_h = (steps_first + q.ksteps_h - 1) / q.ksteps_h;   // every part is written by the first chunk
 
@@ -232,15 +244,18 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   // needs (at least 32 parts, four for every two strips) holds the strip loop's up to 32 ranges and more, too.
   const int part_vals = q.kind == KD_AKL ? kd::kAklThresholds : 5;
   const int parts = 4 * (q.strip ? lean_split : q.n_split);
-  L.partials = take((size_t)parts * part_vals * q.T_pad * 4);
+  const size_t partial_bytes = (size_t)parts * part_vals * q.T_pad * 4;
+  if (!with_backward) L.partials = take(partial_bytes);
   L.prep_h_t = L.prep_W_t = L.prep_h_s = L.prep_W_s = 0;
   const size_t h_rows = q.strip ? q.T_pad : q.T;         // the strip loop reads whole token tiles of packed rows
   if (q.prep_hs) L.prep_h_s = take(h_rows * q.K_s * 2);
   if (q.prep_Ws) L.prep_W_s = take((size_t)q.V * q.K_s * 2);
   if (with_backward) {
-    L.h_sT = take((size_t)q.H_s * q.T_pad * 2);
+    L.partials = off;           // read for the last time before the backward pass writes its first byte
+    L.h_sT = take((size_t)round_up(q.H_s, 16) * q.T_pad * 2);
     L.dz = take((size_t)q.T_pad * q.V_c * 2);
     L.gh32 = take((size_t)q.n_ksplit_h * q.T * q.H_s * 4);
+    if (off < L.partials + partial_bytes) off = (size_t)round_up((int64_t)(L.partials + partial_bytes), 256);
   } else {
     L.h_sT = L.dz = L.gh32 = off;
   }
@@ -388,60 +403,22 @@ kd_status run_forward(const Problem& q, hipStream_t st, bool first_teacher = tru
 // summed in fp32 over the chunks and converted once at the end.
 kd_status run_backward(const Problem* qs, int n_teachers, hipStream_t st) {
   const Problem& q = qs[0];          // everything on the student side is the same for all teachers
-  // h_s^T [H_s][T_pad] once (token axis zero-padded): the K-contiguous operand of grad_W_s
-  KD_TRY(kd::launch_transpose_rows(q, st));
+  KD_TRY(kd::launch_pack_columns(q, st));       // h_s^T once: the hidden-row operand of grad_W_s
 
-  const size_t gsz = q.grad_f32 ? 4 : 2;
-  bool first = true;
   for (int64_t v0 = 0; v0 < q.V; v0 += q.V_c) {
     const int width = (int)((q.V - v0 < q.V_c) ? q.V - v0 : q.V_c);
     for (int k = 0; k < n_teachers; ++k) {
       ProfileScope ps(KD_PROF_GRAD, st);
       KD_TRY(kd::launch_grad_chunk(qs[k], (int)v0, width, k > 0, st));
     }
-    kd::GemmDesc gw{}, gh{};
-    gw.K = q.T_pad; gw.k_per_split = 0;
-    gw.meta = q.meta; gw.k_from_meta = 1;        // only the token tiles that hold valid tokens
-    gw.out_split_stride = 0;
-    gw.out_f32 = q.grad_f32; gw.accumulate = q.accumulate_grad_W;
-    gh.B = q.dz; gh.ldb = q.V_c; gh.N = q.T;
-    gh.meta = q.meta; gh.n_from_meta = 1;        // rows = valid tokens
-    gh.K = (int)round_up(width, 64); gh.k_per_split = q.ksteps_h * 64;
-    gh.out = q.gh32; gh.ldo = q.H_s; gh.out_split_stride = (int64_t)q.T * q.H_s;
-    gh.out_f32 = 1; gh.accumulate = first ? 0 : 1;
-    if (!q.w_hv) {
-      // grad_W_s[v][h] = sum_t h_sT[h][t] dz[t][v]   (dz read token-major as it lies)
-      gw.A = q.h_sT; gw.lda = q.T_pad; gw.M = q.H_s;
-      gw.B = q.dz; gw.ldb = q.V_c; gw.N = width;
-      gw.k_major = 2; gw.k_rows = q.T_pad;
-      gw.out = static_cast<char*>(q.grad_W_s) + (size_t)v0 * q.H_s * gsz; gw.ldo = q.H_s;
-    } else {
-      // the caller keeps grad_W_s as [H][V]: grad_W_s[h][v] = sum_t dz[t][v] h_sT[h][t], dz again read as it
-      // lies, now as the first operand so that the output rows run along the vocabulary
-      gw.A = q.dz; gw.lda = q.V_c; gw.M = width;
-      gw.B = q.h_sT; gw.ldb = q.T_pad; gw.N = q.H_s;
-      gw.k_major = 1; gw.k_rows = q.T_pad;
-      gw.out = static_cast<char*>(q.grad_W_s) + (size_t)v0 * gsz; gw.ldo = q.V;
-    }
-    if (!q.w_hv_inplace) {
-      // grad_h_s[t][h] += sum_v W_s[v][h] dz[t][v]   (the [V][K] head read vocabulary-major as it lies; dz is
-      // zero from the chunk's last valid column to the next multiple of 64, where the product's last k-step ends)
-      gh.A = static_cast<const char*>(q.W_s) + (size_t)v0 * q.K_s * 2; gh.lda = q.K_s; gh.M = q.H_s;
-      gh.k_major = 1; gh.k_rows = width;
-    } else {
-      // head read in place as [H][V]: grad_h_s[t][h] += sum_v W_s[h][v] dz[t][v], both operands K-contiguous
-      gh.A = static_cast<const char*>(q.W_s) + (size_t)v0 * 2; gh.lda = q.V; gh.M = q.H_s;
-      gh.k_major = 0; gh.k_rows = width;
-    }
     {
       ProfileScope ps(KD_PROF_GEMM_GRAD_W, st);
-      KD_TRY(kd::launch_gemm(gw, q.n_cu, st));
+      KD_TRY(kd::launch_grad_W(q, (int)v0, width, st));
     }
     {
       ProfileScope ps(KD_PROF_GEMM_GRAD_H, st);
-      KD_TRY(kd::launch_gemm(gh, q.n_cu, st));
+      KD_TRY(kd::launch_grad_h(q, (int)v0, width, v0 == 0, st));
     }
-    first = false;
   }
   KD_TRY(kd::launch_gradh_finish(q, st));
   return KD_OK;

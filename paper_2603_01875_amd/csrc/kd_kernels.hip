@@ -7,25 +7,15 @@
 //   akl search : (AKL) teacher logit tiles only, a few times -> the teacher probability that splits head from tail
 //   finalize : n = sum mask, loss, per-row gradient scale mask/(n tau)
 //   per vocabulary chunk:
-//     grad   : logit tiles again -> dL/dz_s tile in bf16, stored once as [T,Vc]
-//     gemm   : grad_W_s[chunk] = dz^T . h_s     and     grad_h_s += dz . W_s[chunk]
-//              (dz in the first and W_s in the second are contracted over their OUTER index:
-//              they are read as they lie, through the k-major operand path of tile_loop)
-//   gradh_finish : fp32 partial sums -> grad_h_s
+//     grad   : logit tiles again -> dL/dz_s tile in bf16, stored once in the order of dz_chunk (kd_common.hpp)
+//     the backward products: grad_W_s[chunk] = dz^T . h_s     and     grad_h_s += dz . W_s[chunk]     (kd_products.hip)
+//   gradh_finish : fp32 partial sums -> grad_h_s (kd_products.hip)
 // All logarithms inside the kernels are base 2: a = z * log2(e)/tau.
-#include "kd_mfma.hpp"
-#include "kd_strip.hpp"
-#include "kd_launch.h"
-
-#include <atomic>
+#include "kd_common.hpp"
 
 // tile configurations (overridable for tuning experiments)
 #ifndef KD_LOGIT_CFG
 #define KD_LOGIT_CFG 2, 2, 4, 64, 3     // MI, NI, WN, BK, NST: 128 x 256 tile, 8 waves
-#endif
-#ifndef KD_GEMM_CFG
-#define KD_GEMM_CFG 2, 2, 4, 64, 3      // 128 x 256 tile, 8 waves (the second wave per SIMD hides the
-                                        // bursts of transposing LDS reads of the k-major operand)
 #endif
 
 // Ablation builds for measurements (never the product: RESULTS ARE WRONG when this is not 0).  They take one
@@ -45,10 +35,9 @@
 namespace kd {
 
 typedef TileCfg<KD_LOGIT_CFG> LCfg;   // logit tiles: two accumulators per tile
-typedef TileCfg<KD_GEMM_CFG> GCfg;    // backward products: one accumulator
 constexpr int BK = LCfg::BK;
 constexpr int NI = LCfg::NI;
-static_assert(LCfg::BM == kTileM && BN == kTileN && GCfg::BM == kGemmTileM, "planner and kernels disagree");
+static_assert(LCfg::BM == kTileM && BN == kTileN, "planner and kernels disagree");
 constexpr int BM = LCfg::BM;
 constexpr int MI = LCfg::MI;
 typedef LCfg::Acc AccTile;
@@ -59,21 +48,6 @@ __device__ __forceinline__ int acc_n(int wn, int nt, int lane) { return LCfg::ac
 // work maps
 // ------------------------------------------------------------------------------------------
 
-// Workgroups are dealt to the 8 XCDs round-robin by workgroup id.  Renumber so
-// that consecutive logical ids sit on one XCD (and share its L2).
-__device__ __forceinline__ int xcd_logical_id(int b, int G) {
-  const int x = b % 8, q = G / 8, r = G % 8;       // XCD x holds q (+1 if x < r) of the G workgroups
-  return x * q + (x < r ? x : r) + b / 8;
-}
-
-// Device-side plan, written by rowmap_kernel once the mask has been counted (the host never
-// learns how many tokens are valid, so everything that depends on it is decided on the device).
-// META_N_SPLIT: vocabulary ranges per token tile in the statistics passes; META_G_SPLIT, META_G_SPLIT_LAST: in the
-// gradient kernel, for a full chunk and for the last one (strip loop).
-enum { META_N_VALID = 0, META_N_TT = 1, META_N_SPLIT = 2, META_T_EFF = 3, META_G_SPLIT = 4, META_G_SPLIT_LAST = 5,
-       META_WORDS = 6 };
-__device__ __forceinline__ int meta_get(const int* meta, int i) { return uniform(meta[i]); }
-
 // Index q over an (na x nb) grid walked in (ba x bb) blocks, a fastest inside a block.
 __device__ __forceinline__ void block_decode(int q, int na, int ba, int bb, int& a, int& b) {
   const int per = ba * bb;
@@ -81,20 +55,6 @@ __device__ __forceinline__ void block_decode(int q, int na, int ba, int bb, int&
   const int nblk_a = na / ba;
   a = (blk % nblk_a) * ba + w % ba;
   b = (blk / nblk_a) * bb + w / ba;
-}
-
-// Index q over n_tt token tiles x n_split vocabulary splits: the token tiles in groups of at most four (of sizes
-// that differ by one where four does not divide them), a group's splits one after the other.  32 consecutive
-// indices, the workgroups of an XCD, then cover 4 x 8: the shape that streams the fewest rows into one L2.
-__device__ __forceinline__ void group_decode(int q, int n_tt, int n_split, int& tt, int& split) {
-  const int ng = (n_tt + 3) / 4, small = n_tt / ng, n_big = n_tt - small * ng;
-  const int big_units = n_big * (small + 1) * n_split;
-  int g = small, base = 0;
-  if (q < big_units) g = small + 1;
-  else { q -= big_units; base = n_big * (small + 1); }
-  const int grp = q / (g * n_split), w = q - grp * g * n_split;
-  tt = base + grp * g + w % g;
-  split = w / g;
 }
 
 struct LogitArgs {
@@ -115,7 +75,7 @@ struct LogitArgs {
   float* partials;     // stats: [parts][5][T_pad];  jsd: [parts][2][T_pad]
   const f32x4* rowinfo;// [T_pad]: {lse2_t, lse2_s, mask/(n tau), row term}
   const float* akl;    // AKL only: [AKL_ROWS][T_pad] per-token values (see the AKL_* indices)
-  bf16_t* dz;          // [T_pad][ldz]   chunk of dL/dz_s, vocabulary contiguous
+  bf16_t* dz;          // chunk of dL/dz_s, ldz columns, in the order of dz_chunk
   int ldz;
   int last_chunk;      // this launch handles the last chunk of the vocabulary
   int dz_accumulate;   // add to dz instead of overwriting it (further teachers of a multi-teacher call)
@@ -211,6 +171,7 @@ struct StripWork {
   }
   __device__ int n_items() const { return cnt; }
   __device__ StripItem item(int i) const {
+    const auto p = kernel_args<LogitArgs>();
     StripItem it;
     int m0 = row0 + i * StripCfg::BM, n0 = tt * BN, end = row1;
     if (n_vt > 0) {
@@ -218,8 +179,8 @@ struct StripWork {
       const int g = grp < n_four ? 4 : n_tt - 4 * n_four;
       const int vt = w / g;
       n0 = (4 * grp + w - vt * g) * BN;
-      m0 = a.v0 + vt * StripCfg::BM;
-      end = a.v_end;
+      m0 = p->v0 + vt * StripCfg::BM;
+      end = p->v_end;
     }
     it.a_rows = min(StripCfg::BM, end - m0);
     it.out_rows = (it.a_rows + 63) / 64 * 64;        // zeros behind the chunk's last row: the k-steps of grad_h_s are whole
@@ -228,10 +189,14 @@ struct StripWork {
 #if KD_ABLATE & 1
     m0 = n0 = 0;       // same operand rows for every tile (the tile's coordinates stay its own)
 #endif
-    it.A0 = (const char*)(a.W_s + (int64_t)m0 * a.H_s);
-    it.A1 = (const char*)(a.W_t + (int64_t)m0 * a.H_t);
-    it.B0 = (const char*)(a.h_s + (int64_t)n0 * a.H_s);
-    it.B1 = (const char*)(a.h_t + (int64_t)n0 * a.H_t);
+    it.k0 = p->H_s; it.k1 = p->H_t;
+    it.lda0 = 2 * it.k0; it.ldb0 = 128 * it.k0;
+    it.lda1 = 2 * it.k1; it.ldb1 = 128 * it.k1;
+    it.A0 = (const char*)p->W_s + (int64_t)m0 * it.lda0;
+    it.A1 = (const char*)p->W_t + (int64_t)m0 * it.lda1;
+    it.B0 = (const char*)p->h_s + (int64_t)n0 * (2 * it.k0);
+    it.B1 = (const char*)p->h_t + (int64_t)n0 * (2 * it.k1);
+    it.aux = it.b_blocks = 0;
     return it;
   }
 };
@@ -309,10 +274,11 @@ struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
   __device__ __forceinline__ int n(int j) const { return acc_n(wn, j, lane); }
   __device__ __forceinline__ int part() const { return wm * 2 + (lane >> 5); }
   static constexpr int MERGE = 64;                   // lanes of one token merged before they leave: none
-  // o: entries 16 p .. 16 p + 15 of the lane's column; row: the token's row at the tile's first vocabulary entry
-  __device__ __forceinline__ void store(bf16_t* row, int p, bf16x4 (&o)[4], int) const {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) *(bf16x4*)(row + m(16 * p + 4 * q)) = o[q];
+  // dz (dz_chunk): entries 16 p .. + 15 of column j are pieces of four rows, piece q at rows 8 q + 4 (lane / 32) of 32;
+  // pieces u and u + 2 are a lane's 16 bytes (u = 0, 1)
+  static constexpr int PAIR = 2;
+  __device__ __forceinline__ int64_t dz_at(int ldz, int n0, int m0, int j, int p, int u) const {
+    return dz_chunk(ldz, (n0 >> 6) + wn, ((m0 + wm * 32 * MI) >> 5) + p, 2 * j + ((lane >> 4) & 1), 16 * (2 * u + (lane >> 5)) + (lane & 15));
   }
 };
 struct StripGeo {        // 192 x 256 tile of four waves (kd_strip.hpp)
@@ -326,33 +292,11 @@ struct StripGeo {        // 192 x 256 tile of four waves (kd_strip.hpp)
   __device__ __forceinline__ int n(int j) const { return StripCfg::acc_n(j, lane, wave); }
   __device__ __forceinline__ int part() const { return 0; }
   static constexpr int MERGE = 16;                   // lanes 16 and 32 apart hold the same token
-  // Four lanes share a token, each with four rows of every 16-row block: a 4 x 4 transposition of these 8-byte
-  // pieces between them gives each lane 16 rows of one block, so that the wave's stores fill whole 128-byte
-  // lines instead of 32-byte pieces.  rows: those that may be stored, a multiple of 64.
-  __device__ __forceinline__ void store(bf16_t* row, int p, bf16x4 (&o)[4], int rows) const {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    uint32_t x[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const u32x2 w = __builtin_bit_cast(u32x2, o[i]);
-      x[i][0] = w[0]; x[i][1] = w[1];
-    }
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-      // (x0, x2), (x1, x3): the upper 32 lanes of the first against the lower 32 of the second; then
-      // (x0, x1), (x2, x3) in the same way by rows of 16 lanes
-      auto r0 = __builtin_amdgcn_permlane32_swap(x[0][d], x[2][d], false, false);
-      auto r1 = __builtin_amdgcn_permlane32_swap(x[1][d], x[3][d], false, false);
-      auto s0 = __builtin_amdgcn_permlane16_swap(r0[0], r1[0], false, false);
-      auto s1 = __builtin_amdgcn_permlane16_swap(r0[1], r1[1], false, false);
-      x[0][d] = s0[0]; x[1][d] = s0[1]; x[2][d] = s1[0]; x[3][d] = s1[1];
-    }
-    if (64 * p < rows) {
-      u32x4* const dst = (u32x4*)(row + 64 * p + 16 * (lane >> 4));
-      dst[0] = u32x4{x[0][0], x[0][1], x[1][0], x[1][1]};
-      dst[1] = u32x4{x[2][0], x[2][1], x[3][0], x[3][1]};
-    }
-    __builtin_amdgcn_sched_barrier(0);       // (or all of a column is computed before anything is stored: spills)
+  // dz (dz_chunk): entries 16 p .. + 15 of column j are four rows of each of four blocks; two neighbouring blocks are a
+  // lane's 16 bytes, a wave's stores whole KiB
+  static constexpr int PAIR = 1;
+  __device__ __forceinline__ int64_t dz_at(int ldz, int n0, int m0, int j, int p, int u) const {
+    return dz_chunk(ldz, (n0 >> 6) + wave, (m0 >> 5) + 2 * p + u, j, lane);
   }
 };
 
@@ -401,6 +345,7 @@ struct TileEpi {
 // ... and from strip_loop.
 template <class Epi>
 struct StripEpi {
+  static constexpr bool WHOLE = false;
   Epi& epi;
   __device__ StripEpi(Epi& e) : epi(e) {}
   __device__ void begin_item(const StripItem& it) { epi.begin_item(it.m0, it.n0, it.out_rows); }
@@ -637,15 +582,16 @@ struct GradEpi {
   __device__ __forceinline__ void emit(J, const float (&S)[NE], const float (&T)[NE]) {
     constexpr int j = J::value;
     const float c = a.c, w = a.beta, s = sc[j];
-    bf16_t* const row = a.dz + (int64_t)(n0 + geo.n(j)) * a.ldz + m0;
 #pragma unroll
     for (int p = 0; p < NE / 16; ++p) {
       bf16x4 o[4];
+      if (64 * p >= out_rows) break;             // (whole entries of 64 rows: only the strip loop's last tile has fewer)
       if (ADD)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int m = geo.m(16 * p + 4 * q);
-          o[q] = *(const bf16x4*)(row + (m < out_rows ? m : 0));       // (rows that are not stored: any valid address)
+        for (int u = 0; u < 2; ++u) {
+          const bf16x8 v = *(const bf16x8*)(a.dz + geo.dz_at(a.ldz, n0, m0, j, p, u));
+          o[Geo::PAIR == 1 ? 2 * u : u] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+          o[Geo::PAIR == 1 ? 2 * u + 1 : u + 2] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
         }
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
@@ -666,7 +612,11 @@ struct GradEpi {
         const float d = s * g;
         o[e >> 2][e & 3] = (bf16_t)(ADD ? (float)o[e >> 2][e & 3] + d : d);
       }
-      geo.store(row, p, o, out_rows);
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        *(bf16x8*)(a.dz + geo.dz_at(a.ldz, n0, m0, j, p, u)) =
+            __builtin_shufflevector(o[Geo::PAIR == 1 ? 2 * u : u], o[Geo::PAIR == 1 ? 2 * u + 1 : u + 2], 0, 1, 2, 3, 4, 5, 6, 7);
+      __builtin_amdgcn_sched_barrier(0);       // (or all of a column is computed before anything is stored: spills)
     }
   }
   // (two bodies: a shared one would wait for the loads of the adding one, and for everything older, on both paths)
@@ -732,8 +682,6 @@ struct SearchEpi {
 // transposing reads), and where the teacher is fp8
 // ------------------------------------------------------------------------------------------
 #define KD_LOGIT_KERNEL __global__ __launch_bounds__(LCfg::NT)
-#define KD_GEMM_KERNEL __global__ __launch_bounds__(GCfg::NT)
-#define KD_STRIP_KERNEL __global__ __launch_bounds__(StripCfg::NT, 1) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
 // measurement aid, off unless asked for
 struct LoopClock {
@@ -756,7 +704,7 @@ KD_STRIP_KERNEL void stats_strip_kernel(const LogitArgs a) {
   StatsEpi<KIND, StripGeo> epi(a.c);
   StripEpi<StatsEpi<KIND, StripGeo>> drive(epi);
   LoopClock clk(a);
-  strip_loop<2, true>(work, drive, 2 * a.H_s, 2 * a.H_t, smem);
+  strip_loop<2, true>(work, drive, smem);
   clk.stop(a);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
@@ -767,7 +715,7 @@ KD_STRIP_KERNEL void rows_strip_kernel(const LogitArgs a) {
   StripWork work(a, meta_get(a.meta, META_N_SPLIT));
   RowsEpi<KIND, StripGeo> epi(a, work.tt);
   StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
-  strip_loop<2, true>(work, drive, 2 * a.H_s, 2 * a.H_t, smem);
+  strip_loop<2, true>(work, drive, smem);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
 
@@ -776,7 +724,7 @@ KD_STRIP_KERNEL void akl_search_strip_kernel(const LogitArgs a) {
   StripWork work(a, meta_get(a.meta, META_N_SPLIT));
   SearchEpi<StripGeo> epi(a, work.tt);
   StripEpi<SearchEpi<StripGeo>> drive(epi);
-  strip_loop<1, true>(work, drive, 0, 2 * a.H_t, smem);
+  strip_loop<1, true>(work, drive, smem);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
 
@@ -786,7 +734,7 @@ KD_STRIP_KERNEL void grad_strip_kernel(const LogitArgs a) {
   StripWork work(a, meta_get(a.meta, a.last_chunk ? META_G_SPLIT_LAST : META_G_SPLIT));
   GradEpi<KIND, StripGeo> epi(a);
   StripEpi<GradEpi<KIND, StripGeo>> drive(epi);
-  strip_loop<2, false>(work, drive, 2 * a.H_s, 2 * a.H_t, smem);
+  strip_loop<2, false>(work, drive, smem);
 }
 
 template <int KIND, bool TF8, bool WHV>
@@ -834,117 +782,6 @@ KD_LOGIT_KERNEL void grad_kernel(const LogitArgs a) {
   GradEpi<KIND, TileGeo> epi(a);
   TileEpi<GradEpi<KIND, TileGeo>> drive(epi, a.t_scale);
   tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
-}
-
-// ------------------------------------------------------------------------------------------
-// plain products for the backward pass:  out[n][m] (+)= sum_k A[m][k] B[n][k]
-// ------------------------------------------------------------------------------------------
-struct GemmArgs {
-  const bf16_t* A; const bf16_t* B;
-  int lda, ldb;
-  int M, N;            // valid rows of A / of B
-  int K;               // contraction length, a multiple of 64
-  int n_ksplit;        // split-K parts; part s writes out + s * out_split_stride
-  int ksteps;          // k-steps per part
-  void* out; int64_t ldo; int64_t out_split_stride;   // in elements
-  int out_f32;         // 1: float, 0: bf16
-  int accumulate;      // 1: out += D
-  int n_mt, n_nt;
-  int ba, bb;          // block shape of the work map (ba | n_mt, bb | n_nt)
-  const int* meta;     // device-side plan (may be null when neither flag below is set)
-  int n_from_meta;     // N = number of valid tokens (rows of the compacted B operand)
-  int k_from_meta;     // K = valid tokens rounded up to whole token tiles
-  int k_rows;          // k-major operand: k-rows that exist in memory (rows beyond are clamped)
-};
-
-// KM: which operand is stored k-major (0: none, 1: A[k][m], 2: B[k][n]); the others are K-contiguous.
-template <int KM>
-struct GemmWork {
-  const GemmArgs& a;
-  int L, G, n_tiles, N, K, n_nt, bb;
-  __device__ GemmWork(const GemmArgs& a_) : a(a_) {
-    G = gridDim.x;
-    L = xcd_logical_id(blockIdx.x, G);
-    N = a.N; K = a.K; n_nt = a.n_nt; bb = a.bb;
-    if (a.n_from_meta) {
-      N = meta_get(a.meta, META_N_VALID);
-      n_nt = (N + BN - 1) / BN;
-      bb = n_nt % 4 == 0 ? 4 : (n_nt % 3 == 0 ? 3 : (n_nt % 2 == 0 ? 2 : 1));
-    }
-    if (a.k_from_meta) K = meta_get(a.meta, META_T_EFF);
-    n_tiles = a.n_mt * n_nt * a.n_ksplit;
-  }
-  __device__ int n_items() const { return L < n_tiles ? (n_tiles - L + G - 1) / G : 0; }
-  __device__ WorkItem item(int i) const {
-    const int q = i * G + L;
-    const int per_split = a.n_mt * n_nt;
-    const int ks = q / per_split;
-    int mt, nt;
-    block_decode(q - ks * per_split, a.n_mt, a.ba, bb, mt, nt);
-    const int k0 = ks * a.ksteps * GCfg::BK;
-    WorkItem it;
-    it.A0 = it.A1 = (KM & 1) ? a.A + (int64_t)k0 * a.lda + mt * GCfg::BM : a.A + (int64_t)mt * GCfg::BM * a.lda + k0;
-    it.B0 = it.B1 = (KM & 2) ? a.B + (int64_t)k0 * a.ldb + nt * BN : a.B + (int64_t)nt * BN * a.ldb + k0;
-    it.ka_rows = it.kb_rows = a.k_rows - k0;
-    it.a_rows = min(GCfg::BM, a.M - mt * GCfg::BM);
-    it.b_rows = min(BN, N - nt * BN);
-    it.nk0 = it.nk1 = a.k_from_meta ? K / GCfg::BK : min(a.ksteps, K / GCfg::BK - ks * a.ksteps);
-    it.m0 = mt * GCfg::BM;
-    it.n0 = nt * BN;
-    it.aux = ks;
-    return it;
-  }
-};
-
-struct StoreEpi {
-  const GemmArgs& a;
-  int wm, wn, lane;
-  __device__ StoreEpi(const GemmArgs& a_) : a(a_) {
-    lane = threadIdx.x & 63;
-    wm = (threadIdx.x >> 6) & 1;
-    wn = threadIdx.x >> 7;
-  }
-  __device__ void begin_item(const WorkItem&) {}
-  __device__ void end_item(const WorkItem& it, GCfg::Acc& acc, GCfg::Acc&) {
-#pragma unroll
-    for (int nt = 0; nt < GCfg::NI; ++nt) {
-      const int nl = GCfg::acc_n(wn, nt, lane);
-      if (nl >= it.b_rows) continue;
-      const int64_t row = (int64_t)(it.n0 + nl) * a.ldo + (int64_t)it.aux * a.out_split_stride;
-#pragma unroll
-      for (int mt = 0; mt < GCfg::MI; ++mt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int ml = GCfg::acc_m(wm, mt, 4 * q, lane);
-          if (ml >= it.a_rows) continue;
-          f32x4 v = {acc[mt][nt][4 * q], acc[mt][nt][4 * q + 1], acc[mt][nt][4 * q + 2], acc[mt][nt][4 * q + 3]};
-          if (a.out_f32) {
-            f32x4* p = (f32x4*)((float*)a.out + row + it.m0 + ml);
-            if (a.accumulate) v += *p;
-            *p = v;
-          } else {
-            bf16x4* p = (bf16x4*)((bf16_t*)a.out + row + it.m0 + ml);
-            if (a.accumulate) {
-              const bf16x4 old = *p;
-#pragma unroll
-              for (int i = 0; i < 4; ++i) v[i] += (float)old[i];
-            }
-            bf16x4 o;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) o[i] = (bf16_t)v[i];
-            *p = o;
-          }
-        }
-    }
-  }
-};
-
-template <int KM>
-KD_GEMM_KERNEL void gemm_kernel(const GemmArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  GemmWork<KM> work(a);
-  StoreEpi epi(a);
-  tile_loop<1, GCfg, KM>(work, epi, a.lda, a.lda, a.ldb, a.ldb, smem);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1262,27 +1099,6 @@ __global__ void transpose_kernel(const E* src, int64_t ld_src, int R, int C, E* 
   }
 }
 
-// h_s^T of the compacted tokens: dst[c][j] = src[rowmap[j]][c] in bf16 for j < n_valid, zero up to R_pad.
-template <class E>
-__global__ void transpose_rows_kernel(const E* src, int C, bf16_t* dst, int R_pad, const int* rowmap, const int* meta) {
-  __shared__ bf16_t tile[64][66];
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int n_valid = meta[META_N_VALID];
-  const int c = c0 + tx, cc = min(c, C - 1);
-  E v[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i)           // (rowmap holds a valid row for every r < R_pad: the loads need no test)
-    v[i] = src[(int64_t)rowmap[r0 + ty + 4 * i] * C + cc];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) tile[ty + 4 * i][tx] = r0 + ty + 4 * i < n_valid && c < C ? (bf16_t)v[i] : (bf16_t)0.f;
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int c = c0 + i, r = r0 + tx;
-    if (c < C && r < R_pad) dst[(int64_t)c * R_pad + r] = tile[tx][i];
-  }
-}
-
 // The token operand of the strip loop: the compacted rows (row j = row rowmap[j] of src for j < n_valid, zero
 // beyond) in the order in which its waves load them: [64-token panel][32-element sub-step][16-token block][lane][8],
 // lane l holding elements 8 (l / 16) .. + 7 of token l mod 16.  fp32 rows become [hi | lo | hi] (see
@@ -1474,31 +1290,6 @@ __global__ void quantize_e4m3_kernel(const void* src, int src_f32, int64_t n, fl
   }
 }
 
-// grad_h_s row t = sum over split-K parts of the fp32 partial sums of its compacted row (zero for a
-// masked token), converted to the output dtype.
-__global__ void gradh_finish_kernel(const float* parts, int n_parts, int T, int H, const int* inv,
-                                    int out_f32, void* out) {
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  const int64_t n = (int64_t)T * H;
-  if (i >= n) return;
-  const int t = (int)(i / H), h = (int)(i % H);
-  const int j = inv[t];
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
-  if (j >= 0) {
-    const float* src = parts + (int64_t)j * H + h;
-    v = *(const f32x4*)src;
-    for (int p = 1; p < n_parts; ++p) v += *(const f32x4*)(src + (int64_t)p * n);
-  }
-  if (out_f32) {
-    *(f32x4*)((float*)out + i) = v;
-  } else {
-    bf16x4 o;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = (bf16_t)v[k];
-    *(bf16x4*)((bf16_t*)out + i) = o;
-  }
-}
-
 // ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
@@ -1506,25 +1297,6 @@ static int largest_divisor_le(int n, int cap) {
   for (int d = cap; d > 1; --d)
     if (n % d == 0) return d;
   return 1;
-}
-
-// Launch of a kernel that needs more dynamic LDS than the default limit.  The limit is a property of
-// the kernel on a device: it is raised once per kernel and device (one flag word per instantiation,
-// one bit per device), not on every launch.
-template <auto Kern>
-static hipError_t launch_big(int grid, int threads, int smem_bytes, hipStream_t st, const void* args_ptr) {
-  static std::atomic<uint64_t> attr_done{0};
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = 1ull << (dev & 63);
-  if (!(attr_done.load(std::memory_order_acquire) & bit)) {
-    e = hipFuncSetAttribute((const void*)Kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem_bytes);
-    if (e != hipSuccess) return e;
-    attr_done.fetch_or(bit, std::memory_order_release);
-  }
-  void* params[] = {const_cast<void*>(args_ptr)};
-  return hipLaunchKernel((const void*)Kern, dim3(grid), dim3(threads), params, smem_bytes, st);
 }
 
 static LogitArgs make_logit_args(const Problem& p) {
@@ -1706,17 +1478,6 @@ hipError_t launch_transpose_bytes(const void* src, int64_t ld_src, int R, int C,
   return hipGetLastError();
 }
 
-hipError_t launch_transpose_rows(const Problem& p, hipStream_t st) {
-  dim3 grid(p.T_pad / 64, (p.H_s + 63) / 64);
-  if (p.in_f32)
-    hipLaunchKernelGGL(transpose_rows_kernel<float>, grid, dim3(256), 0, st, (const float*)p.user_h_s, p.H_s,
-                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
-  else
-    hipLaunchKernelGGL(transpose_rows_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)p.user_h_s, p.H_s,
-                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
-  return hipGetLastError();
-}
-
 hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst, int K, hipStream_t st) {
   // (neighbouring workgroups share rows, so the panels stay on the slow axis; 2^22 tokens are 65536 of them, one more
   // than an axis other than the first takes, and a multiple of 4 always)
@@ -1724,29 +1485,6 @@ hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst,
   hipLaunchKernelGGL(pack_rows_kernel, dim3(K / 32, panels / z, z), dim3(256), 0, st, src, p.in_f32, H, (bf16_t*)dst, K,
                      p.rowmap, p.meta);
   return hipGetLastError();
-}
-
-hipError_t launch_gemm(const GemmDesc& d, int n_cu, hipStream_t st) {
-  GemmArgs a{};
-  a.A = (const bf16_t*)d.A; a.B = (const bf16_t*)d.B;
-  a.lda = d.lda; a.ldb = d.ldb; a.M = d.M; a.N = d.N; a.K = d.K;
-  const int ksteps_total = d.K / GCfg::BK;
-  a.ksteps = d.k_per_split > 0 ? d.k_per_split / GCfg::BK : ksteps_total;
-  a.n_ksplit = (ksteps_total + a.ksteps - 1) / a.ksteps;     // every part has at least one k-step
-  a.out = d.out; a.ldo = d.ldo; a.out_split_stride = d.out_split_stride;
-  a.out_f32 = d.out_f32; a.accumulate = d.accumulate;
-  a.n_mt = (d.M + GCfg::BM - 1) / GCfg::BM;
-  a.n_nt = (d.N + BN - 1) / BN;
-  a.ba = largest_divisor_le(a.n_mt, 8);
-  a.bb = largest_divisor_le(a.n_nt, 4);
-  a.meta = d.meta; a.n_from_meta = d.n_from_meta; a.k_from_meta = d.k_from_meta;
-  a.k_rows = d.k_rows;
-  const int tiles = a.n_mt * a.n_nt * a.n_ksplit;       // worst case (no token masked)
-  const int grid = tiles < n_cu ? tiles : n_cu;
-  if (d.k_major == 0) return launch_big<gemm_kernel<0>>(grid, GCfg::NT, GCfg::SMEM_BYTES, st, &a);
-  if (d.k_major == 1) return launch_big<gemm_kernel<1>>(grid, GCfg::NT, GCfg::SMEM_BYTES, st, &a);
-  if (d.k_major == 2) return launch_big<gemm_kernel<2>>(grid, GCfg::NT, GCfg::SMEM_BYTES, st, &a);
-  return hipErrorInvalidValue;
 }
 
 hipError_t launch_prepare(const void* src, int src_f32, int R, int H, void* dst, int K, int split_mode,
@@ -1789,16 +1527,8 @@ hipError_t launch_quantize_e4m3(const void* src, int src_f32, int64_t n, float i
 const char* build_info() {
   static_assert(StripCfg::BM == 192 && StripCfg::NT == 256 && StripCfg::NST == 3, "as named below");
   return "logit tile cfg (MI,NI,WN,BK,NST) = " KD_STR(KD_LOGIT_CFG) "; strip loop = 192 x 256 tiles, 4 waves, 3 stages"
-         "; product tile cfg = " KD_STR(KD_GEMM_CFG) "; ablation = " KD_STR(KD_ABLATE);
+         "; ablation = " KD_STR(KD_ABLATE);
 }
 int build_ablation() { return KD_ABLATE; }
-
-hipError_t launch_gradh_finish(const Problem& p, hipStream_t st) {
-  const int64_t n = (int64_t)p.T * p.H_s;
-  const int64_t threads = (n + 3) / 4;
-  hipLaunchKernelGGL(gradh_finish_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, p.gh32,
-                     p.n_ksplit_h, p.T, p.H_s, p.inv, p.grad_f32, p.grad_h_s);
-  return hipGetLastError();
-}
 
 }  // namespace kd

@@ -9,10 +9,18 @@ namespace kd {
 constexpr int kNumCU = 256;            // MI355X: 8 XCDs x 32 CUs; persistent grids are sized for it
 constexpr int kTileM = 128;            // vocabulary rows per logit tile of the eight-wave loop
 constexpr int kTileN = 256;            // token rows per logit tile
-#ifndef KD_GEMM_TILE_M
-#define KD_GEMM_TILE_M 128
-#endif
-constexpr int kGemmTileM = KD_GEMM_TILE_M;        // rows of the first operand per tile of the backward products
+
+// Hidden rows per tile of grad_W_s (beside 256 vocabulary columns): of 128, 192, 256 the number that covers H_s cheapest, a
+// tile's price being its rows and 48 more.
+inline int grad_W_tile(int64_t H_s) {
+  int best = 256;
+  int64_t low = INT64_MAX;
+  for (int rows = 256; rows >= 128; rows -= 64) {
+    const int64_t price = (H_s + rows - 1) / rows * (rows + 48);
+    if (price < low) { low = price; best = rows; }
+  }
+  return best;
+}
 
 // Everything a launch needs, resolved by the planner in kd_api.hip.
 struct Problem {
@@ -42,6 +50,7 @@ struct Problem {
   int strip;                    // bf16 logit operands, [V][K] heads: strip loop on packed hidden states
   int parts;                    // partial results per token and vocabulary split
   int g_split;                  // strip loop: most vocabulary ranges per token tile in the gradient kernel
+  int gh_rows;                  // hidden rows per tile of the grad_h_s product
   int T_pad, n_tt, n_vt, n_split, V_c, n_ksplit_h, ksteps_h, n_cu;
   // workspace carve-up
   int* meta;           // device-side plan written by the row-map kernel
@@ -51,28 +60,9 @@ struct Problem {
   float* akl;          // AKL only: [6][T_pad] per-token values between its passes (null otherwise)
   float* row_loss;     // [T_pad]
   float* partials;     // [n_split*parts][5][T_pad]
-  void* h_sT;          // bf16 [H_s][T_pad]
-  void* dz;            // bf16 [T_pad][V_c]
+  void* h_sT;          // bf16, T_pad tokens x H_s rounded up to 16, packed (launch_pack_columns)
+  void* dz;            // bf16, T_pad x V_c, in the order of dz_chunk (kd_common.hpp)
   float* gh32;         // [n_ksplit_h][T][H_s]
-};
-
-// out[n][m] (+)= sum_k A[m][k] B[n][k]; A is [M][lda], B is [N][ldb], both K-contiguous bf16.
-struct GemmDesc {
-  const void *A, *B;
-  int lda, ldb, M, N;
-  int K;                  // multiple of 64
-  int k_per_split;        // split-K: elements per part, a multiple of 64 (0 = no split); part s writes
-                          // out + s * out_split_stride
-  void* out;
-  int64_t ldo, out_split_stride;
-  int out_f32, accumulate;
-  const int* meta;        // device-side plan, needed when a flag below is set
-  int n_from_meta;        // N = number of valid tokens
-  int k_from_meta;        // K = valid tokens rounded up to whole token tiles (no split-K)
-  int k_major;            // 0: both K-contiguous; 1: A is stored [K][M] (element (m, k) at A[k * lda + m]);
-                          // 2: B is stored [K][N]
-  int k_rows;             // rows of the k-major operand that exist; K may round up beyond, the other
-                          // operand must be zero there
 };
 
 hipError_t launch_rowmap(const Problem& p, hipStream_t st);
@@ -92,11 +82,13 @@ hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulat
 // dst[c][r] = src[r][c] (zero for R <= r < R_pad), one-byte elements
 hipError_t launch_transpose_bytes(const void* src, int64_t ld_src, int R, int C, void* dst, int64_t ld_dst, int R_pad,
                                   hipStream_t st);
-// h_s^T of the compacted tokens (bf16 [H_s][T_pad]), from the caller's array
-hipError_t launch_transpose_rows(const Problem& p, hipStream_t st);
+// h_s of the compacted tokens transposed and packed for grad_W_s, from the caller's array
+hipError_t launch_pack_columns(const Problem& p, hipStream_t st);
 // hidden states [T][H] -> compacted, packed for the strip loop (T_pad rows of K elements)
 hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst, int K, hipStream_t st);
-hipError_t launch_gemm(const GemmDesc& d, int n_cu, hipStream_t st);
+// the backward products on the chunk of `width` columns from v0; `first`: grad_h_s's parts are written, not added to
+hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st);
+hipError_t launch_grad_h(const Problem& p, int v0, int width, bool first, hipStream_t st);
 hipError_t launch_gradh_finish(const Problem& p, hipStream_t st);
 const char* build_info();     // compile-time configuration of the kernels (tile shapes, ablation switch)
 int build_ablation();

@@ -1,0 +1,440 @@
+// The backward products on a chunk of dL/dz_s (dz), and what prepares and finishes them:
+//   grad_W_s[v][h] (+)= sum_t dz[t][v] h_s[t][h]        complete per chunk, stored straight to the output
+//   grad_h_s[t][h]  +=  sum_v dz[t][v] W_s[v][h]        fp32 partial sums, split over v where there are few tiles
+// Both run on the strip loop (kd_strip.hpp) with one accumulator of up to 256 x 256: one operand goes through the LDS, the
+// other straight to registers.  dz lies in the order in which a lane of a logit tile held it (dz_chunk): as the token
+// operand of grad_h_s it is loaded as it is; as the column operand of grad_W_s its tokens are the contraction, and the
+// transposing LDS reads turn it.  W_s is read over its outer index by the same reads; h_s is packed transposed once a call.
+// Bound by the matrix pipe and the chip's power, like the logit passes, and, the shorter the contraction, by the start and
+// the stores of a tile, which one wave per SIMD does not hide.  Measured against the eight-wave loop that read both operands
+// through the LDS and dz as [T][V_c] (us a chunk; T tokens x columns x H_s): grad_W_s 32768 x 8192 x 4096 1686 -> 1511 (1.45
+// PFLOP/s), 3584 x 16384 x 1024 111 -> 101, 256 x 151936 x 1024 224 -> 158; grad_h_s 32768 x 8192 x 4096 1866 -> 1674,
+// 7424 x 8192 x 2048 238 -> 211, 3584 x 16384 x 1024 118 -> 122.
+#include "kd_common.hpp"
+
+namespace kd {
+
+// Where lane (g, n) holds rows 4 g .. + 3 of each of four 16-row blocks, as two words of two bf16: a 4 x 4 transposition of
+// these 8-byte pieces between the four lanes of n gives each of them the 16 rows of one block.
+__device__ __forceinline__ void quad_transpose(uint32_t (&x)[4][2]) {
+#pragma unroll
+  for (int d = 0; d < 2; ++d) {
+    // (x0, x2), (x1, x3): the upper 32 lanes of the first against the lower 32 of the second; then
+    // (x0, x1), (x2, x3) in the same way by rows of 16 lanes
+    auto r0 = __builtin_amdgcn_permlane32_swap(x[0][d], x[2][d], false, false);
+    auto r1 = __builtin_amdgcn_permlane32_swap(x[1][d], x[3][d], false, false);
+    auto s0 = __builtin_amdgcn_permlane16_swap(r0[0], r1[0], false, false);
+    auto s1 = __builtin_amdgcn_permlane16_swap(r0[1], r1[1], false, false);
+    x[0][d] = s0[0]; x[1][d] = s0[1]; x[2][d] = s1[0]; x[3][d] = s1[1];
+  }
+}
+__device__ __forceinline__ bf16x4 to_bf16(const f32x4& v) {
+  bf16x4 o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = (bf16_t)v[i];
+  return o;
+}
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x2 pack4(const f32x4& v) { return __builtin_bit_cast(u32x2, to_bf16(v)); }
+
+// Results leave, and what they are added to comes, by buffer operations: one whose offset lies past the buffer's end does
+// nothing (a load gives 0), so rows and columns that do not exist take no branch.  (Behind one, all of the accumulator would
+// be copied from accumulation to vector registers at once.)
+constexpr uint32_t NOWHERE = 0xfffffff0u;
+// The lane, as something that has to be worked out again: offsets made from it are not kept from tile to tile (spills).
+__device__ __forceinline__ int fresh(int lane) {
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+// four neighbouring results of F32 or bf16 elements
+template <bool F32>
+__device__ __forceinline__ f32x4 load4(const rsrc_t& r, uint32_t at) {
+  if constexpr (F32) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, at, 0, 0));
+  } else {
+    const bf16x4 x = __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(r, at, 0, 0));
+    return f32x4{(float)x[0], (float)x[1], (float)x[2], (float)x[3]};
+  }
+}
+template <bool F32>
+__device__ __forceinline__ void store4(const rsrc_t& r, uint32_t at, const f32x4& v) {
+  if constexpr (F32) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, at, 0, 0);
+  else __builtin_amdgcn_raw_buffer_store_b64(pack4(v), r, at, 0, 0);
+}
+
+// ------------------------------------------------------------------------------------------
+// grad_W_s
+// ------------------------------------------------------------------------------------------
+struct GradWArgs {
+  const char* dz;          // the chunk
+  const char* hT;          // h_s transposed and packed (pack_columns_kernel)
+  void* out;               // grad_W_s at the chunk's first column
+  int64_t ldo;             // elements from vocabulary row to row ([V][H]) or from hidden row to row ([H][V])
+  int width, H_s;
+  int n_vt, n_ht;          // tiles
+  uint32_t lda, ldb;       // as in StripItem
+  int b_blocks;
+  const int* meta;
+};
+
+// 256 vocabulary columns (LDS) x 64 NB hidden rows (16 NB per wave)
+template <int NB>
+struct GradWWork {
+  typedef StripShape<16, NB> C;
+  const GradWArgs& a;
+  int L, G, k;
+  __device__ GradWWork(const GradWArgs& a_) : a(a_) {
+    G = gridDim.x;
+    L = xcd_logical_id(blockIdx.x, G);
+    k = meta_get(a.meta, META_T_EFF);
+  }
+  __device__ int n_items() const { const int n = a.n_vt * a.n_ht; return L < n ? (n - L + G - 1) / G : 0; }
+  __device__ StripItem item(int i) const {
+    int vt, ht;
+    const auto p = kernel_args<GradWArgs>();
+    group_decode(i * G + L, p->n_ht, p->n_vt, ht, vt);
+    StripItem it;
+    it.m0 = vt * C::BM;
+    it.n0 = ht * C::BN;
+    it.A0 = it.A1 = p->dz + (int64_t)it.m0 * 128;     // (of the first panel)
+    it.B0 = it.B1 = p->hT;
+    it.lda0 = it.lda1 = p->lda;
+    it.ldb0 = it.ldb1 = p->ldb;
+    it.b_blocks = p->b_blocks;
+    it.k0 = it.k1 = k;
+    it.a_rows = it.out_rows = C::BM;                 // (the buffer holds whole tiles: its width is a multiple of 256)
+    it.aux = 0;
+    return it;
+  }
+};
+
+// HV: the output is [H][V], the accumulator's rows are vocabulary columns; else [V][H], and its rows are hidden rows.
+// ADD: to what is there, with one rounding behind the whole sum.
+template <int NB, bool HV, bool F32, bool ADD>
+struct GradWEpi {
+  static constexpr bool WHOLE = true;
+  static constexpr int MB = 16, ES = F32 ? 4 : 2;
+  static constexpr bool PAIRS = HV && !F32 && !ADD, QUADS = !HV && !F32 && !ADD && NB == 4;   // 16-byte stores of bf16, by exchanges between lanes
+  static constexpr int STORES = PAIRS || QUADS ? MB * NB / 2 : ADD ? 2 * MB * NB : MB * NB;
+  const GradWArgs& a;
+  int lane, wave;
+  __device__ GradWEpi(const GradWArgs& a_) : a(a_), lane(threadIdx.x & 63), wave(uniform(threadIdx.x >> 6)) {}
+  __device__ void begin_item(const StripItem&) {}
+  // The buffer of blocks j ([H][V]: 16 hidden rows) or of the tile ([V][H]: its columns' rows).
+  __device__ __forceinline__ rsrc_t buffer(const StripItem& it, int j) const {
+    const int h = it.n0 + 16 * NB * wave + (HV ? 16 * j : 0);
+    const int64_t at = HV ? (int64_t)h * a.ldo + it.m0 : (int64_t)it.m0 * a.ldo + h;
+    const int rows = HV ? min(16, a.H_s - h) : min(256, a.width - it.m0);
+    // (rows - 1 whole ones and the rest of the last: the columns are checked by place())
+    const int64_t bytes = ((rows - 1) * a.ldo + (HV ? a.width - it.m0 : a.H_s - h)) * ES;
+    return make_rsrc((char*)a.out + at * ES, rows > 0 && bytes > 0 ? (uint32_t)bytes : 0u);
+  }
+  // offset of four results of block (i, j) in it
+  __device__ __forceinline__ uint32_t place(const StripItem& it, int ln, int i, int j) const {
+    const int g = ln >> 4, n = ln & 15;
+    if (HV) {
+      const int v = dz_column(i, 4 * g);
+      return it.m0 + v < a.width ? ((uint32_t)n * (uint32_t)a.ldo + v) * ES : NOWHERE;
+    }
+    const int h = 16 * j + 4 * g;
+    return it.n0 + 16 * NB * wave + h < a.H_s ? ((uint32_t)dz_column(i, n) * (uint32_t)a.ldo + h) * ES : NOWHERE;
+  }
+  __device__ __forceinline__ void start(const StripItem&, f32x4 (&T)[MB * NB]) const {
+#pragma unroll
+    for (int i = 0; i < MB * NB; ++i) T[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ void tile(const StripItem& it, f32x4 (&T)[MB * NB]) const {
+    const int ln = fresh(lane), g = ln >> 4, n = ln & 15;
+    if constexpr (ADD) {
+      // four blocks at a time, the loads of the next four in flight
+      f32x4 old[2][4];
+      auto block = [](int q, int e) { const int i = HV ? 4 * (q % (MB / 4)) + e : 4 * (q / NB) + e; return MB * (HV ? q / (MB / 4) : q % NB) + i; };
+      auto load = [&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        const rsrc_t r = buffer(it, block(q, 0) / MB);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) old[q & 1][e] = load4<F32>(r, place(it, ln, block(q, e) % MB, block(q, e) / MB));
+      };
+      load(IntC<0>{});
+      static_for<0, MB * NB / 4>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        if constexpr (q + 1 < MB * NB / 4) load(IntC<q + 1>{});
+        const rsrc_t r = buffer(it, block(q, 0) / MB);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          store4<F32>(r, place(it, ln, block(q, e) % MB, block(q, e) / MB), T[block(q, e)] + old[q & 1][e]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    } else if constexpr (HV) {
+      static_for<0, NB>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const rsrc_t r = buffer(it, j);
+        if constexpr (PAIRS) {
+          // two blocks' pieces change places between the halves of the wave: eight neighbouring columns per lane
+          static_for<0, MB / 2>([&](auto ic) {
+            constexpr int i = 2 * decltype(ic)::value;
+            const u32x2 x = pack4(T[MB * j + i]), y = pack4(T[MB * j + i + 1]);
+            auto r0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
+            auto r1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+            const int v = 16 * i + 16 * (g & 1) + 8 * (g >> 1);
+            const uint32_t at = it.m0 + v < a.width ? ((uint32_t)n * (uint32_t)a.ldo + v) * ES : NOWHERE;
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4{r0[0], r1[0], r0[1], r1[1]}, r, at, 0, 0);
+          });
+        } else {
+          static_for<0, MB>([&](auto ic) { store4<F32>(r, place(it, ln, decltype(ic)::value, j), T[MB * j + decltype(ic)::value]); });
+        }
+      });
+    } else {
+      const rsrc_t r = buffer(it, 0);
+      static_for<0, MB>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (QUADS) {
+          uint32_t x[4][2];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const u32x2 w = pack4(T[MB * (j % NB) + i]);
+            x[j][0] = w[0]; x[j][1] = w[1];
+          }
+          quad_transpose(x);
+          const int h = it.n0 + 16 * NB * wave + 16 * g;
+          const uint32_t at = ((uint32_t)dz_column(i, n) * (uint32_t)a.ldo + 16 * g) * ES;
+          __builtin_amdgcn_raw_buffer_store_b128(u32x4{x[0][0], x[0][1], x[1][0], x[1][1]}, r, h < a.H_s ? at : NOWHERE, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(u32x4{x[2][0], x[2][1], x[3][0], x[3][1]}, r, h + 8 < a.H_s ? at + 16 : NOWHERE, 0, 0);
+        } else {
+          static_for<0, NB>([&](auto jc) { store4<F32>(r, place(it, ln, i, decltype(jc)::value), T[MB * decltype(jc)::value + i]); });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+  }
+};
+
+template <int NB, bool HV, bool F32, bool ADD>
+KD_STRIP_KERNEL void grad_w_kernel(const GradWArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  GradWWork<NB> work(a);
+  GradWEpi<NB, HV, F32, ADD> epi(a);
+  strip_loop<1, false, StripShape<16, NB>, A_DZ, true, !HV>(work, epi, smem);
+}
+
+// ------------------------------------------------------------------------------------------
+// grad_h_s
+// ------------------------------------------------------------------------------------------
+struct GradHArgs {
+  const char* dz;
+  const char* W;           // the student's head at the chunk's first column
+  float* out;              // part s at out + s * part_stride
+  int64_t part_stride;
+  int width, H_s, ldz;
+  int n_ht, n_split, ksteps;   // hidden tiles; parts of ksteps k-steps of 64 columns
+  int accumulate;
+  uint32_t lda, ldb;
+  const int* meta;
+};
+
+// 16 MB hidden rows (LDS) x 256 tokens; HV: the head is [H][V]
+template <int MB, bool HV>
+struct GradHWork {
+  typedef StripShape<MB, 4> C;
+  const GradHArgs& a;
+  int L, G, n_tt;
+  __device__ GradHWork(const GradHArgs& a_) : a(a_) {
+    G = gridDim.x;
+    L = xcd_logical_id(blockIdx.x, G);
+    n_tt = meta_get(a.meta, META_N_TT);
+  }
+  __device__ int n_items() const { const int n = a.n_ht * n_tt * a.n_split; return L < n ? (n - L + G - 1) / G : 0; }
+  __device__ StripItem item(int i) const {
+    const auto p = kernel_args<GradHArgs>();
+    const int q = i * G + L, per = p->n_ht * n_tt, part = q / per;
+    int ht, tt;
+    group_decode(q - part * per, p->n_ht, n_tt, ht, tt);
+    const int k0 = part * p->ksteps * 64;
+    StripItem it;
+    it.m0 = ht * C::BM;
+    it.n0 = tt * 256;
+    it.lda0 = it.lda1 = p->lda;
+    it.ldb0 = it.ldb1 = p->ldb;
+    it.A0 = it.A1 = HV ? p->W + (int64_t)it.m0 * it.lda1 + k0 * 2 : p->W + (int64_t)k0 * it.lda1 + it.m0 * 2;
+    it.B0 = it.B1 = p->dz + (int64_t)(it.n0 >> 6) * it.ldb1 + (int64_t)k0 * 128;
+    it.k0 = it.k1 = min(p->ksteps * 64, p->width - k0);
+    it.a_rows = it.out_rows = min(C::BM, p->H_s - it.m0);
+    it.b_blocks = 0;
+    it.aux = part;
+    return it;
+  }
+};
+
+template <int MB>
+struct GradHEpi {
+  static constexpr bool WHOLE = true;
+  static constexpr int STORES = 4 * MB;
+  const GradHArgs& a;
+  int lane, wave, n_valid;
+  __device__ GradHEpi(const GradHArgs& a_) : a(a_), lane(threadIdx.x & 63), wave(threadIdx.x >> 6), n_valid(meta_get(a_.meta, META_N_VALID)) {}
+  __device__ void begin_item(const StripItem&) {}
+  // the tile's valid tokens of its part
+  __device__ __forceinline__ rsrc_t buffer(const StripItem& it, bool exists) const {
+    const int rows = exists ? max(min(n_valid - it.n0, 256), 0) : 0;
+    return make_rsrc(a.out + (int64_t)it.aux * a.part_stride + (int64_t)it.n0 * a.H_s, (uint32_t)rows * (uint32_t)a.H_s * 4u);
+  }
+  __device__ __forceinline__ uint32_t place(const StripItem& it, int ln, int i, int j) const {
+    const int h = 16 * i + 4 * (ln >> 4);
+    return h < it.a_rows ? ((uint32_t)(64 * wave + 16 * j + (ln & 15)) * (uint32_t)a.H_s + it.m0 + h) * 4u : NOWHERE;
+  }
+  __device__ __forceinline__ void start(const StripItem& it, f32x4 (&T)[MB * 4]) const {
+    const rsrc_t r = buffer(it, a.accumulate);
+    const int ln = fresh(lane);
+    static_for<0, 4 * MB>([&](auto nc) {
+      constexpr int n = decltype(nc)::value;
+      T[n] = load4<true>(r, place(it, ln, n % MB, n / MB));
+      if constexpr (n % 16 == 15) __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  __device__ __forceinline__ void tile(const StripItem& it, f32x4 (&T)[MB * 4]) const {
+    const rsrc_t r = buffer(it, true);
+    const int ln = fresh(lane);
+    static_for<0, 4 * MB>([&](auto nc) {
+      constexpr int n = decltype(nc)::value;
+      store4<true>(r, place(it, ln, n % MB, n / MB), T[n]);
+      if constexpr (n % 16 == 15) __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+};
+
+template <int MB, bool HV>
+KD_STRIP_KERNEL void grad_h_kernel(const GradHArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  GradHWork<MB, HV> work(a);
+  GradHEpi<MB> epi(a);
+  strip_loop<1, false, StripShape<MB, 4>, HV ? A_ROWS_DZ : A_KMAJOR_DZ>(work, epi, smem);
+}
+
+// ------------------------------------------------------------------------------------------
+// before and behind them
+// ------------------------------------------------------------------------------------------
+
+// h_s of the compacted tokens (row j = row rowmap[j] of src for j < n_valid, zero beyond), transposed and in the order in
+// which the waves of grad_W_s load it: [16-row block of h][32-token sub-step][lane][8], lane 16 g + n with tokens 8 g .. + 7
+// of row n.  64 x 64 tiles through LDS; hidden rows past C are zero.
+template <class E>
+__global__ void pack_columns_kernel(const E* src, int C, bf16_t* dst, int T_pad, const int* rowmap, const int* meta) {
+  __shared__ bf16_t tile[64][66];
+  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const int n_valid = meta[META_N_VALID];
+  const int c = c0 + tx, cc = min(c, C - 1);
+  E v[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i)           // (rowmap holds a valid row for every r < T_pad: the loads need no test)
+    v[i] = src[(int64_t)rowmap[r0 + ty + 4 * i] * C + cc];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) tile[ty + 4 * i][tx] = r0 + ty + 4 * i < n_valid && c < C ? (bf16_t)v[i] : (bf16_t)0.f;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int sub = u, blk = ty;                                     // a wave: 16 hidden rows x 32 tokens, 1 KiB
+    if (c0 + 16 * blk >= C) continue;
+    bf16x8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = tile[32 * sub + 8 * (tx >> 4) + e][16 * blk + (tx & 15)];
+    *(bf16x8*)(dst + ((int64_t)(c0 / 16 + blk) * (T_pad / 32) + r0 / 32 + sub) * 512 + tx * 8) = o;
+  }
+}
+
+// grad_h_s row t = sum over split-K parts of the fp32 partial sums of its compacted row (zero for a
+// masked token), converted to the output dtype.
+__global__ void gradh_finish_kernel(const float* parts, int n_parts, int T, int H, const int* inv,
+                                    int out_f32, void* out) {
+  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+  const int64_t n = (int64_t)T * H;
+  if (i >= n) return;
+  const int t = (int)(i / H), h = (int)(i % H);
+  const int j = inv[t];
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  if (j >= 0) {
+    const float* src = parts + (int64_t)j * H + h;
+    v = *(const f32x4*)src;
+    for (int p = 1; p < n_parts; ++p) v += *(const f32x4*)(src + (int64_t)p * n);
+  }
+  if (out_f32) {
+    *(f32x4*)((float*)out + i) = v;
+  } else {
+    *(bf16x4*)((bf16_t*)out + i) = to_bf16(v);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// launchers
+// ------------------------------------------------------------------------------------------
+hipError_t launch_pack_columns(const Problem& p, hipStream_t st) {
+  dim3 grid(p.T_pad / 64, (p.H_s + 63) / 64);
+  if (p.in_f32)
+    hipLaunchKernelGGL(pack_columns_kernel<float>, grid, dim3(256), 0, st, (const float*)p.user_h_s, p.H_s,
+                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
+  else
+    hipLaunchKernelGGL(pack_columns_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)p.user_h_s, p.H_s,
+                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
+  return hipGetLastError();
+}
+
+hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st) {
+  const int nb = grad_W_tile(p.H_s) / 64;
+  GradWArgs a{};
+  a.dz = (const char*)p.dz; a.hT = (const char*)p.h_sT;
+  a.width = width; a.H_s = p.H_s;
+  a.n_vt = (width + 255) / 256; a.n_ht = (p.H_s + 64 * nb - 1) / (64 * nb);
+  a.ldo = p.w_hv ? p.V : p.H_s;
+  a.out = (char*)p.grad_W_s + (size_t)v0 * (p.w_hv ? 1 : p.H_s) * (p.grad_f32 ? 4 : 2);
+  a.lda = (uint32_t)p.V_c * 128; a.ldb = (uint32_t)p.T_pad * 32;
+  a.b_blocks = (p.H_s + 15) / 16;
+  a.meta = p.meta;
+  const int tiles = a.n_vt * a.n_ht, grid = tiles < p.n_cu ? tiles : p.n_cu;
+#define KD_GW3(N, HV, F32) (p.accumulate_grad_W ? launch_big<grad_w_kernel<N, HV, F32, true>>(grid, 256, StripShape<16, N>::SMEM_BYTES, st, &a) \
+                                               : launch_big<grad_w_kernel<N, HV, F32, false>>(grid, 256, StripShape<16, N>::SMEM_BYTES, st, &a))
+#define KD_GW(N) (p.w_hv ? (p.grad_f32 ? KD_GW3(N, true, true) : KD_GW3(N, true, false)) \
+                         : (p.grad_f32 ? KD_GW3(N, false, true) : KD_GW3(N, false, false)))
+  switch (nb) {
+    case 2: return KD_GW(2);
+    case 3: return KD_GW(3);
+    default: return KD_GW(4);
+  }
+#undef KD_GW3
+#undef KD_GW
+}
+
+hipError_t launch_grad_h(const Problem& p, int v0, int width, bool first, hipStream_t st) {
+  const int mb = p.gh_rows / 16;
+  GradHArgs a{};
+  a.dz = (const char*)p.dz;
+  a.W = (const char*)p.W_s + (p.w_hv_inplace ? (size_t)v0 * 2 : (size_t)v0 * p.K_s * 2);
+  a.out = p.gh32; a.part_stride = (int64_t)p.T * p.H_s;
+  a.width = width; a.H_s = p.H_s; a.ldz = p.V_c;
+  a.n_ht = (p.H_s + 16 * mb - 1) / (16 * mb);
+  a.ksteps = p.ksteps_h;
+  a.n_split = ((width + 63) / 64 + a.ksteps - 1) / a.ksteps;       // every part has at least one k-step
+  a.accumulate = first ? 0 : 1;
+  a.lda = 2u * (uint32_t)(p.w_hv_inplace ? p.V : p.K_s);
+  a.ldb = (uint32_t)p.V_c * 128;
+  a.meta = p.meta;
+  const int tiles = a.n_ht * p.n_tt * a.n_split, grid = tiles < p.n_cu ? tiles : p.n_cu;   // worst case: no token masked
+#define KD_GH(N) (p.w_hv_inplace ? launch_big<grad_h_kernel<N, true>>(grid, 256, StripShape<N, 4>::SMEM_BYTES, st, &a) \
+                                 : launch_big<grad_h_kernel<N, false>>(grid, 256, StripShape<N, 4>::SMEM_BYTES, st, &a))
+  switch (mb) {
+    case 4: return KD_GH(4);
+    case 8: return KD_GH(8);
+    case 12: return KD_GH(12);
+    default: return KD_GH(16);
+  }
+#undef KD_GH
+}
+
+hipError_t launch_gradh_finish(const Problem& p, hipStream_t st) {
+  const int64_t n = (int64_t)p.T * p.H_s;
+  const int64_t threads = (n + 3) / 4;
+  hipLaunchKernelGGL(gradh_finish_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, p.gh32,
+                     p.n_ksplit_h, p.T, p.H_s, p.inv, p.grad_f32, p.grad_h_s);
+  return hipGetLastError();
+}
+
+}  // namespace kd
