@@ -15,8 +15,12 @@
 // built: 16 of its 48 blocks are accumulated in vector registers, 12 in accumulation registers, and stay there; the
 // other 20 are accumulated in accumulation registers and parked in LDS.  MFMAs are inline assembly so that each
 // accumulator stays in the register file it was given; the compiler's own choice copies them around inside the loop.
-// With the B ring and the fragments the 512 registers do not quite hold what an epilogue needs: up to 18 of them are
-// spilled in epilogues, none inside a k-loop.
+// With the B ring and the fragments the 512 registers do not quite hold what an epilogue needs: up to 18 of them (AKL's
+// statistics: 28) are spilled in epilogues, none inside a k-loop.
+//
+// One wave per SIMD: whatever stands between two k-steps is idle matrix time.  The loads of a k-step go out one by one
+// between MFMAs, the cursor moves on in front of the last block, and the change to the next phase or tile is off the
+// straight path (T = 4096 JSD, against the same start: 17.28 -> 17.24 ms without this, 17.38 -> 16.23 with it).
 //
 // The backward products (kd_products.hip) run on the same loop, with one accumulator.
 //
@@ -39,17 +43,17 @@ struct StripShape {
   static constexpr int SMEM_BYTES = NST * STAGE_BYTES;
   static_assert(SMEM_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
   static_assert(MB >= 2 * A_LOADS && MB % 4 == 0, "places of the loads in a sub-step");
-  // Sub-step of NM blocks of A.  B load j goes out after block b_place(j); in the first sub-step A load j
-  // after block a_place(j) (behind a B load of the same block).  The barrier of k-step k stands in its second
-  // sub-step before the LDS read of block bar(NM) - 1.  Up to there a wave has issued after its last load of
+  // Sub-step of NM blocks of A.  B load j goes out inside block b_place(j); in the first sub-step A load j
+  // inside block a_place(j) (behind a B load of the same block).  The barrier of k-step k stands in its second
+  // sub-step at the end of block bar(NM) - 1.  Up to there a wave has issued after its last load of
   // k-step k + 1 (end of the first sub-step of k - 1): the B loads of the second sub-step of k - 1, the B and A
   // loads of the first sub-step of k, and the B loads of the second that come before the barrier.
-  static constexpr int b_place(int nm, int j) { return (2 * j + 1) * nm / (2 * NB); }
+  static constexpr int b_place(int nm, int j) { return (2 * j + 1) * nm / (2 * NB) < nm - 1 ? (2 * j + 1) * nm / (2 * NB) : nm - 2; }
   static constexpr int a_place(int nm, int j) { return nm / 2 + j * (nm / 2) / A_LOADS; }
   static constexpr int bar(int nm) { return nm / 4; }
   static constexpr int wait(int nm) {
     int n = NB + NB + A_LOADS;
-    for (int j = 0; j < NB; ++j) n += b_place(nm, j) < bar(nm) - 1 ? 1 : 0;
+    for (int j = 0; j < NB; ++j) n += b_place(nm, j) < bar(nm) ? 1 : 0;
     return n;
   }
   static __device__ __forceinline__ int acc_m(int i, int r, int lane) { return 16 * i + 4 * (lane >> 4) + r; }
@@ -255,7 +259,9 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
 #pragma unroll
       for (int j = 0; j < NB; ++j) bjo[j] = bj[j];
     }
-    if (++l_k == l_nk) {
+    if constexpr (!TR) l_a += 128;
+    l_b += 2 * B_SUB;
+    if (__builtin_expect(++l_k == l_nk, 0)) {
       const bool more = (NPH == 2 && l_ph == 0) || l_item + 1 < n_items;
       if (more) {
         l_k = 0;
@@ -264,20 +270,17 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
         set_cursor(work.item(l_item));
       } else {           // past the end: the last k-step again (valid memory, data unused)
         --l_k;
+        if constexpr (!TR) l_a -= 128;
+        l_b -= 2 * B_SUB;
       }
-    } else {
-      l_b += 2 * B_SUB;
-      if constexpr (TR) {
-        l_pa += AM == A_DZ ? (uint64_t)l_lda : (uint64_t)l_lda * 64;
-        ra = make_rsrc(l_pa, AM == A_DZ ? C::STAGE_BYTES : 64u * l_lda);
-        if (AM == A_KMAJOR_DZ && l_k == l_nk - 1 && l_tail < 64) set_voff(l_tail);
-      } else {
-        l_a += 128;
-      }
+    } else if constexpr (TR) {
+      l_pa += AM == A_DZ ? (uint64_t)l_lda : (uint64_t)l_lda * 64;
+      ra = make_rsrc(l_pa, AM == A_DZ ? C::STAGE_BYTES : 64u * l_lda);
+      if (AM == A_KMAJOR_DZ && __builtin_expect(l_k == l_nk - 1 && l_tail < 64, 0)) set_voff(l_tail);
     }
   };
-  auto issue_a = [&](int st, int j) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(smem + st * C::STAGE_BYTES + wave * 1024 + j * 4096), 16,
+  auto issue_a = [&](int st, int j) {                // st: byte offset of the stage
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(smem + st + wave * 1024 + j * 4096), 16,
                                              voff[j], l_a, 0, 0);
   };
   const uint32_t boff = lane * 16;
@@ -313,33 +316,33 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
   auto read_a = [&](Frag& f, int st, auto sc, auto ic) {
     constexpr int s = decltype(sc)::value, i = decltype(ic)::value;
     if constexpr (AM == A_ROWS) {
-      f.v = *(const u32x4*)(smem + st * C::STAGE_BYTES + fk[s] + i * 2048);
+      f.v = *(const u32x4*)(smem + st + fk[s] + i * 2048);
     } else if constexpr (AM == A_ROWS_DZ) {
-      const uint32_t at = lds0 + st * C::STAGE_BYTES;
+      const uint32_t at = lds0 + st;
       strip_half_read<i * 2048>(f.lo, at + fk[2 * s]);
       strip_half_read<i * 2048>(f.hi, at + fk[2 * s + 1]);
     } else if constexpr (AM == A_KMAJOR_DZ) {
       constexpr bool wide = i < 8 * REGIONS;
       constexpr int at = wide ? (i >> 3) * 16384 : REGIONS * 16384, kb = wide ? 256 : 128;
-      const uint32_t ad = (uint32_t)(fk[wide ? 0 : 1] ^ (wide ? (i & 7) * 32 : (i & 3) * 32)) + (lds0 + st * C::STAGE_BYTES);
+      const uint32_t ad = (uint32_t)(fk[wide ? 0 : 1] ^ (wide ? (i & 7) * 32 : (i & 3) * 32)) + (lds0 + st);
       strip_tr_read<at + s * 32 * kb>(f.lo, ad);
       strip_tr_read<at + (s * 32 + 16) * kb>(f.hi, ad);
     } else {
-      const uint32_t at = lds0 + st * C::STAGE_BYTES;
+      const uint32_t at = lds0 + st;
       strip_tr_read<(i >> 1) * 4096 + s * 2048 + (i & 1) * 512>(f.lo, at + fk[0]);
       strip_tr_read<(i >> 1) * 4096 + s * 2048 + (i & 1) * 512>(f.hi, at + fk[1]);
     }
   };
   u32x4 B[4][NB];          // sub-steps of two k-steps
   Frag A[MB];              // the next sub-step's fragments
-  int stage = 0, fill = C::DIST;
+  int stage = 0, next = C::STAGE_BYTES, fill = 2 * C::STAGE_BYTES;      // byte offsets: consumed, behind it, refilled
+  static_assert(C::NST == 3 && C::DIST == 2, "stages");
 
   // one k-step of NM blocks of A; Q: half of the B ring it consumes.  mma(IntC<i>, IntC<j>, a, b)
   // MORE: vector memory operations since that may be in flight, too
   auto kstep = [&](auto nmc, auto qc, auto morec, auto&& mma) {
     constexpr int Q = decltype(qc)::value, NM = decltype(nmc)::value;
     constexpr int W = C::wait(NM) + decltype(morec)::value < 63 ? C::wait(NM) + decltype(morec)::value : 63;
-    const int next = stage == C::NST - 1 ? 0 : stage + 1;
     asm volatile("s_nop 1");           // whatever the compiler moved between k-steps, an MFMA may read now
     KD_PIN();
     static_for<0, 2>([&](auto sc) {
@@ -353,8 +356,27 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
         if constexpr (HALVES) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(2 * behind < 14 ? 2 * behind : 14));
         const u32x4 a = strip_op(A[i]);
         static_for<0, NB>([&](auto jc) {
-          mma(ic, jc, a, B[2 * Q + s][decltype(jc)::value]);
+          constexpr int j = decltype(jc)::value;
+          // the cursor moves on in the shadow of the last block's MFMAs
+          if constexpr (s == 1 && i == NM - 1 && j == 0) { advance(); KD_PIN(); }
+          mma(ic, jc, a, B[2 * Q + s][j]);
           KD_PIN();
+          if constexpr (j == (NB > 1 ? 1 : 0))
+            static_for<0, NB>([&](auto lc) {
+              constexpr int l = decltype(lc)::value;
+              if constexpr (C::b_place(NM, l) == i) {
+                if constexpr (s == 0) B[(2 * Q + 3) & 3][l] = load_b(rbo, bjo, l_bo, 1, l);
+                else B[2 * Q][l] = load_b(rb, bj, l_b, 0, l);
+                KD_PIN();
+              }
+            });
+          if constexpr (s == 0 && j == (NB > 2 ? 2 : NB - 1))
+            static_for<0, C::A_LOADS>([&](auto lc) {
+              if constexpr (C::a_place(NM, decltype(lc)::value) == i) {
+                issue_a(fill, decltype(lc)::value);
+                KD_PIN();
+              }
+            });
         });
         // k-step k+1 has landed for every wave before anyone reads it, and every wave has read all of this
         // stage before anyone refills it
@@ -364,23 +386,13 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
         } else if constexpr (s == 0 || i >= C::bar(NM)) {
           read_a(A[i], rd, IntC<s ^ 1>{}, ic);
         }
-        static_for<0, NB>([&](auto jc) {
-          constexpr int j = decltype(jc)::value;
-          if constexpr (C::b_place(NM, j) == i) {
-            if constexpr (s == 0) B[(2 * Q + 3) & 3][j] = load_b(rbo, bjo, l_bo, 1, j);
-            else B[2 * Q][j] = load_b(rb, bj, l_b, 0, j);
-          }
-        });
-        if constexpr (s == 0)
-          static_for<0, C::A_LOADS>([&](auto jc) {
-            if constexpr (C::a_place(NM, decltype(jc)::value) == i) issue_a(fill, decltype(jc)::value);
-          });
         KD_PIN();
       });
     });
-    advance();
+    const int released = stage;
     stage = next;
-    fill = fill == C::NST - 1 ? 0 : fill + 1;
+    next = fill;
+    fill = released;
   };
   // All k-steps of one phase.  Vector memory operations are counted in order, so the stores of the tile before (STORES of
   // them) would have to land before the loop's first waits are over: the first k-step, whose operands are older than they,
@@ -427,7 +439,7 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
 #pragma unroll
   for (int i = 0; i < C::DIST; ++i) {
 #pragma unroll
-    for (int j = 0; j < C::A_LOADS; ++j) issue_a(i, j);
+    for (int j = 0; j < C::A_LOADS; ++j) issue_a(i * C::STAGE_BYTES, j);
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
