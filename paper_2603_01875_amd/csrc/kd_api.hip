@@ -119,7 +119,7 @@ struct CallPlan {
 // Whether the strip loop (192-row tiles) or the eight-wave loop (128-row tiles) makes the logit tiles.
 //  - A contracted element costs the strip loop 0.91 of what it costs the other, but its one wave per SIMD has nothing to
 //    hide a tile's epilogue behind: that costs as much as 100 more elements (FKL, RKL), 200 (the row pass of JSD, TVD and
-//    the skewed KLs) or 300 (AKL, whose four search passes contract the teacher's elements alone).
+//    the skewed KLs) or 300 (AKL, whose search passes contract the teacher's elements alone; four on the eight-wave loop, three here).
 //  - The gradient kernel walks whole tiles in rounds of n_cu workgroups; the passes before it even out over ranges of the
 //    vocabulary, down to a tile each.
 // Measured over 1178 sizes, T = 257 .. 16384 and V = 256 .. 151936 (steps, eight waves against strips): T = 512, H_t = 8192,
@@ -240,11 +240,13 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   L.inv = take((size_t)q.T * 4);
   L.row_loss = take((size_t)q.T_pad * 4);
   // partial sums per (vocabulary range, part of a workgroup, token): 5 statistics, 6 for AKL, whose
-  // search passes keep one sum per threshold.  A strip range leaves one part, an eight-wave one four: what a lean plan
+  // search passes keep one sum per threshold or bin.  A strip range leaves one part, an eight-wave one four: what a lean plan
   // needs (at least 32 parts, four for every two strips) holds the strip loop's up to 32 ranges and more, too.
   const int part_vals = q.kind == KD_AKL ? kd::kAklThresholds : 5;
   const int parts = 4 * (q.strip ? lean_split : q.n_split);
-  const size_t partial_bytes = (size_t)parts * part_vals * q.T_pad * 4;
+  size_t partial_bytes = (size_t)parts * part_vals * q.T_pad * 4;
+  const size_t bin_bytes = (size_t)q.n_split * (kd::kAklBins + 1) * q.T_pad * 4;
+  if (q.strip && q.kind == KD_AKL && partial_bytes < bin_bytes) partial_bytes = bin_bytes;
   if (!with_backward) L.partials = take(partial_bytes);
   L.prep_h_t = L.prep_W_t = L.prep_h_s = L.prep_W_s = 0;
   const size_t h_rows = q.strip ? q.T_pad : q.T;         // the strip loop reads whole token tiles of packed rows

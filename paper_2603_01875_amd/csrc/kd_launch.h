@@ -74,8 +74,10 @@ hipError_t launch_combine(const Problem& p, hipStream_t st);
 hipError_t launch_rows(const Problem& p, hipStream_t st);
 hipError_t launch_akl_search(const Problem& p, hipStream_t st);      // one search pass and its merge
 hipError_t launch_akl_weights(const Problem& p, hipStream_t st);
-constexpr int kAklSearchPasses = 4;    // 17-fold narrowing each: 40 -> 4.8e-4 in base-2 log-probability
-constexpr int kAklThresholds = 16;     // per pass (the kernels' AKL_K)
+constexpr int kAklSearchPasses = 4;    // eight-wave loop: 17-fold narrowing each, 40 -> 4.8e-4 in base-2 log-probability
+constexpr int kAklThresholds = 16;     // ... per pass (the kernels' AKL_K)
+constexpr int kAklBins = 40;           // strip loop: 40-fold, until kAklResolution is reached: three passes from up to 30
+constexpr float kAklResolution = 4.78e-4f;
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st);
 hipError_t launch_finalize(const Problem& p, hipStream_t st);
 hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulate, hipStream_t st);
