@@ -267,7 +267,7 @@ def main():
 
     # HBM-side traffic of one statistics launch: NOT measured in this run (it needs rocprofv3 --pmc); the value
     # stored with its command under profiles/ is passed through and labelled as such
-    stats_kernel = "stats_strip_kernel" if K.kd_loss_plan_loop(p) else "stats_kernel"
+    stats_kernel = ("stats_strip_hv_kern" if hv else "stats_strip_kernel") if K.kd_loss_plan_loop(p) else "stats_kernel"
     traffic, traffic_source = None, None
     if os.path.exists(args.traffic_file) and not args.teacher_fp8 and not hv:
         try:

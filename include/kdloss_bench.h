@@ -39,7 +39,8 @@ int kd_loss_profile_count(void);
 kd_status kd_loss_profile_clock(void* two_int64_device);
 
 /* Which loop makes the logit tiles of a call with these params: 0 = the eight-wave loop (stats_kernel, rows_kernel,
- * grad_kernel), 1 = the strip loop (stats_strip_kernel, ...).  Host only. */
+ * grad_kernel), 1 = the strip loop (stats_strip_kernel, ...; for [H][V] heads read in place
+ * stats_strip_hv_kern, ...).  Host only. */
 kd_status kd_loss_plan_loop(const kd_loss_params* params, int32_t* loop);
 
 /* Benchmark aid, not part of the method: what the bf16 matrix pipe sustains on this GPU with nothing

@@ -185,9 +185,9 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
     const int64_t K_t = contraction(q.in_f32, call.H_t ? call.H_t[i] : p->H_t);
     logit_k += q.K_s + (q.t_fp8 ? K_t / 2 : K_t);        // (an e4m3 element costs half a bf16 one)
   }
-  // The strip loop takes bf16 operands with [V][K] heads (in place or re-packed).  It reads the hidden states from a
-  // packed copy, so they are re-packed whether a mask is given or not.
-  q.strip = !q.t_fp8 && !q.w_hv_inplace && !call.lean && strips_ahead(q, call.n_teachers, logit_k);
+  // The strip loop takes bf16 operands (heads [V][K], in place or re-packed, or [K][V] in place with 24-bit strides).  It
+  // reads the hidden states from a packed copy, so they are re-packed whether a mask is given or not.
+  q.strip = !q.t_fp8 && !(q.w_hv_inplace && q.V >= (1 << 23)) && !call.lean && strips_ahead(q, call.n_teachers, logit_k);
   q.parts = q.strip ? 1 : 4;
   q.n_vt = (q.V + kd::kTileM - 1) / kd::kTileM;
   // Vocabulary ranges of the statistics passes.  The device picks the actual number once it knows

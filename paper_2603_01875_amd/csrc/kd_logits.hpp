@@ -1,0 +1,774 @@
+// What the logit kernels are made of: the work maps, and the epilogues that turn a finished tile of both models' logits into
+// statistics, row sums or dL/dz_s, on either tile loop.  The kernels are in kd_kernels.hip and kd_strip_hv.hip.
+#pragma once
+#include "kd_common.hpp"
+
+// tile configurations (overridable for tuning experiments)
+#ifndef KD_LOGIT_CFG
+#define KD_LOGIT_CFG 2, 2, 4, 64, 3     // MI, NI, WN, BK, NST: 128 x 256 tile, 8 waves
+#endif
+
+// Ablation builds for measurements (never the product: RESULTS ARE WRONG when this is not 0).  They take one
+// cost out of the logit kernels so that its share of the time and of the shader clock can be read off:
+//   1  every workgroup loads the same head rows and the same token rows (all loads hit the L2: no traffic
+//      behind it), everything else unchanged
+//   2  the statistics epilogue (two exp2 per logit pair, running maxima) is replaced by a plain sum
+//   3  both
+#ifndef KD_ABLATE
+#define KD_ABLATE 0
+#endif
+
+#if KD_LOOP_ABLATE
+#error "KD_LOOP_ABLATE is for tile_loop_bench.hip only: the library's kernels must compute their products"
+#endif
+
+namespace kd {
+
+typedef TileCfg<KD_LOGIT_CFG> LCfg;   // logit tiles: two accumulators per tile
+constexpr int BK = LCfg::BK;
+constexpr int NI = LCfg::NI;
+static_assert(LCfg::BM == kTileM && BN == kTileN, "planner and kernels disagree");
+constexpr int BM = LCfg::BM;
+constexpr int MI = LCfg::MI;
+typedef LCfg::Acc AccTile;
+__device__ __forceinline__ int acc_m(int wm, int mt, int r, int lane) { return LCfg::acc_m(wm, mt, r, lane); }
+__device__ __forceinline__ int acc_n(int wn, int nt, int lane) { return LCfg::acc_n(wn, nt, lane); }
+
+// ------------------------------------------------------------------------------------------
+// work maps
+// ------------------------------------------------------------------------------------------
+
+// Index q over an (na x nb) grid walked in (ba x bb) blocks, a fastest inside a block.
+__device__ __forceinline__ void block_decode(int q, int na, int ba, int bb, int& a, int& b) {
+  const int per = ba * bb;
+  const int blk = q / per, w = q - blk * per;
+  const int nblk_a = na / ba;
+  a = (blk % nblk_a) * ba + w % ba;
+  b = (blk / nblk_a) * bb + w / ba;
+}
+
+struct LogitArgs {
+  const bf16_t* W_s; const bf16_t* h_s; const bf16_t* W_t; const bf16_t* h_t;
+  int T, V, H_s, H_t;  // H_*: contraction length and row stride of the (re-packed) operands
+                       // (heads in [H][V] order: their row stride is V)
+  const int* meta;     // device-side plan: valid tokens, token tiles, vocabulary splits
+  int v0, v_end;       // vocabulary rows [v0, v_end) handled by this launch
+  int n_vt;            // ... in this many tiles
+  int bb;              // grad kernel, eight-wave loop: block width of the work map along the vocabulary (bb | n_vt).
+                       // An XCD's 32 workgroups cover 2 token tiles x 16 vocabulary tiles where the
+                       // counts allow: measured 2-3 % faster than 4 x 8 for this kernel (1 x 32 and
+                       // 8 x 4 are slower), while the statistics kernels do not care
+  float c;             // log2(e) / tau
+  float beta;
+  float t_scale;       // fp8 teacher: z_t = t_scale * (product of the e4m3 codes); 1 otherwise
+  int T_pad;
+  float* partials;     // stats: [parts][5][T_pad];  jsd: [parts][2][T_pad]
+  const f32x4* rowinfo;// [T_pad]: {lse2_t, lse2_s, mask/(n tau), row term}
+  const float* akl;    // AKL only: [AKL_ROWS][T_pad] per-token values (see the AKL_* indices)
+  bf16_t* dz;          // chunk of dL/dz_s, ldz columns, in the order of dz_chunk
+  int ldz;
+  int last_chunk;      // this launch handles the last chunk of the vocabulary
+  int dz_accumulate;   // add to dz instead of overwriting it (further teachers of a multi-teacher call)
+  long long* clock_out;// measurement aid (may be null): workgroup 0 of the statistics kernel stores the shader
+                       // cycles and the 100 MHz ticks its tile loop took
+};
+
+// TF8: the teacher operands are e4m3 bytes (one byte per element, 128 elements per k-step).
+// WHV: the heads are stored [H][V] (vocabulary contiguous), i.e. k-major for the logit products.
+template <bool TF8, bool WHV>
+__device__ __forceinline__ WorkItem logit_item(const LogitArgs& a, int vt, int tt) {
+  WorkItem it;
+  const int m0 = a.v0 + vt * BM;
+  it.B0 = a.h_s + (int64_t)tt * BN * a.H_s;
+  if (WHV) {
+    it.A0 = a.W_s + m0;
+    it.A1 = a.W_t + m0;
+    it.B1 = a.h_t + (int64_t)tt * BN * a.H_t;
+  } else if (TF8) {
+    it.A0 = a.W_s + (int64_t)m0 * a.H_s;
+    it.A1 = (const bf16_t*)((const char*)a.W_t + (int64_t)m0 * a.H_t);
+    it.B1 = (const bf16_t*)((const char*)a.h_t + (int64_t)tt * BN * a.H_t);
+  } else {
+    it.A0 = a.W_s + (int64_t)m0 * a.H_s;
+    it.A1 = a.W_t + (int64_t)m0 * a.H_t;
+    it.B1 = a.h_t + (int64_t)tt * BN * a.H_t;
+  }
+#if KD_ABLATE & 1
+  {   // same operand rows for every tile (the tile's coordinates below stay its own)
+    it.B0 = a.h_s; it.B1 = a.h_t;
+    it.A0 = a.W_s; it.A1 = a.W_t;
+  }
+#endif
+  it.ka_rows = it.kb_rows = 1 << 30;       // hidden sizes are whole k-steps: no k-row is ever missing
+  it.a_rows = min(BM, a.v_end - m0);
+  it.b_rows = min(BN, a.T - tt * BN);
+  it.nk0 = a.H_s / BK;
+  it.nk1 = a.H_t / (TF8 ? 2 * BK : BK);
+  it.m0 = m0;
+  it.n0 = tt * BN;
+  it.aux = 0;
+  return it;
+}
+
+// One workgroup = one (token tile, vocabulary split); it walks the split's tiles in order.
+struct SplitMap {
+  const LogitArgs& a;
+  int tt, split, lo, cnt;
+  __device__ SplitMap(const LogitArgs& a_) : a(a_) {
+    const int n_tt = meta_get(a.meta, META_N_TT), n_split = meta_get(a.meta, META_N_SPLIT);
+    const int active = n_tt * n_split;               // the grid is sized for the unmasked worst case
+    tt = split = lo = cnt = 0;
+    if ((int)blockIdx.x >= active) return;
+    group_decode(xcd_logical_id(blockIdx.x, active), n_tt, n_split, tt, split);
+    lo = (int)(((int64_t)split * a.n_vt) / n_split);
+    const int hi = (int)(((int64_t)(split + 1) * a.n_vt) / n_split);
+    cnt = hi - lo;
+  }
+  __device__ int n_items() const { return cnt; }
+};
+template <bool TF8, bool WHV>
+struct SplitWork : SplitMap {
+  using SplitMap::SplitMap;
+  __device__ WorkItem item(int i) const { return logit_item<TF8, WHV>(a, lo + i, tt); }
+};
+
+// The strip loop's share of a workgroup.  With n_split > 0: one (token tile, vocabulary range), the ranges in units
+// of 64 rows, walked in tiles of three units and a rest.  With n_split == 0: the (token tile x 192-row tile) grid,
+// four token tiles at a time, strided over kNumCU persistent workgroups (which evens out better where few tiles per
+// workgroup meet an awkward number of token tiles: 29 x 43 tiles in five rounds, not six).
+// HV: the heads are stored [H][V] (their rows are k-rows).
+template <bool HV>
+struct StripWork {
+  const LogitArgs& a;
+  int n_tt, tt, split, row0, row1, cnt, L, G, n_vt;
+  __device__ StripWork(const LogitArgs& a_, int n_split) : a(a_) {
+    n_tt = meta_get(a.meta, META_N_TT);
+    tt = split = row0 = row1 = cnt = L = n_vt = 0;
+    G = 1;
+    if (n_split == 0) {
+      G = min((int)gridDim.x, kNumCU);
+      n_vt = (a.v_end - a.v0 + StripCfg::BM - 1) / StripCfg::BM;
+      if ((int)blockIdx.x >= G) return;
+      L = xcd_logical_id(blockIdx.x, G);
+      cnt = L < n_tt * n_vt ? (n_tt * n_vt - L + G - 1) / G : 0;
+      return;
+    }
+    const int active = n_tt * n_split;               // the grid is sized for the unmasked worst case
+    if ((int)blockIdx.x >= active) return;
+    group_decode(xcd_logical_id(blockIdx.x, active), n_tt, n_split, tt, split);
+    const int units = (a.v_end - a.v0 + 63) / 64;
+    row0 = a.v0 + 64 * (int)(((int64_t)split * units) / n_split);
+    row1 = min(a.v_end, a.v0 + 64 * (int)(((int64_t)(split + 1) * units) / n_split));
+    cnt = (row1 - row0 + StripCfg::BM - 1) / StripCfg::BM;
+  }
+  __device__ int n_items() const { return cnt; }
+  __device__ StripItem item(int i) const {
+    const auto p = kernel_args<LogitArgs>();
+    StripItem it;
+    int m0 = row0 + i * StripCfg::BM, n0 = tt * BN, end = row1;
+    if (n_vt > 0) {
+      const int q = i * G + L, n_four = n_tt / 4, grp = q / (4 * n_vt), w = q - grp * 4 * n_vt;
+      const int g = grp < n_four ? 4 : n_tt - 4 * n_four;
+      const int vt = w / g;
+      n0 = (4 * grp + w - vt * g) * BN;
+      m0 = p->v0 + vt * StripCfg::BM;
+      end = p->v_end;
+    }
+    it.a_rows = min(StripCfg::BM, end - m0);
+    it.out_rows = (it.a_rows + 63) / 64 * 64;        // zeros behind the chunk's last row: the k-steps of grad_h_s are whole
+    it.m0 = m0;
+    it.n0 = n0;
+#if KD_ABLATE & 1
+    m0 = n0 = 0;       // same operand rows for every tile (the tile's coordinates stay its own)
+#endif
+    it.k0 = p->H_s; it.k1 = p->H_t;
+    it.lda0 = 2 * (HV ? p->V : it.k0); it.ldb0 = 128 * it.k0;
+    it.lda1 = 2 * (HV ? p->V : it.k1); it.ldb1 = 128 * it.k1;
+    it.A0 = (const char*)p->W_s + (int64_t)m0 * (HV ? 2 : it.lda0);
+    it.A1 = (const char*)p->W_t + (int64_t)m0 * (HV ? 2 : it.lda1);
+    it.B0 = (const char*)p->h_s + (int64_t)n0 * (2 * it.k0);
+    it.B1 = (const char*)p->h_t + (int64_t)n0 * (2 * it.k1);
+    it.aux = it.b_blocks = 0;
+    return it;
+  }
+};
+// Teacher product only (one accumulator): the AKL threshold search.
+template <bool WHV>
+struct TeacherSplitWork : SplitMap {
+  using SplitMap::SplitMap;
+  __device__ WorkItem item(int i) const {
+    WorkItem it = logit_item<false, WHV>(a, lo + i, tt);
+    it.A0 = it.A1; it.B0 = it.B1;       // phase 0 is the teacher product
+    it.nk0 = it.nk1;
+    return it;
+  }
+};
+
+// Persistent workgroups striding over the (token tile x vocabulary tile) grid of a chunk.
+struct ChunkMap {
+  const LogitArgs& a;
+  int L, G, n_tiles, n_tt, ba;
+  __device__ ChunkMap(const LogitArgs& a_) : a(a_) {
+    G = gridDim.x;
+    L = xcd_logical_id(blockIdx.x, G);
+    n_tt = meta_get(a.meta, META_N_TT);
+    ba = 1;                                          // ba | n_tt, ba * bb <= 32: one block per XCD
+    for (int d = 2; d * a.bb <= 32; ++d) if (n_tt % d == 0) ba = d;
+    n_tiles = n_tt * a.n_vt;
+  }
+  __device__ int n_items() const { return L < n_tiles ? (n_tiles - L + G - 1) / G : 0; }
+  __device__ void tile(int i, int& tt, int& vt) const { block_decode(i * G + L, n_tt, ba, a.bb, tt, vt); }
+};
+template <bool TF8, bool WHV>
+struct ChunkWork : ChunkMap {
+  using ChunkMap::ChunkMap;
+  __device__ WorkItem item(int i) const {
+    int tt, vt;
+    tile(i, tt, vt);
+    return logit_item<TF8, WHV>(a, vt, tt);
+  }
+};
+// ------------------------------------------------------------------------------------------
+// epilogues of the logit tiles
+// ------------------------------------------------------------------------------------------
+constexpr float NEG_BIG = -1.0e30f;   // logit given to vocabulary rows beyond V: every exp of it is 0
+// Running maxima start here, far below any real scaled logit and far above NEG_BIG * c (the host
+// bounds tau so that c > 1e-9): a lane that has seen only masked rows keeps this maximum, so the
+// exponent of a masked entry stays hugely negative instead of cancelling to a rounding residual.
+constexpr float M_FLOOR = -1.0e20f;
+constexpr float LN2 = 0.6931471805599453f;
+
+// Adaptive KL: per-token values kept between its passes, [AKL_ROWS][T_pad] floats.
+enum { AKL_FKL = 0, AKL_RKL = 1,   // the token's forward / reverse KL
+       AKL_LO = 2, AKL_HI = 3,     // search interval of the head threshold (base-2 teacher log-probability):
+                                   // mass{lt >= LO} > mu >= mass{lt >= HI}
+       AKL_LTMAX = 4,              // the largest teacher log-probability of the token
+       AKL_WR = 5,                 // weight of the reverse KL (the forward KL has 1 - that)
+       AKL_ROWS = 6 };
+constexpr int AKL_K = kAklThresholds;   // thresholds tried per search pass of the eight-wave loop: 17-fold narrowing
+constexpr int AKL_BINS = kAklBins;      // bins of a search pass of the strip loop
+constexpr float AKL_TOP_EPS = 1.0e-4f;   // entries this close (base-2 log) to the token's largest one count as "the top entry"
+
+__device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
+__device__ __forceinline__ float flog2(float x) { return __builtin_amdgcn_logf(x); }
+
+// How a lane sees a finished tile: NC token columns of (up to) NE vocabulary entries each, entry e of the lane's
+// share lying at vocabulary row m(e) of the tile (four consecutive e are four consecutive rows), column j at
+// token n(j).  PARTS partial results per token and vocabulary split leave a workgroup; this lane's is part().
+struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
+  static constexpr int NC = NI, NE = MI * 16, PARTS = 4;
+  int wm, wn, lane;
+  __device__ TileGeo() {
+    lane = threadIdx.x & 63;
+    wm = (threadIdx.x >> 6) & 1;
+    wn = threadIdx.x >> 7;
+  }
+  __device__ __forceinline__ int m(int e) const { return acc_m(wm, e >> 4, e & 15, lane); }
+  __device__ __forceinline__ int n(int j) const { return acc_n(wn, j, lane); }
+  __device__ __forceinline__ int part() const { return wm * 2 + (lane >> 5); }
+  static constexpr int MERGE = 64;                   // lanes of one token merged before they leave: none
+  // dz (dz_chunk): entries 16 p .. + 15 of column j are pieces of four rows, piece q at rows 8 q + 4 (lane / 32) of 32;
+  // pieces u and u + 2 are a lane's 16 bytes (u = 0, 1)
+  static constexpr int PAIR = 2;
+  __device__ __forceinline__ int64_t dz_at(int ldz, int n0, int m0, int j, int p, int u) const {
+    return dz_chunk(ldz, (n0 >> 6) + wn, ((m0 + wm * 32 * MI) >> 5) + p, 2 * j + ((lane >> 4) & 1), 16 * (2 * u + (lane >> 5)) + (lane & 15));
+  }
+};
+struct StripGeo {        // 192 x 256 tile of four waves (kd_strip.hpp)
+  static constexpr int NC = StripCfg::NB, NE = StripCfg::MB * 4, PARTS = 1;
+  int wave, lane;
+  __device__ StripGeo() {
+    lane = threadIdx.x & 63;
+    wave = threadIdx.x >> 6;
+  }
+  __device__ __forceinline__ int m(int e) const { return StripCfg::acc_m(e >> 2, e & 3, lane); }
+  __device__ __forceinline__ int n(int j) const { return StripCfg::acc_n(j, lane, wave); }
+  __device__ __forceinline__ int part() const { return 0; }
+  static constexpr int MERGE = 16;                   // lanes 16 and 32 apart hold the same token
+  // dz (dz_chunk): entries 16 p .. + 15 of column j are four rows of each of four blocks; two neighbouring blocks are a
+  // lane's 16 bytes, a wave's stores whole KiB
+  static constexpr int PAIR = 1;
+  __device__ __forceinline__ int64_t dz_at(int ldz, int n0, int m0, int j, int p, int u) const {
+    return dz_chunk(ldz, (n0 >> 6) + wave, (m0 >> 5) + 2 * p + u, j, lane);
+  }
+};
+
+// Drives an epilogue (template on the geometry, one column at a time) from tile_loop.
+template <class Epi>
+struct TileEpi {
+  Epi& epi;
+  float ts;
+  __device__ TileEpi(Epi& e, float t_scale) : epi(e), ts(t_scale) {}
+  __device__ void begin_item(const WorkItem& it) { epi.begin_item(it.m0, it.n0, BM); }
+  __device__ void end_item(const WorkItem& it, AccTile& accS, AccTile& accT) {
+    if (ts != 1.f) {     // fp8 teacher: the accumulator holds the product of the e4m3 codes; bring it to logits
+#pragma unroll
+      for (int mt = 0; mt < MI; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NI; ++nt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) accT[mt][nt][r] *= ts;
+    }
+    // Rows of A beyond the vocabulary (last tile only) must not contribute: give them a huge negative logit in
+    // both accumulators (their exp is 0, their difference is 0).
+    if (it.a_rows != BM) {
+#pragma unroll
+      for (int mt = 0; mt < MI; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool ok = epi.geo.m(16 * mt + r) < it.a_rows;
+#pragma unroll
+          for (int nt = 0; nt < NI; ++nt) {
+            accS[mt][nt][r] = ok ? accS[mt][nt][r] : NEG_BIG;
+            accT[mt][nt][r] = ok ? accT[mt][nt][r] : NEG_BIG;
+          }
+        }
+    }
+    static_for<0, NI>([&](auto jc) {
+      constexpr int j = decltype(jc)::value;
+      float S[TileGeo::NE], T[TileGeo::NE];
+#pragma unroll
+      for (int mt = 0; mt < MI; ++mt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { S[16 * mt + r] = accS[mt][j][r]; T[16 * mt + r] = accT[mt][j][r]; }
+      epi.column(jc, S, T);
+    });
+  }
+};
+// ... and from strip_loop.
+template <class Epi>
+struct StripEpi {
+  static constexpr bool WHOLE = false;
+  Epi& epi;
+  __device__ StripEpi(Epi& e) : epi(e) {}
+  __device__ void begin_item(const StripItem& it) { epi.begin_item(it.m0, it.n0, it.out_rows); }
+  __device__ float pad(int) const { return NEG_BIG; }
+  template <class J, int NM>
+  __device__ __forceinline__ void column(const StripItem&, J jc, f32x4 (&S4)[NM], f32x4 (&T4)[NM]) {
+    float S[4 * NM], T[4 * NM];
+#pragma unroll
+    for (int e = 0; e < 4 * NM; ++e) { S[e] = S4[e >> 2][e & 3]; T[e] = T4[e >> 2][e & 3]; }
+    epi.column(jc, S, T);
+  }
+};
+
+// Online log-sum-exp of both models plus the cross term of FKL / RKL.
+//   FKL: X = sum_v 2^(a_t - m_t) (z_t - z_s)      RKL: X = sum_v 2^(a_s - m_s) (z_s - z_t)
+template <int KIND, class Geo>
+struct StatsEpi {
+  static constexpr int NV = KIND == 6 ? 6 : 5;     // values per token and part (AKL keeps both cross terms)
+  static constexpr int NC = Geo::NC;
+  Geo geo;
+  float m_t[NC], S_t[NC], m_s[NC], S_s[NC], X[NC], X2[NC];
+  float c;
+  __device__ StatsEpi(float c_) : c(c_) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      m_t[j] = M_FLOOR; m_s[j] = M_FLOOR; S_t[j] = 0.f; S_s[j] = 0.f; X[j] = 0.f; X2[j] = 0.f;
+    }
+  }
+  __device__ void begin_item(int, int, int) {}
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+#if KD_ABLATE & 2
+#pragma unroll
+    for (int e = 0; e < NE; ++e) { S_t[j] += T[e]; S_s[j] += S[e]; }
+    return;
+#endif
+    float tmax = NEG_BIG, smax = NEG_BIG;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      tmax = fmaxf(tmax, T[e]);
+      smax = fmaxf(smax, S[e]);
+    }
+    const float nmt = fmaxf(m_t[j], tmax * c);
+    const float nms = fmaxf(m_s[j], smax * c);
+    const float sct = fexp2(m_t[j] - nmt);
+    const float scs = fexp2(m_s[j] - nms);
+    float st = S_t[j] * sct, ss = S_s[j] * scs;
+    float x = X[j] * ((KIND == 0 || KIND == 6) ? sct : scs);
+    float x2 = X2[j] * scs;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const float zt = T[e], zs = S[e];
+      const float et = fexp2(fmaf(zt, c, -nmt));
+      const float es = fexp2(fmaf(zs, c, -nms));
+      st += et;
+      ss += es;
+      if (KIND == 0 || KIND == 6) x = fmaf(et, zt - zs, x);
+      if (KIND == 1) x = fmaf(es, zs - zt, x);
+      if (KIND == 6) x2 = fmaf(es, zs - zt, x2);
+    }
+    m_t[j] = nmt; m_s[j] = nms; S_t[j] = st; S_s[j] = ss; X[j] = x; X2[j] = x2;
+  }
+  __device__ void write(const LogitArgs& a, int tt, int split) {
+    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * NV * a.T_pad;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+#pragma unroll
+      for (int off = Geo::MERGE; off < 64; off <<= 1) {      // lanes that hold the same token
+        const float omt = __shfl_xor(m_t[j], off, 64), oms = __shfl_xor(m_s[j], off, 64);
+        const float nmt = fmaxf(m_t[j], omt), nms = fmaxf(m_s[j], oms);
+        const float wt = fexp2(m_t[j] - nmt), ws = fexp2(m_s[j] - nms);
+        const float owt = fexp2(omt - nmt), ows = fexp2(oms - nms);
+        const bool by_t = KIND == 0 || KIND == 6;
+        S_t[j] = fmaf(__shfl_xor(S_t[j], off, 64), owt, S_t[j] * wt);
+        S_s[j] = fmaf(__shfl_xor(S_s[j], off, 64), ows, S_s[j] * ws);
+        X[j] = fmaf(__shfl_xor(X[j], off, 64), by_t ? owt : ows, X[j] * (by_t ? wt : ws));
+        if (KIND == 6) X2[j] = fmaf(__shfl_xor(X2[j], off, 64), ows, X2[j] * ws);
+        m_t[j] = nmt; m_s[j] = nms;
+      }
+      if (geo.lane >= Geo::MERGE) continue;
+      const int t = tt * BN + geo.n(j);
+      p[0 * a.T_pad + t] = m_t[j];
+      p[1 * a.T_pad + t] = S_t[j];
+      p[2 * a.T_pad + t] = m_s[j];
+      p[3 * a.T_pad + t] = S_s[j];
+      p[4 * a.T_pad + t] = X[j];
+      if (KIND == 6) p[5 * a.T_pad + t] = X2[j];
+    }
+  }
+};
+
+// Divergences whose row value needs both log-sum-exps first (JSD, TVD, skewed KL) share one
+// scheme.  With D a function of the student probabilities and c = dD/dp_s, the gradient through the
+// softmax is  dD/dz_s = p_s (c - R) / tau,  R = sum_v p_s c.  A row pass over the logit tiles
+// accumulates two sums (a1, a2) per token, from which the row loss and R follow; the gradient pass
+// evaluates c element by element.  lt, ls are base-2 log-probabilities, w is beta (JSD) or the skew
+// weight alpha.
+//   JSD       M = w p_t + (1-w) p_s    a1 = sum p_t (lt - lm)   a2 = sum p_s (ls - lm)
+//             loss = ln2 (w a1 + (1-w) a2)     c = (1-w) ln2 (ls - lm)          R = (1-w) ln2 a2
+//   TVD       d = p_s - p_t            a1 = sum |d|             a2 = sum p_s sign(d)
+//             loss = a1 / 2                    c = sign(d) / 2                  R = a2 / 2
+//   skew FKL  M = w p_t + (1-w) p_s    a1 = sum p_t (lt - lm)   a2 = sum p_s p_t / M
+//             loss = ln2 a1                    c = -(1-w) p_t / M               R = -(1-w) a2
+//   skew RKL  M = (1-w) p_t + w p_s    a1 = sum p_s (ls - lm)   a2 = sum p_s c
+//             loss = ln2 a1                    c = ln2 (ls - lm) + 1 - w p_s / M   R = a2
+template <int KIND>
+struct RowTerm {
+  // c for one element; also adds the element's contribution to (a1, a2) when ACC is set
+  template <bool ACC>
+  static __device__ __forceinline__ float eval(float lt, float ls, float w, float& a1, float& a2) {
+    const float pt = fexp2(lt), ps = fexp2(ls);
+    if (KIND == 3) {
+      const float d = ps - pt;
+      const float sg = (d > 0.f ? 1.f : 0.f) - (d < 0.f ? 1.f : 0.f);
+      if (ACC) { a1 += fabsf(d); a2 = fmaf(ps, sg, a2); }
+      return 0.5f * sg;
+    }
+    const float wt = (KIND == 5) ? 1.f - w : w;          // weight of p_t in the mixture
+    // log M is taken relative to the larger of the two probabilities: with d = ls - lt and q = 2^-|d| <= 1,
+    //   p_t >= p_s:  M / p_t = wt + (1-wt) q      p_t < p_s:  M / p_s = wt q + (1-wt)
+    // so the logarithm's argument lies in [min(wt, 1-wt), 1]: no large logarithms are subtracted from one
+    // another (the hardware log of M itself, of size log2 V, is half an ulp short on average, which
+    // showed as a bias of 3e-7 in small losses), and nothing degenerates where p_t and p_s underflow.
+    const float d = ls - lt;
+    const bool t_big = d <= 0.f;
+    const float q = fexp2(t_big ? d : -d);
+    const float mix = t_big ? fmaf(1.f - wt, q, wt) : fmaf(wt, q, 1.f - wt);
+    const float lmix = flog2(mix);
+    const float lt_lm = t_big ? -lmix : -d - lmix;       // lt - lm
+    const float ls_lm = t_big ? d - lmix : -lmix;        // ls - lm
+    const float inv = __builtin_amdgcn_rcpf(mix);
+    if (KIND == 2) {
+      if (ACC) { a1 = fmaf(pt, lt_lm, a1); a2 = fmaf(ps, ls_lm, a2); }
+      return (1.f - w) * LN2 * ls_lm;
+    }
+    if (KIND == 4) {
+      const float r = t_big ? inv : q * inv;             // p_t / M
+      if (ACC) { a1 = fmaf(pt, lt_lm, a1); a2 = fmaf(ps, r, a2); }
+      return -(1.f - w) * r;
+    }
+    const float r = t_big ? q * inv : inv;               // p_s / M
+    const float cc = fmaf(LN2, ls_lm, 1.f - w * r);
+    if (ACC) { a1 = fmaf(ps, ls_lm, a1); a2 = fmaf(ps, cc, a2); }
+    return cc;
+  }
+};
+
+// AKL (KIND 6) uses the same pass for its gaps:  a1 = sum over the head of |p_t - p_s|,  a2 = the same over
+// the tail, the head being the entries whose teacher log-probability reaches the token's threshold.
+template <int KIND, class Geo>
+struct RowsEpi {
+  static constexpr int NC = Geo::NC;
+  Geo geo;
+  float A1[NC], A2[NC], Lt[NC], Ls[NC], Thr[NC];
+  float c, w;
+  __device__ RowsEpi(const LogitArgs& a, int tt) : c(a.c), w(a.beta) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = tt * BN + geo.n(j);
+      const f32x4 ri = a.rowinfo[t];
+      Lt[j] = ri[0]; Ls[j] = ri[1]; A1[j] = 0.f; A2[j] = 0.f;
+      Thr[j] = 0.f;
+      if (KIND == 6)    // the top entry is head whatever its mass
+        Thr[j] = fminf(a.akl[AKL_HI * a.T_pad + t], a.akl[AKL_LTMAX * a.T_pad + t] - AKL_TOP_EPS);
+    }
+  }
+  __device__ void begin_item(int, int, int) {}
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+    float a1 = A1[j], a2 = A2[j];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const float lt = fmaf(T[e], c, -Lt[j]);
+      const float ls = fmaf(S[e], c, -Ls[j]);
+      if constexpr (KIND == 6) {
+        const float gap = fabsf(fexp2(lt) - fexp2(ls));
+        const bool head = lt >= Thr[j];
+        a1 += head ? gap : 0.f;
+        a2 += head ? 0.f : gap;
+      } else {
+        (void)RowTerm<KIND>::template eval<true>(lt, ls, w, a1, a2);
+      }
+    }
+    A1[j] = a1; A2[j] = a2;
+  }
+  __device__ void write(const LogitArgs& a, int tt, int split) {
+    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * 2 * a.T_pad;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+#pragma unroll
+      for (int off = Geo::MERGE; off < 64; off <<= 1) {
+        A1[j] += __shfl_xor(A1[j], off, 64);
+        A2[j] += __shfl_xor(A2[j], off, 64);
+      }
+      if (geo.lane >= Geo::MERGE) continue;
+      const int t = tt * BN + geo.n(j);
+      p[0 * a.T_pad + t] = A1[j];
+      p[1 * a.T_pad + t] = A2[j];
+    }
+  }
+};
+
+// dL/dz_s tile.  rowinfo = {lse2_t, lse2_s, s = mask/(n tau), R}
+//   FKL: dz = s (p_s - p_t)
+//   RKL: dz = s p_s (ln2 (l_s - l_t) - R),   R = row loss
+//   JSD, TVD, skewed KL: dz = s p_s (c - R)  (RowTerm above)
+//   AKL: dz = s (w_f (p_s - p_t) + w_r p_s (ln2 (l_s - l_t) - RKL)) = s (p_s (w_r ln2 (l_s - l_t) + R) - w_f p_t),
+//        R = w_f - w_r RKL, the weights being constants for the gradient
+// Vocabulary entries that do not exist carry the logit NEG_BIG in both models: their dz comes out 0 in every
+// kind, and that is what the chunk buffer holds from its last valid column to the end of a 64-column step.
+template <int KIND, class Geo>
+struct GradEpi {
+  static constexpr int NC = Geo::NC;
+  Geo geo;
+  const LogitArgs& a;
+  float Lt[NC], Ls[NC], sc[NC], R[NC], Wr[NC];
+  int m0, n0, out_rows;
+  __device__ GradEpi(const LogitArgs& a_) : a(a_) {}
+  __device__ void begin_item(int m0_, int n0_, int out_rows_) {
+    out_rows = out_rows_;
+    m0 = m0_ - a.v0;                           // vocabulary offset inside the chunk
+    n0 = n0_;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const f32x4 ri = a.rowinfo[n0 + geo.n(j)];
+      Lt[j] = ri[0]; Ls[j] = ri[1]; sc[j] = ri[2]; R[j] = ri[3];
+      Wr[j] = 0.f;
+      if (KIND == 6) Wr[j] = a.akl[AKL_WR * a.T_pad + n0 + geo.n(j)];
+    }
+  }
+  template <bool ADD, class J, int NE>
+  __device__ __forceinline__ void emit(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+    const float c = a.c, w = a.beta, s = sc[j];
+#pragma unroll
+    for (int p = 0; p < NE / 16; ++p) {
+      bf16x4 o[4];
+      if (64 * p >= out_rows) break;             // (whole entries of 64 rows: only the strip loop's last tile has fewer)
+      if (ADD)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const bf16x8 v = *(const bf16x8*)(a.dz + geo.dz_at(a.ldz, n0, m0, j, p, u));
+          o[Geo::PAIR == 1 ? 2 * u : u] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+          o[Geo::PAIR == 1 ? 2 * u + 1 : u + 2] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+        }
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float lt = fmaf(T[16 * p + e], c, -Lt[j]);
+        const float ls = fmaf(S[16 * p + e], c, -Ls[j]);
+        const float ps = fexp2(ls);
+        float g;
+        if (KIND == 0) {
+          g = ps - fexp2(lt);
+        } else if (KIND == 1) {
+          g = ps * fmaf(LN2, ls - lt, -R[j]);
+        } else if (KIND == 6) {
+          g = fmaf(ps, fmaf(Wr[j] * LN2, ls - lt, R[j]), -(1.f - Wr[j]) * fexp2(lt));
+        } else {
+          float u1, u2;
+          g = ps * (RowTerm<KIND>::template eval<false>(lt, ls, w, u1, u2) - R[j]);
+        }
+        const float d = s * g;
+        o[e >> 2][e & 3] = (bf16_t)(ADD ? (float)o[e >> 2][e & 3] + d : d);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        *(bf16x8*)(a.dz + geo.dz_at(a.ldz, n0, m0, j, p, u)) =
+            __builtin_shufflevector(o[Geo::PAIR == 1 ? 2 * u : u], o[Geo::PAIR == 1 ? 2 * u + 1 : u + 2], 0, 1, 2, 3, 4, 5, 6, 7);
+      __builtin_amdgcn_sched_barrier(0);       // (or all of a column is computed before anything is stored: spills)
+    }
+  }
+  // (two bodies: a shared one would wait for the loads of the adding one, and for everything older, on both paths)
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J jc, const float (&S)[NE], const float (&T)[NE]) {
+    if (a.dz_accumulate) emit<true>(jc, S, T);
+    else emit<false>(jc, S, T);
+  }
+};
+
+// AKL threshold search on the eight-wave loop, one pass: for AKL_K thresholds spread evenly inside the token's current interval
+// (LO, HI), the teacher mass of the entries at or above each threshold.
+template <class Geo>
+struct SearchEpi {
+  static constexpr int NC = Geo::NC;
+  Geo geo;
+  float Lt[NC], th0[NC], step[NC];
+  float mass[NC][AKL_K];
+  float c;
+  __device__ SearchEpi(const LogitArgs& a, int tt) : c(a.c) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = tt * BN + geo.n(j);
+      Lt[j] = a.rowinfo[t][0];
+      const float lo = a.akl[AKL_LO * a.T_pad + t], hi = a.akl[AKL_HI * a.T_pad + t];
+      step[j] = (hi - lo) * (1.f / (AKL_K + 1));
+      th0[j] = lo + step[j];
+#pragma unroll
+      for (int k = 0; k < AKL_K; ++k) mass[j][k] = 0.f;
+    }
+  }
+  __device__ void begin_item(int, int, int) {}
+  // T alone: the teacher's logits (entries that do not exist are NEG_BIG: below every threshold)
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const float lt = fmaf(T[e], c, -Lt[j]);
+      const float p = fexp2(lt);
+#pragma unroll
+      for (int k = 0; k < AKL_K; ++k) mass[j][k] += (lt >= fmaf((float)k, step[j], th0[j])) ? p : 0.f;
+    }
+  }
+  __device__ void write(const LogitArgs& a, int tt, int split) {
+    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * AKL_K * a.T_pad;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = tt * BN + geo.n(j);
+#pragma unroll
+      for (int k = 0; k < AKL_K; ++k) {
+#pragma unroll
+        for (int off = Geo::MERGE; off < 64; off <<= 1) mass[j][k] += __shfl_xor(mass[j][k], off, 64);
+        if (geo.lane < Geo::MERGE) p[k * a.T_pad + t] = mass[j][k];
+      }
+    }
+  }
+};
+
+// ... and on the strip loop, which has one accumulator here and so LDS to spare: the mass of the entries inside the
+// interval by AKL_BINS bins in LDS, [bin][token], and in one more bin that of the entries at or above HI.  A token belongs to one wave: no
+// barrier, and its sums come in the order of that wave's tiles.  A compare, a select and an addition for each of 16 thresholds
+// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes ten, and past the
+// first pass hardly any entry lies in the interval.  With 40 bins three passes narrow it further than four did with 16
+// thresholds.  T = 2048, V = 151936, H = 4096 / 1024: a pass 2.39 -> 2.88 ms (the first) and 1.74 (the others, 1.47 PFLOP/s),
+// a step 18.15 -> 14.50.
+struct BinsEpi {
+  static constexpr int NC = StripGeo::NC;
+  static constexpr int BINS_AT = StripCfg::NST * StripCfg::STAGE_BYTES;      // in LDS, where other passes park student blocks
+  static_assert((AKL_BINS + 1) * BN * 4 <= StripCfg::PARK_BYTES, "bins of a token tile");
+  StripGeo geo;
+  float Lt[NC], Lo[NC], scale[NC];
+  float* bins;             // of this lane's token of column 0
+  float c;
+  __device__ BinsEpi(const LogitArgs& a, int tt, char* smem) : c(a.c) {
+    bins = (float*)(smem + BINS_AT) + geo.n(0);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int t = tt * BN + geo.n(j);
+      const float lo = a.akl[AKL_LO * a.T_pad + t], hi = a.akl[AKL_HI * a.T_pad + t];
+      Lt[j] = a.rowinfo[t][0];
+      Lo[j] = lo;
+      scale[j] = hi > lo ? (float)AKL_BINS / (hi - lo) : 0.f;
+    }
+    for (int k = geo.lane >> 4; k <= AKL_BINS; k += 4)
+#pragma unroll
+      for (int j = 0; j < NC; ++j) bins[k * BN + 16 * j] = 0.f;
+  }
+  __device__ void begin_item(int, int, int) {}
+  // T alone: the teacher's logits (entries that do not exist are NEG_BIG: below the interval)
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const float lt = fmaf(T[e], c, -Lt[j]), f = (lt - Lo[j]) * scale[j];
+      if (f >= 0.f) {
+        const int k = (int)fminf(f, (float)AKL_BINS);
+        __hip_atomic_fetch_add(bins + k * BN + 16 * j, fexp2(lt), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+  }
+  __device__ void write(const LogitArgs& a, int tt, int split) {
+    float* p = a.partials + (int64_t)split * (AKL_BINS + 1) * a.T_pad + tt * BN + geo.n(0);
+    for (int k = geo.lane >> 4; k <= AKL_BINS; k += 4)
+#pragma unroll
+      for (int j = 0; j < NC; ++j) p[(int64_t)k * a.T_pad + 16 * j] = bins[k * BN + 16 * j];
+  }
+};
+// Whether a token's search goes on; a workgroup of the strip loop whose tokens are all done leaves.
+__device__ __forceinline__ bool akl_open(float lo, float hi) { return hi - lo > kAklResolution; }
+template <class Work>
+__device__ __forceinline__ bool akl_search_open(const LogitArgs& a, const Work& work) {
+  const int t = work.tt * BN + threadIdx.x;
+  return __syncthreads_or(work.cnt > 0 && akl_open(a.akl[AKL_LO * a.T_pad + t], a.akl[AKL_HI * a.T_pad + t]));
+}
+
+// measurement aid, off unless asked for
+struct LoopClock {
+  long long c0 = 0, r0 = 0;
+  __device__ LoopClock(const LogitArgs& a) {
+    if (a.clock_out) { c0 = clock64(); r0 = wall_clock64(); }
+  }
+  __device__ void stop(const LogitArgs& a) {
+    if (a.clock_out && blockIdx.x == 0 && threadIdx.x == 0) {
+      a.clock_out[0] = clock64() - c0;
+      a.clock_out[1] = wall_clock64() - r0;
+    }
+  }
+};
+
+// ------------------------------------------------------------------------------------------
+// launching
+// ------------------------------------------------------------------------------------------
+inline int largest_divisor_le(int n, int cap) {
+  for (int d = cap; d > 1; --d)
+    if (n % d == 0) return d;
+  return 1;
+}
+
+inline LogitArgs make_logit_args(const Problem& p) {
+  LogitArgs a{};
+  a.W_s = (const bf16_t*)p.W_s; a.h_s = (const bf16_t*)p.h_s;
+  a.W_t = (const bf16_t*)p.W_t; a.h_t = (const bf16_t*)p.h_t;
+  a.T = p.T; a.V = p.V; a.H_s = p.K_s; a.H_t = p.K_t;   // contraction lengths = row strides
+  a.meta = p.meta;
+  a.c = 1.4426950408889634f / p.tau;
+  a.beta = p.beta;
+  a.t_scale = p.t_fp8 ? p.t_scale : 1.f;
+  a.T_pad = p.T_pad;
+  a.rowinfo = (const f32x4*)p.rowinfo;
+  a.akl = p.akl;
+  return a;
+}
+// The strip loop's kernels for heads kept as [H][V] (kd_strip_hv.hip), by the divergence of `p`.
+hipError_t launch_strip_hv_stats(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
+hipError_t launch_strip_hv_rows(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
+hipError_t launch_strip_hv_grad(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
+hipError_t launch_strip_hv_search(const LogitArgs& a, int grid, hipStream_t st);
+
+}  // namespace kd

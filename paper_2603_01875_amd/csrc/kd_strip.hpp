@@ -151,6 +151,12 @@ template <int AM>
 __device__ __forceinline__ u32x4 strip_op(const StripFrag<AM>& f) {
   return __builtin_bit_cast(u32x4, __builtin_shufflevector(f.lo, f.hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
+// Keeps a fragment's registers until here.
+template <int AM>
+__device__ __forceinline__ void strip_hold(const StripFrag<AM>& f) {
+  asm volatile("" ::"v"(f.lo), "v"(f.hi));
+}
+__device__ __forceinline__ void strip_hold(const StripFrag<A_ROWS>&) {}
 template <int OFF>
 __device__ __forceinline__ void strip_tr_read(s16x4& d, uint32_t addr) {
   static_assert(OFF >= 0 && OFF < 65536, "ds offset field");
@@ -185,7 +191,7 @@ template <int NPH, bool SHORT_LAST, class C = StripCfg, int AM = A_ROWS, bool B_
 __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* smem) {
   constexpr int MB = C::MB, NB = C::NB;
   constexpr bool HALVES = AM != A_ROWS, TR = AM == A_KMAJOR_DZ || AM == A_DZ;
-  static_assert(NPH == 1 || AM == A_ROWS, "two phases");
+  static_assert(NPH == 1 || AM == A_ROWS || AM == A_KMAJOR_DZ, "two phases");
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int n_items = work.n_items();
   if (n_items <= 0) return;
@@ -451,7 +457,16 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
   for (int j = 0; j < NB; ++j) B[3][j] = B[2][j];          // (refilled by the first sub-step)
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
   static_for<0, MB>([&](auto ic) { read_a(A[decltype(ic)::value], 0, IntC<0>{}, ic); });
-  if constexpr (HALVES) asm volatile("s_waitcnt lgkmcnt(0)");      // (here and behind a tile's last k-step: the compiler may move them)
+  // Here and behind a phase's last k-step: the compiler may move the fragments.  KEEP: their registers are theirs until then, also
+  // where nothing reads them any more (behind a workgroup's last tile an epilogue would take them while a read is in flight).
+  auto landed = [&](auto keepc) {
+    if constexpr (HALVES) asm volatile("s_waitcnt lgkmcnt(0)");
+    if constexpr (HALVES && decltype(keepc)::value != 0) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) strip_hold(A[i]);
+    }
+  };
+  landed(IntC<0>{});
 
   // one tile of NM blocks of A
   auto tile = [&](auto nmc, const StripItem& ci) {
@@ -466,7 +481,7 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
         if constexpr (SWAP) strip_mfma_a(T[id], b, a);
         else strip_mfma_a(T[id], a, b);
       });
-      if constexpr (HALVES) asm volatile("s_waitcnt lgkmcnt(0)");
+      landed(IntC<0>{});
       strip_settle<true, N>(T);
       epi.tile(ci, T);
     } else {
@@ -492,6 +507,7 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
           else if constexpr (id < HV + HA) strip_mfma_a(SA[id - HV], a, b);
           else strip_mfma_a(SP[id - HV - HA], a, b);
         });
+        landed(IntC<1>{});
         strip_settle<false, HV>(SV);
         strip_settle<true, HA>(SA);
         strip_settle<true, NP>(SP);
@@ -507,6 +523,7 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
       run(nmc, IntC<0>{}, (ci.k1 + 63) >> 6, [&](auto ic, auto jc, const u32x4& a, const u32x4& b) {
         strip_mfma_a(T[NM * decltype(jc)::value + decltype(ic)::value], a, b);
       });
+      landed(IntC<1>{});
       strip_settle<true, N>(T);
       static_for<0, NB>([&](auto jc) {
         f32x4 S[NM], Tj[NM];
