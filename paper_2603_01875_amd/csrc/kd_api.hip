@@ -343,37 +343,10 @@ struct ProfileScope {
   } while (0)
 #endif
 
-// Re-pack the operands that need it (fp32 split / K padding / compaction) into the workspace.
-kd_status prepare_operands(const Problem& q, hipStream_t st, bool student, bool teacher) {
-  const int* map = q.mask ? q.rowmap : nullptr;     // gather valid tokens to the front
-  if (q.strip) {
-    if (teacher) KD_TRY(kd::launch_pack_rows(q, q.user_h_t, q.H_t, const_cast<void*>(q.h_t), q.K_t, st));
-    if (student) KD_TRY(kd::launch_pack_rows(q, q.user_h_s, q.H_s, const_cast<void*>(q.h_s), q.K_s, st));
-  } else {
-    if (teacher && q.prep_ht && q.t_fp8)     // rows of H_t bytes are gathered as rows of H_t / 2 two-byte words
-      KD_TRY(kd::launch_prepare(q.user_h_t, 0, q.T, q.H_t / 2, const_cast<void*>(q.h_t), q.K_t / 2, 2, map, q.meta, 0, st));
-    else if (teacher && q.prep_ht)
-      KD_TRY(kd::launch_prepare(q.user_h_t, q.in_f32, q.T, q.H_t, const_cast<void*>(q.h_t), q.K_t, 2, map, q.meta, 0, st));
-    if (student && q.prep_hs)
-      KD_TRY(kd::launch_prepare(q.user_h_s, q.in_f32, q.T, q.H_s, const_cast<void*>(q.h_s), q.K_s, 2, map, q.meta, 0, st));
-  }
-  if (teacher && q.prep_Wt && q.t_fp8)      // only ever an [H][V] head of e4m3 bytes: transposed copy
-    KD_TRY(kd::launch_transpose_bytes(q.user_W_t, q.V, q.H_t, q.V, const_cast<void*>(q.W_t), q.K_t, q.K_t, st));
-  else if (teacher && q.prep_Wt)
-    KD_TRY(kd::launch_prepare(q.user_W_t, q.in_f32, q.V, q.H_t, const_cast<void*>(q.W_t), q.K_t, 1, nullptr, q.meta, q.w_hv, st));
-  if (student && q.prep_Ws)
-    KD_TRY(kd::launch_prepare(q.user_W_s, q.in_f32, q.V, q.H_s, const_cast<void*>(q.W_s), q.K_s, 1, nullptr, q.meta, q.w_hv, st));
-  return KD_OK;
-}
-
 // Forward pass of one teacher.  The token compaction and the student operands are shared by the
-// teachers of a call: only the first one makes them.
-kd_status run_forward(const Problem& q, hipStream_t st, bool first_teacher = true) {
-  if (first_teacher) KD_TRY(kd::launch_rowmap(q, st));
-  {
-    kd_status ps = prepare_operands(q, st, first_teacher, true);
-    if (ps != KD_OK) return ps;
-  }
+// teachers of a call: only the first one makes them.  `backward`: a backward pass follows (behind the last teacher).
+kd_status run_forward(const Problem& q, hipStream_t st, bool backward, bool first_teacher = true) {
+  KD_TRY(kd::launch_operands(q, first_teacher, first_teacher, true, st));
   {
     ProfileScope ps(KD_PROF_STATS, st);
     KD_TRY(kd::launch_stats(q, st));
@@ -395,7 +368,7 @@ kd_status run_forward(const Problem& q, hipStream_t st, bool first_teacher = tru
     }
     KD_TRY(kd::launch_combine_rows(q, st));
   }
-  KD_TRY(kd::launch_finalize(q, st));
+  KD_TRY(kd::launch_finalize(q, backward, st));       // (h_s^T once: the hidden-row operand of grad_W_s)
   return KD_OK;
 }
 
@@ -405,8 +378,6 @@ kd_status run_forward(const Problem& q, hipStream_t st, bool first_teacher = tru
 // summed in fp32 over the chunks and converted once at the end.
 kd_status run_backward(const Problem* qs, int n_teachers, hipStream_t st) {
   const Problem& q = qs[0];          // everything on the student side is the same for all teachers
-  KD_TRY(kd::launch_pack_columns(q, st));       // h_s^T once: the hidden-row operand of grad_W_s
-
   for (int64_t v0 = 0; v0 < q.V; v0 += q.V_c) {
     const int width = (int)((q.V - v0 < q.V_c) ? q.V - v0 : q.V_c);
     for (int k = 0; k < n_teachers; ++k) {
@@ -501,11 +472,11 @@ kd_status kd_loss_plan_info(const kd_loss_params* params, int64_t* vocab_chunk, 
   plan(params, q, L, true);
   const int64_t chunks = (q.V + q.V_c - 1) / q.V_c;
   if (vocab_chunk) *vocab_chunk = q.V_c;
-  // compaction, operand copies (as with a mask), statistics + merge, row pass + merge, loss,
-  // h_s^T, per chunk the gradient kernel and the two products, grad_h_s conversion
+  // compaction with the copies of the heads, copies of the hidden states (as with a mask), heads turned, statistics + merge,
+  // row pass + merge, loss and h_s^T, per chunk the gradient kernel and the two products, grad_h_s conversion
   if (n_launches)
-    *n_launches = 1 + (q.prep_ht + q.prep_Wt + q.prep_hs + q.prep_Ws) + 2 + (q.kind >= KD_JSD ? 2 : 0) +
-                  (q.kind == KD_AKL ? 2 * kd::kAklSearchPasses : 0) + 1 + 1 + chunks * 3 + 1;
+    *n_launches = 1 + 1 + (q.w_hv ? q.prep_Wt + q.prep_Ws : 0) + 2 + (q.kind >= KD_JSD ? 2 : 0) +
+                  (q.kind == KD_AKL ? 2 * kd::kAklSearchPasses : 0) + 1 + chunks * 3 + 1;
   return KD_OK;
 }
 
@@ -529,7 +500,7 @@ kd_status kd_loss_fwd(const kd_loss_params* params, const void* h_t, const void*
                               nullptr, nullptr, q, L);
   if (s != KD_OK) return s;
   q.per_token_loss = per_token_loss;
-  return run_forward(q, static_cast<hipStream_t>(hip_stream));
+  return run_forward(q, static_cast<hipStream_t>(hip_stream), false);
 }
 
 kd_status kd_loss_fwd_bwd(const kd_loss_params* params, const void* h_t, const void* W_t, const void* h_s,
@@ -544,7 +515,7 @@ kd_status kd_loss_fwd_bwd(const kd_loss_params* params, const void* h_t, const v
   q.per_token_loss = per_token_loss;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
 
-  s = run_forward(q, st);
+  s = run_forward(q, st, true);
   if (s != KD_OK) return s;
   return run_backward(&q, 1, st);
 }
@@ -607,7 +578,7 @@ kd_status kd_loss_fwd_bwd_static(const kd_loss_params* params, const void* h_t, 
   if (s != KD_OK) return s;
   q.per_token_loss = per_token_loss;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  s = run_forward(q, st);
+  s = run_forward(q, st, true);
   if (s != KD_OK) return s;
   return run_backward(&q, 1, st);
 }
@@ -671,7 +642,7 @@ kd_status kd_loss_fwd_bwd_multi(const kd_loss_params* params, int n_teachers, co
   }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   for (int k = 0; k < n_teachers; ++k) {
-    kd_status s = run_forward(q[k], st, k == 0);
+    kd_status s = run_forward(q[k], st, k + 1 == n_teachers, k == 0);
     if (s != KD_OK) return s;
   }
   return run_backward(q, n_teachers, st);

@@ -15,7 +15,7 @@ __device__ __forceinline__ int xcd_logical_id(int b, int G) {
   return x * q + (x < r ? x : r) + b / 8;
 }
 
-// Device-side plan, written by rowmap_kernel once the mask has been counted (the host never
+// Device-side plan, written by make_rowmap once the mask has been counted (the host never
 // learns how many tokens are valid, so everything that depends on it is decided on the device).
 // META_N_SPLIT: vocabulary ranges per token tile in the statistics passes; META_G_SPLIT, META_G_SPLIT_LAST: in the
 // gradient kernel, for a full chunk and for the last one (strip loop).

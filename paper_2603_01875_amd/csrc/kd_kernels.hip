@@ -127,8 +127,16 @@ KD_LOGIT_KERNEL void grad_kernel(const LogitArgs a) {
 // three rounds, where eight leave 24 of 256 CUs idle; one token tile x 151936 rows: 256 ranges of three tiles and at most
 // a short one, where whole tiles would take four.
 struct SplitChoice { int units, per_tile, short_units, most, strided; };
-__global__ void rowmap_kernel(const uint8_t* mask, int T, int T_pad, int n_cu, SplitChoice stats, SplitChoice grad,
-                              SplitChoice grad_last, int* rowmap, int* inv, int* meta) {
+struct RowmapArgs {
+  const uint8_t* mask;
+  int T, T_pad, n_cu;
+  SplitChoice stats, grad, grad_last;
+  int *rowmap, *inv, *meta;
+};
+__device__ __forceinline__ void make_rowmap(const RowmapArgs& a) {
+  const uint8_t* const mask = a.mask;
+  const int T = a.T, T_pad = a.T_pad, n_cu = a.n_cu;
+  int *const rowmap = a.rowmap, *const inv = a.inv, *const meta = a.meta;
   __shared__ int s_scan[1024];
   __shared__ int s_running;
   __shared__ unsigned long long s_best[3];
@@ -163,7 +171,7 @@ __global__ void rowmap_kernel(const uint8_t* mask, int T, int T_pad, int n_cu, S
   for (int j = n + tid; j < T_pad; j += 1024) rowmap[j] = last;   // never dereferenced for results
   const int n_tt = max((n + BN - 1) / BN, 1);
   if (const int k = tid >> 8; k < 3) {               // 256 threads per choice
-    const SplitChoice c = k == 0 ? stats : k == 1 ? grad : grad_last;
+    const SplitChoice c = k == 0 ? a.stats : k == 1 ? a.grad : a.grad_last;
     for (int sp = (tid & 255) + 1; sp <= c.most; sp += 256) {
       if (c.strided && sp == 1) {                    // (n_split 0; dearer by a hair: 2 % slower at equal counts)
         const int r = (n_tt * ((c.units + c.per_tile - 1) / c.per_tile) + n_cu - 1) / n_cu;
@@ -417,14 +425,53 @@ __global__ __launch_bounds__(NT) void combine_rows_kernel(const float* partials,
   row_loss[t] = loss;
 }
 
-// One workgroup: loss = sum of the valid rows' losses / n (fixed-order fp64 tree), per-row gradient
+// The token operand of grad_W_s: h_s of the compacted rows transposed, as [16 hidden rows][32-token sub-step][lane][8], lane l
+// holding tokens 8 (l / 16) .. + 7 of hidden row l mod 16; zero beyond the valid tokens.  Block (r0, c0) of 64 tokens x 64
+// hidden rows through LDS, by 16 waves.
+template <class E>
+__device__ __forceinline__ void pack_columns(const E* src, int C, bf16_t* dst, int T_pad, const int* rowmap, int n_valid, int r0,
+                                             int c0, bf16_t (*tile)[66]) {
+  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  const int c = c0 + tx, cc = min(c, C - 1);
+  E v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)            // (rowmap holds a valid row for every r < T_pad: the loads need no test)
+    v[i] = src[(int64_t)rowmap[r0 + ty + 16 * i] * C + cc];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) tile[ty + 16 * i][tx] = r0 + ty + 16 * i < n_valid && c < C ? (bf16_t)v[i] : (bf16_t)0.f;
+  __syncthreads();
+  const int sub = ty >> 2, blk = ty & 3;                             // a wave: 16 hidden rows x 32 tokens, 1 KiB
+  if (sub > 1 || c0 + 16 * blk >= C) return;
+  bf16x8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = tile[32 * sub + 8 * (tx >> 4) + e][16 * blk + (tx & 15)];
+  *(bf16x8*)(dst + ((int64_t)(c0 / 16 + blk) * (T_pad / 32) + r0 / 32 + sub) * 512 + tx * 8) = o;
+}
+
+struct PackColumnsArgs {
+  const void* src;
+  bf16_t* dst;
+  const int* rowmap;
+  int src_f32, C, T_pad;
+};
+
+// Workgroup 0: loss = sum of the valid rows' losses / n (fixed-order fp64 tree), per-row gradient
 // scale 1 / (n tau), and the caller's per-token losses (0 for masked tokens).
 // `weight` scales what leaves the call (teacher weight, optional tau^2); with `accumulate` the loss
 // outputs are added to (further teachers of a multi-teacher call).
-__global__ void finalize_kernel(const int* meta, const int* inv, const float* row_loss, int T, float tau,
-                                float weight, int accumulate, f32x4* rowinfo, float* loss_out,
-                                float* per_token_out) {
+// The others, if there is a backward pass: h_s transposed and packed (pack_columns), beside it (a launch, 4 to 6 us).
+__global__ __launch_bounds__(1024) void finalize_kernel(const int* meta, const int* inv, const float* row_loss, int T, float tau,
+                                                        float weight, int accumulate, f32x4* rowinfo, float* loss_out,
+                                                        float* per_token_out, const PackColumnsArgs pc) {
   __shared__ double s_sum[1024];
+  __shared__ bf16_t tile[64][66];
+  if (blockIdx.x > 0) {
+    const int b = blockIdx.x - 1, wide = pc.T_pad / 64, by = b / wide, r0 = (b - by * wide) * 64, c0 = by * 64;
+    const int n = meta[META_N_VALID];
+    if (pc.src_f32) pack_columns((const float*)pc.src, pc.C, pc.dst, pc.T_pad, pc.rowmap, n, r0, c0, tile);
+    else pack_columns((const bf16_t*)pc.src, pc.C, pc.dst, pc.T_pad, pc.rowmap, n, r0, c0, tile);
+    return;
+  }
   const int tid = threadIdx.x;
   const int n = meta[META_N_VALID];
   double acc = 0.0;
@@ -469,13 +516,14 @@ __global__ void transpose_kernel(const E* src, int64_t ld_src, int R, int C, E* 
 // The token operand of the strip loop: the compacted rows (row j = row rowmap[j] of src for j < n_valid, zero
 // beyond) in the order in which its waves load them: [64-token panel][32-element sub-step][16-token block][lane][8],
 // lane l holding elements 8 (l / 16) .. + 7 of token l mod 16.  fp32 rows become [hi | lo | hi] (see
-// prepare_kernel).  A workgroup writes 4 KiB; bound by its reads, 64-byte pieces of each row.
+// prepare).  A block of 256 threads writes 4 KiB; bound by its reads, 64-byte pieces of each row.
 // dz_order (bf16 only): elements 4 (l / 16) .. + 3 and 16 + 4 (l / 16) .. + 3 instead, the order in which transposing reads
 // bring the heads kept as [H][V] (A_KMAJOR_DZ in kd_strip.hpp).
-__global__ void pack_rows_kernel(const void* src, int src_f32, int dz_order, int H, bf16_t* dst, int K, const int* rowmap,
-                                 const int* meta) {
-  const int lane = threadIdx.x & 63, blk = threadIdx.x >> 6;
-  const int kb = blockIdx.x, panel = blockIdx.z * gridDim.y + blockIdx.y;
+__device__ __forceinline__ void pack_rows(int block, int tid, const void* src, int src_f32, int dz_order, int R, int H, bf16_t* dst, int K,
+                                          const int* rowmap, const int* meta) {
+  const int lane = tid & 63, blk = tid >> 6;
+  const int panel = block / (K / 32), kb = block - panel * (K / 32);
+  if (panel * 64 >= R) return;
   const int j = panel * 64 + 16 * blk + (lane & 15), k0 = 32 * kb + 8 * (lane >> 4);
   bf16x8 v;
 #pragma unroll
@@ -514,9 +562,10 @@ __global__ void pack_rows_kernel(const void* src, int src_f32, int dz_order, int
 // Bound by memory: a thread makes 16 bytes of four rows (lanes along K, so that reads and writes are whole lines,
 // and four independent loads in flight); element by element, with two 64-bit divisions each, the heads of
 // V = 50264, H = 1000 and 520 took 124 and 70 us; two micro-batches of 777 tokens went from 1545 to 1396 us.
-__global__ __launch_bounds__(256) void prepare_kernel(const void* src, int src_f32, int R, int H, bf16_t* dst, int K,
-                                                      int split_mode, const int* rowmap, const int* meta) {
-  const int k0 = (blockIdx.y * 64 + (threadIdx.x & 63)) * 8;
+__device__ __forceinline__ void prepare(int block, int tid, const void* src, int src_f32, int R, int H, bf16_t* dst, int K,
+                                        int split_mode, const int* rowmap, const int* meta) {
+  const int wide = (R + 15) / 16, by = block / wide, bx = block - by * wide;
+  const int k0 = (by * 64 + (tid & 63)) * 8;
   if (k0 >= K) return;
   const int part = src_f32 ? k0 / H : 0, col = k0 - part * H;      // H is a multiple of 8: eight values of one part
   const bool lo = (split_mode == 1 && part == 2) || (split_mode == 2 && part == 1);
@@ -524,7 +573,7 @@ __global__ __launch_bounds__(256) void prepare_kernel(const void* src, int src_f
   const int n = rowmap ? meta[META_N_VALID] : R;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int r = blockIdx.x * 16 + (threadIdx.x >> 6) + 4 * i;
+    const int r = bx * 16 + (tid >> 6) + 4 * i;
     if (r >= R) return;
     bf16x8 v;
 #pragma unroll
@@ -583,14 +632,50 @@ __global__ __launch_bounds__(256) void prepare_transposed_kernel(const void* src
 
 // The common case of the above, 16 bytes per thread: bf16 (or byte) rows that only have to be gathered
 // (K == H, H a multiple of 8).  Row j of dst is row rowmap[j] of src for j < n_valid, zero beyond.
-__global__ void gather_rows_kernel(const u32x4* src, u32x4* dst, int R, int chunks_per_row, const int* rowmap,
-                                   const int* meta) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void gather_rows(int block, int tid, const u32x4* src, u32x4* dst, int R, int chunks_per_row,
+                                            const int* rowmap, const int* meta) {
+  const int64_t i = (int64_t)block * 256 + tid;
   if (i >= (int64_t)R * chunks_per_row) return;
   const int j = (int)(i / chunks_per_row), c = (int)(i % chunks_per_row);
   u32x4 v = {0u, 0u, 0u, 0u};
   if (j < meta[META_N_VALID]) v = src[(int64_t)rowmap[j] * chunks_per_row + c];
   dst[i] = v;
+}
+
+// The row map and the operand copies of a call (pack_rows, prepare, gather_rows) share launches: each is small or independent
+// of the others, and a launch costs 4 us.  Copies that do not look at the row map go with it, in the first launch; those that
+// do, in a second.  Workgroups of 1024 threads (what the row map wants) work as four blocks of 256; a job's blocks are
+// rounded up to whole workgroups.  T = 128, V = 4096, fp32 (four copies): five launches, 23 us -> one.
+struct OperandJob {
+  int kind;                // 0: prepare, 1: pack_rows, 2: gather_rows
+  int groups;              // workgroups
+  int R, H, K, mode;       // mode: split_mode of prepare, dz_order of pack_rows
+  int src_f32;
+  const int* rowmap;
+  const void* src;
+  bf16_t* dst;
+};
+struct OperandArgs {
+  RowmapArgs rm;
+  int with_rowmap, n;
+  OperandJob job[4];
+};
+__global__ __launch_bounds__(1024) void operands_kernel(const OperandArgs a) {
+  int b = blockIdx.x;
+  if (a.with_rowmap) {
+    if (b == 0) {
+      make_rowmap(a.rm);
+      return;
+    }
+    --b;
+  }
+  int i = 0;
+  while (i + 1 < a.n && b >= a.job[i].groups) b -= a.job[i++].groups;
+  const OperandJob& q = a.job[i];
+  const int block = 4 * b + (int)(threadIdx.x >> 8), tid = threadIdx.x & 255;
+  if (q.kind == 0) prepare(block, tid, q.src, q.src_f32, q.R, q.H, q.dst, q.K, q.mode, q.rowmap, a.rm.meta);
+  else if (q.kind == 1) pack_rows(block, tid, q.src, q.src_f32, q.mode, q.R, q.H, q.dst, q.K, a.rm.rowmap, a.rm.meta);
+  else gather_rows(block, tid, (const u32x4*)q.src, (u32x4*)q.dst, q.R, q.K / 8, q.rowmap, a.rm.meta);
 }
 
 // Measurement aid: what the matrix pipe sustains with nothing else going on.  Same occupancy as the
@@ -757,7 +842,7 @@ hipError_t launch_akl_weights(const Problem& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_rowmap(const Problem& p, hipStream_t st) {
+static RowmapArgs rowmap_args(const Problem& p) {
   // units: 64 vocabulary rows for the strip loop, tiles for the eight-wave one (whose gradient kernel strides)
   const int last = p.V - (p.V - 1) / p.V_c * p.V_c;      // width of the last chunk
   SplitChoice stats{p.n_vt, 1, 0, p.n_split, 0}, grad{1, 1, 0, 1, 0}, grad_last = grad;
@@ -771,8 +856,63 @@ hipError_t launch_rowmap(const Problem& p, hipStream_t st) {
     grad = choice(full, p.g_split, 0, 1);
     grad_last = choice(last, p.g_split, 0, 1);
   }
-  hipLaunchKernelGGL(rowmap_kernel, dim3(1), dim3(1024), 0, st, p.mask, p.T, p.T_pad, p.n_cu, stats, grad, grad_last,
-                     p.rowmap, p.inv, p.meta);
+  return RowmapArgs{p.mask, p.T, p.T_pad, p.n_cu, stats, grad, grad_last, p.rowmap, p.inv, p.meta};
+}
+
+hipError_t launch_operands(const Problem& p, bool rowmap, bool student, bool teacher, hipStream_t st) {
+  OperandArgs first{}, second{};       // what does not look at the row map, and what does
+  first.rm = second.rm = rowmap_args(p);
+  first.with_rowmap = rowmap;
+  int groups_first = rowmap ? 1 : 0, groups_second = 0;
+  auto add = [&](bool mapped, OperandJob j, int64_t blocks) {
+    j.groups = (int)((blocks + 3) / 4);
+    OperandArgs& to = mapped ? second : first;
+    to.job[to.n++] = j;
+    (mapped ? groups_second : groups_first) += j.groups;
+  };
+  // hidden states: packed for the strip loop; else copied where they are gathered, split or padded
+  auto hidden = [&](const void* src, int H, void* dst, int K, bool fp8) {
+    OperandJob j{};
+    j.src = src; j.dst = (bf16_t*)dst; j.src_f32 = p.in_f32 && !fp8;
+    j.R = p.T; j.H = H; j.K = K;
+    if (fp8) { j.H /= 2; j.K /= 2; }      // rows of bytes as rows of two-byte words
+    j.rowmap = p.mask ? p.rowmap : nullptr;
+    if (p.strip) {
+      j.kind = 1; j.mode = p.w_hv_inplace; j.R = p.T_pad;
+      add(true, j, (int64_t)(p.T_pad / 64) * (K / 32));
+    } else if (!j.src_f32 && j.K == j.H && p.mask) {
+      j.kind = 2;
+      add(true, j, ((int64_t)j.R * j.K / 8 + 255) / 256);
+    } else {
+      j.mode = 2;
+      add(p.mask != nullptr, j, (int64_t)((j.R + 15) / 16) * ((j.K + 511) / 512));
+    }
+  };
+  auto head = [&](const void* src, int H, void* dst, int K) {
+    OperandJob j{};
+    j.src = src; j.dst = (bf16_t*)dst; j.src_f32 = p.in_f32;
+    j.R = p.V; j.H = H; j.K = K; j.mode = 1;
+    add(false, j, (int64_t)((j.R + 15) / 16) * ((j.K + 511) / 512));
+  };
+  if (teacher && p.prep_ht) hidden(p.user_h_t, p.H_t, const_cast<void*>(p.h_t), p.K_t, p.t_fp8);
+  if (student && p.prep_hs) hidden(p.user_h_s, p.H_s, const_cast<void*>(p.h_s), p.K_s, false);
+  if (teacher && p.prep_Wt && !p.w_hv) head(p.user_W_t, p.H_t, const_cast<void*>(p.W_t), p.K_t);
+  if (student && p.prep_Ws && !p.w_hv) head(p.user_W_s, p.H_s, const_cast<void*>(p.W_s), p.K_s);
+  if (groups_first) hipLaunchKernelGGL(operands_kernel, dim3(groups_first), dim3(1024), 0, st, first);
+  if (groups_second) hipLaunchKernelGGL(operands_kernel, dim3(groups_second), dim3(1024), 0, st, second);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !p.w_hv) return e;
+  // heads kept as [H][V] that are not read in place: transposed copies
+  auto turned = [&](const void* src, int H, void* dst, int K) {
+    hipLaunchKernelGGL(prepare_transposed_kernel, dim3((p.V + 63) / 64, ((p.in_f32 ? H : K) + 63) / 64), dim3(256), 0, st, src,
+                       p.in_f32, p.V, H, (bf16_t*)dst, K);
+  };
+  if (teacher && p.prep_Wt && p.t_fp8)      // e4m3 bytes
+    hipLaunchKernelGGL(transpose_kernel<uint8_t>, dim3((p.K_t + 63) / 64, (p.V + 63) / 64), dim3(256), 0, st,
+                       (const uint8_t*)p.user_W_t, (int64_t)p.V, p.H_t, p.V, (uint8_t*)const_cast<void*>(p.W_t), (int64_t)p.K_t, p.K_t);
+  else if (teacher && p.prep_Wt)
+    turned(p.user_W_t, p.H_t, const_cast<void*>(p.W_t), p.K_t);
+  if (student && p.prep_Ws) turned(p.user_W_s, p.H_s, const_cast<void*>(p.W_s), p.K_s);
   return hipGetLastError();
 }
 
@@ -801,9 +941,11 @@ hipError_t launch_combine_rows(const Problem& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_finalize(const Problem& p, hipStream_t st) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, st, p.meta, p.inv, p.row_loss, p.T, p.tau,
-                     p.out_weight, p.accumulate_loss, (f32x4*)p.rowinfo, p.loss, p.per_token_loss);
+hipError_t launch_finalize(const Problem& p, bool pack_h_s, hipStream_t st) {
+  const PackColumnsArgs pc{p.user_h_s, (bf16_t*)p.h_sT, p.rowmap, p.in_f32, p.H_s, p.T_pad};
+  const int grid = 1 + (pack_h_s ? p.T_pad / 64 * ((p.H_s + 63) / 64) : 0);
+  hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(1024), 0, st, p.meta, p.inv, p.row_loss, p.T, p.tau,
+                     p.out_weight, p.accumulate_loss, (f32x4*)p.rowinfo, p.loss, p.per_token_loss, pc);
   return hipGetLastError();
 }
 
@@ -837,41 +979,6 @@ hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulat
     default: return KD_GRAD(5);
   }
 #undef KD_GRAD
-}
-
-hipError_t launch_transpose_bytes(const void* src, int64_t ld_src, int R, int C, void* dst, int64_t ld_dst, int R_pad,
-                                  hipStream_t st) {
-  dim3 grid((R_pad + 63) / 64, (C + 63) / 64);
-  hipLaunchKernelGGL(transpose_kernel<uint8_t>, grid, dim3(256), 0, st, (const uint8_t*)src, ld_src, R, C, (uint8_t*)dst,
-                     ld_dst, R_pad);
-  return hipGetLastError();
-}
-
-hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst, int K, hipStream_t st) {
-  // (neighbouring workgroups share rows, so the panels stay on the slow axis; 2^22 tokens are 65536 of them, one more
-  // than an axis other than the first takes, and a multiple of 4 always)
-  const int panels = p.T_pad / 64, z = panels > 32768 ? 2 : 1;
-  hipLaunchKernelGGL(pack_rows_kernel, dim3(K / 32, panels / z, z), dim3(256), 0, st, src, p.in_f32, p.w_hv_inplace, H,
-                     (bf16_t*)dst, K, p.rowmap, p.meta);
-  return hipGetLastError();
-}
-
-hipError_t launch_prepare(const void* src, int src_f32, int R, int H, void* dst, int K, int split_mode,
-                          const int* rowmap, const int* meta, int src_transposed, hipStream_t st) {
-  const int64_t n = (int64_t)R * K;
-  if (!src_f32 && !src_transposed && K == H && H % 8 == 0 && rowmap) {
-    const int64_t chunks = n / 8;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st,
-                       (const u32x4*)src, (u32x4*)dst, R, H / 8, rowmap, meta);
-    return hipGetLastError();
-  }
-  if (src_transposed)        // (a head: split mode 1, no row map; its columns and the padding behind them)
-    hipLaunchKernelGGL(prepare_transposed_kernel, dim3((R + 63) / 64, ((src_f32 ? H : K) + 63) / 64), dim3(256), 0, st, src,
-                       src_f32, R, H, (bf16_t*)dst, K);
-  else
-    hipLaunchKernelGGL(prepare_kernel, dim3((R + 15) / 16, (K + 511) / 512), dim3(256), 0, st, src, src_f32, R, H,
-                       (bf16_t*)dst, K, split_mode, rowmap, meta);
-  return hipGetLastError();
 }
 
 hipError_t launch_mfma_probe(const void* operands, int iters, float* sink, long long* clock_out, int n_cu,

@@ -60,12 +60,13 @@ struct Problem {
   float* akl;          // AKL only: [6][T_pad] per-token values between its passes (null otherwise)
   float* row_loss;     // [T_pad]
   float* partials;     // [n_split*parts][5][T_pad]
-  void* h_sT;          // bf16, T_pad tokens x H_s rounded up to 16, packed (launch_pack_columns)
+  void* h_sT;          // bf16, T_pad tokens x H_s rounded up to 16, packed (pack_columns)
   void* dz;            // bf16, T_pad x V_c, in the order of dz_chunk (kd_common.hpp)
   float* gh32;         // [n_ksplit_h][T][H_s]
 };
 
-hipError_t launch_rowmap(const Problem& p, hipStream_t st);
+// the row map (first teacher of a call), and the operand copies of the student and of the teacher that the call needs
+hipError_t launch_operands(const Problem& p, bool rowmap, bool student, bool teacher, hipStream_t st);
 hipError_t launch_mfma_probe(const void* operands, int iters, float* sink, long long* clock_out, int n_cu,
                              hipStream_t st);
 hipError_t launch_quantize_e4m3(const void* src, int src_f32, int64_t n, float inv_scale, void* dst, hipStream_t st);
@@ -79,23 +80,13 @@ constexpr int kAklThresholds = 16;     // ... per pass (the kernels' AKL_K)
 constexpr int kAklBins = 40;           // strip loop: 40-fold, until kAklResolution is reached: three passes from up to 30
 constexpr float kAklResolution = 4.78e-4f;
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st);
-hipError_t launch_finalize(const Problem& p, hipStream_t st);
+// ... and, for the backward pass, h_s of the compacted tokens transposed and packed for grad_W_s, from the caller's array
+hipError_t launch_finalize(const Problem& p, bool pack_h_s, hipStream_t st);
 hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulate, hipStream_t st);
-// dst[c][r] = src[r][c] (zero for R <= r < R_pad), one-byte elements
-hipError_t launch_transpose_bytes(const void* src, int64_t ld_src, int R, int C, void* dst, int64_t ld_dst, int R_pad,
-                                  hipStream_t st);
-// h_s of the compacted tokens transposed and packed for grad_W_s, from the caller's array
-hipError_t launch_pack_columns(const Problem& p, hipStream_t st);
-// hidden states [T][H] -> compacted, packed for the strip loop (T_pad rows of K elements)
-hipError_t launch_pack_rows(const Problem& p, const void* src, int H, void* dst, int K, hipStream_t st);
 // the backward products on the chunk of `width` columns from v0; `first`: grad_h_s's parts are written, not added to
 hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st);
 hipError_t launch_grad_h(const Problem& p, int v0, int width, bool first, hipStream_t st);
 hipError_t launch_gradh_finish(const Problem& p, hipStream_t st);
 const char* build_info();     // compile-time configuration of the kernels (tile shapes, ablation switch)
 int build_ablation();
-// dst bf16 [R][K]: mode 0 = copy, 1 = fp32 split as [hi|hi|lo], 2 = fp32 split as [hi|lo|hi]; zero-padded to K
-hipError_t launch_prepare(const void* src, int src_f32, int R, int H, void* dst, int K, int split_mode,
-                          const int* rowmap, const int* meta, int src_transposed, hipStream_t st);
-
 }  // namespace kd

@@ -67,7 +67,7 @@ __device__ __forceinline__ void store4(const rsrc_t& r, uint32_t at, const f32x4
 // ------------------------------------------------------------------------------------------
 struct GradWArgs {
   const char* dz;          // the chunk
-  const char* hT;          // h_s transposed and packed (pack_columns_kernel)
+  const char* hT;          // h_s transposed and packed (pack_columns in kd_kernels.hip)
   void* out;               // grad_W_s at the chunk's first column
   int64_t ldo;             // elements from vocabulary row to row ([V][H]) or from hidden row to row ([H][V])
   int width, H_s;
@@ -314,34 +314,6 @@ KD_STRIP_KERNEL void grad_h_kernel(const GradHArgs a) {
 // before and behind them
 // ------------------------------------------------------------------------------------------
 
-// h_s of the compacted tokens (row j = row rowmap[j] of src for j < n_valid, zero beyond), transposed and in the order in
-// which the waves of grad_W_s load it: [16-row block of h][32-token sub-step][lane][8], lane 16 g + n with tokens 8 g .. + 7
-// of row n.  64 x 64 tiles through LDS; hidden rows past C are zero.
-template <class E>
-__global__ void pack_columns_kernel(const E* src, int C, bf16_t* dst, int T_pad, const int* rowmap, const int* meta) {
-  __shared__ bf16_t tile[64][66];
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  const int n_valid = meta[META_N_VALID];
-  const int c = c0 + tx, cc = min(c, C - 1);
-  E v[16];
-#pragma unroll
-  for (int i = 0; i < 16; ++i)           // (rowmap holds a valid row for every r < T_pad: the loads need no test)
-    v[i] = src[(int64_t)rowmap[r0 + ty + 4 * i] * C + cc];
-#pragma unroll
-  for (int i = 0; i < 16; ++i) tile[ty + 4 * i][tx] = r0 + ty + 4 * i < n_valid && c < C ? (bf16_t)v[i] : (bf16_t)0.f;
-  __syncthreads();
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int sub = u, blk = ty;                                     // a wave: 16 hidden rows x 32 tokens, 1 KiB
-    if (c0 + 16 * blk >= C) continue;
-    bf16x8 o;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = tile[32 * sub + 8 * (tx >> 4) + e][16 * blk + (tx & 15)];
-    *(bf16x8*)(dst + ((int64_t)(c0 / 16 + blk) * (T_pad / 32) + r0 / 32 + sub) * 512 + tx * 8) = o;
-  }
-}
-
 // grad_h_s row t = sum over split-K parts of the fp32 partial sums of its compacted row (zero for a
 // masked token), converted to the output dtype.
 __global__ void gradh_finish_kernel(const float* parts, int n_parts, int T, int H, const int* inv,
@@ -367,17 +339,6 @@ __global__ void gradh_finish_kernel(const float* parts, int n_parts, int T, int 
 // ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
-hipError_t launch_pack_columns(const Problem& p, hipStream_t st) {
-  dim3 grid(p.T_pad / 64, (p.H_s + 63) / 64);
-  if (p.in_f32)
-    hipLaunchKernelGGL(pack_columns_kernel<float>, grid, dim3(256), 0, st, (const float*)p.user_h_s, p.H_s,
-                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
-  else
-    hipLaunchKernelGGL(pack_columns_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)p.user_h_s, p.H_s,
-                       (bf16_t*)p.h_sT, p.T_pad, p.rowmap, p.meta);
-  return hipGetLastError();
-}
-
 hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st) {
   const int nb = grad_W_tile(p.H_s) / 64;
   GradWArgs a{};

@@ -5,7 +5,7 @@
 // 192 vocabulary rows x 64 tokens in 16 x 16 x 32 MFMAs (half the accumulator traffic per flop of 32 x 32 x 16):
 //   - the vocabulary rows (A) go global -> LDS by direct loads and are read by all four waves;
 //   - the tokens (B) belong to one wave each, so they skip the LDS: the hidden states are re-packed once per
-//     call in the order in which a wave consumes them (pack_rows_kernel) and come straight into registers,
+//     call in the order in which a wave consumes them (pack_rows) and come straight into registers,
 //     1 KiB per load, three sub-steps (2300 cycles) ahead.
 // Measured on a plain product of 153600 x 4096 x 4096: 1401 TFLOP/s (1.75 GHz, matrix pipe busy 0.76); the same
 // with 32 x 32 x 16 MFMAs 1337 (1.53 GHz, 0.83); the 128 x 256 tile of eight waves with both operands through

@@ -1,7 +1,7 @@
 // The strip loop's logit kernels for bf16 heads kept as [H][V] and read in place (those for [V][H] heads: kd_kernels.hip).
 //
 // The vocabulary is the contiguous index, so a stage of the LDS holds k-rows of a tile, and the fragments come by the transposing
-// reads of the backward products, in the order of k in which dz lies (A_KMAJOR_DZ in kd_strip.hpp); pack_rows_kernel packs
+// reads of the backward products, in the order of k in which dz lies (A_KMAJOR_DZ in kd_strip.hpp); pack_rows packs
 // the hidden states in the same order, and nothing else differs.  Bound as the [V][H] kernels are, by the matrix pipe and the
 // chip's power.  Steps against the eight-wave loop, which takes both operands through the LDS: T = 2048, H = 4096 / 1024, V = 151936
 // 6.80 -> 6.19 ms (JSD 9.54 -> 8.90), T = 4096 13.33 -> 12.51, T = 512 1957 -> 1766 us, T = 1024, H = 8192 / 2048, V = 128256 5.98 -> 5.47
