@@ -26,12 +26,12 @@ template <int KIND>
 KD_STRIP_KERNEL void stats_strip_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<false> work(a, meta_get(a.meta, META_N_SPLIT));
-  StatsEpi<KIND, StripGeo> epi(a.c);
-  StripEpi<StatsEpi<KIND, StripGeo>> drive(epi);
+  StripStatsEpi<KIND> epi(a.c, smem);
+  StripEpi<StripStatsEpi<KIND>> drive(epi);
   LoopClock clk(a);
   strip_loop<2, true>(work, drive, smem);
   clk.stop(a);
-  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
 
 template <int KIND>
@@ -58,7 +58,7 @@ template <int KIND>
 KD_STRIP_KERNEL void grad_strip_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<false> work(a, meta_get(a.meta, a.last_chunk ? META_G_SPLIT_LAST : META_G_SPLIT));
-  GradEpi<KIND, StripGeo> epi(a);
+  GradEpi<KIND, StripGeo> epi(a, smem);
   StripEpi<GradEpi<KIND, StripGeo>> drive(epi);
   strip_loop<2, false>(work, drive, smem);
 }
@@ -67,8 +67,8 @@ template <int KIND, bool TF8, bool WHV>
 KD_LOGIT_KERNEL void stats_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   SplitWork<TF8, WHV> work(a);
-  StatsEpi<KIND, TileGeo> epi(a.c);
-  TileEpi<StatsEpi<KIND, TileGeo>> drive(epi, a.t_scale);
+  StatsEpi<KIND> epi(a.c);
+  TileEpi<StatsEpi<KIND>> drive(epi, a.t_scale);
   LoopClock clk(a);
   tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
   clk.stop(a);
@@ -105,7 +105,7 @@ template <int KIND, bool TF8, bool WHV>
 KD_LOGIT_KERNEL void grad_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   ChunkWork<TF8, WHV> work(a);
-  GradEpi<KIND, TileGeo> epi(a);
+  GradEpi<KIND, TileGeo> epi(a, smem);
   TileEpi<GradEpi<KIND, TileGeo>> drive(epi, a.t_scale);
   tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
 }
@@ -760,7 +760,7 @@ hipError_t launch_stats(const Problem& p, hipStream_t st) {
   a.clock_out = p.clock_out;
   const int grid = p.n_tt * p.n_split;      // worst case; workgroups beyond the device-side plan exit
 #define KD_STATS(K) (p.strip && p.w_hv_inplace ? launch_strip_hv_stats(p, a, grid, st) \
-                     : p.strip ? launch_big<stats_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a) \
+                     : p.strip ? launch_big<stats_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a) \
                      : p.t_fp8 ? launch_big<stats_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                      : p.w_hv_inplace ? launch_big<stats_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                                : launch_big<stats_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
@@ -769,7 +769,7 @@ hipError_t launch_stats(const Problem& p, hipStream_t st) {
     case 1: return KD_STATS(1);
     case 6:                        // both cross terms (AKL; never with the fp8 teacher)
       return p.strip && p.w_hv_inplace ? launch_strip_hv_stats(p, a, grid, st)
-             : p.strip ? launch_big<stats_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+             : p.strip ? launch_big<stats_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a)
              : p.w_hv_inplace ? launch_big<stats_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                               : launch_big<stats_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
     default: return KD_STATS(2);   // log-sum-exps only
@@ -961,7 +961,7 @@ hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulat
   // strip loop: one workgroup per (token tile, range), surplus ones exit; eight-wave loop: persistent workgroups
   const int grid = p.strip ? p.n_tt * p.g_split : tiles < p.n_cu ? tiles : p.n_cu;
 #define KD_GRAD(K) (p.strip && p.w_hv_inplace ? launch_strip_hv_grad(p, a, grid, st) \
-                     : p.strip ? launch_big<grad_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a) \
+                     : p.strip ? launch_big<grad_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a) \
                      : p.t_fp8 ? launch_big<grad_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                      : p.w_hv_inplace ? launch_big<grad_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                                : launch_big<grad_kernel<K, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a))
@@ -973,7 +973,7 @@ hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulat
     case 4: return KD_GRAD(4);
     case 6:
       return p.strip && p.w_hv_inplace ? launch_strip_hv_grad(p, a, grid, st)
-             : p.strip ? launch_big<grad_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+             : p.strip ? launch_big<grad_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a)
              : p.w_hv_inplace ? launch_big<grad_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                               : launch_big<grad_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
     default: return KD_GRAD(5);

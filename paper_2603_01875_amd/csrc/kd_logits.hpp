@@ -257,6 +257,7 @@ __device__ __forceinline__ float flog2(float x) { return __builtin_amdgcn_logf(x
 // token n(j).  PARTS partial results per token and vocabulary split leave a workgroup; this lane's is part().
 struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
   static constexpr int NC = NI, NE = MI * 16, PARTS = 4;
+  static constexpr bool IN_LDS = false;              // where GradEpi keeps what it knows of the tokens
   int wm, wn, lane;
   __device__ TileGeo() {
     lane = threadIdx.x & 63;
@@ -276,6 +277,7 @@ struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
 };
 struct StripGeo {        // 192 x 256 tile of four waves (kd_strip.hpp)
   static constexpr int NC = StripCfg::NB, NE = StripCfg::MB * 4, PARTS = 1;
+  static constexpr bool IN_LDS = true;
   int wave, lane;
   __device__ StripGeo() {
     lane = threadIdx.x & 63;
@@ -354,11 +356,11 @@ struct StripEpi {
 
 // Online log-sum-exp of both models plus the cross term of FKL / RKL.
 //   FKL: X = sum_v 2^(a_t - m_t) (z_t - z_s)      RKL: X = sum_v 2^(a_s - m_s) (z_s - z_t)
-template <int KIND, class Geo>
+template <int KIND>
 struct StatsEpi {
   static constexpr int NV = KIND == 6 ? 6 : 5;     // values per token and part (AKL keeps both cross terms)
-  static constexpr int NC = Geo::NC;
-  Geo geo;
+  static constexpr int NC = TileGeo::NC;
+  TileGeo geo;
   float m_t[NC], S_t[NC], m_s[NC], S_s[NC], X[NC], X2[NC];
   float c;
   __device__ StatsEpi(float c_) : c(c_) {
@@ -403,23 +405,9 @@ struct StatsEpi {
     m_t[j] = nmt; m_s[j] = nms; S_t[j] = st; S_s[j] = ss; X[j] = x; X2[j] = x2;
   }
   __device__ void write(const LogitArgs& a, int tt, int split) {
-    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * NV * a.T_pad;
+    float* p = a.partials + (int64_t)(split * TileGeo::PARTS + geo.part()) * NV * a.T_pad;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-#pragma unroll
-      for (int off = Geo::MERGE; off < 64; off <<= 1) {      // lanes that hold the same token
-        const float omt = __shfl_xor(m_t[j], off, 64), oms = __shfl_xor(m_s[j], off, 64);
-        const float nmt = fmaxf(m_t[j], omt), nms = fmaxf(m_s[j], oms);
-        const float wt = fexp2(m_t[j] - nmt), ws = fexp2(m_s[j] - nms);
-        const float owt = fexp2(omt - nmt), ows = fexp2(oms - nms);
-        const bool by_t = KIND == 0 || KIND == 6;
-        S_t[j] = fmaf(__shfl_xor(S_t[j], off, 64), owt, S_t[j] * wt);
-        S_s[j] = fmaf(__shfl_xor(S_s[j], off, 64), ows, S_s[j] * ws);
-        X[j] = fmaf(__shfl_xor(X[j], off, 64), by_t ? owt : ows, X[j] * (by_t ? wt : ws));
-        if (KIND == 6) X2[j] = fmaf(__shfl_xor(X2[j], off, 64), ows, X2[j] * ws);
-        m_t[j] = nmt; m_s[j] = nms;
-      }
-      if (geo.lane >= Geo::MERGE) continue;
       const int t = tt * BN + geo.n(j);
       p[0 * a.T_pad + t] = m_t[j];
       p[1 * a.T_pad + t] = S_t[j];
@@ -428,6 +416,80 @@ struct StatsEpi {
       p[4 * a.T_pad + t] = X[j];
       if (KIND == 6) p[5 * a.T_pad + t] = X2[j];
     }
+  }
+};
+
+// The same on the strip loop, whose lanes have no registers for what lasts from tile to tile: 20 of them, held by every lane for
+// its own rows, were spilled to memory, and each reload waited for every load in flight, four times a tile.  They live in LDS,
+// [token][8], one copy for the four lanes of a token, which merge what a tile adds to them; a token belongs to one wave, so there is
+// no barrier.  T = 4096, V = 151936, H = 4096 / 1024: statistics 4.33 -> 4.16 ms; with the gradient kernels' rows there, too, a step of
+// T = 4096 1.057 -> 1.062 (JSD 1.070) times the speed of the same earlier state, forward pass alone at T = 1003 1.004 -> 1.022.
+__device__ __forceinline__ float quad_max(float x) {          // over the lanes of a token, 16 and 32 apart
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+__device__ __forceinline__ float quad_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+template <int KIND>
+struct StripStatsEpi {
+  static constexpr int NV = KIND == 6 ? 6 : 5;
+  StripGeo geo;
+  float* state;            // m_t, S_t, m_s, S_s, X, X2 of this lane's token of column 0
+  float c;
+  __device__ StripStatsEpi(float c_, char* smem) : c(c_) {
+    float* const all = (float*)(smem + StripCfg::STATE_AT);
+    float* const own = all + threadIdx.x * 8;                 // (thread i: token i of the tile, its wave's)
+    *(f32x4*)own = f32x4{M_FLOOR, 0.f, M_FLOOR, 0.f};
+    own[4] = own[5] = 0.f;
+    state = all + geo.n(0) * 8;
+  }
+  __device__ void begin_item(int, int, int) {}
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+    float* const at = state + 16 * 8 * j;
+#if KD_ABLATE & 2
+#pragma unroll
+    for (int e = 0; e < NE; ++e) { at[1] += T[e]; at[3] += S[e]; }
+    return;
+#endif
+    const f32x4 old = *(const f32x4*)at;
+    float tmax = NEG_BIG, smax = NEG_BIG;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      tmax = fmaxf(tmax, T[e]);
+      smax = fmaxf(smax, S[e]);
+    }
+    const float nmt = fmaxf(old[0], quad_max(tmax) * c);
+    const float nms = fmaxf(old[2], quad_max(smax) * c);
+    float st = 0.f, ss = 0.f, x = 0.f, x2 = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const float zt = T[e], zs = S[e];
+      const float et = fexp2(fmaf(zt, c, -nmt));
+      const float es = fexp2(fmaf(zs, c, -nms));
+      st += et;
+      ss += es;
+      if (KIND == 0 || KIND == 6) x = fmaf(et, zt - zs, x);
+      if (KIND == 1) x = fmaf(es, zs - zt, x);
+      if (KIND == 6) x2 = fmaf(es, zs - zt, x2);
+    }
+    const float sct = fexp2(old[0] - nmt), scs = fexp2(old[2] - nms);
+    *(f32x4*)at = f32x4{nmt, fmaf(old[1], sct, quad_sum(st)), nms, fmaf(old[3], scs, quad_sum(ss))};
+    if (KIND != 2) at[4] = fmaf(at[4], KIND == 1 ? scs : sct, quad_sum(x));
+    if (KIND == 6) at[5] = fmaf(at[5], scs, quad_sum(x2));
+  }
+  __device__ void write(const LogitArgs& a, char* smem, int tt, int split) {
+    const float* const own = (const float*)(smem + StripCfg::STATE_AT) + threadIdx.x * 8;
+    float* p = a.partials + (int64_t)split * NV * a.T_pad + tt * BN + threadIdx.x;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) p[(int64_t)i * a.T_pad] = own[i];
   }
 };
 
@@ -556,15 +618,29 @@ struct GradEpi {
   static constexpr int NC = Geo::NC;
   Geo geo;
   const LogitArgs& a;
-  float Lt[NC], Ls[NC], sc[NC], R[NC], Wr[NC];
+  // Of the lane's tokens, in registers; on the strip loop, which has none for them (spills whose reloads waited for every load in
+  // flight, at the start of each phase), in LDS, [token] of rowinfo and behind them [token] of w_r.  A token belongs to one
+  // wave, and a workgroup stays with its token tile but for a few changes.
+  float Lt[Geo::IN_LDS ? 1 : NC], Ls[Geo::IN_LDS ? 1 : NC], sc[Geo::IN_LDS ? 1 : NC], R[Geo::IN_LDS ? 1 : NC], Wr[Geo::IN_LDS ? 1 : NC];
+  f32x4* info;
   int m0, n0, out_rows;
-  __device__ GradEpi(const LogitArgs& a_) : a(a_) {}
+  __device__ GradEpi(const LogitArgs& a_, char* smem) : a(a_), n0(-1) {
+    info = (f32x4*)(smem + (Geo::IN_LDS ? StripCfg::STATE_AT : 0));
+  }
   __device__ void begin_item(int m0_, int n0_, int out_rows_) {
     out_rows = out_rows_;
     m0 = m0_ - a.v0;                           // vocabulary offset inside the chunk
+    if constexpr (Geo::IN_LDS) {
+      if (n0 != n0_) {
+        info[threadIdx.x] = a.rowinfo[n0_ + threadIdx.x];
+        if (KIND == 6) ((float*)(info + BN))[threadIdx.x] = a.akl[AKL_WR * a.T_pad + n0_ + threadIdx.x];
+      }
+      n0 = n0_;
+      return;
+    }
     n0 = n0_;
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
+    for (int j = 0; j < (Geo::IN_LDS ? 0 : NC); ++j) {
       const f32x4 ri = a.rowinfo[n0 + geo.n(j)];
       Lt[j] = ri[0]; Ls[j] = ri[1]; sc[j] = ri[2]; R[j] = ri[3];
       Wr[j] = 0.f;
@@ -574,7 +650,15 @@ struct GradEpi {
   template <bool ADD, class J, int NE>
   __device__ __forceinline__ void emit(J, const float (&S)[NE], const float (&T)[NE]) {
     constexpr int j = J::value;
-    const float c = a.c, w = a.beta, s = sc[j];
+    const float c = a.c, w = a.beta;
+    float Lt_, Ls_, s, R_, Wr_ = 0.f;
+    if constexpr (Geo::IN_LDS) {
+      const f32x4 ri = info[geo.n(j)];
+      Lt_ = ri[0]; Ls_ = ri[1]; s = ri[2]; R_ = ri[3];
+      if (KIND == 6) Wr_ = ((const float*)(info + BN))[geo.n(j)];
+    } else {
+      Lt_ = Lt[j]; Ls_ = Ls[j]; s = sc[j]; R_ = R[j]; Wr_ = Wr[j];
+    }
 #pragma unroll
     for (int p = 0; p < NE / 16; ++p) {
       bf16x4 o[4];
@@ -588,19 +672,19 @@ struct GradEpi {
         }
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const float lt = fmaf(T[16 * p + e], c, -Lt[j]);
-        const float ls = fmaf(S[16 * p + e], c, -Ls[j]);
+        const float lt = fmaf(T[16 * p + e], c, -Lt_);
+        const float ls = fmaf(S[16 * p + e], c, -Ls_);
         const float ps = fexp2(ls);
         float g;
         if (KIND == 0) {
           g = ps - fexp2(lt);
         } else if (KIND == 1) {
-          g = ps * fmaf(LN2, ls - lt, -R[j]);
+          g = ps * fmaf(LN2, ls - lt, -R_);
         } else if (KIND == 6) {
-          g = fmaf(ps, fmaf(Wr[j] * LN2, ls - lt, R[j]), -(1.f - Wr[j]) * fexp2(lt));
+          g = fmaf(ps, fmaf(Wr_ * LN2, ls - lt, R_), -(1.f - Wr_) * fexp2(lt));
         } else {
           float u1, u2;
-          g = ps * (RowTerm<KIND>::template eval<false>(lt, ls, w, u1, u2) - R[j]);
+          g = ps * (RowTerm<KIND>::template eval<false>(lt, ls, w, u1, u2) - R_);
         }
         const float d = s * g;
         o[e >> 2][e & 3] = (bf16_t)(ADD ? (float)o[e >> 2][e & 3] + d : d);

@@ -15,8 +15,9 @@
 // built: 16 of its 48 blocks are accumulated in vector registers, 12 in accumulation registers, and stay there; the
 // other 20 are accumulated in accumulation registers and parked in LDS.  MFMAs are inline assembly so that each
 // accumulator stays in the register file it was given; the compiler's own choice copies them around inside the loop.
-// With the B ring and the fragments the 512 registers do not quite hold what an epilogue needs: up to 18 of them (AKL's
-// statistics: 28) are spilled in epilogues, none inside a k-loop.
+// With the B ring and the fragments the 512 registers are full: what the statistics and the gradient kernels keep from tile to
+// tile lives in LDS (STATE_AT).  A spilled register costs more than its traffic: its reload waits for every load in flight.
+// (Left: 12 of RKL's and AKL's gradient kernels, 5 of the skewed FKL's row pass, up to 24 for [H][V] heads.)
 //
 // One wave per SIMD: whatever stands between two k-steps is idle matrix time.  The loads of a k-step go out one by one
 // between MFMAs, the cursor moves on in front of the last block, and the change to the next phase or tile is off the
@@ -67,7 +68,9 @@ struct StripCfg : StripShape<12, 4> {
   static constexpr int PARKED = MB * NB - HELD;      // ... and in LDS
   static constexpr int PARK_BYTES = PARKED * 16 * NT;
   static constexpr int SMEM_BYTES = NST * STAGE_BYTES + PARK_BYTES;
-  static_assert(SMEM_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
+  // Behind it, 32 bytes per token for the epilogues that keep something of them (with STATE: what their kernels ask for).
+  static constexpr int STATE_AT = SMEM_BYTES, STATE_SMEM_BYTES = SMEM_BYTES + 32 * BN;
+  static_assert(STATE_SMEM_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
   // A workgroup's last tile, if it has at most SHORT rows, is multiplied as four blocks (its loads stay as they are:
   // rows that do not exist repeat the last one).  Priced at 0.45 of a full tile by the choice of ranges.
   static constexpr int SHORT = 64;                   // (rows behind those that exist are stored up to 64: see out_rows)

@@ -15,12 +15,12 @@ template <int KIND>
 KD_STRIP_KERNEL void stats_strip_hv_kern(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<true> work(a, meta_get(a.meta, META_N_SPLIT));
-  StatsEpi<KIND, StripGeo> epi(a.c);
-  StripEpi<StatsEpi<KIND, StripGeo>> drive(epi);
+  StripStatsEpi<KIND> epi(a.c, smem);
+  StripEpi<StripStatsEpi<KIND>> drive(epi);
   LoopClock clk(a);
   strip_loop<2, true, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
   clk.stop(a);
-  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
 
 template <int KIND>
@@ -37,7 +37,7 @@ template <int KIND>
 KD_STRIP_KERNEL void grad_strip_hv_kern(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<true> work(a, meta_get(a.meta, a.last_chunk ? META_G_SPLIT_LAST : META_G_SPLIT));
-  GradEpi<KIND, StripGeo> epi(a);
+  GradEpi<KIND, StripGeo> epi(a, smem);
   StripEpi<GradEpi<KIND, StripGeo>> drive(epi);
   strip_loop<2, false, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
 }
@@ -53,13 +53,14 @@ KD_STRIP_KERNEL void search_strip_hv_kern(const LogitArgs a) {
 }
 
 #define KD_LAUNCH(kern) launch_big<kern>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+#define KD_LAUNCH_STATE(kern) launch_big<kern>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a)
 
 hipError_t launch_strip_hv_stats(const Problem& p, const LogitArgs& a, int grid, hipStream_t st) {
   switch (p.kind) {
-    case 0: return KD_LAUNCH(stats_strip_hv_kern<0>);
-    case 1: return KD_LAUNCH(stats_strip_hv_kern<1>);
-    case 6: return KD_LAUNCH(stats_strip_hv_kern<6>);
-    default: return KD_LAUNCH(stats_strip_hv_kern<2>);
+    case 0: return KD_LAUNCH_STATE(stats_strip_hv_kern<0>);
+    case 1: return KD_LAUNCH_STATE(stats_strip_hv_kern<1>);
+    case 6: return KD_LAUNCH_STATE(stats_strip_hv_kern<6>);
+    default: return KD_LAUNCH_STATE(stats_strip_hv_kern<2>);
   }
 }
 hipError_t launch_strip_hv_rows(const Problem& p, const LogitArgs& a, int grid, hipStream_t st) {
@@ -73,13 +74,13 @@ hipError_t launch_strip_hv_rows(const Problem& p, const LogitArgs& a, int grid, 
 }
 hipError_t launch_strip_hv_grad(const Problem& p, const LogitArgs& a, int grid, hipStream_t st) {
   switch (p.kind) {
-    case 0: return KD_LAUNCH(grad_strip_hv_kern<0>);
-    case 1: return KD_LAUNCH(grad_strip_hv_kern<1>);
-    case 2: return KD_LAUNCH(grad_strip_hv_kern<2>);
-    case 3: return KD_LAUNCH(grad_strip_hv_kern<3>);
-    case 4: return KD_LAUNCH(grad_strip_hv_kern<4>);
-    case 6: return KD_LAUNCH(grad_strip_hv_kern<6>);
-    default: return KD_LAUNCH(grad_strip_hv_kern<5>);
+    case 0: return KD_LAUNCH_STATE(grad_strip_hv_kern<0>);
+    case 1: return KD_LAUNCH_STATE(grad_strip_hv_kern<1>);
+    case 2: return KD_LAUNCH_STATE(grad_strip_hv_kern<2>);
+    case 3: return KD_LAUNCH_STATE(grad_strip_hv_kern<3>);
+    case 4: return KD_LAUNCH_STATE(grad_strip_hv_kern<4>);
+    case 6: return KD_LAUNCH_STATE(grad_strip_hv_kern<6>);
+    default: return KD_LAUNCH_STATE(grad_strip_hv_kern<5>);
   }
 }
 hipError_t launch_strip_hv_search(const LogitArgs& a, int grid, hipStream_t st) { return KD_LAUNCH(search_strip_hv_kern); }
