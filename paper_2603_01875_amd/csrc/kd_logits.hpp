@@ -758,8 +758,8 @@ struct SearchEpi {
 // barrier, and its sums come in the order of that wave's tiles.  A compare, a select and an addition for each of 16 thresholds
 // were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes ten, and past the
 // first pass hardly any entry lies in the interval.  With 40 bins three passes narrow it further than four did with 16
-// thresholds.  T = 2048, V = 151936, H = 4096 / 1024: a pass 2.39 -> 2.88 ms (the first) and 1.74 (the others, 1.47 PFLOP/s),
-// a step 18.15 -> 14.50.
+// thresholds.  T = 2048, V = 151936, H = 4096 / 1024: a pass 2.39 -> 2.73 ms (the first) and 1.67 (the others, 1.5 PFLOP/s),
+// a step 17.6 -> 13.9.
 struct BinsEpi {
   static constexpr int NC = StripGeo::NC;
   static constexpr int BINS_AT = StripCfg::NST * StripCfg::STAGE_BYTES;      // in LDS, where other passes park student blocks
@@ -767,9 +767,14 @@ struct BinsEpi {
   StripGeo geo;
   float Lt[NC], Lo[NC], scale[NC];
   float* bins;             // of this lane's token of column 0
+  // (The atomic is inline assembly: in front of the compiler's stands a wait for the loads into LDS, which it might alias
+  // (4 % of the search).  The
+  // strip loop's prologue and its end order it against the bins' first and last accesses.)
+  uint32_t bins_lds;
   float c;
   __device__ BinsEpi(const LogitArgs& a, int tt, char* smem) : c(a.c) {
     bins = (float*)(smem + BINS_AT) + geo.n(0);
+    bins_lds = (uint32_t)(uintptr_t)(lds_void_t*)bins;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       const int t = tt * BN + geo.n(j);
@@ -791,9 +796,8 @@ struct BinsEpi {
     for (int e = 0; e < NE; ++e) {
       const float lt = fmaf(T[e], c, -Lt[j]), f = (lt - Lo[j]) * scale[j];
       if (f >= 0.f) {
-        const int k = (int)fminf(f, (float)AKL_BINS);
-        __hip_atomic_fetch_add(bins + k * BN + 16 * j, fexp2(lt), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t at = bins_lds + (uint32_t)fminf(f, (float)AKL_BINS) * (BN * 4);
+        asm volatile("ds_add_f32 %0, %1 offset:%2" ::"v"(at), "v"(fexp2(lt)), "n"(64 * j));
       }
     }
   }
