@@ -801,9 +801,9 @@ hipError_t launch_rows(const Problem& p, hipStream_t st) {
 #undef KD_ROWS
 }
 
-// Shape of the merges: 8 tokens x 128 threads each where a token may have more than 128 parts, else 32 tokens x 8
-// threads each (see merge_parts).
-static bool many_parts(const Problem& p) { return p.parts * p.n_split > 128; }
+// Shape of the merges: 8 tokens x 128 threads each where a token may have 128 parts or more, else 32 tokens x 8
+// threads each (see merge_parts).  128 parts, T = 128: combine_kernel 10.4 -> 5.8 us by the first.
+static bool many_parts(const Problem& p) { return p.parts * p.n_split >= 128; }
 
 // AKL: one pass of the threshold search (teacher logit tiles only) and its merge.
 hipError_t launch_akl_search(const Problem& p, hipStream_t st) {
