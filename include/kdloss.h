@@ -240,7 +240,7 @@ const char* kd_status_string(kd_status status);
 
 /* For reports: the vocabulary chunk kd_loss_fwd_bwd uses for these params and the number of kernels
  * one call launches (counted as for a call with a mask, whose hidden states are compacted into the
- * workspace).  Either output pointer may be NULL.  Host only. */
+ * workspace, and with four search passes for AKL, where one of the two logit loops needs three).  Either output pointer may be NULL.  Host only. */
 kd_status kd_loss_plan_info(const kd_loss_params* params, int64_t* vocab_chunk,
                             int64_t* n_launches);
 

@@ -245,7 +245,7 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   const int part_vals = q.kind == KD_AKL ? kd::kAklThresholds : 5;
   const int parts = 4 * (q.strip ? lean_split : q.n_split);
   size_t partial_bytes = (size_t)parts * part_vals * q.T_pad * 4;
-  const size_t bin_bytes = (size_t)q.n_split * (kd::kAklBins + 1) * q.T_pad * 4;
+  const size_t bin_bytes = (size_t)q.n_split * kd::kAklBins * q.T_pad * 4;
   if (q.strip && q.kind == KD_AKL && partial_bytes < bin_bytes) partial_bytes = bin_bytes;
   if (!with_backward) L.partials = take(partial_bytes);
   L.prep_h_t = L.prep_W_t = L.prep_h_s = L.prep_W_s = 0;
@@ -355,7 +355,7 @@ kd_status run_forward(const Problem& q, hipStream_t st, bool backward, bool firs
   if (q.kind == KD_AKL) {
     // the teacher probability that splits each token's vocabulary into head and tail, by a multi-way search
     // over the teacher logit tiles; then the head and tail gaps, which weigh the two KLs
-    for (int pass = 0; pass < kd::kAklSearchPasses; ++pass) KD_TRY(kd::launch_akl_search(q, st));
+    for (int pass = 0; pass < kd::akl_search_passes(q.strip); ++pass) KD_TRY(kd::launch_akl_search(q, pass, st));
     {
       ProfileScope ps(KD_PROF_ROWS, st);
       KD_TRY(kd::launch_rows(q, st));
@@ -473,10 +473,10 @@ kd_status kd_loss_plan_info(const kd_loss_params* params, int64_t* vocab_chunk, 
   const int64_t chunks = (q.V + q.V_c - 1) / q.V_c;
   if (vocab_chunk) *vocab_chunk = q.V_c;
   // compaction with the copies of the heads, copies of the hidden states (as with a mask), heads turned, statistics + merge,
-  // row pass + merge, loss and h_s^T, per chunk the gradient kernel and the two products, grad_h_s conversion
+  // row pass + merge, AKL's search as on the eight-wave loop, loss and h_s^T, per chunk the gradient kernel and the two products, grad_h_s conversion
   if (n_launches)
     *n_launches = 1 + 1 + (q.w_hv ? q.prep_Wt + q.prep_Ws : 0) + 2 + (q.kind >= KD_JSD ? 2 : 0) +
-                  (q.kind == KD_AKL ? 2 * kd::kAklSearchPasses : 0) + 1 + chunks * 3 + 1;
+                  (q.kind == KD_AKL ? 2 * kd::akl_search_passes(false) : 0) + 1 + chunks * 3 + 1;
   return KD_OK;
 }
 

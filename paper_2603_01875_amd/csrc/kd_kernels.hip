@@ -47,7 +47,6 @@ KD_STRIP_KERNEL void rows_strip_kernel(const LogitArgs a) {
 KD_STRIP_KERNEL void akl_search_strip_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<false> work(a, meta_get(a.meta, META_N_SPLIT));
-  if (!akl_search_open(a, work)) return;
   BinsEpi epi(a, work.tt, smem);
   StripEpi<BinsEpi> drive(epi);
   strip_loop<1, true>(work, drive, smem);
@@ -233,7 +232,7 @@ __device__ __forceinline__ void merge_parts(float (&v)[NV], float* lds) {
 // Merge the partial statistics of one (compacted) token; write log-sum-exps and, for FKL / RKL, the
 // row loss.
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind, float c, float least,
+__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind, float c, int strip,
                                                      f32x4* rowinfo, float* row_loss, float* akl) {
   __shared__ float lds[NT / 64 * 4 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
@@ -284,8 +283,7 @@ __global__ __launch_bounds__(NT) void combine_kernel(const float* partials, cons
     const float ltmax = (float)((double)Mt - Ltd);
     akl[AKL_FKL * T_pad + t] = (float)(0.6931471805599453 * fkl);
     akl[AKL_RKL * T_pad + t] = (float)(0.6931471805599453 * rkl);
-    // Less than 1 - mu lies below log2((1 - mu) / V), so more than mu at or above it (one more for the rounding of the sums).
-    akl[AKL_LO * T_pad + t] = fmaxf(ltmax - 40.f, least);
+    akl[AKL_LO * T_pad + t] = strip ? 0.f : ltmax - 40.f;
     akl[AKL_HI * T_pad + t] = ltmax + 1.0e-3f;         // above every entry: mass 0
     akl[AKL_LTMAX * T_pad + t] = ltmax;
     akl[AKL_WR * T_pad + t] = 0.f;
@@ -327,44 +325,36 @@ __global__ __launch_bounds__(NT) void akl_search_combine_kernel(const float* par
   akl[AKL_HI * T_pad + t] = new_hi;
 }
 
-// The same for the strip loop's bins: the interval becomes the bin in which the mass from the top on passes mu.  Rounding may
-// put an entry beside a bin's edge into the neighbour (edges are off by an ulp of lo, a bin's number by 1e-5), and the entry
-// that passes mu must not end up at or above HI: the interval is that much wider on both sides.
+// The same for the strip loop's bins of `width` cells: the interval becomes the bin in which the mass from the top on passes mu, or
+// the lowest one.  Behind the last pass (bins of one cell) its upper edge is the threshold.
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void akl_bins_combine_kernel(const float* partials, const int* meta, int T_pad, float mu, float* akl) {
-  constexpr int NV = AKL_BINS + 1;
-  __shared__ float lds[NT / 64 * NV * TX];
+__global__ __launch_bounds__(NT) void akl_bins_combine_kernel(const float* partials, const int* meta, int T_pad, float mu, float width,
+                                                              float* akl) {
+  __shared__ float lds[NT / 64 * AKL_BINS * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
   const int n_valid = meta[META_N_VALID], n_parts = meta[META_N_SPLIT];
-  const float lo = akl[AKL_LO * T_pad + t], hi = akl[AKL_HI * T_pad + t];
-  const bool open = t < n_valid && akl_open(lo, hi);
-  if (!__syncthreads_or(open)) return;
-  float m[NV];
+  if ((int)(blockIdx.x * TX) >= n_valid) return;
+  float m[AKL_BINS];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) m[k] = 0.f;
+  for (int k = 0; k < AKL_BINS; ++k) m[k] = 0.f;
   for (int p = g; p < n_parts; p += NT / TX) {
-    const float* q = partials + (int64_t)p * NV * T_pad + t;
+    const float* q = partials + (int64_t)p * AKL_BINS * T_pad + t;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) m[k] += q[(int64_t)k * T_pad];
+    for (int k = 0; k < AKL_BINS; ++k) m[k] += q[(int64_t)k * T_pad];
   }
-  merge_parts<TX, NT, NV, MergeSum>(m, lds);
-  if (g != 0 || !open) return;
-  const float step = (hi - lo) * (1.f / AKL_BINS);
-  float above = m[AKL_BINS], new_lo = lo, new_hi = hi;
+  merge_parts<TX, NT, AKL_BINS, MergeSum>(m, lds);
+  if (g != 0 || t >= n_valid) return;
+  float above = akl[AKL_WR * T_pad + t], bin = 0.f;
   bool found = false;
 #pragma unroll
-  for (int k = AKL_BINS - 1; k >= 0; --k) {
-    above += m[k];
-    if (!found) {
-      new_lo = k > 0 ? fmaf((float)k, step, lo) : lo;
-      if (above > mu) found = true;
-      else new_hi = new_lo;
-    }
+  for (int k = AKL_BINS - 1; k > 0; --k) {
+    if (!found && above + m[k] > mu) { bin = (float)k; found = true; }
+    if (!found) above += m[k];
   }
-  if (!found) new_hi = lo + step;      // (mu within rounding of 1: the lowest bin)
-  const float margin = fmaf(2.4e-7f, fabsf(lo), 1.e-5f * step);
-  akl[AKL_LO * T_pad + t] = new_lo - margin;
-  akl[AKL_HI * T_pad + t] = new_hi + margin;
+  const float lo = fmaf(bin, width, akl[AKL_LO * T_pad + t]);
+  akl[AKL_LO * T_pad + t] = lo;
+  akl[AKL_HI * T_pad + t] = akl_edge(lo + width, akl[AKL_LTMAX * T_pad + t]);
+  akl[AKL_WR * T_pad + t] = above;
 }
 
 // The two row sums (a1, a2) of a token, in every thread of the token.
@@ -806,10 +796,11 @@ hipError_t launch_rows(const Problem& p, hipStream_t st) {
 static bool many_parts(const Problem& p) { return p.parts * p.n_split >= 128; }
 
 // AKL: one pass of the threshold search (teacher logit tiles only) and its merge.
-hipError_t launch_akl_search(const Problem& p, hipStream_t st) {
+hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st) {
   LogitArgs a = make_logit_args(p);
   a.v0 = 0; a.v_end = p.V; a.n_vt = p.n_vt;
   a.partials = p.partials;
+  a.akl_width = pass == 0 ? kAklBins * kAklBins : pass == 1 ? kAklBins : 1;
   const int grid = p.n_tt * p.n_split;
   hipError_t e = p.strip && p.w_hv_inplace ? launch_strip_hv_search(a, grid, st)
            : p.strip ? launch_big<akl_search_strip_kernel>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
@@ -818,7 +809,7 @@ hipError_t launch_akl_search(const Problem& p, hipStream_t st) {
   if (e != hipSuccess) return e;
   if (p.strip) {
     hipLaunchKernelGGL((akl_bins_combine_kernel<8, 512>), dim3(p.T_pad / 8), dim3(512), 0, st, p.partials, p.meta, p.T_pad, p.beta,
-                       p.akl);
+                       a.akl_width, p.akl);
     return hipGetLastError();
   }
   if (many_parts(p))
@@ -916,18 +907,15 @@ hipError_t launch_operands(const Problem& p, bool rowmap, bool student, bool tea
   return hipGetLastError();
 }
 
-// Where AKL's search starts at the lowest.
-static float akl_least(const Problem& p) { return p.kind == 6 ? std::log2((1.f - p.beta) / (float)p.V) - 1.f : 0.f; }
-
 hipError_t launch_combine(const Problem& p, hipStream_t st) {
   if (many_parts(p))
     hipLaunchKernelGGL((combine_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
                        p.parts, p.T_pad,
-                       p.kind, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
+                       p.kind, 1.4426950408889634f / p.tau, p.strip, (f32x4*)p.rowinfo, p.row_loss, p.akl);
   else
     hipLaunchKernelGGL((combine_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
                        p.parts, p.T_pad,
-                       p.kind, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
+                       p.kind, 1.4426950408889634f / p.tau, p.strip, (f32x4*)p.rowinfo, p.row_loss, p.akl);
   return hipGetLastError();
 }
 

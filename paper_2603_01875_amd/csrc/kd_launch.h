@@ -73,12 +73,14 @@ hipError_t launch_quantize_e4m3(const void* src, int src_f32, int64_t n, float i
 hipError_t launch_stats(const Problem& p, hipStream_t st);
 hipError_t launch_combine(const Problem& p, hipStream_t st);
 hipError_t launch_rows(const Problem& p, hipStream_t st);
-hipError_t launch_akl_search(const Problem& p, hipStream_t st);      // one search pass and its merge
+hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st);      // one search pass and its merge
 hipError_t launch_akl_weights(const Problem& p, hipStream_t st);
-constexpr int kAklSearchPasses = 4;    // eight-wave loop: 17-fold narrowing each, 40 -> 4.8e-4 in base-2 log-probability
-constexpr int kAklThresholds = 16;     // ... per pass (the kernels' AKL_K)
-constexpr int kAklBins = 40;           // strip loop: 40-fold, until kAklResolution is reached: three passes from up to 30
-constexpr float kAklResolution = 4.78e-4f;
+// AKL's border lies on a grid of 17^4 cells, from 40 below a token's largest base-2 log-probability to 1e-3 above it: 4.8e-4 each.
+constexpr int kAklThresholds = 16;     // eight-wave loop: four passes, 17-fold narrowing each (the kernels' AKL_K)
+constexpr int kAklBins = 44;           // strip loop: three passes by bins of 44^2, 44 and 1 cells
+constexpr int kAklCells = 17 * 17 * 17 * 17;
+static_assert(kAklBins * kAklBins * kAklBins >= kAklCells, "three passes reach a cell");
+inline int akl_search_passes(bool strip) { return strip ? 3 : 4; }
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st);
 // ... and, for the backward pass, h_s of the compacted tokens transposed and packed for grad_W_s, from the caller's array
 hipError_t launch_finalize(const Problem& p, bool pack_h_s, hipStream_t st);

@@ -65,6 +65,7 @@ struct LogitArgs {
   float* partials;     // stats: [parts][5][T_pad];  jsd: [parts][2][T_pad]
   const f32x4* rowinfo;// [T_pad]: {lse2_t, lse2_s, mask/(n tau), row term}
   const float* akl;    // AKL only: [AKL_ROWS][T_pad] per-token values (see the AKL_* indices)
+  float akl_width;     // ... cells in a bin of this search pass (strip loop)
   bf16_t* dz;          // chunk of dL/dz_s, ldz columns, in the order of dz_chunk
   int ldz;
   int last_chunk;      // this launch handles the last chunk of the vocabulary
@@ -242,11 +243,17 @@ constexpr float LN2 = 0.6931471805599453f;
 enum { AKL_FKL = 0, AKL_RKL = 1,   // the token's forward / reverse KL
        AKL_LO = 2, AKL_HI = 3,     // search interval of the head threshold (base-2 teacher log-probability):
                                    // mass{lt >= LO} > mu >= mass{lt >= HI}
+                                   // (strip loop: LO as the number of its cell of the grid, HI only behind the search)
        AKL_LTMAX = 4,              // the largest teacher log-probability of the token
        AKL_WR = 5,                 // weight of the reverse KL (the forward KL has 1 - that)
+                                   // (strip loop, between search passes: the mass above the interval)
        AKL_ROWS = 6 };
 constexpr int AKL_K = kAklThresholds;   // thresholds tried per search pass of the eight-wave loop: 17-fold narrowing
 constexpr int AKL_BINS = kAklBins;      // bins of a search pass of the strip loop
+constexpr float AKL_CELL = 40.001f / kAklCells;
+// Edge j of the grid for a token whose largest log-probability is `ltmax`.  The search and its merge must both use this
+// expression: an entry lies in the cell between the two edges that it compares with, and in no other pass in another one.
+__device__ __forceinline__ float akl_edge(float j, float ltmax) { return fmaf(j, AKL_CELL, ltmax - 40.f); }
 constexpr float AKL_TOP_EPS = 1.0e-4f;   // entries this close (base-2 log) to the token's largest one count as "the top entry"
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -753,68 +760,64 @@ struct SearchEpi {
   }
 };
 
-// ... and on the strip loop, which has one accumulator here and so LDS to spare: the mass of the entries inside the
-// interval by AKL_BINS bins in LDS, [bin][token], and in one more bin that of the entries at or above HI.  A token belongs to one wave: no
+// ... and on the strip loop, which has one accumulator here and so LDS to spare: the mass of the entries inside the interval by
+// AKL_BINS bins in LDS, [bin][token].  What lies above the interval is known from the pass before.  A token belongs to one wave: no
 // barrier, and its sums come in the order of that wave's tiles.  A compare, a select and an addition for each of 16 thresholds
-// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes ten, and past the
-// first pass hardly any entry lies in the interval.  With 40 bins three passes narrow it further than four did with 16
-// thresholds.  T = 2048, V = 151936, H = 4096 / 1024: a pass 2.39 -> 2.73 ms (the first) and 1.67 (the others, 1.5 PFLOP/s),
-// a step 17.6 -> 13.9.
+// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes 14, and past the
+// first pass hardly any entry lies in the interval.
 struct BinsEpi {
   static constexpr int NC = StripGeo::NC;
   static constexpr int BINS_AT = StripCfg::NST * StripCfg::STAGE_BYTES;      // in LDS, where other passes park student blocks
-  static_assert((AKL_BINS + 1) * BN * 4 <= StripCfg::PARK_BYTES, "bins of a token tile");
+  static_assert(AKL_BINS * BN * 4 <= StripCfg::PARK_BYTES, "bins of a token tile");
   StripGeo geo;
-  float Lt[NC], Lo[NC], scale[NC];
+  float Lt[NC], Top[NC], Lo[NC], off[NC];      // of the lane's tokens: log-sum-exp, largest log-probability, first cell; see column
   float* bins;             // of this lane's token of column 0
   // (The atomic is inline assembly: in front of the compiler's stands a wait for the loads into LDS, which it might alias
-  // (4 % of the search).  The
-  // strip loop's prologue and its end order it against the bins' first and last accesses.)
+  // (4 % of the search).  The strip loop's prologue and its end order it against the bins' first and last accesses.)
   uint32_t bins_lds;
-  float c;
-  __device__ BinsEpi(const LogitArgs& a, int tt, char* smem) : c(a.c) {
+  float c, width, scale;
+  __device__ BinsEpi(const LogitArgs& a, int tt, char* smem) : c(a.c), width(a.akl_width), scale(1.f / (a.akl_width * AKL_CELL)) {
     bins = (float*)(smem + BINS_AT) + geo.n(0);
     bins_lds = (uint32_t)(uintptr_t)(lds_void_t*)bins;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       const int t = tt * BN + geo.n(j);
-      const float lo = a.akl[AKL_LO * a.T_pad + t], hi = a.akl[AKL_HI * a.T_pad + t];
       Lt[j] = a.rowinfo[t][0];
-      Lo[j] = lo;
-      scale[j] = hi > lo ? (float)AKL_BINS / (hi - lo) : 0.f;
+      Top[j] = a.akl[AKL_LTMAX * a.T_pad + t];
+      Lo[j] = a.akl[AKL_LO * a.T_pad + t];
+      off[j] = -fmaf(akl_edge(Lo[j], Top[j]), scale, 0.0625f);
     }
-    for (int k = geo.lane >> 4; k <= AKL_BINS; k += 4)
+    for (int k = geo.lane >> 4; k < AKL_BINS; k += 4)
 #pragma unroll
       for (int j = 0; j < NC; ++j) bins[k * BN + 16 * j] = 0.f;
   }
   __device__ void begin_item(int, int, int) {}
-  // T alone: the teacher's logits (entries that do not exist are NEG_BIG: below the interval)
+  // T alone: the teacher's logits (entries that do not exist are NEG_BIG: below the interval).
+  // lt * scale + off is the entry's place in units of bins, less 1/16: more than its rounding in the narrowest bins (log-probabilities
+  // of size 64 and edges half an ulp off are 0.024 of a cell), so that its floor is the bin's number or one less, and the comparison
+  // with the edge above says which.
   template <class J, int NE>
   __device__ __forceinline__ void column(J, const float (&)[NE], const float (&T)[NE]) {
     constexpr int j = J::value;
+    const float above = Lo[j] + width;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
-      const float lt = fmaf(T[e], c, -Lt[j]), f = (lt - Lo[j]) * scale[j];
-      if (f >= 0.f) {
-        const uint32_t at = bins_lds + (uint32_t)fminf(f, (float)AKL_BINS) * (BN * 4);
+      const float lt = fmaf(T[e], c, -Lt[j]);
+      float k = floorf(fmaf(lt, scale, off[j]));
+      if (lt >= akl_edge(fmaf(k, width, above), Top[j])) k += 1.f;
+      if (k >= 0.f && k < (float)AKL_BINS) {
+        const uint32_t at = bins_lds + (uint32_t)k * (BN * 4);
         asm volatile("ds_add_f32 %0, %1 offset:%2" ::"v"(at), "v"(fexp2(lt)), "n"(64 * j));
       }
     }
   }
   __device__ void write(const LogitArgs& a, int tt, int split) {
-    float* p = a.partials + (int64_t)split * (AKL_BINS + 1) * a.T_pad + tt * BN + geo.n(0);
-    for (int k = geo.lane >> 4; k <= AKL_BINS; k += 4)
+    float* p = a.partials + (int64_t)split * AKL_BINS * a.T_pad + tt * BN + geo.n(0);
+    for (int k = geo.lane >> 4; k < AKL_BINS; k += 4)
 #pragma unroll
       for (int j = 0; j < NC; ++j) p[(int64_t)k * a.T_pad + 16 * j] = bins[k * BN + 16 * j];
   }
 };
-// Whether a token's search goes on; a workgroup of the strip loop whose tokens are all done leaves.
-__device__ __forceinline__ bool akl_open(float lo, float hi) { return hi - lo > kAklResolution; }
-template <class Work>
-__device__ __forceinline__ bool akl_search_open(const LogitArgs& a, const Work& work) {
-  const int t = work.tt * BN + threadIdx.x;
-  return __syncthreads_or(work.cnt > 0 && akl_open(a.akl[AKL_LO * a.T_pad + t], a.akl[AKL_HI * a.T_pad + t]));
-}
 
 // measurement aid, off unless asked for
 struct LoopClock {

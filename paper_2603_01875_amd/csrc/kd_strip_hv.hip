@@ -45,7 +45,6 @@ KD_STRIP_KERNEL void grad_strip_hv_kern(const LogitArgs a) {
 KD_STRIP_KERNEL void search_strip_hv_kern(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<true> work(a, meta_get(a.meta, META_N_SPLIT));
-  if (!akl_search_open(a, work)) return;
   BinsEpi epi(a, work.tt, smem);
   StripEpi<BinsEpi> drive(epi);
   strip_loop<1, true, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
