@@ -803,7 +803,7 @@ hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st) {
   a.akl_width = pass == 0 ? kAklBins * kAklBins : pass == 1 ? kAklBins : 1;
   const int grid = p.n_tt * p.n_split;
   hipError_t e = p.strip && p.w_hv_inplace ? launch_strip_hv_search(a, grid, st)
-           : p.strip ? launch_big<akl_search_strip_kernel>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+           : p.strip ? launch_big<akl_search_strip_kernel>(grid, StripCfg::NT, BinsEpi::SMEM_BYTES, st, &a)
            : p.w_hv_inplace ? launch_big<akl_search_kernel<true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                             : launch_big<akl_search_kernel<false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
   if (e != hipSuccess) return e;

@@ -762,22 +762,26 @@ struct SearchEpi {
 
 // ... and on the strip loop, which has one accumulator here and so LDS to spare: the mass of the entries inside the interval by
 // AKL_BINS bins in LDS, [bin][token].  What lies above the interval is known from the pass before.  A token belongs to one wave: no
-// barrier, and its sums come in the order of that wave's tiles.  A compare, a select and an addition for each of 16 thresholds
-// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes 14, and past the
+// barrier.  Its four lanes may meet in one bin, and in no stated order, so the sums are whole numbers, of units of 2^-56: the same
+// in any order.  (An entry loses less than a unit: 2^-32 in all at 2^24 entries, where a sum in fp32 is 2^-25 off by its last addition
+// alone.)  A compare, a select and an addition for each of 16 thresholds
+// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes 20, and past the
 // first pass hardly any entry lies in the interval.
 struct BinsEpi {
   static constexpr int NC = StripGeo::NC;
   static constexpr int BINS_AT = StripCfg::NST * StripCfg::STAGE_BYTES;      // in LDS, where other passes park student blocks
-  static_assert(AKL_BINS * BN * 4 <= StripCfg::PARK_BYTES, "bins of a token tile");
+  static constexpr int SMEM_BYTES = BINS_AT + AKL_BINS * BN * 8;
+  static_assert(SMEM_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
+  static constexpr float FIRST = 0x1p24f, SECOND = 0x1p32f, UNIT = 0x1p-56f;       // upper and lower word of a mass in units
   StripGeo geo;
   float Lt[NC], Top[NC], Lo[NC], off[NC];      // of the lane's tokens: log-sum-exp, largest log-probability, first cell; see column
-  float* bins;             // of this lane's token of column 0
+  uint64_t* bins;          // of this lane's token of column 0
   // (The atomic is inline assembly: in front of the compiler's stands a wait for the loads into LDS, which it might alias
   // (4 % of the search).  The strip loop's prologue and its end order it against the bins' first and last accesses.)
   uint32_t bins_lds;
   float c, width, scale;
   __device__ BinsEpi(const LogitArgs& a, int tt, char* smem) : c(a.c), width(a.akl_width), scale(1.f / (a.akl_width * AKL_CELL)) {
-    bins = (float*)(smem + BINS_AT) + geo.n(0);
+    bins = (uint64_t*)(smem + BINS_AT) + geo.n(0);
     bins_lds = (uint32_t)(uintptr_t)(lds_void_t*)bins;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
@@ -789,7 +793,7 @@ struct BinsEpi {
     }
     for (int k = geo.lane >> 4; k < AKL_BINS; k += 4)
 #pragma unroll
-      for (int j = 0; j < NC; ++j) bins[k * BN + 16 * j] = 0.f;
+      for (int j = 0; j < NC; ++j) bins[k * BN + 16 * j] = 0;
   }
   __device__ void begin_item(int, int, int) {}
   // T alone: the teacher's logits (entries that do not exist are NEG_BIG: below the interval).
@@ -806,8 +810,10 @@ struct BinsEpi {
       float k = floorf(fmaf(lt, scale, off[j]));
       if (lt >= akl_edge(fmaf(k, width, above), Top[j])) k += 1.f;
       if (k >= 0.f && k < (float)AKL_BINS) {
-        const uint32_t at = bins_lds + (uint32_t)k * (BN * 4);
-        asm volatile("ds_add_f32 %0, %1 offset:%2" ::"v"(at), "v"(fexp2(lt)), "n"(64 * j));
+        const uint32_t at = bins_lds + (uint32_t)k * (BN * 8);
+        const float p = fexp2(lt) * FIRST;
+        const uint32_t hi = (uint32_t)p, lo = (uint32_t)((p - (float)hi) * SECOND);
+        asm volatile("ds_add_u64 %0, %1 offset:%2" ::"v"(at), "v"((uint64_t)hi << 32 | lo), "n"(128 * j));
       }
     }
   }
@@ -815,7 +821,7 @@ struct BinsEpi {
     float* p = a.partials + (int64_t)split * AKL_BINS * a.T_pad + tt * BN + geo.n(0);
     for (int k = geo.lane >> 4; k < AKL_BINS; k += 4)
 #pragma unroll
-      for (int j = 0; j < NC; ++j) p[(int64_t)k * a.T_pad + 16 * j] = bins[k * BN + 16 * j];
+      for (int j = 0; j < NC; ++j) p[(int64_t)k * a.T_pad + 16 * j] = (float)bins[k * BN + 16 * j] * UNIT;
   }
 };
 

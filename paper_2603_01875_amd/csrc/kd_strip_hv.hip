@@ -82,6 +82,8 @@ hipError_t launch_strip_hv_grad(const Problem& p, const LogitArgs& a, int grid, 
     default: return KD_LAUNCH_STATE(grad_strip_hv_kern<5>);
   }
 }
-hipError_t launch_strip_hv_search(const LogitArgs& a, int grid, hipStream_t st) { return KD_LAUNCH(search_strip_hv_kern); }
+hipError_t launch_strip_hv_search(const LogitArgs& a, int grid, hipStream_t st) {
+  return launch_big<search_strip_hv_kern>(grid, StripCfg::NT, BinsEpi::SMEM_BYTES, st, &a);
+}
 
 }  // namespace kd

@@ -32,7 +32,7 @@ def _teachers(V, rng):
         p = np.exp(O.log_softmax(z[None], 1.0)[0])
         k = int((np.cumsum(p[order]) <= MU).sum())
         c[order[k]] = c[order[k - 1]]
-        f[order[k]] = bf16(f[order[k - 1]] - rng.uniform(0.02, 0.9) * CELL * np.log(2) * 1024)
+        f[order[k]] = bf16([f[order[k - 1]] - rng.uniform(0.02, 0.9) * CELL * np.log(2) * 1024])[0]
         z = c + f / 1024
         lt = O.log_softmax(z[None], 1.0)[0] / np.log(2)
         p = 2.0 ** lt
