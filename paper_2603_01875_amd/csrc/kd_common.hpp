@@ -8,6 +8,9 @@
 
 namespace kd {
 
+// Number of this workgroup in a grid of flat_grid (kd_launch.h).
+__device__ __forceinline__ int64_t flat_group() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // Workgroups are dealt to the 8 XCDs round-robin by workgroup id.  Renumber so
 // that consecutive logical ids sit on one XCD (and share its L2).
 __device__ __forceinline__ int xcd_logical_id(int b, int G) {

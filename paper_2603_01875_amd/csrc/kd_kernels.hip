@@ -455,8 +455,9 @@ __global__ __launch_bounds__(1024) void finalize_kernel(const int* meta, const i
                                                         float* per_token_out, const PackColumnsArgs pc) {
   __shared__ double s_sum[1024];
   __shared__ bf16_t tile[64][66];
-  if (blockIdx.x > 0) {
-    const int b = blockIdx.x - 1, wide = pc.T_pad / 64, by = b / wide, r0 = (b - by * wide) * 64, c0 = by * 64;
+  if (flat_group() > 0) {
+    const int b = (int)(flat_group() - 1), wide = pc.T_pad / 64, by = b / wide, r0 = (b - by * wide) * 64, c0 = by * 64;
+    if (c0 >= pc.C) return;
     const int n = meta[META_N_VALID];
     if (pc.src_f32) pack_columns((const float*)pc.src, pc.C, pc.dst, pc.T_pad, pc.rowmap, n, r0, c0, tile);
     else pack_columns((const bf16_t*)pc.src, pc.C, pc.dst, pc.T_pad, pc.rowmap, n, r0, c0, tile);
@@ -651,7 +652,7 @@ struct OperandArgs {
   OperandJob job[4];
 };
 __global__ __launch_bounds__(1024) void operands_kernel(const OperandArgs a) {
-  int b = blockIdx.x;
+  int64_t b = flat_group();
   if (a.with_rowmap) {
     if (b == 0) {
       make_rowmap(a.rm);
@@ -662,7 +663,8 @@ __global__ __launch_bounds__(1024) void operands_kernel(const OperandArgs a) {
   int i = 0;
   while (i + 1 < a.n && b >= a.job[i].groups) b -= a.job[i++].groups;
   const OperandJob& q = a.job[i];
-  const int block = 4 * b + (int)(threadIdx.x >> 8), tid = threadIdx.x & 255;
+  if (b >= q.groups) return;
+  const int block = 4 * (int)b + (int)(threadIdx.x >> 8), tid = threadIdx.x & 255;
   if (q.kind == 0) prepare(block, tid, q.src, q.src_f32, q.R, q.H, q.dst, q.K, q.mode, q.rowmap, a.rm.meta);
   else if (q.kind == 1) pack_rows(block, tid, q.src, q.src_f32, q.mode, q.R, q.H, q.dst, q.K, a.rm.rowmap, a.rm.meta);
   else gather_rows(block, tid, (const u32x4*)q.src, (u32x4*)q.dst, q.R, q.K / 8, q.rowmap, a.rm.meta);
@@ -854,7 +856,7 @@ hipError_t launch_operands(const Problem& p, bool rowmap, bool student, bool tea
   OperandArgs first{}, second{};       // what does not look at the row map, and what does
   first.rm = second.rm = rowmap_args(p);
   first.with_rowmap = rowmap;
-  int groups_first = rowmap ? 1 : 0, groups_second = 0;
+  int64_t groups_first = rowmap ? 1 : 0, groups_second = 0;
   auto add = [&](bool mapped, OperandJob j, int64_t blocks) {
     j.groups = (int)((blocks + 3) / 4);
     OperandArgs& to = mapped ? second : first;
@@ -889,8 +891,12 @@ hipError_t launch_operands(const Problem& p, bool rowmap, bool student, bool tea
   if (student && p.prep_hs) hidden(p.user_h_s, p.H_s, const_cast<void*>(p.h_s), p.K_s, false);
   if (teacher && p.prep_Wt && !p.w_hv) head(p.user_W_t, p.H_t, const_cast<void*>(p.W_t), p.K_t);
   if (student && p.prep_Ws && !p.w_hv) head(p.user_W_s, p.H_s, const_cast<void*>(p.W_s), p.K_s);
-  if (groups_first) hipLaunchKernelGGL(operands_kernel, dim3(groups_first), dim3(1024), 0, st, first);
-  if (groups_second) hipLaunchKernelGGL(operands_kernel, dim3(groups_second), dim3(1024), 0, st, second);
+  auto launch = [&](int64_t groups, const OperandArgs& a) {
+    const FlatGrid g = flat_grid(groups);
+    if (groups) hipLaunchKernelGGL(operands_kernel, dim3(g.x, g.y), dim3(1024), 0, st, a);
+  };
+  launch(groups_first, first);
+  launch(groups_second, second);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !p.w_hv) return e;
   // heads kept as [H][V] that are not read in place: transposed copies
@@ -931,8 +937,8 @@ hipError_t launch_combine_rows(const Problem& p, hipStream_t st) {
 
 hipError_t launch_finalize(const Problem& p, bool pack_h_s, hipStream_t st) {
   const PackColumnsArgs pc{p.user_h_s, (bf16_t*)p.h_sT, p.rowmap, p.in_f32, p.H_s, p.T_pad};
-  const int grid = 1 + (pack_h_s ? p.T_pad / 64 * ((p.H_s + 63) / 64) : 0);
-  hipLaunchKernelGGL(finalize_kernel, dim3(grid), dim3(1024), 0, st, p.meta, p.inv, p.row_loss, p.T, p.tau,
+  const FlatGrid g = flat_grid(1 + (pack_h_s ? (int64_t)(p.T_pad / 64) * ((p.H_s + 63) / 64) : 0));
+  hipLaunchKernelGGL(finalize_kernel, dim3(g.x, g.y), dim3(1024), 0, st, p.meta, p.inv, p.row_loss, p.T, p.tau,
                      p.out_weight, p.accumulate_loss, (f32x4*)p.rowinfo, p.loss, p.per_token_loss, pc);
   return hipGetLastError();
 }

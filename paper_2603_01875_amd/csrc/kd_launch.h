@@ -22,6 +22,14 @@ inline int grad_W_tile(int64_t H_s) {
   return best;
 }
 
+// Shape of a grid of `groups` workgroups of up to 1024 threads that are numbered in a row (kernels: flat_group).  A grid has fewer
+// than 2^32 threads along one axis, so beyond 2^21 workgroups it takes a second one, and the last row has some too many.
+struct FlatGrid { uint32_t x, y; };
+inline FlatGrid flat_grid(int64_t groups) {
+  const int64_t most = (int64_t)1 << 21;
+  return groups <= most ? FlatGrid{(uint32_t)groups, 1} : FlatGrid{(uint32_t)most, (uint32_t)((groups + most - 1) / most)};
+}
+
 // Everything a launch needs, resolved by the planner in kd_api.hip.
 struct Problem {
   int T, V, H_s, H_t;
