@@ -725,7 +725,7 @@ __device__ __forceinline__ uint32_t f32_to_e4m3(float x) {
 
 // dst[i] = e4m3(src[i] * inv_scale), 8 values per thread
 __global__ void quantize_e4m3_kernel(const void* src, int src_f32, int64_t n, float inv_scale, uint8_t* dst) {
-  const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 8;
+  const int64_t i0 = (flat_group() * blockDim.x + threadIdx.x) * 8;
   if (i0 >= n) return;
   uint32_t w[2] = {0u, 0u};
 #pragma unroll
@@ -986,8 +986,8 @@ hipError_t launch_mfma_probe(const void* operands, int iters, float* sink, long 
 }
 
 hipError_t launch_quantize_e4m3(const void* src, int src_f32, int64_t n, float inv_scale, void* dst, hipStream_t st) {
-  const int64_t threads = (n + 7) / 8;
-  hipLaunchKernelGGL(quantize_e4m3_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, src, src_f32, n,
+  const FlatGrid g = flat_grid(((n + 7) / 8 + 255) / 256);
+  hipLaunchKernelGGL(quantize_e4m3_kernel, dim3(g.x, g.y), dim3(256), 0, st, src, src_f32, n,
                      inv_scale, (uint8_t*)dst);
   return hipGetLastError();
 }

@@ -318,7 +318,7 @@ KD_STRIP_KERNEL void grad_h_kernel(const GradHArgs a) {
 // masked token), converted to the output dtype.
 __global__ void gradh_finish_kernel(const float* parts, int n_parts, int T, int H, const int* inv,
                                     int out_f32, void* out) {
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+  const int64_t i = (flat_group() * blockDim.x + threadIdx.x) * 4;
   const int64_t n = (int64_t)T * H;
   if (i >= n) return;
   const int t = (int)(i / H), h = (int)(i % H);
@@ -392,8 +392,8 @@ hipError_t launch_grad_h(const Problem& p, int v0, int width, bool first, hipStr
 
 hipError_t launch_gradh_finish(const Problem& p, hipStream_t st) {
   const int64_t n = (int64_t)p.T * p.H_s;
-  const int64_t threads = (n + 3) / 4;
-  hipLaunchKernelGGL(gradh_finish_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, p.gh32,
+  const FlatGrid g = flat_grid(((n + 3) / 4 + 255) / 256);
+  hipLaunchKernelGGL(gradh_finish_kernel, dim3(g.x, g.y), dim3(256), 0, st, p.gh32,
                      p.n_ksplit_h, p.T, p.H_s, p.inv, p.grad_f32, p.grad_h_s);
   return hipGetLastError();
 }
