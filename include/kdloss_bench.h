@@ -43,6 +43,10 @@ kd_status kd_loss_profile_clock(void* two_int64_device);
  * stats_strip_hv_kern, ...).  Host only. */
 kd_status kd_loss_plan_loop(const kd_loss_params* params, int32_t* loop);
 
+/* How the grad_h_s product of a call with these params is cut: hidden rows of a tile (64, 128, 192 or 256; beside 256
+ * tokens) and parts that the vocabulary is split into.  Either output pointer may be NULL.  Host only. */
+kd_status kd_loss_plan_grad_h(const kd_loss_params* params, int32_t* tile_rows, int32_t* parts);
+
 /* Benchmark aid, not part of the method: what the bf16 matrix pipe sustains on this GPU with nothing
  * else going on.  One launch of 256 workgroups x 8 waves (the occupancy of the logit kernels), each wave
  * issuing `iters` x 8 independent MFMA 32x32x16 on operands taken from `operands` (device, 128 KiB of

@@ -211,21 +211,25 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   q.V_c = (int)(vc < v_all ? vc : v_all);
 
   // Tile and split-K of the grad_h_s product: a chunk's tiles are rounds of n_cu workgroups, each of so many k-steps of 64
-  // columns; 1.48, 1.15, 0.85, 0.6 us a k-step for 256, 192, 128, 64 hidden rows (1.41 PFLOP/s down to 0.9), and 4 us a
-  // tile to start and 11 us per 256 rows to write its sums, as much again to read them where there are several chunks;
-  // and every part is read once more at the end of the call (4 TB/s).  Measured: T = 256, one chunk of 151936 columns,
-  // H_s = 1024 112 us with 128 rows x 32 parts, 167 us with 256 x 32, which is half of the workgroups.
+  // columns; 1.54, 1.17, 0.85, 0.6 us a k-step for 256, 192, 128, 64 hidden rows (1.36 PFLOP/s down to 0.9), and 2.5 us a
+  // tile to start and 9.5 us per 256 rows to write its sums, 28 us with reading them where there are several chunks;
+  // and every part is read once more at the end of the call (4 TB/s).  The mean of all tokens and of an eighth of them masked, as in
+  // choose_chunk.  Fitted to 80 sizes, T = 257 .. 16384, H_s = 256 .. 4096, each with up to 16 tiles and splits (product and
+  // gradh_finish): 3.3 % behind the best one of each on average (with 1.48, 1.15, 22 us and all tokens alone 5.1 %).  T = 4096,
+  // H_s = 1024, V = 151936 128 rows x 2 parts 1123 us a call, 256 x 4 1213; T = 256 128 x 32 119 us, 256 x 32, which is half of the
+  // workgroups, 141.
   const int steps_first = (int)(round_up(q.V < q.V_c ? q.V : q.V_c, 64) / 64);
   double least = 1e300;
   int sk = 1;
   for (int rows = call.lean ? 128 : 256; rows >= 64; rows -= 64) {
     if (q.w_hv_inplace && q.V > (1 << 23) && rows > 128) continue;              // (32-bit offsets: rows of 2 V bytes)
-    const double step = rows == 256 ? 1.48 : rows == 192 ? 1.15 : rows == 128 ? 0.85 : 0.6;
-    const double ends = 4. + rows / 256. * (q.V > q.V_c ? 22. : 11.);
-    const int64_t tiles = (int64_t)((q.H_s + rows - 1) / rows) * q.n_tt;
+    const double step = rows == 256 ? 1.54 : rows == 192 ? 1.17 : rows == 128 ? 0.85 : 0.6;
+    const double ends = 2.5 + rows / 256. * (q.V > q.V_c ? 28. : 9.5);
+    const int64_t h_tiles = (q.H_s + rows - 1) / rows, tiles = h_tiles * q.n_tt, masked_tiles = h_tiles * ((q.n_tt * 7 + 7) / 8);
+    auto rounds = [&](int64_t n) { return (double)((n + q.n_cu - 1) / q.n_cu); };
     for (int s = 1; s <= 32 && (s == 1 || q.V_c / s >= 512) && s <= steps_first; ++s) {
       if (call.lean && s > 1 && s * tiles > q.n_cu) break;
-      const double t = (double)((tiles * s + q.n_cu - 1) / q.n_cu) * ((steps_first + s - 1) / s * step + ends) +
+      const double t = 0.5 * (rounds(tiles * s) + rounds(masked_tiles * s)) * ((steps_first + s - 1) / s * step + ends) +
                        (double)s * q.T * q.H_s * 1e-6 * q.V_c / q.V;
       if (t < least) { least = t; q.gh_rows = rows; sk = s; }
     }
@@ -488,6 +492,17 @@ kd_status kd_loss_plan_loop(const kd_loss_params* params, int32_t* loop) {
   Layout L{};
   plan(params, q, L, true);
   *loop = q.strip;
+  return KD_OK;
+}
+
+kd_status kd_loss_plan_grad_h(const kd_loss_params* params, int32_t* tile_rows, int32_t* parts) {
+  kd_status s = check_params(params);
+  if (s != KD_OK) return s;
+  Problem q{};
+  Layout L{};
+  plan(params, q, L, true);
+  if (tile_rows) *tile_rows = q.gh_rows;
+  if (parts) *parts = q.n_ksplit_h;
   return KD_OK;
 }
 

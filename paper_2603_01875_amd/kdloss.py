@@ -64,6 +64,8 @@ def lib():
         L.kd_loss_plan_info.restype = ctypes.c_int
         L.kd_loss_plan_loop.argtypes = [P, ctypes.POINTER(ctypes.c_int32)]
         L.kd_loss_plan_loop.restype = ctypes.c_int
+        L.kd_loss_plan_grad_h.argtypes = [P, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)]
+        L.kd_loss_plan_grad_h.restype = ctypes.c_int
         L.kd_loss_fwd_bwd.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_size_t, vp]
         L.kd_loss_fwd_bwd.restype = ctypes.c_int
         L.kd_loss_fwd_bwd_static.argtypes = [P, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
@@ -152,6 +154,15 @@ def kd_loss_plan_loop(params: KdLossParams):
     if st != KD_OK:
         raise KdLossError(st)
     return int(loop.value)
+
+
+def kd_loss_plan_grad_h(params: KdLossParams):
+    """(hidden rows of a tile of the grad_h_s product, parts that it splits the vocabulary into) for such a call."""
+    rows, parts = ctypes.c_int32(0), ctypes.c_int32(0)
+    st = lib().kd_loss_plan_grad_h(ctypes.byref(params), ctypes.byref(rows), ctypes.byref(parts))
+    if st != KD_OK:
+        raise KdLossError(st)
+    return int(rows.value), int(parts.value)
 
 
 PROF_STATS, PROF_ROWS, PROF_GRAD, PROF_GEMM_GRAD_W, PROF_GEMM_GRAD_H = range(5)
