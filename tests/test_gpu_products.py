@@ -1,5 +1,5 @@
-"""The backward products (csrc/kd_products.hip) at the edges of their tiles: hidden sizes around every tile height and the
-16-row blocks, vocabulary chunks around 256 columns and around a 64-column k-step, one token tile and several, both head
+"""The backward products (csrc/kd_products.hip) at the edges of their tiles: hidden sizes around every tile height of grad_W_s and
+the 16-row blocks (grad_h_s takes its 64-row tile at these sizes; its others: test_gpu_product_tiles.py), vocabulary chunks around 256 columns and around a 64-column k-step, one token tile and several, both head
 orders, both gradient types, written and added to.  Against the fp64 oracle with the tolerances of the other parity tests."""
 import numpy as np
 import pytest
