@@ -232,7 +232,7 @@ __device__ __forceinline__ void merge_parts(float (&v)[NV], float* lds) {
 // Merge the partial statistics of one (compacted) token; write log-sum-exps and, for FKL / RKL, the
 // row loss.
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind, float c, int strip,
+__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind, float c, float least,
                                                      f32x4* rowinfo, float* row_loss, float* akl) {
   __shared__ float lds[NT / 64 * 4 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
@@ -283,8 +283,9 @@ __global__ __launch_bounds__(NT) void combine_kernel(const float* partials, cons
     const float ltmax = (float)((double)Mt - Ltd);
     akl[AKL_FKL * T_pad + t] = (float)(0.6931471805599453 * fkl);
     akl[AKL_RKL * T_pad + t] = (float)(0.6931471805599453 * rkl);
-    akl[AKL_LO * T_pad + t] = strip ? 0.f : ltmax - 40.f;
-    akl[AKL_HI * T_pad + t] = ltmax + 1.0e-3f;         // above every entry: mass 0
+    // (one part a range: the strip loop, whose grid may start higher: less than 1 - mu lies below `least`)
+    akl[AKL_LO * T_pad + t] = per_split == 1 ? 0.f : ltmax - 40.f;
+    akl[AKL_HI * T_pad + t] = per_split == 1 ? fmaxf(ltmax - 40.f, least) : ltmax + 1.0e-3f;         // (1e-3: above every entry)
     akl[AKL_LTMAX * T_pad + t] = ltmax;
     akl[AKL_WR * T_pad + t] = 0.f;
   }
@@ -351,9 +352,9 @@ __global__ __launch_bounds__(NT) void akl_bins_combine_kernel(const float* parti
     if (!found && above + m[k] > mu) { bin = (float)k; found = true; }
     if (!found) above += m[k];
   }
-  const float lo = fmaf(bin, width, akl[AKL_LO * T_pad + t]);
+  const float lo = fmaf(bin, width, akl[AKL_LO * T_pad + t]), low = akl[AKL_HI * T_pad + t];
   akl[AKL_LO * T_pad + t] = lo;
-  akl[AKL_HI * T_pad + t] = akl_edge(lo + width, akl[AKL_LTMAX * T_pad + t]);
+  if (width == 1.f) akl[AKL_HI * T_pad + t] = akl_edge(lo + 1.f, low, akl_cell(low, akl[AKL_LTMAX * T_pad + t]));
   akl[AKL_WR * T_pad + t] = above;
 }
 
@@ -913,15 +914,19 @@ hipError_t launch_operands(const Problem& p, bool rowmap, bool student, bool tea
   return hipGetLastError();
 }
 
+// Where AKL's search on the strip loop starts at the lowest: entries below log2((1 - mu) / V) hold less than 1 - mu (one more for
+// the rounding of the sums).
+static float akl_least(const Problem& p) { return p.kind == 6 ? std::log2((1.f - p.beta) / (float)p.V) - 1.f : 0.f; }
+
 hipError_t launch_combine(const Problem& p, hipStream_t st) {
   if (many_parts(p))
     hipLaunchKernelGGL((combine_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
                        p.parts, p.T_pad,
-                       p.kind, 1.4426950408889634f / p.tau, p.strip, (f32x4*)p.rowinfo, p.row_loss, p.akl);
+                       p.kind, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
   else
     hipLaunchKernelGGL((combine_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
                        p.parts, p.T_pad,
-                       p.kind, 1.4426950408889634f / p.tau, p.strip, (f32x4*)p.rowinfo, p.row_loss, p.akl);
+                       p.kind, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
   return hipGetLastError();
 }
 

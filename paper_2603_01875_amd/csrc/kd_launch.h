@@ -83,11 +83,12 @@ hipError_t launch_combine(const Problem& p, hipStream_t st);
 hipError_t launch_rows(const Problem& p, hipStream_t st);
 hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st);      // one search pass and its merge
 hipError_t launch_akl_weights(const Problem& p, hipStream_t st);
-// AKL's border lies on a grid of 17^4 cells, from 40 below a token's largest base-2 log-probability to 1e-3 above it: 4.8e-4 each.
+// AKL's border lies on a grid of cells between a lowest base-2 log-probability and 1e-3 above a token's largest one: 17^4 of them from
+// 40 below the largest on the eight-wave loop (4.8e-4 each), 44^3 from wherever less than 1 - mu can lie below on the strip loop
+// (4.7e-4 at most, 1e-5 for a flat teacher).
 constexpr int kAklThresholds = 16;     // eight-wave loop: four passes, 17-fold narrowing each (the kernels' AKL_K)
 constexpr int kAklBins = 44;           // strip loop: three passes by bins of 44^2, 44 and 1 cells
-constexpr int kAklCells = 17 * 17 * 17 * 17;
-static_assert(kAklBins * kAklBins * kAklBins >= kAklCells, "three passes reach a cell");
+constexpr int kAklCells = kAklBins * kAklBins * kAklBins;
 inline int akl_search_passes(bool strip) { return strip ? 3 : 4; }
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st);
 // ... and, for the backward pass, h_s of the compacted tokens transposed and packed for grad_W_s, from the caller's array

@@ -243,17 +243,17 @@ constexpr float LN2 = 0.6931471805599453f;
 enum { AKL_FKL = 0, AKL_RKL = 1,   // the token's forward / reverse KL
        AKL_LO = 2, AKL_HI = 3,     // search interval of the head threshold (base-2 teacher log-probability):
                                    // mass{lt >= LO} > mu >= mass{lt >= HI}
-                                   // (strip loop: LO as the number of its cell of the grid, HI only behind the search)
+                                   // (strip loop, during the search: LO as the number of its cell, HI the grid's lower end)
        AKL_LTMAX = 4,              // the largest teacher log-probability of the token
        AKL_WR = 5,                 // weight of the reverse KL (the forward KL has 1 - that)
                                    // (strip loop, between search passes: the mass above the interval)
        AKL_ROWS = 6 };
 constexpr int AKL_K = kAklThresholds;   // thresholds tried per search pass of the eight-wave loop: 17-fold narrowing
 constexpr int AKL_BINS = kAklBins;      // bins of a search pass of the strip loop
-constexpr float AKL_CELL = 40.001f / kAklCells;
-// Edge j of the grid for a token whose largest log-probability is `ltmax`.  The search and its merge must both use this
-// expression: an entry lies in the cell between the two edges that it compares with, and in no other pass in another one.
-__device__ __forceinline__ float akl_edge(float j, float ltmax) { return fmaf(j, AKL_CELL, ltmax - 40.f); }
+// The strip loop's grid of a token, from `low` up: its cell, and edge j.  The search and its merge must both use these expressions:
+// an entry lies in the cell between the two edges that it compares with, and in no other pass in another one.
+__device__ __forceinline__ float akl_cell(float low, float ltmax) { return (ltmax + 1.0e-3f - low) * (1.f / kAklCells); }
+__device__ __forceinline__ float akl_edge(float j, float low, float cell) { return fmaf(j, cell, low); }
 constexpr float AKL_TOP_EPS = 1.0e-4f;   // entries this close (base-2 log) to the token's largest one count as "the top entry"
 
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -765,7 +765,7 @@ struct SearchEpi {
 // barrier.  Its four lanes may meet in one bin, and in no stated order, so the sums are whole numbers, of units of 2^-56: the same
 // in any order.  (An entry loses less than a unit: 2^-32 in all at 2^24 entries, where a sum in fp32 is 2^-25 off by its last addition
 // alone.)  A compare, a select and an addition for each of 16 thresholds
-// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes 20, and past the
+// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes 21, and past the
 // first pass hardly any entry lies in the interval.
 struct BinsEpi {
   static constexpr int NC = StripGeo::NC;
@@ -774,22 +774,26 @@ struct BinsEpi {
   static_assert(SMEM_BYTES <= 160 * 1024, "LDS of a gfx950 CU");
   static constexpr float FIRST = 0x1p24f, SECOND = 0x1p32f, UNIT = 0x1p-56f;       // upper and lower word of a mass in units
   StripGeo geo;
-  float Lt[NC], Top[NC], Lo[NC], off[NC];      // of the lane's tokens: log-sum-exp, largest log-probability, first cell; see column
+  float Lt[NC], low[NC], cell[NC];             // of the lane's tokens: log-sum-exp and grid; the first cell above the lowest bin,
+  float above[NC], first[NC], scale[NC];       // the lowest bin's lower edge, bins per unit of log-probability
   uint64_t* bins;          // of this lane's token of column 0
   // (The atomic is inline assembly: in front of the compiler's stands a wait for the loads into LDS, which it might alias
   // (4 % of the search).  The strip loop's prologue and its end order it against the bins' first and last accesses.)
   uint32_t bins_lds;
-  float c, width, scale;
-  __device__ BinsEpi(const LogitArgs& a, int tt, char* smem) : c(a.c), width(a.akl_width), scale(1.f / (a.akl_width * AKL_CELL)) {
+  float c, width;
+  __device__ BinsEpi(const LogitArgs& a, int tt, char* smem) : c(a.c), width(a.akl_width) {
     bins = (uint64_t*)(smem + BINS_AT) + geo.n(0);
     bins_lds = (uint32_t)(uintptr_t)(lds_void_t*)bins;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
       const int t = tt * BN + geo.n(j);
       Lt[j] = a.rowinfo[t][0];
-      Top[j] = a.akl[AKL_LTMAX * a.T_pad + t];
-      Lo[j] = a.akl[AKL_LO * a.T_pad + t];
-      off[j] = -fmaf(akl_edge(Lo[j], Top[j]), scale, 0.0625f);
+      low[j] = a.akl[AKL_HI * a.T_pad + t];
+      cell[j] = akl_cell(low[j], a.akl[AKL_LTMAX * a.T_pad + t]);
+      const float lo = a.akl[AKL_LO * a.T_pad + t];
+      first[j] = akl_edge(lo, low[j], cell[j]);
+      above[j] = lo + width;
+      scale[j] = 1.f / (width * cell[j]);
     }
     for (int k = geo.lane >> 4; k < AKL_BINS; k += 4)
 #pragma unroll
@@ -797,18 +801,16 @@ struct BinsEpi {
   }
   __device__ void begin_item(int, int, int) {}
   // T alone: the teacher's logits (entries that do not exist are NEG_BIG: below the interval).
-  // lt * scale + off is the entry's place in units of bins, less 1/16: more than its rounding in the narrowest bins (log-probabilities
-  // of size 64 and edges half an ulp off are 0.024 of a cell), so that its floor is the bin's number or one less, and the comparison
-  // with the edge above says which.
+  // k: floor of the entry's place in units of bins, less 1/4: more than its rounding in the narrowest bins (edges of size 24 are
+  // 1e-6 off, a tenth of the smallest cell), so it is the bin's number or one less, and the comparison with the edge above says which.
   template <class J, int NE>
   __device__ __forceinline__ void column(J, const float (&)[NE], const float (&T)[NE]) {
     constexpr int j = J::value;
-    const float above = Lo[j] + width;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
       const float lt = fmaf(T[e], c, -Lt[j]);
-      float k = floorf(fmaf(lt, scale, off[j]));
-      if (lt >= akl_edge(fmaf(k, width, above), Top[j])) k += 1.f;
+      float k = floorf(fmaf(lt - first[j], scale[j], -0.25f));
+      if (lt >= akl_edge(fmaf(k, width, above[j]), low[j], cell[j])) k += 1.f;
       if (k >= 0.f && k < (float)AKL_BINS) {
         const uint32_t at = bins_lds + (uint32_t)k * (BN * 8);
         const float p = fexp2(lt) * FIRST;

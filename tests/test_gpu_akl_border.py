@@ -1,8 +1,9 @@
-"""Where AKL's border between head and tail lies: on a grid of 17^4 cells that reaches from 40 below a token's largest base-2
-teacher log-probability to 1e-3 above it, one cell above the entry that passes mu.  Entries of one cell lie on one side,
-whichever loop makes the logits.  The teachers here have two entries closer than a cell at the border, each of several per cent
-of the mass, so a border on another grid shows in the token's loss; on rows whose entries stay clear of a cell's edge (fp32
-rounding of log-probabilities of size 40: 1e-5, a fiftieth of a cell) the split is known exactly."""
+"""Where AKL's border between head and tail lies: on a grid, one cell above the entry that passes mu.  Entries of one cell lie on one
+side.  The eight-wave loop's grid has 17^4 cells from 40 below a token's largest base-2 teacher log-probability to 1e-3 above
+it; the strip loop's 44^3, from log2((1 - mu) / V) - 1 where that is higher.  The teachers here have two entries close together at
+the border, each of several per cent of the mass, so a border on another grid shows in the token's loss; on rows whose entries
+stay clear of a cell's edge (fp32 rounding of log-probabilities: 1e-5 at 40, a fiftieth of a cell; 2e-6 at 16, a seventieth) the split
+is known exactly."""
 import numpy as np
 import pytest
 
@@ -13,11 +14,10 @@ from tests import gpu_util as G
 
 pytestmark = pytest.mark.gpu
 
-CELL = 40.001 / 17 ** 4
 ROWS, ENTRIES, MU = 60, 24, 0.5
 
 
-def _teachers(V, rng):
+def _teachers(V, rng, strip):
     """Logits [ROWS, V] as the sum of a coarse and a fine part / 1024, both bf16 values, and the split on the grid."""
     coarse, fine, head = np.zeros((ROWS, V)), np.zeros((ROWS, V)), np.zeros((ROWS, V), bool)
     bf16 = lambda x: I.round_to_bf16(np.asarray(x, np.float32)).astype(np.float64)
@@ -32,16 +32,17 @@ def _teachers(V, rng):
         p = np.exp(O.log_softmax(z[None], 1.0)[0])
         k = int((np.cumsum(p[order]) <= MU).sum())
         c[order[k]] = c[order[k - 1]]
-        f[order[k]] = bf16([f[order[k - 1]] - rng.uniform(0.02, 0.9) * CELL * np.log(2) * 1024])[0]
+        f[order[k]] = bf16([f[order[k - 1]] - rng.uniform(0.02, 0.9) * 4.8e-4 * np.log(2) * 1024])[0]
         z = c + f / 1024
         lt = O.log_softmax(z[None], 1.0)[0] / np.log(2)
         p = 2.0 ** lt
         order = np.argsort(-z)
-        at_cell = (lt - (lt.max() - 40)) / CELL
+        low = max(lt.max() - 40, np.log2((1 - MU) / V) - 1) if strip else lt.max() - 40
+        at_cell = (lt - low) / ((lt.max() + 1e-3 - low) / (44 ** 3 if strip else 17 ** 4))
         mass = np.cumsum(p[order])
         k = int((mass <= MU).sum())                    # entry k passes mu
-        near = np.abs(at_cell[at] - np.round(at_cell[at])).min() < 0.04 or np.abs(mass - MU).min() < 1e-3
-        if near or z[order[k - 1]] - z[order[k]] > CELL or k < 3:
+        near = np.abs(at_cell[at] - np.round(at_cell[at])).min() < 0.05 or np.abs(mass - MU).min() < 1e-3
+        if near or z[order[k - 1]] - z[order[k]] > 4.8e-4 or k < 3:
             continue
         cut = np.floor(at_cell)
         coarse[done], fine[done], head[done] = c, f, cut > cut[order[k]]
@@ -56,7 +57,7 @@ def test_border_lies_on_the_grid(loop, T, H_t, H_s, V, layout):
     import torch
     assert K.kd_loss_plan_loop(K.make_params(T, H_t, H_s, V, I.AKL, beta=MU, w_layout=layout)) == loop
     rng = np.random.default_rng(V)
-    coarse, fine, head = _teachers(V, rng)
+    coarse, fine, head = _teachers(V, rng, loop == 1)
     row = rng.permutation(T) % ROWS                    # token -> row of the teacher
     W_t, h_t = np.zeros((V, H_t)), np.zeros((T, H_t))
     W_t[:, 0:2 * ROWS:2], W_t[:, 1:2 * ROWS:2] = coarse.T, fine.T
