@@ -85,7 +85,13 @@ int64_t choose_chunk(const Problem& q, int64_t v_all, int64_t logit_k) {
   const int64_t step = 1536, most = (208ll << 20) / (2 * q.T_pad);      // a multiple of 192, 256 and 128
   if (most >= v_all) return v_all;
   const int tile_m = q.strip ? 192 : kd::kTileM, masked_tt = (q.n_tt * 7 + 7) / 8;
-  const int64_t gw_rows = kd::grad_W_tile(q.H_s), m_tiles = (q.H_s + gw_rows - 1) / gw_rows;
+  // (the grad_W_s tile that covers H_s cheapest, whatever the width; priced by each width's own, grad_W_tile, a twelfth of the widths
+  // below 4096 tokens change, for the worse as often as for the better: T = 1764, H = 576, V = 151936 1.59 -> 1.68 ms, T = 2880,
+  // H = 512 / 192 1.63 -> 1.57)
+  int64_t gw_rows = 256;
+  auto cover = [&](int64_t rows) { return (q.H_s + rows - 1) / rows * (rows + 48); };
+  for (int64_t rows : {192, 128}) if (cover(rows) < cover(gw_rows)) gw_rows = rows;
+  const int64_t m_tiles = (q.H_s + gw_rows - 1) / gw_rows;
   // multiply-adds of one workgroup: a logit tile, a grad_W_s tile, and what a chunk costs besides (three launches
   // and the sums of grad_h_s: 20 us and 8 bytes per element at 5 TB/s, at 2.6e12 a second)
   const double logit = (double)tile_m * kd::kTileN * (double)logit_k;

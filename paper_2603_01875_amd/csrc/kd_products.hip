@@ -340,7 +340,7 @@ __global__ void gradh_finish_kernel(const float* parts, int n_parts, int T, int 
 // launchers
 // ------------------------------------------------------------------------------------------
 hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st) {
-  const int nb = grad_W_tile(p.H_s) / 64;
+  const int nb = grad_W_tile(p.H_s, width, p.n_cu) / 64;
   GradWArgs a{};
   a.dz = (const char*)p.dz; a.hT = (const char*)p.h_sT;
   a.width = width; a.H_s = p.H_s;
