@@ -55,7 +55,7 @@ kd_status kd_loss_plan_grad_h(const kd_loss_params* params, int32_t* tile_rows, 
  * only keep the work alive.  Time the launch with events on `hip_stream`. */
 /* Compile-time configuration of the loaded library as text (tile shapes, ablation switch), and the ablation
  * switch alone: 0 for the product; anything else is a measurement build (-DKD_ABLATE=n, see the top of
- * kd_kernels.hip) whose results are wrong by design. */
+ * kd_logits.hpp) whose results are wrong by design. */
 const char* kd_build_info(void);
 int kd_build_ablation(void);
 

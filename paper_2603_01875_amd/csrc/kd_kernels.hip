@@ -69,7 +69,7 @@ KD_LOGIT_KERNEL void stats_kernel(const LogitArgs a) {
   StatsEpi<KIND> epi(a.c);
   TileEpi<StatsEpi<KIND>> drive(epi, a.t_scale);
   LoopClock clk(a);
-  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
   clk.stop(a);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
@@ -80,7 +80,7 @@ KD_LOGIT_KERNEL void rows_kernel(const LogitArgs a) {
   SplitWork<TF8, WHV> work(a);
   RowsEpi<KIND, TileGeo> epi(a, work.tt);
   TileEpi<RowsEpi<KIND, TileGeo>> drive(epi, a.t_scale);
-  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
 
@@ -96,7 +96,7 @@ KD_LOGIT_KERNEL void akl_search_kernel(const LogitArgs a) {
   TeacherSplitWork<WHV> work(a);
   SearchEpi<TileGeo> epi(a, work.tt);
   SearchTileEpi<SearchEpi<TileGeo>> drive(epi, 1.f);
-  tile_loop<1, LCfg, WHV ? 1 : 0, false>(work, drive, WHV ? a.V : a.H_t, WHV ? a.V : a.H_t, a.H_t, a.H_t, smem);
+  tile_loop<1, LCfg, WHV, false>(work, drive, WHV ? a.V : a.H_t, WHV ? a.V : a.H_t, a.H_t, a.H_t, smem);
   if (work.cnt > 0) epi.write(a, work.tt, work.split);
 }
 
@@ -106,7 +106,7 @@ KD_LOGIT_KERNEL void grad_kernel(const LogitArgs a) {
   ChunkWork<TF8, WHV> work(a);
   GradEpi<KIND, TileGeo> epi(a, smem);
   TileEpi<GradEpi<KIND, TileGeo>> drive(epi, a.t_scale);
-  tile_loop<2, LCfg, WHV ? 1 : 0, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
 }
 
 // ------------------------------------------------------------------------------------------

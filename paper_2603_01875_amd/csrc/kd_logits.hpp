@@ -100,7 +100,6 @@ __device__ __forceinline__ WorkItem logit_item(const LogitArgs& a, int vt, int t
     it.A0 = a.W_s; it.A1 = a.W_t;
   }
 #endif
-  it.ka_rows = it.kb_rows = 1 << 30;       // hidden sizes are whole k-steps: no k-row is ever missing
   it.a_rows = min(BM, a.v_end - m0);
   it.b_rows = min(BN, a.T - tt * BN);
   it.nk0 = a.H_s / BK;
@@ -764,9 +763,9 @@ struct SearchEpi {
 // AKL_BINS bins in LDS, [bin][token].  What lies above the interval is known from the pass before.  A token belongs to one wave: no
 // barrier.  Its four lanes may meet in one bin, and in no stated order, so the sums are whole numbers, of units of 2^-56: the same
 // in any order.  (An entry loses less than a unit: 2^-32 in all at 2^24 entries, where a sum in fp32 is 2^-25 off by its last addition
-// alone.)  A compare, a select and an addition for each of 16 thresholds
-// were 52 instructions per logit, 0.4 of the time that its MFMAs take and hidden by nothing; a bin takes 21, and past the
-// first pass hardly any entry lies in the interval.
+// alone.)
+// A compare, a select and an addition for each of 16 thresholds were 52 instructions per logit, 0.4 of the time that its MFMAs take
+// and hidden by nothing; a bin takes 21, and past the first pass hardly any entry lies in the interval.
 struct BinsEpi {
   static constexpr int NC = StripGeo::NC;
   static constexpr int BINS_AT = StripCfg::NST * StripCfg::STAGE_BYTES;      // in LDS, where other passes park student blocks

@@ -4,8 +4,8 @@
 // two backward products; paper Sec. 3.1-3.2) has the form
 //     D[m][n] = sum_k A[m][k] * B[n][k].
 // An operand is normally stored K-contiguous ("row m of A" is a contiguous run
-// of K bf16 values); the backward products also take one operand stored the
-// other way round (k-major, see tile_loop).  One workgroup owns a BM (M) x 256
+// of K bf16 values); heads kept as [H][V] are stored the other way round
+// (k-major, see tile_loop).  One workgroup owns a BM (M) x 256
 // (N) tile, its waves arranged 2 (M) x WN (N), each wave owning MI x NI MFMA
 // 32x32x16 blocks.  The M axis is the register axis of the MFMA result (a lane
 // holds 4 consecutive m for one n), the N axis the lane axis.  For the logit
@@ -104,7 +104,6 @@ struct WorkItem {
   const bf16_t *B0, *B1;   // first row of the tile in B
   int a_rows;              // valid rows of A in this tile (1..BM); rows beyond are clamped
   int b_rows;              // valid rows of B in this tile (1..BN)
-  int ka_rows, kb_rows;    // k-major operands only: k-rows that exist from the item's k origin on
   int nk0, nk1;            // k-steps of BK elements per phase (>= 1 for phases in use)
   int m0, n0;              // tile origin, passed through to the epilogue
   int aux;                 // free for the work map (e.g. split-K index)
@@ -148,16 +147,14 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 constexpr int SG_MFMA = 0x008, SG_VMEM = 0x010, SG_DSREAD = 0x100;
 
 //
-// k-major operands (KM bit 0: A, bit 1: B).  An operand may instead be stored with the
-// contraction index outermost: element (row r, k) at P[k * ld + r], P pointing at (k origin,
-// first row of the tile).  Its LDS tile is then [BK][R] (R = BM or BN rows, contiguous), the
-// 16-byte chunks of a k-row permuted by XOR with 4 (k mod 4), and a fragment is fetched by
-// two transposing reads (ds_read_b64_tr_b16): in every group of 16 lanes, lane i receives as
+// k-major A (AKM).  A may instead be stored with the contraction index outermost: element
+// (row r, k) at P[k * ld + r], P pointing at (k origin, first row of the tile).  Its LDS
+// tile is then [BK][BM] (rows contiguous), the 16-byte chunks of a k-row permuted by XOR
+// with 4 (k mod 4), and a fragment is fetched by two transposing reads (ds_read_b64_tr_b16): in every group of 16 lanes, lane i receives as
 // element j the (i mod 4)-th of the four values addressed by lane i/4 + 4j, so lane i
 // addresses k-row i/4 (+4 for the second read), rows 4 (i mod 4) .. +3 of its group's 16.
 // The four k-rows that half a wave reads at once then fall into four different 64-byte
-// bank groups.  Chunks past the valid rows and k-rows past ka_rows / kb_rows are clamped to
-// the last valid one (the other operand must be zero there).
+// bank groups.  Chunks past the valid rows are clamped to the last valid one.
 //
 // The transposing reads are written as inline assembly with hand-placed waits: issued through
 // the compiler's builtin, every one of them is preceded by a wait for ALL outstanding direct
@@ -186,20 +183,9 @@ __device__ __forceinline__ void km_read(KmFrag& f, uint32_t addr) {
                : "=&v"(f.lo), "=&v"(f.hi)
                : "v"(addr), "n"(OFF), "n"(OFF + ROWB4));
 }
-template <int N>
-__device__ __forceinline__ void km_wait(KmFrag (&f)[N]) {
-  static_assert(N >= 1 && N <= 4, "fragments per wave and operand");
-  if constexpr (N == 1)
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0].lo), "+v"(f[0].hi));
-  else if constexpr (N == 2)
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi));
-  else if constexpr (N == 3)
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi), "+v"(f[2].lo), "+v"(f[2].hi));
-  else
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi), "+v"(f[2].lo), "+v"(f[2].hi),
-                   "+v"(f[3].lo), "+v"(f[3].hi));
+// waits for the k-major fragments about to be multiplied (nothing for K-contiguous ones, whose reads the compiler tracks)
+__device__ __forceinline__ void km_wait(KmFrag (&f)[2]) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f[0].lo), "+v"(f[0].hi), "+v"(f[1].lo), "+v"(f[1].hi));
 }
 template <int N>
 __device__ __forceinline__ void km_wait(bf16x8 (&)[N]) {}
@@ -222,7 +208,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // matter.  ld*1 are then in bytes (= elements).
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-template <int NPHASE, class Cfg, int KM = 0, bool P1F8 = false, class Work, class Epi>
+template <int NPHASE, class Cfg, bool AKM = false, bool P1F8 = false, class Work, class Epi>
 __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
                                           const int lda0, const int lda1, const int ldb0, const int ldb1,
                                           char* smem) {
@@ -230,12 +216,11 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
   constexpr int A_LOADS = Cfg::A_LOADS, LOADS = Cfg::LOADS, LPS = Cfg::LOADS_PER_SUB;
   constexpr int A_STAGE_BYTES = Cfg::A_STAGE_BYTES, STAGE_BYTES = Cfg::STAGE_BYTES;
   constexpr int ROWB = Cfg::ROWB;
-  constexpr bool AKM = (KM & 1) != 0, BKM = (KM & 2) != 0;
   constexpr int BK = Cfg::BK;
-  constexpr int CPR_A = Cfg::BM / 8, CPR_B = BN / 8;                 // chunks per k-row
-  constexpr int KPL_A = Cfg::NT / CPR_A, KPL_B = Cfg::NT / CPR_B;    // k-rows per load instruction
-  static_assert(KM == 0 || (KPL_A % 4 == 0 && KPL_B % 4 == 0 && BK % 16 == 0), "k-major swizzle");
-  static_assert(!P1F8 || (KM == 0 && NPHASE == 2 && BK == 64 && Cfg::LOADS_BEFORE_BARRIER == LOADS),
+  constexpr int CPR = Cfg::BM / 8;             // chunks per k-row
+  constexpr int KPL = Cfg::NT / CPR;           // k-rows per load instruction
+  static_assert(!AKM || (MI == 2 && KPL % 4 == 0 && BK % 16 == 0), "k-major swizzle; km_wait's fragments");
+  static_assert(!P1F8 || (!AKM && NPHASE == 2 && BK == 64 && Cfg::LOADS_BEFORE_BARRIER == LOADS),
                 "fp8 phase: 128-byte rows, every load of a k-step issued before its barrier");
   typedef typename Cfg::Acc Acc;
 
@@ -258,52 +243,26 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
   bool more = true;
   WorkItem li = work.item(0);
   const char *l_pa, *l_pb;      // uniform: tile base + k offset, in bytes
-  int64_t l_step_a = ROWB, l_step_b = ROWB;   // bytes from one k-step to the next
+  int64_t l_step_a = ROWB;      // bytes of A from one k-step to the next (k-major: BK of its k-rows)
   uint32_t loff[LOADS];         // per lane: byte offset of its 16 bytes inside the k-slab
-  const int kma_row = tid / CPR_A, kma_c = (tid % CPR_A) ^ (4 * (kma_row & 3));
-  const int kmb_row = tid / CPR_B, kmb_c = (tid % CPR_B) ^ (4 * (kmb_row & 3));
-  // offsets of the k-major operands for the k-step that starts k_done elements into the phase
-  auto km_offsets = [&](int k_done) {
-    if (AKM) {
-      const uint32_t la = (uint32_t)(l_phase ? lda1 : lda0);
-      const int clim = (li.a_rows + 7) / 8 - 1, rem = li.ka_rows - k_done - 1;
-      const int c = kma_c < clim ? kma_c : clim;
-#pragma unroll
-      for (int j = 0; j < A_LOADS; ++j) {
-        int kr = kma_row + KPL_A * j;
-        kr = kr < rem ? kr : rem;
-        kr = kr > 0 ? kr : 0;
-        loff[j] = ((uint32_t)kr * la + c * 8) * 2;
-      }
-    }
-    if (BKM) {
-      const uint32_t lb = (uint32_t)(l_phase ? ldb1 : ldb0);
-      const int clim = (li.b_rows + 7) / 8 - 1, rem = li.kb_rows - k_done - 1;
-      const int c = kmb_c < clim ? kmb_c : clim;
-#pragma unroll
-      for (int j = 0; j < Cfg::B_LOADS; ++j) {
-        int kr = kmb_row + KPL_B * j;
-        kr = kr < rem ? kr : rem;
-        kr = kr > 0 ? kr : 0;
-        loff[A_LOADS + j] = ((uint32_t)kr * lb + c * 8) * 2;
-      }
-    }
-  };
+  const int km_row = tid / CPR, km_c = (tid % CPR) ^ (4 * (km_row & 3));
   auto set_cursor = [&]() {
     const uint32_t la = (uint32_t)(l_phase ? lda1 : lda0), lb = (uint32_t)(l_phase ? ldb1 : ldb0);
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
       const bool isA = j < A_LOADS;
-      if (isA ? AKM : BKM) continue;
+      if (AKM && isA) {
+        const int clim = (li.a_rows + 7) / 8 - 1;
+        loff[j] = ((uint32_t)(km_row + KPL * j) * la + (km_c < clim ? km_c : clim) * 8) * 2;
+        continue;
+      }
       int r = lrow + Cfg::ROWS_PER_LOAD * (isA ? j : j - A_LOADS);
       const int lim = isA ? li.a_rows : li.b_rows;
       r = r < lim ? r : lim - 1;
       const uint32_t es = (P1F8 && l_phase) ? 1 : 2;       // bytes per element
       loff[j] = (uint32_t)r * (isA ? la : lb) * es + lchunk * 16;
     }
-    if (KM) km_offsets(0);
     if (AKM) l_step_a = (int64_t)BK * 2 * la;
-    if (BKM) l_step_b = (int64_t)BK * 2 * lb;
     l_pa = (const char*)uniform(l_phase ? li.A1 : li.A0);
     l_pb = (const char*)uniform(l_phase ? li.B1 : li.B0);
     l_nk = l_phase ? li.nk1 : li.nk0;
@@ -322,12 +281,7 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
   };
   auto advance = [&]() {
     l_pa += AKM ? l_step_a : ROWB;
-    l_pb += BKM ? l_step_b : ROWB;
-    if (KM && l_k + 1 < l_nk) {
-      // the k-step now under the cursor runs past the last k-row that exists: clamp its rows
-      const int k_end = (l_k + 2) * BK;
-      if ((AKM && k_end > li.ka_rows) || (BKM && k_end > li.kb_rows)) km_offsets((l_k + 1) * BK);
-    }
+    l_pb += ROWB;
     if (++l_k == l_nk) {
       l_k = 0;
       if (NPHASE > 1 && l_phase == 0) {
@@ -347,7 +301,7 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
         l_phase = NPHASE - 1;
         l_k = l_nk - 1;
         l_pa -= AKM ? l_step_a : ROWB;
-        l_pb -= BKM ? l_step_b : ROWB;
+        l_pb -= ROWB;
       }
     }
   };
@@ -368,21 +322,18 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
 #pragma unroll
     for (int j = 0; j < 2; ++j) fk8[sb][j] = ((4 * sb + 2 * (lane >> 5) + j) ^ fsw) << 4;
 
-  // k-major fragments: byte offset of the lane's first transposing read of sub-step 0
-  int kma_f[MI], kmb_f[NI];
+  // k-major fragments of A: byte offset of the lane's first transposing read of sub-step 0
+  int km_f[MI];
   {
     const int g = lane >> 4, r = lane & 15;
     const int sw = 4 * (r >> 2), low = 2 * (g & 1) + ((r & 3) >> 1), kr = 8 * (g >> 1) + (r >> 2);
 #pragma unroll
     for (int mt = 0; mt < MI; ++mt)
-      kma_f[mt] = kr * (2 * Cfg::BM) + ((((wm * 32 * MI + mt * 32) / 8) ^ sw) + low) * 16 + (r & 1) * 8;
-#pragma unroll
-    for (int nt = 0; nt < NI; ++nt)
-      kmb_f[nt] = A_STAGE_BYTES + kr * (2 * BN) + ((((wn * 32 * NI + nt * 32) / 8) ^ sw) + low) * 16 + (r & 1) * 8;
+      km_f[mt] = kr * (2 * Cfg::BM) + ((((wm * 32 * MI + mt * 32) / 8) ^ sw) + low) * 16 + (r & 1) * 8;
   }
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_void_t*)smem;   // LDS byte address of stage 0
   typedef typename FragT<AKM>::type AFrag;
-  typedef typename FragT<BKM>::type BFrag;
+  typedef bf16x8 BFrag;
 
   Acc acc0, acc1;
   Cfg::zero(acc0);
@@ -398,14 +349,11 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
     const uint32_t lbase = lds0 + st * STAGE_BYTES;
 #pragma unroll
     for (int mt = 0; mt < MI; ++mt) {
-      if constexpr (AKM) km_read<ks * 16 * (2 * Cfg::BM), 4 * (2 * Cfg::BM)>(af[mt], lbase + kma_f[mt]);
+      if constexpr (AKM) km_read<ks * 16 * (2 * Cfg::BM), 4 * (2 * Cfg::BM)>(af[mt], lbase + km_f[mt]);
       else af[mt] = *(const bf16x8*)(base + a_base + mt * 32 * ROWB + fk[ks]);
     }
 #pragma unroll
-    for (int nt = 0; nt < NI; ++nt) {
-      if constexpr (BKM) km_read<ks * 16 * (2 * BN), 4 * (2 * BN)>(bfr[nt], lbase + kmb_f[nt]);
-      else bfr[nt] = *(const bf16x8*)(base + b_base + nt * 32 * ROWB + fk[ks]);
-    }
+    for (int nt = 0; nt < NI; ++nt) bfr[nt] = *(const bf16x8*)(base + b_base + nt * 32 * ROWB + fk[ks]);
   };
   auto read_frags8 = [&](int st, auto s_c, i32x8 (&af)[MI], i32x8 (&bfr)[NI]) {
     constexpr int sb = decltype(s_c)::value;
@@ -442,22 +390,16 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // waits for the k-major fragments about to be multiplied (no-op for K-contiguous operands,
-  // whose reads the compiler tracks itself)
-  auto wait_frags = [&](AFrag (&af)[MI], BFrag (&bfr)[NI]) {
-    km_wait(af);
-    km_wait(bfr);
-  };
   auto mma = [&](Acc& acc, const AFrag (&af)[MI], const BFrag (&bfr)[NI]) {
 #pragma unroll
     for (int mt = 0; mt < MI; ++mt)
 #pragma unroll
       for (int nt = 0; nt < NI; ++nt)
-        acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_op(af[mt]), frag_op(bfr[nt]), acc[mt][nt], 0, 0, 0);
+        acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_op(af[mt]), bfr[nt], acc[mt][nt], 0, 0, 0);
   };
   // Order inside one sub-step: fragment reads first (two per MFMA), then one load per MFMA.
   auto schedule_substep = [&]() {
-    constexpr int n_mfma = MI * NI, n_ds = (AKM ? 0 : MI) + (BKM ? 0 : NI);   // reads the scheduler sees
+    constexpr int n_mfma = MI * NI, n_ds = (AKM ? 0 : MI) + NI;   // reads the scheduler sees
     constexpr int ds_slots = (n_ds + 1) / 2 < n_mfma ? (n_ds + 1) / 2 : n_mfma - 1;
     constexpr int vm_slots = n_mfma - ds_slots < LPS ? n_mfma - ds_slots : (LPS > 0 ? LPS : 1);
     constexpr int vm_per = (LPS + vm_slots - 1) / vm_slots;
@@ -511,12 +453,12 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
       constexpr int ks = decltype(ks_c)::value;
       // even sub-steps multiply (fa0, fb0) and fetch into (fa1, fb1); odd ones the reverse
       if constexpr (ks % 2 == 0) {
-        wait_frags(fa0, fb0);
+        km_wait(fa0);
         read_frags(stage, IntC<ks + 1>{}, fa1, fb1);
         issue_loads(fill, ks * LPS < LOADS ? ks * LPS : LOADS, (ks + 1) * LPS < LOADS ? (ks + 1) * LPS : LOADS);
         mma(acc, fa0, fb0);
       } else {
-        wait_frags(fa1, fb1);
+        km_wait(fa1);
         read_frags(stage, IntC<ks + 1>{}, fa0, fb0);
         issue_loads(fill, ks * LPS < LOADS ? ks * LPS : LOADS, (ks + 1) * LPS < LOADS ? (ks + 1) * LPS : LOADS);
         mma(acc, fa1, fb1);
@@ -527,7 +469,7 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
     if (KD_LOOP_ABLATE & 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(Cfg::WAIT_STEADY) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(Cfg::WAIT_STEADY) : "memory");
     // last sub-step (KS-1, odd): multiplies (fa1, fb1), fetches sub-step 0 of the next k-step
-    wait_frags(fa1, fb1);
+    km_wait(fa1);
     issue_loads(fill, Cfg::LOADS_BEFORE_BARRIER, LOADS);
     if constexpr (NEXT8) read_frags8(next, IntC<0>{}, ga0, gb0);
     else read_frags(next, IntC<0>{}, fa0, fb0);

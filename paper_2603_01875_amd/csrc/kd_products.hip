@@ -225,7 +225,7 @@ struct GradHArgs {
   const char* W;           // the student's head at the chunk's first column
   float* out;              // part s at out + s * part_stride
   int64_t part_stride;
-  int width, H_s, ldz;
+  int width, H_s;
   int n_ht, n_split, ksteps;   // hidden tiles; parts of ksteps k-steps of 64 columns
   int accumulate;
   uint32_t lda, ldb;
@@ -370,7 +370,7 @@ hipError_t launch_grad_h(const Problem& p, int v0, int width, bool first, hipStr
   a.dz = (const char*)p.dz;
   a.W = (const char*)p.W_s + (p.w_hv_inplace ? (size_t)v0 * 2 : (size_t)v0 * p.K_s * 2);
   a.out = p.gh32; a.part_stride = (int64_t)p.T * p.H_s;
-  a.width = width; a.H_s = p.H_s; a.ldz = p.V_c;
+  a.width = width; a.H_s = p.H_s;
   a.n_ht = (p.H_s + 16 * mb - 1) / (16 * mb);
   a.ksteps = p.ksteps_h;
   a.n_split = ((width + 63) / 64 + a.ksteps - 1) / a.ksteps;       // every part has at least one k-step

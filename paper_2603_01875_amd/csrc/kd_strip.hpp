@@ -78,7 +78,7 @@ struct StripCfg : StripShape<12, 4> {
 
 // How A lies in memory and which eight k of a sub-step a lane multiplies.  The lanes of an MFMA operand hold one row each
 // and, by groups of 16, eight of the 32 k of a sub-step; which k is free as long as both operands agree.  In the natural
-// order group g has k = 8 g .. + 7.  In the order of dz (see dz_store in kd_common.hpp) it has 4 g .. + 3 and 16 + 4 g .. + 3,
+// order group g has k = 8 g .. + 7.  In the order of dz (dz_chunk in kd_common.hpp) it has 4 g .. + 3 and 16 + 4 g .. + 3,
 // which is what a lane of a finished logit tile holds.
 //   A_ROWS       rows of K-contiguous elements, natural order: one 16-byte LDS read per fragment
 //   A_ROWS_DZ    the same in the order of dz: two 8-byte reads

@@ -46,7 +46,6 @@ struct Work {
     it.A0 = it.A1 = a.A + (int64_t)mt * Cfg::BM * a.K;
     it.B0 = it.B1 = a.B + (int64_t)nt * BN * a.K;
     it.a_rows = Cfg::BM; it.b_rows = BN;
-    it.ka_rows = it.kb_rows = 1 << 30;
     it.nk0 = it.nk1 = a.K / Cfg::BK;
     it.m0 = mt * Cfg::BM; it.n0 = nt * BN; it.aux = 0;
     return it;
