@@ -53,9 +53,8 @@ kd_status kd_loss_plan_grad_h(const kd_loss_params* params, int32_t* tile_rows, 
  * bf16 values; the shader clock under this load depends on them, so pass values like real data).
  * Executes KD_PROBE_FLOP_PER_ITER * iters flop.  `sink` (device, 256 * 512 floats) receives sums that
  * only keep the work alive.  Time the launch with events on `hip_stream`. */
-/* Compile-time configuration of the loaded library as text (tile shapes, ablation switch), and the ablation
- * switch alone: 0 for the product; anything else is a measurement build (-DKD_ABLATE=n, see the top of
- * kd_logits.hpp) whose results are wrong by design. */
+/* Compile-time configuration of the loaded library as text (tile shapes).  kd_build_ablation: 0; anything else would be a
+ * measurement build of one's own whose results are wrong by design. */
 const char* kd_build_info(void);
 int kd_build_ablation(void);
 

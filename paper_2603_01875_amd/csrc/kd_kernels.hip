@@ -1002,8 +1002,7 @@ hipError_t launch_quantize_e4m3(const void* src, int src_f32, int64_t n, float i
 const char* build_info() {
   static_assert(StripCfg::BM == 192 && StripCfg::NT == 256 && StripCfg::NST == 3, "as named below");
   return "logit tile cfg (MI,NI,WN,BK,NST) = " KD_STR(KD_LOGIT_CFG) "; strip loop = 192 x 256 tiles, 4 waves, 3 stages"
-         "; ablation = " KD_STR(KD_ABLATE);
+         "; ablation = 0";
 }
-int build_ablation() { return KD_ABLATE; }
 
 }  // namespace kd

@@ -102,6 +102,5 @@ hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulat
 hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st);
 hipError_t launch_grad_h(const Problem& p, int v0, int width, bool first, hipStream_t st);
 hipError_t launch_gradh_finish(const Problem& p, hipStream_t st);
-const char* build_info();     // compile-time configuration of the kernels (tile shapes, ablation switch)
-int build_ablation();
+const char* build_info();     // compile-time configuration of the kernels (tile shapes)
 }  // namespace kd

@@ -8,20 +8,6 @@
 #define KD_LOGIT_CFG 2, 2, 4, 64, 3     // MI, NI, WN, BK, NST: 128 x 256 tile, 8 waves
 #endif
 
-// Ablation builds for measurements (never the product: RESULTS ARE WRONG when this is not 0).  They take one
-// cost out of the logit kernels so that its share of the time and of the shader clock can be read off:
-//   1  every workgroup loads the same head rows and the same token rows (all loads hit the L2: no traffic
-//      behind it), everything else unchanged
-//   2  the statistics epilogue (two exp2 per logit pair, running maxima) is replaced by a plain sum
-//   3  both
-#ifndef KD_ABLATE
-#define KD_ABLATE 0
-#endif
-
-#if KD_LOOP_ABLATE
-#error "KD_LOOP_ABLATE is for tile_loop_bench.hip only: the library's kernels must compute their products"
-#endif
-
 namespace kd {
 
 typedef TileCfg<KD_LOGIT_CFG> LCfg;   // logit tiles: two accumulators per tile
@@ -94,12 +80,6 @@ __device__ __forceinline__ WorkItem logit_item(const LogitArgs& a, int vt, int t
     it.A1 = a.W_t + (int64_t)m0 * a.H_t;
     it.B1 = a.h_t + (int64_t)tt * BN * a.H_t;
   }
-#if KD_ABLATE & 1
-  {   // same operand rows for every tile (the tile's coordinates below stay its own)
-    it.B0 = a.h_s; it.B1 = a.h_t;
-    it.A0 = a.W_s; it.A1 = a.W_t;
-  }
-#endif
   it.a_rows = min(BM, a.v_end - m0);
   it.b_rows = min(BN, a.T - tt * BN);
   it.nk0 = a.H_s / BK;
@@ -178,9 +158,6 @@ struct StripWork {
     it.out_rows = (it.a_rows + 63) / 64 * 64;        // zeros behind the chunk's last row: the k-steps of grad_h_s are whole
     it.m0 = m0;
     it.n0 = n0;
-#if KD_ABLATE & 1
-    m0 = n0 = 0;       // same operand rows for every tile (the tile's coordinates stay its own)
-#endif
     it.k0 = p->H_s; it.k1 = p->H_t;
     it.lda0 = 2 * (HV ? p->V : it.k0); it.ldb0 = 128 * it.k0;
     it.lda1 = 2 * (HV ? p->V : it.k1); it.ldb1 = 128 * it.k1;
@@ -379,11 +356,6 @@ struct StatsEpi {
   template <class J, int NE>
   __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
     constexpr int j = J::value;
-#if KD_ABLATE & 2
-#pragma unroll
-    for (int e = 0; e < NE; ++e) { S_t[j] += T[e]; S_s[j] += S[e]; }
-    return;
-#endif
     float tmax = NEG_BIG, smax = NEG_BIG;
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
@@ -460,11 +432,6 @@ struct StripStatsEpi {
   __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
     constexpr int j = J::value;
     float* const at = state + 16 * 8 * j;
-#if KD_ABLATE & 2
-#pragma unroll
-    for (int e = 0; e < NE; ++e) { at[1] += T[e]; at[3] += S[e]; }
-    return;
-#endif
     const f32x4 old = *(const f32x4*)at;
     float tmax = NEG_BIG, smax = NEG_BIG;
 #pragma unroll

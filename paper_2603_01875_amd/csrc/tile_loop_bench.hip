@@ -7,8 +7,6 @@
 //         -DCFG="4,2,4,32,4" tile_loop_bench.hip -o tile_loop_bench_256x256 && ./tile_loop_bench_256x256 153600 4096 4096
 //
 // CFG = MI, NI, WN, BK, NST (see TileCfg): tile = 64 MI x 256, 2 x WN waves, NST stages of BK elements.
-// -DKD_LOOP_ABLATE=n (bit 1: no global->LDS loads, 2: no LDS fragment reads, 4: no barrier; see kd_mfma.hpp)
-// takes one consumer out of the loop: what is left runs that much faster.
 // Operands are N(0,1) and N(0,0.02^2) values rounded to bf16, drawn on the device (the shader clock the chip
 // holds under MFMA load depends on the operand values).  The result is reduced to one number per lane and stored
 // only if it matches a value it cannot have: nothing is written, nothing is checked here.
@@ -128,8 +126,8 @@ int main(int argc, char** argv) {
   HIP_OK(hipMemcpy(hc, clocks, 16, hipMemcpyDeviceToHost));
   const double ghz = (double)hc[0] / (double)hc[1] * 0.1;
   const double tflops = 2.0 * M * N * K / ms / 1e9;
-  printf("loop ablation %d, tile cfg (MI,NI,WN,BK,NST) = %s: tile %d x %d, %d waves, %d KB LDS | M=%d N=%d K=%d: %.3f ms, %.0f TFLOP/s, shader clock %.2f GHz, MFMA busy %.2f\n",
-         KD_LOOP_ABLATE, STR(CFG), Cfg::BM, BN, Cfg::NT / 64, Cfg::SMEM_BYTES / 1024, M, N, K, ms, tflops, ghz,
+  printf("tile cfg (MI,NI,WN,BK,NST) = %s: tile %d x %d, %d waves, %d KB LDS | M=%d N=%d K=%d: %.3f ms, %.0f TFLOP/s, shader clock %.2f GHz, MFMA busy %.2f\n",
+         STR(CFG), Cfg::BM, BN, Cfg::NT / 64, Cfg::SMEM_BYTES / 1024, M, N, K, ms, tflops, ghz,
          tflops / (1024 * 1024 * ghz * 1e9 / 1e12));
   return 0;
 }
