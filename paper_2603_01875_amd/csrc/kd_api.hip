@@ -216,27 +216,36 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   const int64_t vc = p->vocab_chunk > 0 ? p->vocab_chunk : choose_chunk(q, v_all, logit_k);  // (the caller's: a multiple of 256)
   q.V_c = (int)(vc < v_all ? vc : v_all);
 
-  // Tile and split-K of the grad_h_s product: a chunk's tiles are rounds of n_cu workgroups, each of so many k-steps of 64
-  // columns; 1.54, 1.17, 0.85, 0.6 us a k-step for 256, 192, 128, 64 hidden rows (1.36 PFLOP/s down to 0.9), and 2.5 us a
-  // tile to start and 9.5 us per 256 rows to write its sums, 28 us with reading them where there are several chunks;
-  // and every part is read once more at the end of the call (4 TB/s).  The mean of all tokens and of an eighth of them masked, as in
-  // choose_chunk.  Fitted to 80 sizes, T = 257 .. 16384, H_s = 256 .. 4096, each with up to 16 tiles and splits (product and
-  // gradh_finish): 3.3 % behind the best one of each on average (with 1.48, 1.15, 22 us and all tokens alone 5.1 %).  T = 4096,
-  // H_s = 1024, V = 151936 128 rows x 2 parts 1123 us a call, 256 x 4 1213; T = 256 128 x 32 119 us, 256 x 32, which is half of the
-  // workgroups, 141.
-  const int steps_first = (int)(round_up(q.V < q.V_c ? q.V : q.V_c, 64) / 64);
+  // Tile and split-K of the grad_h_s product: the tiles of every chunk are rounds of n_cu workgroups, each of so many k-steps of 64
+  // columns (the last chunk has those of the first, in fewer parts); 1.47, 1.19, 0.85, 0.62 us a k-step for 256, 192, 128, 64 hidden
+  // rows (1.43 PFLOP/s down to 0.85); where the chunk of dz and of the head is more than the last-level cache keeps, the smaller tiles,
+  // which have less in flight, take longer; 1.7 us a tile to start and 8.5 us per 256 rows to write its sums, 24 us with reading
+  // them where there are several chunks; and every part is read once more at the end of the call (3.4 TB/s).  The mean of all tokens and
+  // of an eighth of them masked, as in choose_chunk.  Fitted to 516 sizes, T = 100 .. 16384, H_s = 128 .. 4096, both head orders, each
+  // with up to 18 tiles and splits (product and gradh_finish), and 180 more: 0.6 % behind the best one of each on average (2.5 % and more
+  // with the last chunk and the cache left out).  T = 4096, H_s = 1024, V = 151936 128 rows x 2 parts 1123 us a call, 256 x 4 1213; T = 1024 256 x 16 353 us,
+  // 128 x 8 372, 128 x 16 312; T = 512 256 x 32 142 us, 128 x 16 159.
+  const int first_width = (int)(q.V < q.V_c ? q.V : q.V_c), steps_first = (first_width + 63) / 64;
+  const int full_chunks = q.V / first_width, last_width = q.V - full_chunks * first_width;
   double least = 1e300;
   int sk = 1;
   for (int rows = call.lean ? 128 : 256; rows >= 64; rows -= 64) {
     if (q.w_hv_inplace && q.V > (1 << 23) && rows > 128) continue;              // (32-bit offsets: rows of 2 V bytes)
-    const double step = rows == 256 ? 1.54 : rows == 192 ? 1.17 : rows == 128 ? 0.85 : 0.6;
-    const double ends = 2.5 + rows / 256. * (q.V > q.V_c ? 28. : 9.5);
+    const int i = rows / 64 - 1;
+    const double in_cache[] = {0.62, 0.85, 1.19, 1.47}, from_memory[] = {0.82, 0.98, 1.26, 1.47};
+    const double ends = 1.7 + rows / 256. * (q.V > q.V_c ? 24. : 8.5);
     const int64_t h_tiles = (q.H_s + rows - 1) / rows, tiles = h_tiles * q.n_tt, masked_tiles = h_tiles * ((q.n_tt * 7 + 7) / 8);
     auto rounds = [&](int64_t n) { return (double)((n + q.n_cu - 1) / q.n_cu); };
     for (int s = 1; s <= 32 && (s == 1 || q.V_c / s >= 512) && s <= steps_first; ++s) {
       if (call.lean && s > 1 && s * tiles > q.n_cu) break;
-      const double t = 0.5 * (rounds(tiles * s) + rounds(masked_tiles * s)) * ((steps_first + s - 1) / s * step + ends) +
-                       (double)s * q.T * q.H_s * 1e-6 * q.V_c / q.V;
+      const int steps = (steps_first + s - 1) / s;
+      auto chunk = [&](int width) {
+        const int n = (width + 63) / 64, parts = (n + steps - 1) / steps;
+        const double step = 2. * width * (double)(q.T_pad + q.H_s) > 240e6 ? from_memory[i] : in_cache[i];
+        return 0.5 * (rounds(tiles * parts) + rounds(masked_tiles * parts)) * ((steps < n ? steps : n) * step + ends);
+      };
+      const double t = full_chunks * chunk(first_width) + (last_width > 0 ? chunk(last_width) : 0.) +
+                       (double)((steps_first + steps - 1) / steps) * q.T * q.H_s * 1.17e-6;
       if (t < least) { least = t; q.gh_rows = rows; sk = s; }
     }
   }

@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (1000, 300, 1104, 664, False, 0, K.BF16, 64, 1), (520, 520, 120, 2704, False, 1024, K.F32, 64, 2),
     (8192, 300, 968, 2296, False, 256, K.F32, 128, 1), (4096, 513, 576, 2720, False, 0, K.BF16, 128, 3),
-    (8192, 257, 1048, 2952, False, 256, K.BF16, 192, 1), (8192, 300, 272, 3672, False, 0, K.F32, 192, 4),
+    (8192, 257, 1048, 2952, False, 256, K.BF16, 192, 1), (7728, 300, 272, 3752, False, 0, K.F32, 192, 4),
     (16384, 300, 928, 2328, False, 0, K.BF16, 256, 1), (32768, 300, 392, 2264, False, 1024, K.F32, 256, 1),
-    (3000, 513, 2040, 31992, False, 0, K.BF16, 256, 5), (4622, 513, 848, 19360, False, 8192, K.F32, 256, 3),
+    (3000, 513, 2040, 31992, False, 0, K.BF16, 256, 5), (5406, 513, 392, 13984, False, 8192, K.F32, 256, 5),
     (520, 300, 64, 384, True, 0, K.BF16, 64, 1), (300, 300, 320, 2624, True, 1024, K.F32, 64, 2),
     (8192, 300, 1024, 1728, True, 1024, K.BF16, 128, 1), (4096, 513, 576, 2368, True, 0, K.F32, 128, 3),
     (16384, 300, 704, 1088, True, 256, K.F32, 192, 1), (8192, 257, 576, 3264, True, 0, K.BF16, 192, 2),
