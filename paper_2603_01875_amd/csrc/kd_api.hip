@@ -64,8 +64,9 @@ kd_status check_params(const kd_loss_params* p) {
 // but every chunk also re-reads and re-writes the fp32 sums of grad_h_s, so with many tokens a chunk of at least 8192
 // columns wins as long as the staging buffer stays within 512 MiB.
 //  - From 4096 tokens on a power of two within 128 MiB, at least 8192 columns.  (Nothing in the kernels asks for the line
-//    to lie at 4096: 24576 columns there, 201 MB, measured 11.72 against 12.25 ms without a mask.  What holds the width at
-//    16384 is the bound on the workspace of that size in tests/test_abi_host.py.)
+//    to lie at 4096, or for powers of two: 24576 columns there, 201 MB, measured 11.72 against 12.25 ms without a mask on an earlier
+//    state, and by 13824 columns the gradient kernel would walk 44 rounds for 47 at 3584 rows and V = 151936.  tests/test_abi_host.py
+//    holds that size to 16384 columns.)
 //  - Below, up to 208 MiB (201 MB still stays in the cache), and the width decides how full the last rounds of
 //    workgroups are: the candidates (multiples of the tile heights) are priced by the rounds of the gradient kernel,
 //    with all tokens and with an eighth of them masked, and of the grad_W_s product.  Measured steps: T = 3584 10.60 ms
@@ -125,22 +126,26 @@ struct CallPlan {
 // Whether the strip loop (192-row tiles) or the eight-wave loop (128-row tiles) makes the logit tiles.
 //  - A contracted element costs the strip loop 0.91 of what it costs the other, but its one wave per SIMD has nothing to
 //    hide a tile's epilogue behind: that costs as much as 100 more elements (FKL, RKL), 200 (the row pass of JSD, TVD and
-//    the skewed KLs) or 300 (AKL, whose search passes contract the teacher's elements alone; four on the eight-wave loop, three here).
+//    the skewed KLs) or 300 (AKL).
 //  - The gradient kernel walks whole tiles in rounds of n_cu workgroups; the passes before it even out over ranges of the
 //    vocabulary, down to a tile each.
-// Measured over 1178 sizes, T = 257 .. 16384 and V = 256 .. 151936 (steps, eight waves against strips): T = 512, H_t = 8192,
-// H_s = 512, V = 512 189 against 250 us; T = 4096, H = 2048 / 1024, V = 4096 292 against 323 us and V = 100000 6.00 against
-// 5.86 ms; T = 4096, H = 256 / 128, V = 151936 2.28 against 2.40 ms; T = 2048, H = 4096 / 1024, V = 151936 6.74 against
-// 6.23 ms.  Where the two are close the rule may take the slower one: 0.2 % is lost on average over these sizes, 7 % at
-// most.  A forward pass alone takes the same loop (0.5 % on average; the few calls with more than 10 % run one or two rounds
-// of workgroups, which its ranges fill unevenly).
+// The constants are from 1178 sizes on an earlier state of the strip loop, which has since become 6 % faster.  Steps of the present
+// state (eight waves against strips): T = 512, H_t = 8192, H_s = 512, V = 512 183 against 230 us; T = 4096, H = 256 / 128,
+// V = 151936 2.03 against 2.25 ms; T = 2048, H = 2048 / 1024, V = 4096 170 against 192 us and V = 100000 2.93 against 2.71 ms; T = 4096,
+// H = 4096 / 1024, V = 151936 12.5 against 11.8 ms.  Over 60 random sizes, T = 257 .. 16384, V = 256 .. 151936, every kind but AKL, 0.7 % is
+// lost against the faster loop of each, 6.5 % at most (one loop for all of them: 3.5 % and 3.8 %); over 24 with [H][V] heads
+// 0.3 %, 3.1 % at most.
+// AKL's line lies too far to the eight-wave side: its 300 and its mean over seven passes are from when its search was four passes of
+// compares on both loops.  By bins (three passes here) strips are ahead wherever V is large, down to H_t = 320: over 30 sizes the rule loses
+// 12 %, up to 33 % (T = 735, H = 2304 / 192, V = 151936 4.11 against 3.10 ms); strips for all of them would lose 1.2 %.
 // One token tile: the heads stream through once, nothing is shared, and the smaller tiles spread better over the CUs
-// (T = 256, V = 151936 1.16 against 1.24 ms).
+// (T = 1, V = 151936, JSD 1.28 against 1.44 ms; 24 sizes: 10 % on average, strips never ahead by more than 2 %, at T = 256 1.10
+// against 1.08).
 // `logit_k`: the contraction of one logit of all models, summed over the call's teachers.
 bool strips_ahead(const Problem& q, int n_teachers, int64_t logit_k) {
   if (q.n_tt < 2) return false;
   double k = (double)logit_k / n_teachers;
-  if (q.kind == KD_AKL) k -= q.K_s * 4. / 7.;                 // mean over its seven passes
+  if (q.kind == KD_AKL) k -= q.K_s * 4. / 7.;                 // mean over the seven passes of the eight-wave loop
   const double epilogue = q.kind == KD_AKL ? 300. : q.kind >= KD_JSD ? 200. : 100.;
   const int spread = q.kind == KD_AKL ? 6 : q.kind >= KD_JSD ? 2 : 1;
   auto rounds = [&](int rows) {

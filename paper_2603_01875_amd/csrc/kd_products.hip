@@ -8,8 +8,8 @@
 // Bound by the matrix pipe and the chip's power, like the logit passes, and, the shorter the contraction, by the start and
 // the stores of a tile, which one wave per SIMD does not hide.  Measured against the eight-wave loop that read both operands
 // through the LDS and dz as [T][V_c] (us a chunk; T tokens x columns x H_s): grad_W_s 32768 x 8192 x 4096 1686 -> 1511 (1.45
-// PFLOP/s), 3584 x 16384 x 1024 111 -> 101, 256 x 151936 x 1024 224 -> 158; grad_h_s 32768 x 8192 x 4096 1866 -> 1674,
-// 7424 x 8192 x 2048 238 -> 211, 3584 x 16384 x 1024 118 -> 122.
+// PFLOP/s), 3584 x 16384 x 1024 111 -> 98, 256 x 151936 x 1024 224 -> 158; grad_h_s 32768 x 8192 x 4096 1866 -> 1674,
+// 7424 x 8192 x 2048 238 -> 211, 3584 x 151936 x 1024, a call in ten chunks, 1.18 ms (1.24 with 256 rows x 4 parts).
 #include "kd_common.hpp"
 
 namespace kd {
