@@ -71,7 +71,7 @@ typedef enum {
  *                 g = sum |p_t - p_s| over the part (1/2 each if both vanish).  mu is passed in `beta`
  *                 (0 < mu < 1; the cited method uses 1/2).  The weights are constants for the gradient.
  *                 The head boundary is found by a search over teacher log-probabilities to within 5e-4
- *                 (base 2): entries that close to the boundary may fall on either side.  Costs four
+ *                 (base 2): entries that close to the boundary may fall on either side.  Costs two to four
  *                 more passes over the teacher logits and one more over both; not with the fp8 teacher. */
 typedef enum { KD_FKL = 0, KD_RKL = 1, KD_JSD = 2, KD_TVD = 3, KD_SKEW_FKL = 4, KD_SKEW_RKL = 5, KD_AKL = 6 } kd_kind;
 

@@ -24,7 +24,7 @@ inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 struct Layout {
-  size_t meta, rowmap, inv, row_loss, partials, h_sT, dz, gh32;
+  size_t meta, rowmap, inv, row_loss, partials, akl_fine, h_sT, dz, gh32;
   size_t prep_h_s, prep_W_s;                       // re-packed student operands (only when needed)
   size_t common;                                   // end of everything above: the same for every teacher
   size_t rowinfo, akl, prep_h_t, prep_W_t;         // per-teacher block (row statistics, re-packed operands)
@@ -271,6 +271,8 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   size_t partial_bytes = (size_t)parts * part_vals * q.T_pad * 4;
   const size_t bin_bytes = (size_t)q.n_split * kd::kAklBins * q.T_pad * 4;
   if (q.strip && q.kind == KD_AKL && partial_bytes < bin_bytes) partial_bytes = bin_bytes;
+  const size_t fine_at = partial_bytes;                  // behind the partials: the cells that AKL's row pass finds the border by
+  if (q.strip && q.kind == KD_AKL) partial_bytes += (size_t)q.T_pad * kd::kAklBins * 16;
   if (!with_backward) L.partials = take(partial_bytes);
   L.prep_h_t = L.prep_W_t = L.prep_h_s = L.prep_W_s = 0;
   const size_t h_rows = q.strip ? q.T_pad : q.T;         // the strip loop reads whole token tiles of packed rows
@@ -285,12 +287,13 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   } else {
     L.h_sT = L.dz = L.gh32 = off;
   }
+  L.akl_fine = L.partials + fine_at;
   // what belongs to one teacher comes last, so that everything above sits at the same offsets for
   // every teacher of a multi-teacher call and the teachers' blocks can lie side by side
   L.common = off;
   if (call.teacher_base > off) off = call.teacher_base;
   L.rowinfo = take((size_t)q.T_pad * 16);
-  L.akl = q.kind == KD_AKL ? take((size_t)q.T_pad * 6 * 4) : 0;
+  L.akl = q.kind == KD_AKL ? take((size_t)q.T_pad * kd::kAklRows * 4) : 0;
   const size_t t_es = q.t_fp8 ? 1 : 2;
   if (q.prep_ht) L.prep_h_t = take(h_rows * q.K_t * t_es);
   if (q.prep_Wt) L.prep_W_t = take((size_t)q.V * q.K_t * t_es);
@@ -304,6 +307,7 @@ void carve(Problem& q, const Layout& L, void* ws) {
   q.inv = reinterpret_cast<int*>(b + L.inv);
   q.rowinfo = reinterpret_cast<float*>(b + L.rowinfo);
   q.akl = q.kind == KD_AKL ? reinterpret_cast<float*>(b + L.akl) : nullptr;
+  q.akl_fine = reinterpret_cast<unsigned long long*>(b + L.akl_fine);
   q.row_loss = reinterpret_cast<float*>(b + L.row_loss);
   q.partials = reinterpret_cast<float*>(b + L.partials);
   q.h_sT = b + L.h_sT;

@@ -38,15 +38,23 @@ template <int KIND>
 KD_STRIP_KERNEL void rows_strip_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<false> work(a, meta_get(a.meta, META_N_SPLIT));
-  RowsEpi<KIND, StripGeo> epi(a, work.tt);
-  StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
-  strip_loop<2, true>(work, drive, smem);
-  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  if constexpr (KIND == 6) {
+    AklRowsEpi epi(a, work.tt, akl_crowded(a.akl, a.T_pad, work.tt), smem);
+    StripEpi<AklRowsEpi> drive(epi);
+    strip_loop<2, true>(work, drive, smem);
+    if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
+  } else {
+    RowsEpi<KIND, StripGeo> epi(a, work.tt);
+    StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
+    strip_loop<2, true>(work, drive, smem);
+    if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  }
 }
 
 KD_STRIP_KERNEL void akl_search_strip_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<false> work(a, meta_get(a.meta, META_N_SPLIT));
+  if (a.akl_width == 1.f && !akl_crowded(a.akl, a.T_pad, work.tt)) return;
   BinsEpi epi(a, work.tt, smem);
   StripEpi<BinsEpi> drive(epi);
   strip_loop<1, true>(work, drive, smem);
@@ -287,7 +295,7 @@ __global__ __launch_bounds__(NT) void combine_kernel(const float* partials, cons
     akl[AKL_LO * T_pad + t] = per_split == 1 ? 0.f : ltmax - 40.f;
     akl[AKL_HI * T_pad + t] = per_split == 1 ? fmaxf(ltmax - 40.f, least) : ltmax + 1.0e-3f;         // (1e-3: above every entry)
     akl[AKL_LTMAX * T_pad + t] = ltmax;
-    akl[AKL_WR * T_pad + t] = 0.f;
+    akl[AKL_WR * T_pad + t] = akl[AKL_CROWD * T_pad + t] = 0.f;
   }
 }
 
@@ -327,34 +335,45 @@ __global__ __launch_bounds__(NT) void akl_search_combine_kernel(const float* par
 }
 
 // The same for the strip loop's bins of `width` cells: the interval becomes the bin in which the mass from the top on passes mu, or
-// the lowest one.  Behind the last pass (bins of one cell) its upper edge is the threshold.
-template <int TX, int NT>
-__global__ __launch_bounds__(NT) void akl_bins_combine_kernel(const float* partials, const int* meta, int T_pad, float mu, float width,
-                                                              float* akl) {
-  __shared__ float lds[NT / 64 * AKL_BINS * TX];
-  const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
+// the lowest one.  The pass by bins of kAklBins cells is the last one for most: the row pass does the rest (AklRowsEpi), whose sums
+// are cleared here.  Where more entries than AKL_FEW lie in a token's interval (at most its mass over its lowest probability), its
+// token tile takes a third pass, by single cells, behind which the upper edge of the bin is the threshold.  (Two additions to
+// memory an entry: 1024 of them for every token cost about what the third pass does.)
+constexpr float AKL_FEW = 1024.f;
+// A thread sums one bin of one token over the parts, 32 bytes of each.  (With a thread's share of the parts in all bins, 82 registers of 44
+// sums were spilled: T = 2048 31 -> 13 us a merge.)
+__global__ __launch_bounds__(512) void akl_bins_combine_kernel(const float* partials, const int* meta, int T_pad, float mu, float width,
+                                                               float* akl, unsigned long long* fine) {
+  constexpr int TX = 8;
+  __shared__ float m[AKL_BINS][TX];
+  const int t0 = blockIdx.x * TX, tx = threadIdx.x % TX, bin_of = threadIdx.x / TX, t = t0 + tx;
   const int n_valid = meta[META_N_VALID], n_parts = meta[META_N_SPLIT];
-  if ((int)(blockIdx.x * TX) >= n_valid) return;
-  float m[AKL_BINS];
-#pragma unroll
-  for (int k = 0; k < AKL_BINS; ++k) m[k] = 0.f;
-  for (int p = g; p < n_parts; p += NT / TX) {
-    const float* q = partials + (int64_t)p * AKL_BINS * T_pad + t;
-#pragma unroll
-    for (int k = 0; k < AKL_BINS; ++k) m[k] += q[(int64_t)k * T_pad];
+  if (t0 >= n_valid) return;
+  if (width == 1.f && !akl_crowded(akl, T_pad, t0 / BN)) return;
+  if (width == (float)AKL_BINS)
+    for (int i = threadIdx.x; i < TX * AKL_BINS * 2; i += 512) fine[(int64_t)t0 * AKL_BINS * 2 + i] = 0;
+  if (bin_of < AKL_BINS) {
+    const float* const q = partials + (int64_t)bin_of * T_pad + t;
+    float sum = 0.f;
+#pragma unroll 16
+    for (int p = 0; p < n_parts; ++p) sum += q[(int64_t)p * AKL_BINS * T_pad];
+    m[bin_of][tx] = sum;
   }
-  merge_parts<TX, NT, AKL_BINS, MergeSum>(m, lds);
-  if (g != 0 || t >= n_valid) return;
-  float above = akl[AKL_WR * T_pad + t], bin = 0.f;
+  __syncthreads();
+  if (bin_of != 0 || t >= n_valid) return;
+  float above = akl[AKL_WR * T_pad + t], bin = 0.f, mass = m[0][tx];
   bool found = false;
 #pragma unroll
   for (int k = AKL_BINS - 1; k > 0; --k) {
-    if (!found && above + m[k] > mu) { bin = (float)k; found = true; }
-    if (!found) above += m[k];
+    const float mk = m[k][tx];
+    if (!found && above + mk > mu) { bin = (float)k; mass = mk; found = true; }
+    if (!found) above += mk;
   }
   const float lo = fmaf(bin, width, akl[AKL_LO * T_pad + t]), low = akl[AKL_HI * T_pad + t];
+  const float cell = akl_cell(low, akl[AKL_LTMAX * T_pad + t]);
   akl[AKL_LO * T_pad + t] = lo;
-  if (width == 1.f) akl[AKL_HI * T_pad + t] = akl_edge(lo + 1.f, low, akl_cell(low, akl[AKL_LTMAX * T_pad + t]));
+  if (width == (float)AKL_BINS) akl[AKL_CROWD * T_pad + t] = mass > AKL_FEW * fexp2(akl_edge(lo, low, cell)) ? 1.f : 0.f;
+  if (width == 1.f) akl[AKL_HI * T_pad + t] = akl_edge(lo + 1.f, low, cell);
   akl[AKL_WR * T_pad + t] = above;
 }
 
@@ -372,10 +391,12 @@ __device__ __forceinline__ void merge_row_sums(const float* partials, int n_part
   merge_parts<TX, NT, 2, MergeSum>(a, lds);
 }
 
-// AKL: gaps -> weights, row loss and the row term of the gradient (see GradEpi).
+// AKL: gaps -> weights, row loss and the row term of the gradient (see GradEpi).  With `fine`, the strip loop's row pass has left the
+// interval's entries by cells: the border is the cell in which the mass from the top on passes mu, or the lowest one, and the cells
+// above it are head.  (In a crowded tile they are all 0: the third search pass has found the border.)
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, const int* meta, int per_split, int T_pad,
-                                                         f32x4* rowinfo, float* row_loss, float* akl) {
+__global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, const int* meta, int per_split, int T_pad, float mu,
+                                                         const unsigned long long* fine, f32x4* rowinfo, float* row_loss, float* akl) {
   __shared__ float lds[NT / 64 * 2 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
   const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
@@ -383,6 +404,20 @@ __global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, 
   float a[2];
   merge_row_sums<TX, NT>(partials, n_parts, T_pad, t, g, lds, a);
   if (g != 0 || t >= n_valid) return;
+  if (fine) {
+    const unsigned long long* const own = fine + (int64_t)t * AKL_BINS * 2;
+    const float above = akl[AKL_WR * T_pad + t];
+    unsigned long long mass = 0, head = 0, tail = 0;
+    bool found = false;
+#pragma unroll 4
+    for (int k = AKL_BINS - 1; k >= 0; --k) {
+      mass += own[2 * k];
+      found = found || k == 0 || above + (float)mass * 0x1p-56f > mu;
+      (found ? tail : head) += own[2 * k + 1];
+    }
+    a[0] += (float)head * 0x1p-56f;
+    a[1] += (float)tail * 0x1p-56f;
+  }
   const float gt = a[1], tot = a[0] + a[1];
   const float wr = tot > 0.f ? gt / tot : 0.5f, wf = 1.f - wr;
   const float fkl = akl[AKL_FKL * T_pad + t], rkl = akl[AKL_RKL * T_pad + t];
@@ -786,7 +821,7 @@ hipError_t launch_rows(const Problem& p, hipStream_t st) {
     case 4: return KD_ROWS(4);
     case 6:
       return p.strip && p.w_hv_inplace ? launch_strip_hv_rows(p, a, grid, st)
-             : p.strip ? launch_big<rows_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a)
+             : p.strip ? launch_big<rows_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a)
              : p.w_hv_inplace ? launch_big<rows_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                               : launch_big<rows_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
     default: return KD_ROWS(5);
@@ -811,8 +846,8 @@ hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st) {
                             : launch_big<akl_search_kernel<false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
   if (e != hipSuccess) return e;
   if (p.strip) {
-    hipLaunchKernelGGL((akl_bins_combine_kernel<8, 512>), dim3(p.T_pad / 8), dim3(512), 0, st, p.partials, p.meta, p.T_pad, p.beta,
-                       a.akl_width, p.akl);
+    hipLaunchKernelGGL(akl_bins_combine_kernel, dim3(p.T_pad / 8), dim3(512), 0, st, p.partials, p.meta, p.T_pad, p.beta,
+                       a.akl_width, p.akl, p.akl_fine);
     return hipGetLastError();
   }
   if (many_parts(p))
@@ -827,11 +862,11 @@ hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st) {
 hipError_t launch_akl_weights(const Problem& p, hipStream_t st) {
   if (many_parts(p))
     hipLaunchKernelGGL((akl_weights_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad,
+                       p.parts, p.T_pad, p.beta, p.strip ? p.akl_fine : nullptr,
                        (f32x4*)p.rowinfo, p.row_loss, p.akl);
   else
     hipLaunchKernelGGL((akl_weights_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad,
+                       p.parts, p.T_pad, p.beta, p.strip ? p.akl_fine : nullptr,
                        (f32x4*)p.rowinfo, p.row_loss, p.akl);
   return hipGetLastError();
 }

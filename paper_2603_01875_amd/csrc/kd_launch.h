@@ -69,7 +69,8 @@ struct Problem {
   int* rowmap;         // [T_pad] compacted index -> token
   int* inv;            // [T] token -> compacted index or -1
   float* rowinfo;      // [T_pad][4]
-  float* akl;          // AKL only: [6][T_pad] per-token values between its passes (null otherwise)
+  float* akl;          // AKL only: [kAklRows][T_pad] per-token values between its passes (null otherwise)
+  unsigned long long* akl_fine;  // ... strip loop: [T_pad][kAklBins][2] sums of its row pass, behind the partials
   float* row_loss;     // [T_pad]
   float* partials;     // [n_split*parts][values of the pass][T_pad]
   void* h_sT;          // bf16, T_pad tokens x H_s rounded up to 16, packed (pack_columns)
@@ -91,8 +92,9 @@ hipError_t launch_akl_weights(const Problem& p, hipStream_t st);
 // 40 below the largest on the eight-wave loop (4.8e-4 each), 44^3 from wherever less than 1 - mu can lie below on the strip loop
 // (4.7e-4 at most, 1e-5 for a flat teacher).
 constexpr int kAklThresholds = 16;     // eight-wave loop: four passes, 17-fold narrowing each (the kernels' AKL_K)
-constexpr int kAklBins = 44;           // strip loop: three passes by bins of 44^2, 44 and 1 cells
+constexpr int kAklBins = 44;           // strip loop: passes by bins of 44^2 and 44 cells; the row pass (or a third) finds the cell
 constexpr int kAklCells = kAklBins * kAklBins * kAklBins;
+constexpr int kAklRows = 7;            // values kept per token (AKL_* in kd_logits.hpp)
 inline int akl_search_passes(bool strip) { return strip ? 3 : 4; }
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st);
 // ... and, for the backward pass, h_s of the compacted tokens transposed and packed for grad_W_s, from the caller's array

@@ -51,6 +51,7 @@ struct LogitArgs {
   float* partials;     // stats: [parts][5][T_pad];  jsd: [parts][2][T_pad]
   const f32x4* rowinfo;// [T_pad]: {lse2_t, lse2_s, mask/(n tau), row term}
   const float* akl;    // AKL only: [AKL_ROWS][T_pad] per-token values (see the AKL_* indices)
+  unsigned long long* akl_fine;  // ... [T_pad][AKL_BINS][2] sums of the row pass (strip loop)
   float akl_width;     // ... cells in a bin of this search pass (strip loop)
   bf16_t* dz;          // chunk of dL/dz_s, ldz columns, in the order of dz_chunk
   int ldz;
@@ -223,7 +224,8 @@ enum { AKL_FKL = 0, AKL_RKL = 1,   // the token's forward / reverse KL
        AKL_LTMAX = 4,              // the largest teacher log-probability of the token
        AKL_WR = 5,                 // weight of the reverse KL (the forward KL has 1 - that)
                                    // (strip loop, between search passes: the mass above the interval)
-       AKL_ROWS = 6 };
+       AKL_CROWD = 6,              // strip loop: many entries in the token's last interval
+       AKL_ROWS = kAklRows };
 constexpr int AKL_K = kAklThresholds;   // thresholds tried per search pass of the eight-wave loop: 17-fold narrowing
 constexpr int AKL_BINS = kAklBins;      // bins of a search pass of the strip loop
 // The strip loop's grid of a token, from `low` up: its cell, and edge j.  The search and its merge must both use these expressions:
@@ -793,6 +795,84 @@ struct BinsEpi {
   }
 };
 
+// AKL's row pass on the strip loop.  The search has left an interval of AKL_BINS cells per token, which hardly any entry lies in
+// (tens of 150000), so this pass finds the border's cell by itself, where a third search pass took a seventh of a step (T = 2048, H = 4096 /
+// 1024, V = 151936: a step 14.32 -> 12.47 ms, this pass 2.31 -> 2.54): the gaps above and below the interval are summed as ever, an entry inside adds its mass and its gap to its
+// cell in memory, and the merge takes the cells up to the border to the tail.  Those sums are whole numbers, as the search's are, so
+// their order does not matter.  What a token needs lies in LDS, [token][8], like the state of the statistics.
+// A token tile in which a token has too many entries in the interval (AKL_CROWD: equal logits would meet in one word) goes through a
+// third search pass first: its interval is empty here and AKL_HI the border.
+struct AklRowsEpi {
+  static constexpr int NC = StripGeo::NC;
+  StripGeo geo;
+  float* state;            // Lt, Ls, upper edge, first cell, lowest edge, largest log-probability, sums above and below; of the lane's
+                           // token of column 0
+  unsigned long long* fine;
+  float c;
+  __device__ AklRowsEpi(const LogitArgs& a, int tt, bool crowded, char* smem) : c(a.c) {
+    float* const all = (float*)(smem + StripCfg::STATE_AT);
+    float* const own = all + threadIdx.x * 8;                 // (thread i: token i of the tile, its wave's)
+    const int t = tt * BN + threadIdx.x;
+    const f32x4 ri = a.rowinfo[t];
+    const float hi = a.akl[AKL_HI * a.T_pad + t], lo = a.akl[AKL_LO * a.T_pad + t], ltmax = a.akl[AKL_LTMAX * a.T_pad + t];
+    own[0] = ri[0]; own[1] = ri[1];
+    own[2] = crowded ? fminf(hi, ltmax - AKL_TOP_EPS) : akl_edge(lo + AKL_BINS, hi, akl_cell(hi, ltmax));
+    own[3] = crowded ? 0.f : lo;
+    own[4] = crowded ? own[2] : hi;                           // (crowded: the first cell's lower edge is the border, too)
+    own[5] = ltmax;
+    own[6] = own[7] = 0.f;
+    state = all + geo.n(0) * 8;
+    fine = a.akl_fine + (int64_t)(tt * BN + geo.n(0)) * AKL_BINS * 2;
+  }
+  __device__ void begin_item(int, int, int) {}
+  static __device__ __forceinline__ unsigned long long units(float x) {        // of 2^-56
+    const float p = x * 0x1p24f;
+    const uint32_t hi = (uint32_t)p, lo = (uint32_t)((p - (float)hi) * 0x1p32f);
+    return (unsigned long long)hi << 32 | lo;
+  }
+  template <class J, int NE>
+  __device__ __forceinline__ void column(J, const float (&S)[NE], const float (&T)[NE]) {
+    constexpr int j = J::value;
+    float* const at = state + 16 * 8 * j;
+    const f32x4 own = *(const f32x4*)at;
+    const float low = at[4], ltmax = at[5], cell = akl_cell(low, ltmax), first = akl_edge(own[3], low, cell);
+    float a1 = 0.f, a2 = 0.f;
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
+      const float lt = fmaf(T[e], c, -own[0]), pt = fexp2(lt);
+      const float gap = fabsf(pt - fexp2(fmaf(S[e], c, -own[1])));
+      const bool above = lt >= own[2], below = lt < first;
+      a1 = fmaf((float)above, gap, a1);
+      a2 = fmaf((float)below, gap, a2);
+      asm volatile("" : "+v"(a1), "+v"(a2));                  // (or all the column's comparisons are kept for sums at its end)
+      // (One branch an entry and no other: past 1100 blocks the compiler stops inlining, and the loop's state goes to memory.)
+      if (!(above | below)) {
+        // (its cell's number or one less, and the comparison with the edge above says which: see BinsEpi)
+        float k = fmaxf(floorf(fmaf(lt - first, __builtin_amdgcn_rcpf(cell), -0.25f)), 0.f);
+        k = fminf(k + (float)(lt >= akl_edge(own[3] + k + 1.f, low, cell)), (float)(AKL_BINS - 1));
+        unsigned long long* const to = fine + (16 * j * AKL_BINS + (int)k) * 2;
+        const float head = (float)(lt >= ltmax - AKL_TOP_EPS) * gap;          // the top entry, whatever its mass, which counts in its cell
+        a1 += head;
+        __hip_atomic_fetch_add(to, units(pt), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(to + 1, units(gap - head), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    at[6] += quad_sum(a1);
+    at[7] += quad_sum(a2);
+  }
+  __device__ void write(const LogitArgs& a, char* smem, int tt, int split) {
+    const float* const own = (const float*)(smem + StripCfg::STATE_AT) + threadIdx.x * 8;
+    float* p = a.partials + (int64_t)split * 2 * a.T_pad + tt * BN + threadIdx.x;
+    p[0] = own[6];
+    p[a.T_pad] = own[7];
+  }
+};
+// Whether a token of tile tt is crowded (AklRowsEpi); every wave asks for itself.
+__device__ __forceinline__ bool akl_crowded(const float* akl, int T_pad, int tt) {
+  const f32x4 v = *(const f32x4*)(akl + (int64_t)AKL_CROWD * T_pad + tt * BN + 4 * (threadIdx.x & 63));
+  return __ballot(v[0] != 0.f || v[1] != 0.f || v[2] != 0.f || v[3] != 0.f) != 0;
+}
+
 // measurement aid, off unless asked for
 struct LoopClock {
   long long c0 = 0, r0 = 0;
@@ -828,6 +908,7 @@ inline LogitArgs make_logit_args(const Problem& p) {
   a.T_pad = p.T_pad;
   a.rowinfo = (const f32x4*)p.rowinfo;
   a.akl = p.akl;
+  a.akl_fine = p.akl_fine;
   return a;
 }
 // The strip loop's kernels for heads kept as [H][V] (kd_strip_hv.hip), by the divergence of `p`.

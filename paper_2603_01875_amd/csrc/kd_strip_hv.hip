@@ -27,10 +27,17 @@ template <int KIND>
 KD_STRIP_KERNEL void rows_strip_hv_kern(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<true> work(a, meta_get(a.meta, META_N_SPLIT));
-  RowsEpi<KIND, StripGeo> epi(a, work.tt);
-  StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
-  strip_loop<2, true, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
-  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  if constexpr (KIND == 6) {
+    AklRowsEpi epi(a, work.tt, akl_crowded(a.akl, a.T_pad, work.tt), smem);
+    StripEpi<AklRowsEpi> drive(epi);
+    strip_loop<2, true, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
+    if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
+  } else {
+    RowsEpi<KIND, StripGeo> epi(a, work.tt);
+    StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
+    strip_loop<2, true, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
+    if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  }
 }
 
 template <int KIND>
@@ -45,6 +52,7 @@ KD_STRIP_KERNEL void grad_strip_hv_kern(const LogitArgs a) {
 KD_STRIP_KERNEL void search_strip_hv_kern(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   StripWork<true> work(a, meta_get(a.meta, META_N_SPLIT));
+  if (a.akl_width == 1.f && !akl_crowded(a.akl, a.T_pad, work.tt)) return;
   BinsEpi epi(a, work.tt, smem);
   StripEpi<BinsEpi> drive(epi);
   strip_loop<1, true, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
@@ -67,7 +75,7 @@ hipError_t launch_strip_hv_rows(const Problem& p, const LogitArgs& a, int grid, 
     case 2: return KD_LAUNCH(rows_strip_hv_kern<2>);
     case 3: return KD_LAUNCH(rows_strip_hv_kern<3>);
     case 4: return KD_LAUNCH(rows_strip_hv_kern<4>);
-    case 6: return KD_LAUNCH(rows_strip_hv_kern<6>);
+    case 6: return KD_LAUNCH_STATE(rows_strip_hv_kern<6>);
     default: return KD_LAUNCH(rows_strip_hv_kern<5>);
   }
 }
