@@ -41,6 +41,8 @@ __device__ __forceinline__ u32x2 pack4(const f32x4& v) { return __builtin_bit_ca
 // nothing (a load gives 0), so rows and columns that do not exist take no branch.  (Behind one, all of the accumulator would
 // be copied from accumulation to vector registers at once.)
 constexpr uint32_t NOWHERE = 0xfffffff0u;
+// Cache policy of a store that nothing reads soon: it does not push out of the last-level cache what the next kernel reads.
+constexpr int STREAM = 2;
 // The lane, as something that has to be worked out again: offsets made from it are not kept from tile to tile (spills).
 __device__ __forceinline__ int fresh(int lane) {
   asm volatile("" : "+v"(lane));
@@ -74,6 +76,7 @@ struct GradWArgs {
   int n_vt, n_ht;          // tiles
   uint32_t lda, ldb;       // as in StripItem
   int b_blocks;
+  int stream;              // few tokens: the output is stored past the last-level cache
   const int* meta;
 };
 
@@ -139,12 +142,49 @@ struct GradWEpi {
     const int h = 16 * j + 4 * g;
     return it.n0 + 16 * NB * wave + h < a.H_s ? ((uint32_t)dz_column(i, n) * (uint32_t)a.ldo + h) * ES : NOWHERE;
   }
+  // QUADS: blocks (i, 0 .. 3); PAIRS: blocks (i, j), (i + 1, j), whose pieces change places between the halves of the wave (eight
+  // neighbouring columns per lane)
+  template <int CACHE = 0>
+  __device__ __forceinline__ void store_quad(const rsrc_t& r, const StripItem& it, int ln, int i, const f32x4 (&t)[4]) const {
+    const int g = ln >> 4, n = ln & 15;
+    uint32_t x[4][2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const u32x2 w = pack4(t[j]);
+      x[j][0] = w[0]; x[j][1] = w[1];
+    }
+    quad_transpose(x);
+    // A lane now has 32 bytes of one row.  Lanes n and n + 8 trade halves, so that a store writes eight rows' 128 bytes whole.
+    const bool up = n >= 8;
+    u32x4 low, high;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t x0 = x[k >> 1][k & 1], x1 = x[2 + (k >> 1)][k & 1];
+      const uint32_t got = __builtin_amdgcn_mov_dpp(up ? x0 : x1, 0x128, 0xf, 0xf, false);      // (row_ror:8)
+      low[k] = up ? got : x0;
+      high[k] = up ? x1 : got;
+    }
+    const int h = 16 * g + 8 * up;
+    const bool ok = it.n0 + 16 * NB * wave + h < a.H_s;
+    const uint32_t at = ((uint32_t)dz_column(i, n & 7) * (uint32_t)a.ldo + h) * ES, below = 4 * (uint32_t)a.ldo * ES;
+    __builtin_amdgcn_raw_buffer_store_b128(low, r, ok ? at : NOWHERE, 0, CACHE);
+    __builtin_amdgcn_raw_buffer_store_b128(high, r, ok ? at + below : NOWHERE, 0, CACHE);
+  }
+  __device__ __forceinline__ void store_pair(const rsrc_t& r, const StripItem& it, int ln, int i, const f32x4& t0, const f32x4& t1) const {
+    const int g = ln >> 4, n = ln & 15;
+    const u32x2 x = pack4(t0), y = pack4(t1);
+    auto r0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
+    auto r1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+    const int v = 16 * i + 16 * (g & 1) + 8 * (g >> 1);
+    const uint32_t at = it.m0 + v < a.width ? ((uint32_t)n * (uint32_t)a.ldo + v) * ES : NOWHERE;
+    __builtin_amdgcn_raw_buffer_store_b128(u32x4{r0[0], r1[0], r0[1], r1[1]}, r, at, 0, 0);
+  }
   __device__ __forceinline__ void start(const StripItem&, f32x4 (&T)[MB * NB]) const {
 #pragma unroll
     for (int i = 0; i < MB * NB; ++i) T[i] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   __device__ __forceinline__ void tile(const StripItem& it, f32x4 (&T)[MB * NB]) const {
-    const int ln = fresh(lane), g = ln >> 4, n = ln & 15;
+    const int ln = fresh(lane);
     if constexpr (ADD) {
       // four blocks at a time, the loads of the next four in flight
       f32x4 old[2][4];
@@ -170,15 +210,9 @@ struct GradWEpi {
         constexpr int j = decltype(jc)::value;
         const rsrc_t r = buffer(it, j);
         if constexpr (PAIRS) {
-          // two blocks' pieces change places between the halves of the wave: eight neighbouring columns per lane
           static_for<0, MB / 2>([&](auto ic) {
             constexpr int i = 2 * decltype(ic)::value;
-            const u32x2 x = pack4(T[MB * j + i]), y = pack4(T[MB * j + i + 1]);
-            auto r0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
-            auto r1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
-            const int v = 16 * i + 16 * (g & 1) + 8 * (g >> 1);
-            const uint32_t at = it.m0 + v < a.width ? ((uint32_t)n * (uint32_t)a.ldo + v) * ES : NOWHERE;
-            __builtin_amdgcn_raw_buffer_store_b128(u32x4{r0[0], r1[0], r0[1], r1[1]}, r, at, 0, 0);
+            store_pair(r, it, ln, i, T[MB * j + i], T[MB * j + i + 1]);
           });
         } else {
           static_for<0, MB>([&](auto ic) { store4<F32>(r, place(it, ln, decltype(ic)::value, j), T[MB * j + decltype(ic)::value]); });
@@ -189,17 +223,8 @@ struct GradWEpi {
       static_for<0, MB>([&](auto ic) {
         constexpr int i = decltype(ic)::value;
         if constexpr (QUADS) {
-          uint32_t x[4][2];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const u32x2 w = pack4(T[MB * (j % NB) + i]);
-            x[j][0] = w[0]; x[j][1] = w[1];
-          }
-          quad_transpose(x);
-          const int h = it.n0 + 16 * NB * wave + 16 * g;
-          const uint32_t at = ((uint32_t)dz_column(i, n) * (uint32_t)a.ldo + 16 * g) * ES;
-          __builtin_amdgcn_raw_buffer_store_b128(u32x4{x[0][0], x[0][1], x[1][0], x[1][1]}, r, h < a.H_s ? at : NOWHERE, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b128(u32x4{x[2][0], x[2][1], x[3][0], x[3][1]}, r, h + 8 < a.H_s ? at + 16 : NOWHERE, 0, 0);
+          const f32x4 t[4] = {T[i], T[MB * (1 % NB) + i], T[MB * (2 % NB) + i], T[MB * (3 % NB) + i]};
+          store_quad(r, it, ln, i, t);
         } else {
           static_for<0, NB>([&](auto jc) { store4<F32>(r, place(it, ln, i, decltype(jc)::value), T[MB * decltype(jc)::value + i]); });
         }
@@ -215,6 +240,134 @@ KD_STRIP_KERNEL void grad_w_kernel(const GradWArgs a) {
   GradWWork<NB> work(a);
   GradWEpi<NB, HV, F32, ADD> epi(a);
   strip_loop<1, false, StripShape<16, NB>, A_DZ, true, !HV>(work, epi, smem);
+}
+
+// Few tokens (one token tile): the contraction is at most 256 long and the output, V x H_s, is what takes the time, so the tile of the
+// strip loop, four k-steps and then 128 KiB to store, has nothing in flight for most of it: T = 256, H_s = 1024, V = 151936 160 us.  Here a wave keeps its 64 hidden rows of all the tokens in registers for good (128 of them),
+// and 32 columns of dz at a time go through the LDS, three such steps ahead; two workgroups per CU, so that the stores of one are
+// in flight under the other's products: 110 us; T = 100, H_s = 256, V = 8000 12 -> 6.  (Reading and writing take 75 at the rate of a large
+// copy; the stores alone measure 49, the loads alone 27, loads and products 62: the products' LDS reads, by all four waves, are next.)
+// Panels of 64 tokens without a valid one are left out.  Where the output is large it is stored past the last-level cache: grad_h_s behind
+// it 108 -> 92 us.
+struct GradWFew {
+  static constexpr int AHEAD = 3, NST = AHEAD + 1, PANELS = 4;
+  static constexpr int STAGE_BYTES = PANELS * 4096, SMEM_BYTES = NST * STAGE_BYTES;
+  static constexpr int SLOTS = 2 * kNumCU;           // workgroups that run at a time
+};
+// The fragments of 64 tokens (two sub-steps) x 32 columns: two transposing reads each, landed when this returns.
+template <int AT>
+__device__ __forceinline__ void few_read(s16x4 (&f)[2][2][2], uint32_t at0, uint32_t at1) {
+  asm volatile("ds_read_b64_tr_b16 %0, %8 offset:%10\n\tds_read_b64_tr_b16 %1, %9 offset:%10\n\t"
+               "ds_read_b64_tr_b16 %2, %8 offset:%11\n\tds_read_b64_tr_b16 %3, %9 offset:%11\n\t"
+               "ds_read_b64_tr_b16 %4, %8 offset:%12\n\tds_read_b64_tr_b16 %5, %9 offset:%12\n\t"
+               "ds_read_b64_tr_b16 %6, %8 offset:%13\n\tds_read_b64_tr_b16 %7, %9 offset:%13\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&v"(f[0][0][0]), "=&v"(f[0][0][1]), "=&v"(f[0][1][0]), "=&v"(f[0][1][1]), "=&v"(f[1][0][0]), "=&v"(f[1][0][1]),
+                 "=&v"(f[1][1][0]), "=&v"(f[1][1][1])
+               : "v"(at0), "v"(at1), "n"(AT), "n"(AT + 512), "n"(AT + 2048), "n"(AT + 2560));
+}
+template <bool HV, bool F32, bool ADD>
+__global__ __launch_bounds__(256, 2) void grad_w_few_kernel(const GradWArgs a) {
+  typedef GradWFew F;
+  typedef GradWEpi<4, HV, F32, ADD> Epi;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int lane = threadIdx.x & 63, wave = uniform(threadIdx.x >> 6);
+  // workgroup: 256 hidden rows x a range of the chunk's 32-column steps; those of one range side by side on an XCD
+  const int L = xcd_logical_id(blockIdx.x, gridDim.x), range = L / a.n_ht, n_steps = (a.width + 31) / 32;
+  const int first = (int)((int64_t)range * n_steps / a.n_vt), cnt = (int)((int64_t)(range + 1) * n_steps / a.n_vt) - first;
+  const int panels = min(max((meta_get(a.meta, META_N_VALID) + 63) / 64, 1), F::PANELS);
+  StripItem it{};
+  it.n0 = (L - range * a.n_ht) * 256;
+  const Epi epi(a);
+
+  // vector memory operations a step: the loads of a step, and what its results take
+  constexpr int STORES = ADD ? 16 : Epi::PAIRS || Epi::QUADS ? 4 : 8;
+  const rsrc_t ra = make_rsrc(a.dz, F::PANELS * a.lda);
+  uint32_t voff[F::PANELS];
+#pragma unroll
+  for (int p = 0; p < F::PANELS; ++p)          // (a token's chunks change places on the way, as in A_DZ of strip_loop)
+    voff[p] = p < panels ? p * a.lda + wave * 1024 + (lane >> 4) * 256 + ((lane & 15) ^ (4 * ((lane >> 4) & 1))) * 16 : NOWHERE;
+  auto issue = [&](int step) {                 // (past the end: the last step again, into a stage that nobody reads)
+    const int from = (first + min(step, cnt - 1)) * 4096;
+    char* const to = smem + (step % F::NST) * F::STAGE_BYTES + wave * 1024;
+#pragma unroll
+    for (int p = 0; p < F::PANELS; ++p) __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(to + p * 4096), 16, voff[p], from, 0, 0);
+  };
+  // h_s of the wave's rows: [block of 16][sub-step of 32 tokens]; blocks that do not exist are 0
+  const rsrc_t rb = make_rsrc(a.hT, (uint32_t)a.b_blocks * a.ldb);
+  bf16x8 B[4][2 * F::PANELS];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int s = 0; s < 2 * F::PANELS; ++s)
+      B[j][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rb, (uint32_t)(it.n0 / 16 + 4 * wave + j) * a.ldb + s * 1024 + lane * 16, 0, 0));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int s = 0; s < F::AHEAD; ++s) issue(s);
+
+  const int g = lane >> 4, c = lane & 3, t = 8 * (g & 1) + ((lane & 15) >> 2);
+  uint32_t fk[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+    fk[h] = (uint32_t)(uintptr_t)(lds_void_t*)smem + (g >> 1) * 1024 + (c >> 1) * 256 + ((t + 4 * h) ^ (4 * (c >> 1))) * 16 + (c & 1) * 8;
+  for (int step = 0; step < cnt; ++step) {
+    // The step has landed for every wave, and every wave has read the one before, whose stage is refilled.  Since its loads were issued
+    // AHEAD steps ago there have been those of AHEAD - 1 more and, past the first steps, AHEAD times the results.
+    if (step < F::AHEAD) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(F::PANELS * (F::AHEAD - 1)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(F::PANELS * (F::AHEAD - 1) + F::AHEAD * STORES) : "memory");
+    issue(step + F::AHEAD);
+    f32x4 T[2][4];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) T[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint32_t stage = (uint32_t)(step % F::NST) * F::STAGE_BYTES;
+    static_for<0, F::PANELS>([&](auto pc) {
+      constexpr int p = decltype(pc)::value;
+      if (p < panels) {
+        s16x4 f[2][2][2];                      // [sub-step][block of 16 columns][half]
+        few_read<4096 * p>(f, fk[0] + stage, fk[1] + stage);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const bf16x8 x = __builtin_bit_cast(bf16x8, __builtin_shufflevector(f[s][i][0], f[s][i][1], 0, 1, 2, 3, 4, 5, 6, 7));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              T[i][j] = HV ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, B[j][2 * p + s], T[i][j], 0, 0, 0)
+                           : __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[j][2 * p + s], x, T[i][j], 0, 0, 0);
+          }
+      }
+    });
+    it.m0 = (first + step) * 32;
+    if constexpr (ADD) {
+      f32x4 old[2][4];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) old[i][j] = load4<F32>(epi.buffer(it, j), epi.place(it, lane, i, j));
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) store4<F32>(epi.buffer(it, j), epi.place(it, lane, i, j), T[i][j] + old[i][j]);
+    } else if constexpr (Epi::QUADS) {
+      const rsrc_t r = epi.buffer(it, 0);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (a.stream) epi.template store_quad<STREAM>(r, it, lane, i, T[i]);
+        else epi.store_quad(r, it, lane, i, T[i]);
+      }
+    } else if constexpr (Epi::PAIRS) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) epi.store_pair(epi.buffer(it, j), it, lane, 0, T[0][j], T[1][j]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) store4<F32>(epi.buffer(it, j), epi.place(it, lane, i, j), T[i][j]);
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads issued past the end still target this workgroup's LDS
 }
 
 // ------------------------------------------------------------------------------------------
@@ -350,6 +503,20 @@ hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st) {
   a.lda = (uint32_t)p.V_c * 128; a.ldb = (uint32_t)p.T_pad * 32;
   a.b_blocks = (p.H_s + 15) / 16;
   a.meta = p.meta;
+  if (p.n_tt == 1) {
+    const int steps = (width + 31) / 32;
+    a.n_ht = (p.H_s + 255) / 256;
+    a.n_vt = GradWFew::SLOTS / a.n_ht < 1 ? 1 : GradWFew::SLOTS / a.n_ht;
+    if (a.n_vt > steps) a.n_vt = steps;
+    a.stream = (int64_t)width * p.H_s > (64 << 20);       // (128 MiB: half of the cache, which keeps dz and W_s for grad_h_s instead)
+#define KD_GF(HV, F32, ADD) launch_big<grad_w_few_kernel<HV, F32, ADD>>(a.n_vt * a.n_ht, 256, GradWFew::SMEM_BYTES, st, &a)
+    if (p.accumulate_grad_W)
+      return p.w_hv ? (p.grad_f32 ? KD_GF(true, true, true) : KD_GF(true, false, true))
+                    : (p.grad_f32 ? KD_GF(false, true, true) : KD_GF(false, false, true));
+    return p.w_hv ? (p.grad_f32 ? KD_GF(true, true, false) : KD_GF(true, false, false))
+                  : (p.grad_f32 ? KD_GF(false, true, false) : KD_GF(false, false, false));
+#undef KD_GF
+  }
   const int tiles = a.n_vt * a.n_ht, grid = tiles < p.n_cu ? tiles : p.n_cu;
 #define KD_GW3(N, HV, F32) (p.accumulate_grad_W ? launch_big<grad_w_kernel<N, HV, F32, true>>(grid, 256, StripShape<16, N>::SMEM_BYTES, st, &a) \
                                                : launch_big<grad_w_kernel<N, HV, F32, false>>(grid, 256, StripShape<16, N>::SMEM_BYTES, st, &a))
