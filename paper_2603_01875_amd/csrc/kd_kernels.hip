@@ -194,7 +194,7 @@ __device__ __forceinline__ void make_rowmap(const RowmapArgs& a) {
   if (tid == 0) {
     meta[META_N_VALID] = n;
     meta[META_N_TT] = n_tt;
-    meta[META_T_EFF] = n_tt * BN;
+    meta[META_T_EFF] = max((n + 63) / 64, 1) * 64;      // what grad_W_s contracts: whole k-steps (the rest of the tile is 0)
     meta[META_N_SPLIT] = (int)(s_best[0] & 0xffff);
     meta[META_G_SPLIT] = (int)(s_best[1] & 0xffff);
     meta[META_G_SPLIT_LAST] = (int)(s_best[2] & 0xffff);
