@@ -199,7 +199,6 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   // The strip loop takes bf16 operands (heads [V][K], in place or re-packed, or [K][V] in place with 24-bit strides).  It
   // reads the hidden states from a packed copy, so they are re-packed whether a mask is given or not.
   q.strip = !q.t_fp8 && !(q.w_hv_inplace && q.V >= (1 << 23)) && !call.lean && strips_ahead(q, call.n_teachers, logit_k);
-  q.parts = q.strip ? 1 : 4;
   q.n_vt = (q.V + kd::kTileM - 1) / kd::kTileM;
   // Vocabulary ranges of the statistics passes.  The device picks the actual number once it knows
   // how many token tiles survive the mask; this is the upper bound the buffers are sized for:
@@ -263,14 +262,9 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   L.rowmap = take((size_t)q.T_pad * 4);
   L.inv = take((size_t)q.T * 4);
   L.row_loss = take((size_t)q.T_pad * 4);
-  // partial sums per (vocabulary range, part of a workgroup, token): 5 statistics, 6 for AKL, whose
-  // search passes keep one sum per threshold or bin.  A strip range leaves one part, an eight-wave one four: what a lean plan
-  // needs (at least 32 parts, four for every two strips) holds the strip loop's up to 32 ranges and more, too.
-  const int part_vals = q.kind == KD_AKL ? kd::kAklThresholds : 5;
-  const int parts = 4 * (q.strip ? lean_split : q.n_split);
-  size_t partial_bytes = (size_t)parts * part_vals * q.T_pad * 4;
-  const size_t bin_bytes = (size_t)q.n_split * kd::kAklBins * q.T_pad * 4;
-  if (q.strip && q.kind == KD_AKL && partial_bytes < bin_bytes) partial_bytes = bin_bytes;
+  // partial sums per (vocabulary range, token): 5 statistics, 6 for AKL, whose search passes keep one sum per threshold or bin
+  const int part_vals = q.kind != KD_AKL ? 5 : q.strip ? kd::kAklBins : kd::kAklThresholds;
+  size_t partial_bytes = (size_t)q.n_split * part_vals * q.T_pad * 4;
   const size_t fine_at = partial_bytes;                  // behind the partials: the cells that AKL's row pass finds the border by
   if (q.strip && q.kind == KD_AKL) partial_bytes += (size_t)q.T_pad * kd::kAklBins * 16;
   if (!with_backward) L.partials = take(partial_bytes);

@@ -47,7 +47,7 @@ KD_STRIP_KERNEL void rows_strip_kernel(const LogitArgs a) {
     RowsEpi<KIND, StripGeo> epi(a, work.tt);
     StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
     strip_loop<2, true>(work, drive, smem);
-    if (work.cnt > 0) epi.write(a, work.tt, work.split);
+    if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
   }
 }
 
@@ -79,7 +79,7 @@ KD_LOGIT_KERNEL void stats_kernel(const LogitArgs a) {
   LoopClock clk(a);
   tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
   clk.stop(a);
-  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
 
 template <int KIND, bool TF8, bool WHV>
@@ -89,7 +89,7 @@ KD_LOGIT_KERNEL void rows_kernel(const LogitArgs a) {
   RowsEpi<KIND, TileGeo> epi(a, work.tt);
   TileEpi<RowsEpi<KIND, TileGeo>> drive(epi, a.t_scale);
   tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
-  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
 
 // (one accumulator: the driver gets the teacher's tile as the first one)
@@ -105,7 +105,7 @@ KD_LOGIT_KERNEL void akl_search_kernel(const LogitArgs a) {
   SearchEpi<TileGeo> epi(a, work.tt);
   SearchTileEpi<SearchEpi<TileGeo>> drive(epi, 1.f);
   tile_loop<1, LCfg, WHV, false>(work, drive, WHV ? a.V : a.H_t, WHV ? a.V : a.H_t, a.H_t, a.H_t, smem);
-  if (work.cnt > 0) epi.write(a, work.tt, work.split);
+  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
 
 template <int KIND, bool TF8, bool WHV>
@@ -201,12 +201,13 @@ __device__ __forceinline__ void make_rowmap(const RowmapArgs& a) {
   }
 }
 
-// Merging the partial sums.  Every part (one per vocabulary range in the strip loop, four in the eight-wave loop) leaves
-// its values as [part][value][T_pad], and with few tokens there are many parts (up to 1024 at T <= 256).  A merge is bound by the latency of its loads:
+// Merging the partial sums.  Every workgroup (one per token tile and vocabulary range) leaves its values as [range][value][T_pad], and
+// with few tokens there are many ranges (256 at T <= 256; the eight-wave loop's four lanes of a token put theirs
+// together first: a step of T = 200, H = 2048 / 512, V = 32000 148 -> 133 us, AKL at T = 150, H = 1024 / 512 347 -> 291).  A merge is bound by the latency of its loads:
 // one thread walking all the parts of a token took 658 us at T = 256 and 47 us at T = 4096.  So a workgroup owns TX
 // tokens and NT / TX threads share the parts of each: lanes run along the tokens (TX = 8: 32-byte runs, TX = 32:
 // whole lines), the rest of the lanes and the waves along the parts; partial results meet by shuffles, then through
-// LDS, in a fixed order.  Measured: combine_kernel 658 -> 23 us at T = 256, 47 -> 9 us at 128 parts, 6 us at the strip loop's 32 (T = 4096),
+// LDS, in a fixed order.  Measured: combine_kernel 658 -> 23 us at T = 256, 47 -> 9 us at 128 parts, 6 us at 32 (T = 4096),
 // one search merge of AKL 536 -> 15 us at T = 2048.
 struct MergeSum {
   static __device__ __forceinline__ float op(float a, float b) { return a + b; }
@@ -240,11 +241,11 @@ __device__ __forceinline__ void merge_parts(float (&v)[NV], float* lds) {
 // Merge the partial statistics of one (compacted) token; write log-sum-exps and, for FKL / RKL, the
 // row loss.
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind, float c, float least,
+__global__ __launch_bounds__(NT) void combine_kernel(const float* partials, const int* meta, int T_pad, int kind, int strip, float c, float least,
                                                      f32x4* rowinfo, float* row_loss, float* akl) {
   __shared__ float lds[NT / 64 * 4 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = meta[META_N_SPLIT];
   const int nv = kind == 6 ? 6 : 5;
   if ((int)(blockIdx.x * TX) >= n_valid && g > 0) return;     // a whole workgroup of padding rows
   if (t >= n_valid && g == 0) {   // padding rows: probabilities evaluate to 0, gradient scale 0
@@ -291,9 +292,9 @@ __global__ __launch_bounds__(NT) void combine_kernel(const float* partials, cons
     const float ltmax = (float)((double)Mt - Ltd);
     akl[AKL_FKL * T_pad + t] = (float)(0.6931471805599453 * fkl);
     akl[AKL_RKL * T_pad + t] = (float)(0.6931471805599453 * rkl);
-    // (one part a range: the strip loop, whose grid may start higher: less than 1 - mu lies below `least`)
-    akl[AKL_LO * T_pad + t] = per_split == 1 ? 0.f : ltmax - 40.f;
-    akl[AKL_HI * T_pad + t] = per_split == 1 ? fmaxf(ltmax - 40.f, least) : ltmax + 1.0e-3f;         // (1e-3: above every entry)
+    // (the strip loop's grid may start higher: less than 1 - mu lies below `least`)
+    akl[AKL_LO * T_pad + t] = strip ? 0.f : ltmax - 40.f;
+    akl[AKL_HI * T_pad + t] = strip ? fmaxf(ltmax - 40.f, least) : ltmax + 1.0e-3f;         // (1e-3: above every entry)
     akl[AKL_LTMAX * T_pad + t] = ltmax;
     akl[AKL_WR * T_pad + t] = akl[AKL_CROWD * T_pad + t] = 0.f;
   }
@@ -302,11 +303,11 @@ __global__ __launch_bounds__(NT) void combine_kernel(const float* partials, cons
 // AKL: merge one search pass.  mass_k = teacher mass at or above threshold k (decreasing in k); the new
 // interval is the pair of neighbouring thresholds between which the mass drops to mu or below.
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void akl_search_combine_kernel(const float* partials, const int* meta, int per_split, int T_pad,
+__global__ __launch_bounds__(NT) void akl_search_combine_kernel(const float* partials, const int* meta, int T_pad,
                                                                 float mu, float* akl) {
   __shared__ float lds[NT / 64 * AKL_K * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = meta[META_N_SPLIT];
   if ((int)(blockIdx.x * TX) >= n_valid) return;
   float m[AKL_K];
 #pragma unroll
@@ -395,11 +396,11 @@ __device__ __forceinline__ void merge_row_sums(const float* partials, int n_part
 // interval's entries by cells: the border is the cell in which the mass from the top on passes mu, or the lowest one, and the cells
 // above it are head.  (In a crowded tile they are all 0: the third search pass has found the border.)
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, const int* meta, int per_split, int T_pad, float mu,
+__global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, const int* meta, int T_pad, float mu,
                                                          const unsigned long long* fine, f32x4* rowinfo, float* row_loss, float* akl) {
   __shared__ float lds[NT / 64 * 2 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = meta[META_N_SPLIT];
   if ((int)(blockIdx.x * TX) >= n_valid) return;
   float a[2];
   merge_row_sums<TX, NT>(partials, n_parts, T_pad, t, g, lds, a);
@@ -430,11 +431,11 @@ __global__ __launch_bounds__(NT) void akl_weights_kernel(const float* partials, 
 
 // JSD / TVD / skewed KL: merge the row sums into the row loss and R (see RowTerm).
 template <int TX, int NT>
-__global__ __launch_bounds__(NT) void combine_rows_kernel(const float* partials, const int* meta, int per_split, int T_pad, int kind,
+__global__ __launch_bounds__(NT) void combine_rows_kernel(const float* partials, const int* meta, int T_pad, int kind,
                                                           float w, f32x4* rowinfo, float* row_loss) {
   __shared__ float lds[NT / 64 * 2 * TX];
   const int t = blockIdx.x * TX + threadIdx.x % TX, g = threadIdx.x / TX;
-  const int n_valid = meta[META_N_VALID], n_parts = per_split * meta[META_N_SPLIT];
+  const int n_valid = meta[META_N_VALID], n_parts = meta[META_N_SPLIT];
   if ((int)(blockIdx.x * TX) >= n_valid) return;
   float a[2];
   merge_row_sums<TX, NT>(partials, n_parts, T_pad, t, g, lds, a);
@@ -831,7 +832,7 @@ hipError_t launch_rows(const Problem& p, hipStream_t st) {
 
 // Shape of the merges: 8 tokens x 128 threads each where a token may have 128 parts or more, else 32 tokens x 8
 // threads each (see merge_parts).  128 parts, T = 128: combine_kernel 10.4 -> 5.8 us by the first.
-static bool many_parts(const Problem& p) { return p.parts * p.n_split >= 128; }
+static bool many_parts(const Problem& p) { return p.n_split >= 128; }
 
 // AKL: one pass of the threshold search (teacher logit tiles only) and its merge.
 hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st) {
@@ -852,21 +853,21 @@ hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st) {
   }
   if (many_parts(p))
     hipLaunchKernelGGL((akl_search_combine_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad, p.beta, p.akl);
+                       p.T_pad, p.beta, p.akl);
   else
     hipLaunchKernelGGL((akl_search_combine_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad, p.beta, p.akl);
+                       p.T_pad, p.beta, p.akl);
   return hipGetLastError();
 }
 
 hipError_t launch_akl_weights(const Problem& p, hipStream_t st) {
   if (many_parts(p))
     hipLaunchKernelGGL((akl_weights_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad, p.beta, p.strip ? p.akl_fine : nullptr,
+                       p.T_pad, p.beta, p.strip ? p.akl_fine : nullptr,
                        (f32x4*)p.rowinfo, p.row_loss, p.akl);
   else
     hipLaunchKernelGGL((akl_weights_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad, p.beta, p.strip ? p.akl_fine : nullptr,
+                       p.T_pad, p.beta, p.strip ? p.akl_fine : nullptr,
                        (f32x4*)p.rowinfo, p.row_loss, p.akl);
   return hipGetLastError();
 }
@@ -956,22 +957,20 @@ static float akl_least(const Problem& p) { return p.kind == 6 ? std::log2((1.f -
 hipError_t launch_combine(const Problem& p, hipStream_t st) {
   if (many_parts(p))
     hipLaunchKernelGGL((combine_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad,
-                       p.kind, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
+                       p.T_pad, p.kind, p.strip, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
   else
     hipLaunchKernelGGL((combine_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad,
-                       p.kind, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
+                       p.T_pad, p.kind, p.strip, 1.4426950408889634f / p.tau, akl_least(p), (f32x4*)p.rowinfo, p.row_loss, p.akl);
   return hipGetLastError();
 }
 
 hipError_t launch_combine_rows(const Problem& p, hipStream_t st) {
   if (many_parts(p))
     hipLaunchKernelGGL((combine_rows_kernel<8, 1024>), dim3(p.T_pad / 8), dim3(1024), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
+                       p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
   else
     hipLaunchKernelGGL((combine_rows_kernel<32, 256>), dim3(p.T_pad / 32), dim3(256), 0, st, p.partials, p.meta,
-                       p.parts, p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
+                       p.T_pad, p.kind, p.beta, (f32x4*)p.rowinfo, p.row_loss);
   return hipGetLastError();
 }
 

@@ -60,7 +60,6 @@ struct Problem {
   void *grad_h_s, *grad_W_s;
   // plan
   int strip;                    // strip loop on packed hidden states (bf16 logit operands, heads [V][K] or [K][V]), else eight-wave loop
-  int parts;                    // partial results per token and vocabulary split
   int g_split;                  // strip loop: most vocabulary ranges per token tile in the gradient kernel
   int gh_rows;                  // hidden rows per tile of the grad_h_s product
   int T_pad, n_tt, n_vt, n_split, V_c, n_ksplit_h, ksteps_h, n_cu;
@@ -72,7 +71,7 @@ struct Problem {
   float* akl;          // AKL only: [kAklRows][T_pad] per-token values between its passes (null otherwise)
   unsigned long long* akl_fine;  // ... strip loop: [T_pad][kAklBins][2] sums of its row pass, behind the partials
   float* row_loss;     // [T_pad]
-  float* partials;     // [n_split*parts][values of the pass][T_pad]
+  float* partials;     // [n_split][values of the pass][T_pad]
   void* h_sT;          // bf16, T_pad tokens x H_s rounded up to 16, packed (pack_columns)
   void* dz;            // bf16, T_pad x V_c, in the order of dz_chunk (kd_common.hpp)
   float* gh32;         // [n_ksplit_h][T][H_s]

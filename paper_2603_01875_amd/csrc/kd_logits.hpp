@@ -48,7 +48,7 @@ struct LogitArgs {
   float beta;
   float t_scale;       // fp8 teacher: z_t = t_scale * (product of the e4m3 codes); 1 otherwise
   int T_pad;
-  float* partials;     // stats: [parts][5][T_pad];  jsd: [parts][2][T_pad]
+  float* partials;     // stats: [ranges][5][T_pad];  jsd: [ranges][2][T_pad]
   const f32x4* rowinfo;// [T_pad]: {lse2_t, lse2_s, mask/(n tau), row term}
   const float* akl;    // AKL only: [AKL_ROWS][T_pad] per-token values (see the AKL_* indices)
   unsigned long long* akl_fine;  // ... [T_pad][AKL_BINS][2] sums of the row pass (strip loop)
@@ -239,9 +239,9 @@ __device__ __forceinline__ float flog2(float x) { return __builtin_amdgcn_logf(x
 
 // How a lane sees a finished tile: NC token columns of (up to) NE vocabulary entries each, entry e of the lane's
 // share lying at vocabulary row m(e) of the tile (four consecutive e are four consecutive rows), column j at
-// token n(j).  PARTS partial results per token and vocabulary split leave a workgroup; this lane's is part().
+// token n(j).  One partial result per token leaves a workgroup: gather() sums those of the lanes that share a token.
 struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
-  static constexpr int NC = NI, NE = MI * 16, PARTS = 4;
+  static constexpr int NC = NI, NE = MI * 16;
   static constexpr bool IN_LDS = false;              // where GradEpi keeps what it knows of the tokens
   int wm, wn, lane;
   __device__ TileGeo() {
@@ -251,8 +251,26 @@ struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
   }
   __device__ __forceinline__ int m(int e) const { return acc_m(wm, e >> 4, e & 15, lane); }
   __device__ __forceinline__ int n(int j) const { return acc_n(wn, j, lane); }
-  __device__ __forceinline__ int part() const { return wm * 2 + (lane >> 5); }
-  static constexpr int MERGE = 64;                   // lanes of one token merged before they leave: none
+  // A token is shared by the halves of a wave and by two waves, which meet in LDS behind the loop.  merge(i, x, y): value i of two
+  // shares put together.  True in the lanes that hold the result.
+  template <int N, class Merge>
+  __device__ __forceinline__ bool gather(float (&v)[N], char* smem, Merge&& merge) const {
+    float* const box = (float*)smem + wn * N * 32 + (lane & 31);
+    float o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = __shfl_xor(v[i], 32, 64);
+    merge(v, o);
+    __syncthreads();                                 // (every wave has read its last fragments, and its last loads have landed)
+    if (wm == 1 && lane < 32)
+#pragma unroll
+      for (int i = 0; i < N; ++i) box[32 * i] = v[i];
+    __syncthreads();
+    if (wm == 1 || lane >= 32) return false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = box[32 * i];
+    merge(v, o);
+    return true;
+  }
   // dz (dz_chunk): entries 16 p .. + 15 of column j are pieces of four rows, piece q at rows 8 q + 4 (lane / 32) of 32;
   // pieces u and u + 2 are a lane's 16 bytes (u = 0, 1)
   static constexpr int PAIR = 2;
@@ -261,7 +279,7 @@ struct TileGeo {         // 128 x 256 tile of eight waves (kd_mfma.hpp)
   }
 };
 struct StripGeo {        // 192 x 256 tile of four waves (kd_strip.hpp)
-  static constexpr int NC = StripCfg::NB, NE = StripCfg::MB * 4, PARTS = 1;
+  static constexpr int NC = StripCfg::NB, NE = StripCfg::MB * 4;
   static constexpr bool IN_LDS = true;
   int wave, lane;
   __device__ StripGeo() {
@@ -270,13 +288,30 @@ struct StripGeo {        // 192 x 256 tile of four waves (kd_strip.hpp)
   }
   __device__ __forceinline__ int m(int e) const { return StripCfg::acc_m(e >> 2, e & 3, lane); }
   __device__ __forceinline__ int n(int j) const { return StripCfg::acc_n(j, lane, wave); }
-  __device__ __forceinline__ int part() const { return 0; }
-  static constexpr int MERGE = 16;                   // lanes 16 and 32 apart hold the same token
+  template <int N, class Merge>
+  __device__ __forceinline__ bool gather(float (&v)[N], char*, Merge&& merge) const {      // lanes 16 and 32 apart hold the same token
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1) {
+      float o[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) o[i] = __shfl_xor(v[i], off, 64);
+      merge(v, o);
+    }
+    return lane < 16;
+  }
   // dz (dz_chunk): entries 16 p .. + 15 of column j are four rows of each of four blocks; two neighbouring blocks are a
   // lane's 16 bytes, a wave's stores whole KiB
   static constexpr int PAIR = 1;
   __device__ __forceinline__ int64_t dz_at(int ldz, int n0, int m0, int j, int p, int u) const {
     return dz_chunk(ldz, (n0 >> 6) + wave, (m0 >> 5) + 2 * p + u, j, lane);
+  }
+};
+
+struct AddUp {
+  template <int N>
+  __device__ __forceinline__ void operator()(float (&v)[N], const float (&o)[N]) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += o[i];
   }
 };
 
@@ -384,18 +419,32 @@ struct StatsEpi {
     }
     m_t[j] = nmt; m_s[j] = nms; S_t[j] = st; S_s[j] = ss; X[j] = x; X2[j] = x2;
   }
-  __device__ void write(const LogitArgs& a, int tt, int split) {
-    float* p = a.partials + (int64_t)(split * TileGeo::PARTS + geo.part()) * NV * a.T_pad;
+  __device__ void write(const LogitArgs& a, char* smem, int tt, int split) {
+    float v[NC * NV];
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int t = tt * BN + geo.n(j);
-      p[0 * a.T_pad + t] = m_t[j];
-      p[1 * a.T_pad + t] = S_t[j];
-      p[2 * a.T_pad + t] = m_s[j];
-      p[3 * a.T_pad + t] = S_s[j];
-      p[4 * a.T_pad + t] = X[j];
-      if (KIND == 6) p[5 * a.T_pad + t] = X2[j];
+      const float own[6] = {m_t[j], S_t[j], m_s[j], S_s[j], X[j], X2[j]};
+#pragma unroll
+      for (int i = 0; i < NV; ++i) v[NV * j + i] = own[i];
     }
+    const bool mine = geo.gather(v, smem, [](float (&v)[NC * NV], const float (&o)[NC * NV]) {
+#pragma unroll
+      for (int j = 0; j < NC * NV; j += NV) {
+        const float mt = fmaxf(v[j], o[j]), ms = fmaxf(v[j + 2], o[j + 2]);
+        const float vt = fexp2(v[j] - mt), ot = fexp2(o[j] - mt), vs = fexp2(v[j + 2] - ms), os = fexp2(o[j + 2] - ms);
+        v[j] = mt; v[j + 2] = ms;
+        v[j + 1] = fmaf(v[j + 1], vt, o[j + 1] * ot);
+        v[j + 3] = fmaf(v[j + 3], vs, o[j + 3] * os);
+        v[j + 4] = KIND == 1 ? fmaf(v[j + 4], vs, o[j + 4] * os) : fmaf(v[j + 4], vt, o[j + 4] * ot);
+        if constexpr (NV == 6) v[j + 5] = fmaf(v[j + 5], vs, o[j + 5] * os);
+      }
+    });
+    if (!mine) return;
+    float* const p = a.partials + (int64_t)split * NV * a.T_pad + tt * BN;
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+#pragma unroll
+      for (int i = 0; i < NV; ++i) p[(int64_t)i * a.T_pad + geo.n(j)] = v[NV * j + i];
   }
 };
 
@@ -563,19 +612,16 @@ struct RowsEpi {
     }
     A1[j] = a1; A2[j] = a2;
   }
-  __device__ void write(const LogitArgs& a, int tt, int split) {
-    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * 2 * a.T_pad;
+  __device__ void write(const LogitArgs& a, char* smem, int tt, int split) {
+    float v[2 * NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) { v[2 * j] = A1[j]; v[2 * j + 1] = A2[j]; }
+    if (!geo.gather(v, smem, AddUp())) return;
+    float* const p = a.partials + (int64_t)split * 2 * a.T_pad + tt * BN;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-#pragma unroll
-      for (int off = Geo::MERGE; off < 64; off <<= 1) {
-        A1[j] += __shfl_xor(A1[j], off, 64);
-        A2[j] += __shfl_xor(A2[j], off, 64);
-      }
-      if (geo.lane >= Geo::MERGE) continue;
-      const int t = tt * BN + geo.n(j);
-      p[0 * a.T_pad + t] = A1[j];
-      p[1 * a.T_pad + t] = A2[j];
+      p[geo.n(j)] = v[2 * j];
+      p[a.T_pad + geo.n(j)] = v[2 * j + 1];
     }
   }
 };
@@ -686,7 +732,7 @@ struct SearchEpi {
   static constexpr int NC = Geo::NC;
   Geo geo;
   float Lt[NC], th0[NC], step[NC];
-  float mass[NC][AKL_K];
+  float mass[NC * AKL_K];
   float c;
   __device__ SearchEpi(const LogitArgs& a, int tt) : c(a.c) {
 #pragma unroll
@@ -697,7 +743,7 @@ struct SearchEpi {
       step[j] = (hi - lo) * (1.f / (AKL_K + 1));
       th0[j] = lo + step[j];
 #pragma unroll
-      for (int k = 0; k < AKL_K; ++k) mass[j][k] = 0.f;
+      for (int k = 0; k < AKL_K; ++k) mass[AKL_K * j + k] = 0.f;
     }
   }
   __device__ void begin_item(int, int, int) {}
@@ -710,21 +756,16 @@ struct SearchEpi {
       const float lt = fmaf(T[e], c, -Lt[j]);
       const float p = fexp2(lt);
 #pragma unroll
-      for (int k = 0; k < AKL_K; ++k) mass[j][k] += (lt >= fmaf((float)k, step[j], th0[j])) ? p : 0.f;
+      for (int k = 0; k < AKL_K; ++k) mass[AKL_K * j + k] += (lt >= fmaf((float)k, step[j], th0[j])) ? p : 0.f;
     }
   }
-  __device__ void write(const LogitArgs& a, int tt, int split) {
-    float* p = a.partials + (int64_t)(split * Geo::PARTS + geo.part()) * AKL_K * a.T_pad;
+  __device__ void write(const LogitArgs& a, char* smem, int tt, int split) {
+    if (!geo.gather(mass, smem, AddUp())) return;
+    float* const p = a.partials + (int64_t)split * AKL_K * a.T_pad + tt * BN;
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-      const int t = tt * BN + geo.n(j);
+    for (int j = 0; j < NC; ++j)
 #pragma unroll
-      for (int k = 0; k < AKL_K; ++k) {
-#pragma unroll
-        for (int off = Geo::MERGE; off < 64; off <<= 1) mass[j][k] += __shfl_xor(mass[j][k], off, 64);
-        if (geo.lane < Geo::MERGE) p[k * a.T_pad + t] = mass[j][k];
-      }
-    }
+      for (int k = 0; k < AKL_K; ++k) p[(int64_t)k * a.T_pad + geo.n(j)] = mass[AKL_K * j + k];
   }
 };
 

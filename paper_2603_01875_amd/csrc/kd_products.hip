@@ -480,6 +480,7 @@ __global__ void gradh_finish_kernel(const float* parts, int n_parts, int T, int 
   if (j >= 0) {
     const float* src = parts + (int64_t)j * H + h;
     v = *(const f32x4*)src;
+#pragma unroll 8
     for (int p = 1; p < n_parts; ++p) v += *(const f32x4*)(src + (int64_t)p * n);
   }
   if (out_f32) {

@@ -36,7 +36,7 @@ KD_STRIP_KERNEL void rows_strip_hv_kern(const LogitArgs a) {
     RowsEpi<KIND, StripGeo> epi(a, work.tt);
     StripEpi<RowsEpi<KIND, StripGeo>> drive(epi);
     strip_loop<2, true, StripCfg, A_KMAJOR_DZ>(work, drive, smem);
-    if (work.cnt > 0) epi.write(a, work.tt, work.split);
+    if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
   }
 }
 
