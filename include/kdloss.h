@@ -138,7 +138,7 @@ typedef struct {
  * Host only.  The size is O(T * V_c + H_s * V_c + T * (H_t + H_s)) for a vocabulary
  * chunk V_c chosen by the library - staging of dL/dz_s, fp32 sums of grad_h_s,
  * compacted copies of the hidden states - plus copies of the heads only when they
- * must be re-packed (fp32 inputs, hidden sizes that are not multiples of 64).  The
+ * must be re-packed (fp32 inputs; hidden sizes that are not multiples of 64, with more than 1536 tokens, small heads or KD_W_HV).  The
  * staging buffer (2 T V_c bytes, T rounded up to 256) takes at most 208 MiB below
  * 4096 tokens, which may be the whole vocabulary; from there on at most 16384
  * columns and 512 MiB, or 1024 columns.  It never grows like T * V.  Returns KD_OK or the status kd_loss_fwd_bwd would return for

@@ -177,8 +177,14 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   q.t_scale = q.t_fp8 ? p->teacher_scale : 1.f;
   q.K_t = (int)contraction(q.in_f32, q.H_t);                    // fp8: H_t % 128 == 0, used as it is
   q.K_s = (int)contraction(q.in_f32, q.H_s);
-  q.prep_Wt = q.in_f32 || q.K_t != q.H_t;
-  q.prep_Ws = q.in_f32 || q.K_s != q.H_s;
+  // A bf16 [V][H] head with rows off the 64-element grid is read in place with few tokens: the last k-step of a row runs on into the
+  // next one, where the padded hidden states are 0, and behind the last row loads give 0.  Its rows straddle cache lines, so with more
+  // tokens a padded copy is as good or better: H = 1000 / 520, V = 50264, T = 64 203 (copies) against 141 us, T = 300 322 / 266,
+  // T = 2048 902 / 902, T = 4096 1815 / 1847; T = 777, H = 4088 / 1000, V = 151936 3.63 / 3.23 ms.  Copies of small heads share the
+  // row map's launch and cost nothing.
+  auto copied = [&](int64_t K, int64_t H) { return K != H && (q.w_hv || q.T > 1536 || 2 * q.V * K <= (4ll << 20)); };
+  q.prep_Wt = q.in_f32 || copied(q.K_t, q.H_t);
+  q.prep_Ws = q.in_f32 || copied(q.K_s, q.H_s);
   // [H][V] heads are read in place as k-major operands when they are bf16 with whole k-steps and a
   // vocabulary that the K-contiguous operand of the grad_h_s product can walk in whole 64-element
   // steps; otherwise both are re-packed (transposing) and the kernels see [V][K] copies
@@ -310,8 +316,8 @@ void carve(Problem& q, const Layout& L, void* ws) {
   q.user_h_t = q.h_t; q.user_W_t = q.W_t; q.user_h_s = q.h_s; q.user_W_s = q.W_s;
   // without a mask the eight-wave loop uses the hidden states in place unless they need re-packing anyway
   if (!q.mask && !q.strip) {
-    q.prep_ht = q.prep_Wt;
-    q.prep_hs = q.prep_Ws;
+    q.prep_ht = q.prep_Wt || q.K_t != q.H_t;
+    q.prep_hs = q.prep_Ws || q.K_s != q.H_s;
   }
   if (q.prep_ht) q.h_t = b + L.prep_h_t;
   if (q.prep_Wt) q.W_t = b + L.prep_W_t;

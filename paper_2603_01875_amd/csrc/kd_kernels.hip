@@ -77,7 +77,7 @@ KD_LOGIT_KERNEL void stats_kernel(const LogitArgs a) {
   StatsEpi<KIND> epi(a.c);
   TileEpi<StatsEpi<KIND>> drive(epi, a.t_scale);
   LoopClock clk(a);
-  tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  tile_loop<2, LCfg, WHV, TF8>(work, drive, a.ld_s, a.ld_t, a.H_s, a.H_t, smem);
   clk.stop(a);
   if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
@@ -88,7 +88,7 @@ KD_LOGIT_KERNEL void rows_kernel(const LogitArgs a) {
   SplitWork<TF8, WHV> work(a);
   RowsEpi<KIND, TileGeo> epi(a, work.tt);
   TileEpi<RowsEpi<KIND, TileGeo>> drive(epi, a.t_scale);
-  tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  tile_loop<2, LCfg, WHV, TF8>(work, drive, a.ld_s, a.ld_t, a.H_s, a.H_t, smem);
   if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
 
@@ -104,7 +104,7 @@ KD_LOGIT_KERNEL void akl_search_kernel(const LogitArgs a) {
   TeacherSplitWork<WHV> work(a);
   SearchEpi<TileGeo> epi(a, work.tt);
   SearchTileEpi<SearchEpi<TileGeo>> drive(epi, 1.f);
-  tile_loop<1, LCfg, WHV, false>(work, drive, WHV ? a.V : a.H_t, WHV ? a.V : a.H_t, a.H_t, a.H_t, smem);
+  tile_loop<1, LCfg, WHV, false>(work, drive, a.ld_t, a.ld_t, a.H_t, a.H_t, smem);
   if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
 }
 
@@ -114,7 +114,7 @@ KD_LOGIT_KERNEL void grad_kernel(const LogitArgs a) {
   ChunkWork<TF8, WHV> work(a);
   GradEpi<KIND, TileGeo> epi(a, smem);
   TileEpi<GradEpi<KIND, TileGeo>> drive(epi, a.t_scale);
-  tile_loop<2, LCfg, WHV, TF8>(work, drive, WHV ? a.V : a.H_s, WHV ? a.V : a.H_t, a.H_s, a.H_t, smem);
+  tile_loop<2, LCfg, WHV, TF8>(work, drive, a.ld_s, a.ld_t, a.H_s, a.H_t, smem);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -35,8 +35,8 @@ __device__ __forceinline__ void block_decode(int q, int na, int ba, int bb, int&
 
 struct LogitArgs {
   const bf16_t* W_s; const bf16_t* h_s; const bf16_t* W_t; const bf16_t* h_t;
-  int T, V, H_s, H_t;  // H_*: contraction length and row stride of the (re-packed) operands
-                       // (heads in [H][V] order: their row stride is V)
+  int T, V, H_s, H_t;  // H_*: contraction length and row stride of the (re-packed) hidden states
+  int ld_s, ld_t;      // elements from row to row of the heads ([V][H]: H, or the contraction length where re-packed; [H][V]: V)
   const int* meta;     // device-side plan: valid tokens, token tiles, vocabulary splits
   int v0, v_end;       // vocabulary rows [v0, v_end) handled by this launch
   int n_vt;            // ... in this many tiles
@@ -73,12 +73,12 @@ __device__ __forceinline__ WorkItem logit_item(const LogitArgs& a, int vt, int t
     it.A1 = a.W_t + m0;
     it.B1 = a.h_t + (int64_t)tt * BN * a.H_t;
   } else if (TF8) {
-    it.A0 = a.W_s + (int64_t)m0 * a.H_s;
+    it.A0 = a.W_s + (int64_t)m0 * a.ld_s;
     it.A1 = (const bf16_t*)((const char*)a.W_t + (int64_t)m0 * a.H_t);
     it.B1 = (const bf16_t*)((const char*)a.h_t + (int64_t)tt * BN * a.H_t);
   } else {
-    it.A0 = a.W_s + (int64_t)m0 * a.H_s;
-    it.A1 = a.W_t + (int64_t)m0 * a.H_t;
+    it.A0 = a.W_s + (int64_t)m0 * a.ld_s;
+    it.A1 = a.W_t + (int64_t)m0 * a.ld_t;
     it.B1 = a.h_t + (int64_t)tt * BN * a.H_t;
   }
   it.a_rows = min(BM, a.v_end - m0);
@@ -160,8 +160,8 @@ struct StripWork {
     it.m0 = m0;
     it.n0 = n0;
     it.k0 = p->H_s; it.k1 = p->H_t;
-    it.lda0 = 2 * (HV ? p->V : it.k0); it.ldb0 = 128 * it.k0;
-    it.lda1 = 2 * (HV ? p->V : it.k1); it.ldb1 = 128 * it.k1;
+    it.lda0 = 2 * p->ld_s; it.ldb0 = 128 * it.k0;
+    it.lda1 = 2 * p->ld_t; it.ldb1 = 128 * it.k1;
     it.A0 = (const char*)p->W_s + (int64_t)m0 * (HV ? 2 : it.lda0);
     it.A1 = (const char*)p->W_t + (int64_t)m0 * (HV ? 2 : it.lda1);
     it.B0 = (const char*)p->h_s + (int64_t)n0 * (2 * it.k0);
@@ -941,7 +941,9 @@ inline LogitArgs make_logit_args(const Problem& p) {
   LogitArgs a{};
   a.W_s = (const bf16_t*)p.W_s; a.h_s = (const bf16_t*)p.h_s;
   a.W_t = (const bf16_t*)p.W_t; a.h_t = (const bf16_t*)p.h_t;
-  a.T = p.T; a.V = p.V; a.H_s = p.K_s; a.H_t = p.K_t;   // contraction lengths = row strides
+  a.T = p.T; a.V = p.V; a.H_s = p.K_s; a.H_t = p.K_t;
+  a.ld_s = p.w_hv_inplace ? p.V : p.prep_Ws ? p.K_s : p.H_s;
+  a.ld_t = p.w_hv_inplace ? p.V : p.prep_Wt ? p.K_t : p.H_t;
   a.meta = p.meta;
   a.c = 1.4426950408889634f / p.tau;
   a.beta = p.beta;

@@ -112,13 +112,19 @@ __device__ __forceinline__ const T* uniform(const T* p) {
   return (const T*)(((uint64_t)hi << 32) | lo);
 }
 
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>((const void*)uniform((const char*)p)), 0,
+                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
 // Persistent tile loop with a continuous software pipeline.
 //
 // Work:  int n_items() const;  WorkItem item(int i) const;   (wave-uniform)
 // Epi:   void begin_item(const WorkItem&)            called before the first k-step of an item
 //        void end_item(const WorkItem&, Acc& acc0, Acc& acc1)
 //                                                    called after the last k-step of an item
-// ld*[p] are the same for every item of a launch; the k-step counts may differ per item.
+// ld*[p] are the same for every item of a launch (A's: from row to row, which may be less than the k-steps cover, where B is 0); the k-step counts may differ per item.
 //
 // Pipeline: NST LDS stages filled by direct global->LDS loads (16 bytes per lane, no
 // staging registers).  While k-step g is multiplied, the loads of k-step g+NST-1 are
@@ -235,7 +241,9 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
   int l_item = 0, l_phase = 0, l_k = 0, l_nk;
   bool more = true;
   WorkItem li = work.item(0);
-  const char *l_pa, *l_pb;      // uniform: tile base + k offset, in bytes
+  const char *l_pa, *l_pb;      // uniform: tile base + k offset, in bytes (A: of k-major rows; else ra and l_ka)
+  rsrc_t ra;                    // the tile's rows of A, behind which loads give 0 (rows may be shorter than their k-steps)
+  int l_ka = 0;                 // k offset in it (part of what is checked against its end)
   int64_t l_step_a = ROWB;      // bytes of A from one k-step to the next (k-major: BK of its k-rows)
   uint32_t loff[LOADS];         // per lane: byte offset of its 16 bytes inside the k-slab
   const int km_row = tid / CPR, km_c = (tid % CPR) ^ (4 * (km_row & 3));
@@ -257,6 +265,10 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
     }
     if (AKM) l_step_a = (int64_t)BK * 2 * la;
     l_pa = (const char*)uniform(l_phase ? li.A1 : li.A0);
+    if constexpr (!AKM) {
+      ra = make_rsrc(l_pa, (uint32_t)li.a_rows * la * ((P1F8 && l_phase) ? 1 : 2));
+      l_ka = 0;
+    }
     l_pb = (const char*)uniform(l_phase ? li.B1 : li.B0);
     l_nk = l_phase ? li.nk1 : li.nk0;
   };
@@ -266,12 +278,15 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
   auto issue_loads = [&](int stage, int j0, int j1) {
     char* sbase = smem + stage * STAGE_BYTES + wave * 1024;
 #pragma unroll
-    for (int j = j0; j < j1; ++j)
-      __builtin_amdgcn_global_load_lds((const void*)((j < A_LOADS ? l_pa : l_pb) + loff[j]),
-                                       (lds_void_t*)(sbase + j * (Cfg::NT * 16)), 16, 0, 0);
+    for (int j = j0; j < j1; ++j) {
+      lds_void_t* const to = (lds_void_t*)(sbase + j * (Cfg::NT * 16));
+      if (!AKM && j < A_LOADS) __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, to, 16, loff[j], l_ka, 0, 0);
+      else __builtin_amdgcn_global_load_lds((const void*)((j < A_LOADS ? l_pa : l_pb) + loff[j]), to, 16, 0, 0);
+    }
   };
   auto advance = [&]() {
-    l_pa += AKM ? l_step_a : ROWB;
+    if (AKM) l_pa += l_step_a;
+    else l_ka += ROWB;
     l_pb += ROWB;
     if (++l_k == l_nk) {
       l_k = 0;
@@ -291,7 +306,8 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
         l_item = n_items - 1;
         l_phase = NPHASE - 1;
         l_k = l_nk - 1;
-        l_pa -= AKM ? l_step_a : ROWB;
+        if (AKM) l_pa -= l_step_a;
+        else l_ka -= ROWB;
         l_pb -= ROWB;
       }
     }

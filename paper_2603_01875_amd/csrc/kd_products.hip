@@ -536,14 +536,15 @@ hipError_t launch_grad_h(const Problem& p, int v0, int width, bool first, hipStr
   const int mb = p.gh_rows / 16;
   GradHArgs a{};
   a.dz = (const char*)p.dz;
-  a.W = (const char*)p.W_s + (p.w_hv_inplace ? (size_t)v0 * 2 : (size_t)v0 * p.K_s * 2);
+  const int64_t ld = p.w_hv_inplace ? p.V : p.prep_Ws ? p.K_s : p.H_s;
+  a.W = (const char*)p.W_s + (size_t)v0 * 2 * (p.w_hv_inplace ? 1 : ld);
   a.out = p.gh32; a.part_stride = (int64_t)p.T * p.H_s;
   a.width = width; a.H_s = p.H_s;
   a.n_ht = (p.H_s + 16 * mb - 1) / (16 * mb);
   a.ksteps = p.ksteps_h;
   a.n_split = ((width + 63) / 64 + a.ksteps - 1) / a.ksteps;       // every part has at least one k-step
   a.accumulate = first ? 0 : 1;
-  a.lda = 2u * (uint32_t)(p.w_hv_inplace ? p.V : p.K_s);
+  a.lda = 2u * (uint32_t)ld;
   a.ldb = (uint32_t)p.V_c * 128;
   a.meta = p.meta;
   const int tiles = a.n_ht * p.n_tt * a.n_split, grid = tiles < p.n_cu ? tiles : p.n_cu;   // worst case: no token masked

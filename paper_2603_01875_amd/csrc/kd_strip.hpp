@@ -91,7 +91,8 @@ enum { A_ROWS = 0, A_ROWS_DZ = 1, A_KMAJOR_DZ = 2, A_DZ = 3 };
 struct StripItem {
   const char *A0, *A1, *B0, *B1;
   int k0, k1;
-  int a_rows;              // rows of A in the tile (1 .. BM); loads of the others give the last one's
+  int a_rows;              // rows of A in the tile (1 .. BM); loads of the others give the last one's (A_ROWS: a row may be shorter
+                           // than its k-steps, which then run on into the next row, B being 0 there; behind the last row loads give 0)
   int out_rows;            // ... rounded up to 64: what is stored of it
   int m0, n0;              // tile origin
   int aux;                 // free for the work map
@@ -109,12 +110,6 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* kernel_arg
   auto p = (const __attribute__((address_space(4))) T*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(p));
   return p;
-}
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-__device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>((const void*)uniform((const char*)p)), 0,
-                                           __builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
 // Accumulators in accumulation registers (_a) or vector registers (_v).

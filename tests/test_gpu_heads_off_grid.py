@@ -1,0 +1,63 @@
+"""bf16 heads as [V, H] whose rows are off the 64-element grid: large ones are read in place, their last k-step running on past a
+row's end.  Both logit loops, hidden sizes 8 to 56 past the grid and below one k-step, several divergences, the fp8 teacher with such a
+student, two teachers of which one is on the grid, short last tiles.  Behind the heads lie NaNs.  Against the fp64 oracle with the
+tolerances of the other parity tests."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import kd_oracle as O
+from paper_2603_01875_amd import inputs as I
+from paper_2603_01875_amd import kdloss as K
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+
+def _followed_by_nan(x):
+    """x on the device, NaNs right behind it."""
+    x = G.to_device(x, I.BF16)
+    buf = torch.full((x.numel() + 4096,), float("nan"), dtype=x.dtype, device="cuda")
+    buf[:x.numel()] = x.reshape(-1)
+    return buf[:x.numel()].view(x.shape)
+
+
+@pytest.mark.parametrize("T, H_t, H_s, V, kind, loop", [
+    (300, 1000, 520, 5000, I.FKL, 0), (20, 584, 1016, 6008, I.JSD, 0), (300, 1000, 520, 5000, I.AKL, 0), (257, 56, 40, 50264, I.RKL, 0),
+    (600, 2824, 136, 16200, I.FKL, 1), (600, 2872, 200, 16136, I.JSD, 1), (600, 2824, 136, 16200, I.AKL, 1)])
+def test_heads_off_the_grid(T, H_t, H_s, V, kind, loop):
+    assert K.kd_loss_plan_loop(K.make_params(T, H_t, H_s, V, kind, beta=0.5)) == loop
+    # (read in place: no room for copies of both)
+    assert K.kd_loss_workspace_size(K.make_params(T, H_t, H_s, V, kind, beta=0.5)) < \
+        K.kd_loss_workspace_size(K.make_params(T, H_t, H_s, V, kind, beta=0.5, w_layout=K.W_HV)) - 2 * V * min(H_t, H_s)
+    cfg = I.scaled(I.workload("fkl_bf16"), batch=1, seq=T, H_t=H_t, H_s=H_s, V=V, kind=kind, beta=0.5, w_t_std=0.05, mask="bernoulli10")
+    data = I.generate(cfg)
+    data["mask"][0] = 1
+    d = [_followed_by_nan(data[k]) for k in ("h_t", "W_t", "h_s", "W_s")]
+    out = K.kd_loss_fwd_bwd(*d, torch.from_numpy(data["mask"]).cuda(), tau=cfg.tau, kind=kind, beta=0.5)
+    G.check(out, G.run_oracle(cfg, data), "off the grid", G.akl_allowance(cfg, data) if kind == I.AKL else None)
+
+
+def test_student_off_the_grid_with_fp8_teacher():
+    T, H_t, H_s, V = 300, 256, 520, 6000
+    cfg = I.scaled(I.workload("fkl_bf16"), batch=1, seq=T, H_t=H_t, H_s=H_s, V=V, mask="ones")
+    data = I.generate(cfg)
+    codes, scales = [], []
+    for k in ("h_t", "W_t"):
+        scales.append(float(np.abs(data[k]).max()) / 448)
+        codes.append(K.quantize_e4m3(G.to_device(data[k], I.BF16), scales[-1]))
+        data[k] = codes[-1].view(torch.float8_e4m3fn).float().cpu().numpy() * np.float32(scales[-1])
+    out = K.kd_loss_fwd_bwd(codes[0], codes[1], _followed_by_nan(data["h_s"]), _followed_by_nan(data["W_s"]), None,
+                            flags=K.FLAG_TEACHER_FP8, teacher_scale=scales[0] * scales[1])
+    G.check(out, G.run_oracle(cfg, data), "fp8 teacher")
+
+
+def test_two_teachers_one_on_the_grid():
+    base = I.scaled(I.workload("fkl_bf16"), batch=1, seq=300, H_s=520, V=6000, mask="ones")
+    ds = [I.generate(I.scaled(base, H_t=h, seed=900 + h)) for h in (512, 392)]
+    h_s, W_s = ds[0]["h_s"], ds[0]["W_s"]
+    ref = O.kd_loss_multi([d["h_t"] for d in ds], [d["W_t"] for d in ds], (0.6, 0.4), h_s, W_s, np.ones(300, np.uint8), base.tau, base.kind,
+                          0.5, O.W_VH)
+    out = K.kd_loss_fwd_bwd_multi([_followed_by_nan(d["h_t"]) for d in ds], [_followed_by_nan(d["W_t"]) for d in ds], (0.6, 0.4),
+                                  _followed_by_nan(h_s), _followed_by_nan(W_s), None, tau=base.tau, kind=base.kind)
+    G.check(out, ref, "two teachers")
