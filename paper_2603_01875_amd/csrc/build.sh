@@ -6,7 +6,7 @@ FLAGS="--offload-arch=gfx950 -O3 -std=c++17 -fPIC -Xclang -target-feature -Xclan
 OBJ=$(mktemp -d)
 trap 'rm -rf "$OBJ"' EXIT
 pids=()
-for f in kd_kernels kd_strip_hv kd_products kd_api; do
+for f in kd_kernels kd_strip_hv kd_products kd_few kd_api; do
   hipcc $FLAGS "$@" -c $f.hip -o "$OBJ/$f.o" & pids+=($!)
 done
 for p in "${pids[@]}"; do wait $p; done

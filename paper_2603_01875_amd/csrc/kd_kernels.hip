@@ -11,7 +11,7 @@
 //     the backward products: grad_W_s[chunk] = dz^T . h_s     and     grad_h_s += dz . W_s[chunk]     (kd_products.hip)
 //   gradh_finish : fp32 partial sums -> grad_h_s (kd_products.hip)
 // All logarithms inside the kernels are base 2: a = z * log2(e)/tau.
-#include "kd_logits.hpp"
+#include "kd_eight.hpp"
 
 namespace kd {
 
@@ -20,8 +20,6 @@ namespace kd {
 // [H][V]: kd_strip_hv.hip); the eight-wave tile loop for the others (k-major fragments come from LDS by transposing reads)
 // and where the teacher is fp8
 // ------------------------------------------------------------------------------------------
-#define KD_LOGIT_KERNEL __global__ __launch_bounds__(LCfg::NT)
-
 template <int KIND>
 KD_STRIP_KERNEL void stats_strip_kernel(const LogitArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -68,53 +66,6 @@ KD_STRIP_KERNEL void grad_strip_kernel(const LogitArgs a) {
   GradEpi<KIND, StripGeo> epi(a, smem);
   StripEpi<GradEpi<KIND, StripGeo>> drive(epi);
   strip_loop<2, false>(work, drive, smem);
-}
-
-template <int KIND, bool TF8, bool WHV>
-KD_LOGIT_KERNEL void stats_kernel(const LogitArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  SplitWork<TF8, WHV> work(a);
-  StatsEpi<KIND> epi(a.c);
-  TileEpi<StatsEpi<KIND>> drive(epi, a.t_scale);
-  LoopClock clk(a);
-  tile_loop<2, LCfg, WHV, TF8>(work, drive, a.ld_s, a.ld_t, a.H_s, a.H_t, smem);
-  clk.stop(a);
-  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
-}
-
-template <int KIND, bool TF8, bool WHV>
-KD_LOGIT_KERNEL void rows_kernel(const LogitArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  SplitWork<TF8, WHV> work(a);
-  RowsEpi<KIND, TileGeo> epi(a, work.tt);
-  TileEpi<RowsEpi<KIND, TileGeo>> drive(epi, a.t_scale);
-  tile_loop<2, LCfg, WHV, TF8>(work, drive, a.ld_s, a.ld_t, a.H_s, a.H_t, smem);
-  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
-}
-
-// (one accumulator: the driver gets the teacher's tile as the first one)
-template <class Epi>
-struct SearchTileEpi : TileEpi<Epi> {
-  using TileEpi<Epi>::TileEpi;
-  __device__ void end_item(const WorkItem& it, AccTile& accT, AccTile&) { TileEpi<Epi>::end_item(it, accT, accT); }
-};
-template <bool WHV>
-KD_LOGIT_KERNEL void akl_search_kernel(const LogitArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  TeacherSplitWork<WHV> work(a);
-  SearchEpi<TileGeo> epi(a, work.tt);
-  SearchTileEpi<SearchEpi<TileGeo>> drive(epi, 1.f);
-  tile_loop<1, LCfg, WHV, false>(work, drive, a.ld_t, a.ld_t, a.H_t, a.H_t, smem);
-  if (work.cnt > 0) epi.write(a, smem, work.tt, work.split);
-}
-
-template <int KIND, bool TF8, bool WHV>
-KD_LOGIT_KERNEL void grad_kernel(const LogitArgs a) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  ChunkWork<TF8, WHV> work(a);
-  GradEpi<KIND, TileGeo> epi(a, smem);
-  TileEpi<GradEpi<KIND, TileGeo>> drive(epi, a.t_scale);
-  tile_loop<2, LCfg, WHV, TF8>(work, drive, a.ld_s, a.ld_t, a.H_s, a.H_t, smem);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -788,7 +739,7 @@ hipError_t launch_stats(const Problem& p, hipStream_t st) {
   a.partials = p.partials;
   a.clock_out = p.clock_out;
   const int grid = p.n_tt * p.n_split;      // worst case; workgroups beyond the device-side plan exit
-#define KD_STATS(K) (p.strip && p.w_hv_inplace ? launch_strip_hv_stats(p, a, grid, st) \
+#define KD_STATS(K) (few_tokens(p) ? launch_few_stats(p, a, grid, st) : p.strip && p.w_hv_inplace ? launch_strip_hv_stats(p, a, grid, st) \
                      : p.strip ? launch_big<stats_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a) \
                      : p.t_fp8 ? launch_big<stats_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                      : p.w_hv_inplace ? launch_big<stats_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
@@ -797,7 +748,7 @@ hipError_t launch_stats(const Problem& p, hipStream_t st) {
     case 0: return KD_STATS(0);
     case 1: return KD_STATS(1);
     case 6:                        // both cross terms (AKL; never with the fp8 teacher)
-      return p.strip && p.w_hv_inplace ? launch_strip_hv_stats(p, a, grid, st)
+      return few_tokens(p) ? launch_few_stats(p, a, grid, st) : p.strip && p.w_hv_inplace ? launch_strip_hv_stats(p, a, grid, st)
              : p.strip ? launch_big<stats_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a)
              : p.w_hv_inplace ? launch_big<stats_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                               : launch_big<stats_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
@@ -811,7 +762,7 @@ hipError_t launch_rows(const Problem& p, hipStream_t st) {
   a.v0 = 0; a.v_end = p.V; a.n_vt = p.n_vt;
   a.partials = p.partials;
   const int grid = p.n_tt * p.n_split;
-#define KD_ROWS(K) (p.strip && p.w_hv_inplace ? launch_strip_hv_rows(p, a, grid, st) \
+#define KD_ROWS(K) (few_tokens(p) ? launch_few_rows(p, a, grid, st) : p.strip && p.w_hv_inplace ? launch_strip_hv_rows(p, a, grid, st) \
                      : p.strip ? launch_big<rows_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::SMEM_BYTES, st, &a) \
                      : p.t_fp8 ? launch_big<rows_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                      : p.w_hv_inplace ? launch_big<rows_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
@@ -821,7 +772,7 @@ hipError_t launch_rows(const Problem& p, hipStream_t st) {
     case 3: return KD_ROWS(3);
     case 4: return KD_ROWS(4);
     case 6:
-      return p.strip && p.w_hv_inplace ? launch_strip_hv_rows(p, a, grid, st)
+      return few_tokens(p) ? launch_few_rows(p, a, grid, st) : p.strip && p.w_hv_inplace ? launch_strip_hv_rows(p, a, grid, st)
              : p.strip ? launch_big<rows_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a)
              : p.w_hv_inplace ? launch_big<rows_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                               : launch_big<rows_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
@@ -841,7 +792,8 @@ hipError_t launch_akl_search(const Problem& p, int pass, hipStream_t st) {
   a.partials = p.partials;
   a.akl_width = pass == 0 ? kAklBins * kAklBins : pass == 1 ? kAklBins : 1;
   const int grid = p.n_tt * p.n_split;
-  hipError_t e = p.strip && p.w_hv_inplace ? launch_strip_hv_search(a, grid, st)
+  hipError_t e = few_tokens(p) ? launch_few_search(p, a, grid, st)
+           : p.strip && p.w_hv_inplace ? launch_strip_hv_search(a, grid, st)
            : p.strip ? launch_big<akl_search_strip_kernel>(grid, StripCfg::NT, BinsEpi::SMEM_BYTES, st, &a)
            : p.w_hv_inplace ? launch_big<akl_search_kernel<true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                             : launch_big<akl_search_kernel<false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);
@@ -993,7 +945,7 @@ hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulat
   const int tiles = p.n_tt * a.n_vt;
   // strip loop: one workgroup per (token tile, range), surplus ones exit; eight-wave loop: persistent workgroups
   const int grid = p.strip ? p.n_tt * p.g_split : tiles < p.n_cu ? tiles : p.n_cu;
-#define KD_GRAD(K) (p.strip && p.w_hv_inplace ? launch_strip_hv_grad(p, a, grid, st) \
+#define KD_GRAD(K) (few_tokens(p) ? launch_few_grad(p, a, grid, st) : p.strip && p.w_hv_inplace ? launch_strip_hv_grad(p, a, grid, st) \
                      : p.strip ? launch_big<grad_strip_kernel<K>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a) \
                      : p.t_fp8 ? launch_big<grad_kernel<K, true, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
                      : p.w_hv_inplace ? launch_big<grad_kernel<K, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a) \
@@ -1005,7 +957,7 @@ hipError_t launch_grad_chunk(const Problem& p, int v0, int width, bool accumulat
     case 3: return KD_GRAD(3);
     case 4: return KD_GRAD(4);
     case 6:
-      return p.strip && p.w_hv_inplace ? launch_strip_hv_grad(p, a, grid, st)
+      return few_tokens(p) ? launch_few_grad(p, a, grid, st) : p.strip && p.w_hv_inplace ? launch_strip_hv_grad(p, a, grid, st)
              : p.strip ? launch_big<grad_strip_kernel<6>>(grid, StripCfg::NT, StripCfg::STATE_SMEM_BYTES, st, &a)
              : p.w_hv_inplace ? launch_big<grad_kernel<6, false, true>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a)
                               : launch_big<grad_kernel<6, false, false>>(grid, LCfg::NT, LCfg::SMEM_BYTES, st, &a);

@@ -960,4 +960,12 @@ hipError_t launch_strip_hv_rows(const Problem& p, const LogitArgs& a, int grid, 
 hipError_t launch_strip_hv_grad(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
 hipError_t launch_strip_hv_search(const LogitArgs& a, int grid, hipStream_t st);
 
+// Those of the eight-wave loop for at most kFewTokens tokens (kd_few.hip): a pair of waves has 64 of the 256 tokens of a tile.
+constexpr int kFewTokens = 192;
+inline bool few_tokens(const Problem& p) { return !p.strip && p.T <= kFewTokens; }
+hipError_t launch_few_stats(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
+hipError_t launch_few_rows(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
+hipError_t launch_few_grad(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
+hipError_t launch_few_search(const Problem& p, const LogitArgs& a, int grid, hipStream_t st);
+
 }  // namespace kd

@@ -207,10 +207,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 // matter.  ld*1 are then in bytes (= elements).
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
-template <int NPHASE, class Cfg, bool AKM = false, bool P1F8 = false, class Work, class Epi>
+// FEW: one tile of B, of which the first n_live rows count.  A wave that has none of them keeps up its share of the loads and multiplies
+// nothing: its SIMD's other wave has the matrix pipe, and the loop is as fast as A comes in.  (Kernels of their own: the second
+// place that moves the cursor costs the others 1 % in scalar spills, a test in the k-step as much.)
+template <int NPHASE, class Cfg, bool AKM = false, bool P1F8 = false, bool FEW = false, class Work, class Epi>
 __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
                                           const int lda0, const int lda1, const int ldb0, const int ldb1,
-                                          char* smem) {
+                                          char* smem, const int n_live = 0) {
   constexpr int MI = Cfg::MI, NI = Cfg::NI, NST = Cfg::NST, KS = Cfg::KS, CH = Cfg::CH;
   constexpr int A_LOADS = Cfg::A_LOADS, LOADS = Cfg::LOADS, LPS = Cfg::LOADS_PER_SUB;
   constexpr int A_STAGE_BYTES = Cfg::A_STAGE_BYTES, STAGE_BYTES = Cfg::STAGE_BYTES;
@@ -492,6 +495,20 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
     advance();
   }
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(Cfg::WAIT_PROLOGUE) : "memory");
+  if constexpr (FEW) {
+    static_assert(Cfg::LOADS_BEFORE_BARRIER == LOADS, "as in kstep");
+    if (wn * 32 * NI >= n_live) {
+      const WorkItem any = work.item(0);              // (the k-steps are the same for all items of these launches)
+      for (int k = n_items * (NPHASE > 1 ? any.nk0 + any.nk1 : any.nk0); k > 0; --k) {
+        issue_loads(fill, 0, LOADS);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(Cfg::WAIT_STEADY) : "memory");
+        advance();
+        fill = fill == NST - 1 ? 0 : fill + 1;
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      return;
+    }
+  }
   read_frags(0, IntC<0>{}, fa0, fb0);
 
   for (int c_item = 0; c_item < n_items; ++c_item) {
