@@ -60,13 +60,15 @@ kd_status check_params(const kd_loss_params* p) {
 }
 
 // Vocabulary chunk of the backward pass.  The [T_pad, V_c] bf16 staging buffer of dL/dz_s is written by the gradient
-// kernel and read back by both products, so it should stay in the 256 MB last-level cache together with the operands;
-// but every chunk also re-reads and re-writes the fp32 sums of grad_h_s, so with many tokens a chunk of at least 8192
-// columns wins as long as the staging buffer stays within 512 MiB.
-//  - From 4096 tokens on a power of two within 128 MiB, at least 8192 columns.  (Nothing in the kernels asks for the line
-//    to lie at 4096, or for powers of two: 24576 columns there, 201 MB, measured 11.72 against 12.25 ms without a mask on an earlier
-//    state, and by 13824 columns the gradient kernel would walk 44 rounds for 47 at 3584 rows and V = 151936.  tests/test_abi_host.py
-//    holds that size to 16384 columns.)
+// kernel and read back by both products; it should stay in the 256 MB last-level cache together with the operands, but every chunk also
+// costs the ends of three launches and re-reads and re-writes the fp32 sums of grad_h_s.
+//  - From 4096 tokens on 16384 columns, halved until the staging buffer is within 512 MiB (at least 1024).  Against 8192 columns, which
+//    keep it within the cache up to 12288 tokens: T = 6144, H = 1024 / 512, V = 128256, JSD 9.16 -> 8.46 ms; T = 8192, H = 2048 / 1024,
+//    V = 151936, JSD 22.4 -> 21.3, [H][V] heads 15.3 -> 14.5; T = 16384, H = 2048 / 512, RKL 26.2 -> 23.9, H = 4096 / 2048, V = 128256 50.1 ->
+//    49.9.  Out of the cache it no longer pays where the contraction is long, whose products hide a chunk's ends best: T = 8192, H = 8192 /
+//    2048, a tenth of the tokens masked 33.96 -> 34.39 ms (none masked 38.4 -> 36.9, where the rounds of workgroups come out better), nor past
+//    512 MiB (T = 32768, H = 5120 / 4096, JSD 262.6 -> 265.4).  (At 4096 tokens 24576 columns, 201 MB, measured 11.72 against 12.25 ms
+//    without a mask on an earlier state; tests/test_abi_host.py holds that size to 16384 columns.)
 //  - Below, up to 208 MiB (201 MB still stays in the cache), and the width decides how full the last rounds of
 //    workgroups are: the candidates (multiples of the tile heights) are priced by the rounds of the gradient kernel,
 //    with all tokens and with an eighth of them masked, and of the grad_W_s product.  Measured steps: T = 3584 10.60 ms
@@ -75,12 +77,9 @@ kd_status check_params(const kd_loss_params* p) {
 // `logit_k`: elements contracted for one logit of every model of the call (each teacher with the student again).
 int64_t choose_chunk(const Problem& q, int64_t v_all, int64_t logit_k) {
   if (q.T_pad >= 4096) {
-    int64_t vc = 1 << 20;
-    while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (128ll << 20)) vc >>= 1;
-    if (vc < 8192) {
-      vc = 8192;
-      while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (512ll << 20)) vc >>= 1;
-    }
+    int64_t vc = 16384;
+    while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (512ll << 20)) vc >>= 1;
+    if (vc == 16384 && (int64_t)q.T_pad * vc * 2 > (208ll << 20) && logit_k > 6144) vc = 8192;
     return vc;
   }
   const int64_t step = 1536, most = (208ll << 20) / (2 * q.T_pad);      // a multiple of 192, 256 and 128

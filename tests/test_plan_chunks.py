@@ -1,0 +1,19 @@
+"""Width of the vocabulary chunk with many tokens: 16384 columns while the staging buffer of dL/dz_s is within 512 MiB, then halved; with a
+long contraction 8192 from where the buffer leaves the last-level cache."""
+import pytest
+
+from paper_2603_01875_amd import kdloss as K
+
+
+@pytest.mark.parametrize("T, width", [(4096, 16384), (6000, 16384), (16384, 16384), (16385, 8192), (32768, 8192), (32769, 4096), (262144, 1024),
+                                      (1 << 22, 1024)])
+def test_chunk_of_many_tokens(T, width):
+    for V in (151936, 128256):
+        assert K.kd_loss_plan_info(K.make_params(T, 512, 256, V))[0] == width
+    assert K.kd_loss_plan_info(K.make_params(T, 512, 256, 1000))[0] == min(width, 1024)
+
+
+@pytest.mark.parametrize("T, H_t, H_s, width", [(4096, 4096, 4096, 16384), (6656, 8192, 2048, 16384), (6657, 8192, 2048, 8192),
+                                                (6657, 4096, 2048, 16384), (16384, 4096, 2112, 8192), (32768, 5120, 4096, 8192)])
+def test_chunk_with_a_long_contraction(T, H_t, H_s, width):
+    assert K.kd_loss_plan_info(K.make_params(T, H_t, H_s, 128256))[0] == width
