@@ -135,7 +135,7 @@ struct CallPlan {
 // lost against the faster loop of each, 6.5 % at most (one loop for all of them: 3.5 % and 3.8 %); over 24 with [H][V] heads
 // 0.3 %, 3.1 % at most.
 // AKL's line lies too far to the eight-wave side: its 300 and its mean over seven passes are from when its search was four passes of
-// compares on both loops.  By bins (three passes here) strips are ahead wherever V is large, down to H_t = 320: over 30 sizes the rule loses
+// compares on both loops.  By bins (three passes then, two now) strips are ahead wherever V is large, down to H_t = 320: over 30 sizes the rule loses
 // 12 %, up to 33 % (T = 735, H = 2304 / 192, V = 151936 4.11 against 3.10 ms); strips for all of them would lose 1.2 %.
 // One token tile: the heads stream through once, nothing is shared, and the smaller tiles spread better over the CUs
 // (T = 1, V = 151936, JSD 1.28 against 1.44 ms; 24 sizes: 10 % on average, strips never ahead by more than 2 %, at T = 256 1.10
