@@ -176,11 +176,10 @@ void plan(const kd_loss_params* p, Problem& q, Layout& L, bool with_backward, co
   q.t_scale = q.t_fp8 ? p->teacher_scale : 1.f;
   q.K_t = (int)contraction(q.in_f32, q.H_t);                    // fp8: H_t % 128 == 0, used as it is
   q.K_s = (int)contraction(q.in_f32, q.H_s);
-  // A bf16 [V][H] head with rows off the 64-element grid is read in place with few tokens: the last k-step of a row runs on into the
-  // next one, where the padded hidden states are 0, and behind the last row loads give 0.  Its rows straddle cache lines, so with more
-  // tokens a padded copy is as good or better: H = 1000 / 520, V = 50264, T = 64 203 (copies) against 141 us, T = 300 322 / 266,
-  // T = 2048 902 / 902, T = 4096 1815 / 1847; T = 777, H = 4088 / 1000, V = 151936 3.63 / 3.23 ms.  Copies of small heads share the
-  // row map's launch and cost nothing.
+  // A bf16 [V][H] head with rows off the 64-element grid is read in place with few tokens: what a row's last k-step covers behind the
+  // row's end is loaded as 0, whatever lies there.  Its rows straddle cache lines, so with more tokens a padded copy is as good or
+  // better: H = 1000 / 520, V = 50264, T = 64 203 (copies) against 141 us, T = 300 322 / 266, T = 2048 902 / 902, T = 4096 1815 / 1847;
+  // T = 777, H = 4088 / 1000, V = 151936 3.63 / 3.23 ms.  Copies of small heads share the row map's launch and cost nothing.
   auto copied = [&](int64_t K, int64_t H) { return K != H && (q.w_hv || q.T > 1536 || 2 * q.V * K <= (4ll << 20)); };
   q.prep_Wt = q.in_f32 || copied(q.K_t, q.H_t);
   q.prep_Ws = q.in_f32 || copied(q.K_s, q.H_s);

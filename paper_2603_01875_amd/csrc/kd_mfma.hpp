@@ -124,7 +124,8 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* p, uint32_t bytes) {
 // Epi:   void begin_item(const WorkItem&)            called before the first k-step of an item
 //        void end_item(const WorkItem&, Acc& acc0, Acc& acc1)
 //                                                    called after the last k-step of an item
-// ld*[p] are the same for every item of a launch (A's: from row to row, which may be less than the k-steps cover, where B is 0); the k-step counts may differ per item.
+// ld*[p] are the same for every item of a launch (A's: from row to row, which may be less than the k-steps cover: behind a row's end
+// loads give 0); the k-step counts may differ per item.
 //
 // Pipeline: NST LDS stages filled by direct global->LDS loads (16 bytes per lane, no
 // staging registers).  While k-step g is multiplied, the loads of k-step g+NST-1 are
@@ -245,13 +246,17 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
   bool more = true;
   WorkItem li = work.item(0);
   const char *l_pa, *l_pb;      // uniform: tile base + k offset, in bytes (A: of k-major rows; else ra and l_ka)
-  rsrc_t ra;                    // the tile's rows of A, behind which loads give 0 (rows may be shorter than their k-steps)
-  int l_ka = 0;                 // k offset in it (part of what is checked against its end)
+  rsrc_t ra;                    // the tile's rows of A, behind which loads give 0
+  int l_ka = 0, l_row = 0;      // k offset in it (part of what is checked against its end), bytes of a row
   int64_t l_step_a = ROWB;      // bytes of A from one k-step to the next (k-major: BK of its k-rows)
   uint32_t loff[LOADS];         // per lane: byte offset of its 16 bytes inside the k-slab
   const int km_row = tid / CPR, km_c = (tid % CPR) ^ (4 * (km_row & 3));
+  // The k-steps from l_k (l_ka) on.  Rows of A: up to the one that a row ends in, if it ends inside one, which is then gone to by
+  // itself: its chunks behind the row's end are not the row's (0 x infinity is not 0, so that B is 0 there is not enough).
+  constexpr uint32_t BEHIND = 0x80000000u;             // an offset whose load gives 0
   auto set_cursor = [&]() {
     const uint32_t la = (uint32_t)(l_phase ? lda1 : lda0), lb = (uint32_t)(l_phase ? ldb1 : ldb0);
+    if (!AKM) l_row = (int)la * ((P1F8 && l_phase) ? 1 : 2);
 #pragma unroll
     for (int j = 0; j < LOADS; ++j) {
       const bool isA = j < A_LOADS;
@@ -264,16 +269,17 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
       const int lim = isA ? li.a_rows : li.b_rows;
       r = r < lim ? r : lim - 1;
       const uint32_t es = (P1F8 && l_phase) ? 1 : 2;       // bytes per element
-      loff[j] = (uint32_t)r * (isA ? la : lb) * es + lchunk * 16;
+      loff[j] = (uint32_t)r * (isA ? la : lb) * es + (isA && lchunk * 16 >= l_row - l_ka ? BEHIND : lchunk * 16);
     }
     if (AKM) l_step_a = (int64_t)BK * 2 * la;
     l_pa = (const char*)uniform(l_phase ? li.A1 : li.A0);
     if constexpr (!AKM) {
-      ra = make_rsrc(l_pa, (uint32_t)li.a_rows * la * ((P1F8 && l_phase) ? 1 : 2));
-      l_ka = 0;
+      ra = make_rsrc(l_pa, (uint32_t)(li.a_rows * l_row));
+      l_nk = l_k + max((l_row - l_ka) / ROWB, 1);
+    } else {
+      l_nk = l_phase ? li.nk1 : li.nk0;
     }
-    l_pb = (const char*)uniform(l_phase ? li.B1 : li.B0);
-    l_nk = l_phase ? li.nk1 : li.nk0;
+    l_pb = (const char*)uniform(l_phase ? li.B1 : li.B0) + l_ka;
   };
   set_cursor();
 
@@ -292,16 +298,19 @@ __device__ __forceinline__ void tile_loop(const Work& work, Epi& epi,
     else l_ka += ROWB;
     l_pb += ROWB;
     if (++l_k == l_nk) {
-      l_k = 0;
-      if (NPHASE > 1 && l_phase == 0) {
-        l_phase = 1;
-      } else {
-        l_phase = 0;
-        ++l_item;
-        if (l_item < n_items) li = work.item(l_item);
-        else more = false;
+      const bool rest = !AKM && l_ka < l_row;
+      if (!rest) {
+        if (NPHASE > 1 && l_phase == 0) {
+          l_phase = 1;
+        } else {
+          l_phase = 0;
+          ++l_item;
+          if (l_item < n_items) li = work.item(l_item);
+          else more = false;
+        }
       }
       if (more) {
+        if (!rest) l_k = l_ka = 0;
         set_cursor();
       } else {
         // past the end: keep re-reading the last k-step (valid memory, data unused) so that

@@ -92,7 +92,7 @@ struct StripItem {
   const char *A0, *A1, *B0, *B1;
   int k0, k1;
   int a_rows;              // rows of A in the tile (1 .. BM); loads of the others give the last one's (A_ROWS: a row may be shorter
-                           // than its k-steps, which then run on into the next row, B being 0 there; behind the last row loads give 0)
+                           // than its k-steps; behind its end loads give 0)
   int out_rows;            // ... rounded up to 64: what is stored of it
   int m0, n0;              // tile origin
   int aux;                 // free for the work map
@@ -204,6 +204,7 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
   //   A_DZ               as in memory (1 KiB for 16 tokens x 32 columns), a token's four chunks permuted by two bits
   // so that the fragment reads of half a wave always fall into different banks.
   constexpr int REGIONS = C::BM / 128;
+  constexpr uint32_t BEHIND = 0x80000000u;           // an offset whose load gives 0
   int l_item = 0, l_ph = NPH == 2 ? 0 : 1, l_k = 0, l_nk = 0, l_a = 0, l_b = 0, l_bo = 0;
   int l_rows = 0, l_tail = 64;   // rows of the tile and k of its last k-step that exist
   const char* l_pa = nullptr;    // (only where A advances by whole k-rows)
@@ -226,17 +227,25 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
         voff[j] = __umul24(min(kr, kv - 1), l_lda) + (uint32_t)min(c, (l_rows >> 3) - 1) * 16;
       } else {
         const uint32_t row = min(lrow + 32 * j, l_rows - 1);
-        voff[j] = (AM == A_ROWS ? __umul24(row, l_lda) : row * l_lda) + lchunk * 16;       // (rows of 2 K bytes; of 2 V bytes)
+        // (rows of 2 K bytes; of 2 V bytes)
+        if constexpr (AM == A_ROWS) voff[j] = __umul24(row, l_lda) + (lchunk * 16 < (int)l_lda - l_a ? lchunk * 16 : BEHIND);
+        else voff[j] = row * l_lda + lchunk * 16;
       }
     }
   };
+  // The k-steps from l_k on.  A_ROWS: up to the one that a row ends in, if it ends inside one, which is then gone to by itself: its
+  // chunks behind the row's end are not the row's (0 x infinity is not 0, so that B is 0 there is not enough).
   auto set_cursor = [&](const StripItem& it) {
     const uint32_t bstride = l_ph ? it.ldb1 : it.ldb0;
     const int k = l_ph ? it.k1 : it.k0;
     l_lda = l_ph ? it.lda1 : it.lda0;
     l_rows = it.a_rows;
-    l_nk = (k + 63) >> 6;
-    l_tail = k - 64 * (l_nk - 1);
+    if constexpr (AM == A_ROWS) {
+      l_nk = l_k + max(((int)l_lda - l_a) >> 7, 1);
+    } else {
+      l_nk = (k + 63) >> 6;
+      l_tail = k - 64 * (l_nk - 1);
+    }
     if constexpr (TR) {
       l_pa = uniform(l_ph ? it.A1 : it.A0);
       ra = make_rsrc(l_pa, AM == A_DZ ? C::STAGE_BYTES : 64u * l_lda);
@@ -253,7 +262,6 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
       rb = make_rsrc((l_ph ? it.B1 : it.B0) + (int64_t)wave * bstride, bstride);
     }
     set_voff(AM == A_KMAJOR_DZ && l_nk == 1 ? l_tail : 64);
-    l_a = l_b = 0;
   };
   set_cursor(work.item(0));
   constexpr int B_SUB = B_BLOCKS ? 1024 : 4096;      // bytes of B from one sub-step to the next
@@ -266,11 +274,14 @@ __device__ __forceinline__ void strip_loop(const Work& work, Epi& epi, char* sme
     if constexpr (!TR) l_a += 128;
     l_b += 2 * B_SUB;
     if (__builtin_expect(++l_k == l_nk, 0)) {
-      const bool more = (NPH == 2 && l_ph == 0) || l_item + 1 < n_items;
+      const bool rest = AM == A_ROWS && l_a < (int)l_lda;
+      const bool more = rest || (NPH == 2 && l_ph == 0) || l_item + 1 < n_items;
       if (more) {
-        l_k = 0;
-        if (NPH == 2) l_ph ^= 1;
-        if (NPH == 1 || l_ph == 0) ++l_item;
+        if (!rest) {
+          l_k = l_a = l_b = 0;
+          if (NPH == 2) l_ph ^= 1;
+          if (NPH == 1 || l_ph == 0) ++l_item;
+        }
         set_cursor(work.item(l_item));
       } else {           // past the end: the last k-step again (valid memory, data unused)
         --l_k;

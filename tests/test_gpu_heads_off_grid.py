@@ -1,4 +1,4 @@
-"""bf16 heads as [V, H] whose rows are off the 64-element grid: large ones are read in place, their last k-step running on past a
+"""bf16 heads as [V, H] whose rows are off the 64-element grid: large ones are read in place, their last k-step reaching past a
 row's end.  Both logit loops, hidden sizes 8 to 56 past the grid and below one k-step, several divergences, the fp8 teacher with such a
 student, two teachers of which one is on the grid, short last tiles.  Behind the heads lie NaNs.  Against the fp64 oracle with the
 tolerances of the other parity tests."""
