@@ -5,6 +5,7 @@ and gradients for; infinite student entries finite losses.  Both logit loops, fe
 below one k-step, rows at the edges of tiles.  Against the fp64 oracle with the tolerances of the other parity tests."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import kd_oracle as O
 from paper_2603_01875_amd import inputs as I
@@ -48,3 +49,19 @@ def test_infinite_student_entries(T, H_t, H_s, V, loop):
     assert np.isfinite(want).all()
     got = K.kd_loss_fwd(*[G.to_device(data[k], I.BF16) for k in ("h_t", "W_t", "h_s", "W_s")], None, kind=I.TVD)["per_token_loss"]
     np.testing.assert_allclose(G.to_host(got), want, rtol=2e-3, atol=5e-7)
+
+
+@pytest.mark.parametrize("T, H_t, H_s, V, hv", [(20, 584, 1016, 6008, False), (300, 1000, 520, 5000, False), (300, 512, 256, 1024, True),
+                                                (600, 2824, 136, 16200, False), (600, 2816, 128, 16200, False), (600, 2816, 128, 16192, True)])
+def test_infinite_teacher_entries_beside_padding(T, H_t, H_s, V, hv):
+    """Masked tokens and the rest of the last token tile, which the copies of the hidden states fill up: their dL/dz is 0 there, too."""
+    cfg = I.scaled(I.workload("fkl_bf16"), batch=1, seq=T, H_t=H_t, H_s=H_s, V=V, kind=I.SKEW_RKL, beta=0.5, w_t_std=0.05, mask="bernoulli10")
+    data = _with_infinities(I.generate(cfg), "t", H_t, V)
+    with np.errstate(invalid="ignore"):
+        ref = G.run_oracle(cfg, data)
+    head = (lambda x: np.ascontiguousarray(x.T)) if hv else (lambda x: x)
+    d = [G.to_device(x, I.BF16) for x in (data["h_t"], head(data["W_t"]), data["h_s"], head(data["W_s"]))]
+    out = K.kd_loss_fwd_bwd(*d, torch.from_numpy(data["mask"]).cuda(), tau=cfg.tau, kind=cfg.kind, beta=0.5, w_layout=K.W_HV if hv else K.W_VH)
+    if hv:
+        out["grad_W_s"] = out["grad_W_s"].t()
+    G.check(out, ref, "beside padding")
