@@ -62,13 +62,15 @@ kd_status check_params(const kd_loss_params* p) {
 // Vocabulary chunk of the backward pass.  The [T_pad, V_c] bf16 staging buffer of dL/dz_s is written by the gradient
 // kernel and read back by both products; it should stay in the 256 MB last-level cache together with the operands, but every chunk also
 // costs the ends of three launches and re-reads and re-writes the fp32 sums of grad_h_s.
-//  - From 4096 tokens on 16384 columns, halved until the staging buffer is within 512 MiB (at least 1024).  Against 8192 columns, which
-//    keep it within the cache up to 12288 tokens: T = 6144, H = 1024 / 512, V = 128256, JSD 9.16 -> 8.46 ms; T = 8192, H = 2048 / 1024,
-//    V = 151936, JSD 22.4 -> 21.3, [H][V] heads 15.3 -> 14.5; T = 16384, H = 2048 / 512, RKL 26.2 -> 23.9, H = 4096 / 2048, V = 128256 50.1 ->
-//    49.9.  Out of the cache it no longer pays where the contraction is long, whose products hide a chunk's ends best: T = 8192, H = 8192 /
-//    2048, a tenth of the tokens masked 33.96 -> 34.39 ms (none masked 38.4 -> 36.9, where the rounds of workgroups come out better), nor past
-//    512 MiB (T = 32768, H = 5120 / 4096, JSD 262.6 -> 265.4).  (At 4096 tokens 24576 columns, 201 MB, measured 11.72 against 12.25 ms
-//    without a mask on an earlier state; tests/test_abi_host.py holds that size to 16384 columns.)
+//  - From 4096 tokens on 16384 columns, halved until the staging buffer is within 512 MiB (at least 1024).  Against 8192 columns, means of
+//    steps with all tokens and with a tenth masked, 59 sizes, FKL and JSD, T = 4190 .. 16384, V = 54032 .. 151936: 0.966 of the time where
+//    the buffer stays in the cache (up to 6656 tokens; 12 sizes, 0.90 .. 0.99), beyond 0.971 with up to 6144 elements contracted for a
+//    logit (13 sizes, 0.93 .. 1.00) and 0.991 with more (34 sizes, 0.966 .. 1.013), whose products hide a chunk's ends best.  What a size
+//    gains or loses follows the rounds of workgroups: T = 8192, H = 8192 / 2048, V = 128256 38.4 -> 37.0 ms with all tokens, 34.7 -> 34.9
+//    with a tenth masked, two teachers, H = 4096 + 2048 / 1024, V = 151936 36.3 -> 34.7; fp32, T = 16384, H = 2048 / 1024, V = 32000
+//    15.9 -> 16.0.  (The rounds as priced below would take 16384 at every one of the 59.)  12288 columns: 0.970, 0.991, 0.993.
+//    Past 512 MiB wider chunks lose (T = 32768, H = 5120 / 4096, JSD 262.6 -> 265.4).  (At 4096 tokens 24576 columns, 201 MB, measured 11.72
+//    against 12.25 ms without a mask on an earlier state; tests/test_abi_host.py holds that size to 16384 columns.)
 //  - Below, up to 208 MiB (201 MB still stays in the cache), and the width decides how full the last rounds of
 //    workgroups are: the candidates (multiples of the tile heights) are priced by the rounds of the gradient kernel,
 //    with all tokens and with an eighth of them masked, and of the grad_W_s product.  Measured steps: T = 3584 10.60 ms
@@ -79,7 +81,6 @@ int64_t choose_chunk(const Problem& q, int64_t v_all, int64_t logit_k) {
   if (q.T_pad >= 4096) {
     int64_t vc = 16384;
     while (vc > 1024 && (int64_t)q.T_pad * vc * 2 > (512ll << 20)) vc >>= 1;
-    if (vc == 16384 && (int64_t)q.T_pad * vc * 2 > (208ll << 20) && logit_k > 6144) vc = 8192;
     return vc;
   }
   const int64_t step = 1536, most = (208ll << 20) / (2 * q.T_pad);      // a multiple of 192, 256 and 128
