@@ -76,7 +76,7 @@ struct GradWArgs {
   int n_vt, n_ht;          // tiles
   uint32_t lda, ldb;       // as in StripItem
   int b_blocks;
-  int stream;              // few tokens: the output is stored past the last-level cache
+  int stream;              // few tokens, bf16 heads [V][H], written: the output is stored past the last-level cache
   const int* meta;
 };
 
@@ -247,8 +247,8 @@ KD_STRIP_KERNEL void grad_w_kernel(const GradWArgs a) {
 // and 32 columns of dz at a time go through the LDS, three such steps ahead; two workgroups per CU, so that the stores of one are
 // in flight under the other's products: 110 us; T = 100, H_s = 256, V = 8000 12 -> 6.  (Reading and writing take 75 at the rate of a large
 // copy; the stores alone measure 49, the loads alone 27, loads and products 62: the products' LDS reads, by all four waves, are next.)
-// Panels of 64 tokens without a valid one are left out.  Where the output is large it is stored past the last-level cache: grad_h_s behind
-// it 108 -> 92 us.
+// Panels of 64 tokens without a valid one are left out.  A large output in bf16, [V][H], is stored past the last-level cache: grad_h_s
+// behind it 108 -> 92 us.  (The other forms are not: one that is added to has just been read, fp32 and [H][V] have not been tried.)
 struct GradWFew {
   static constexpr int AHEAD = 3, NST = AHEAD + 1, PANELS = 4;
   static constexpr int STAGE_BYTES = PANELS * 4096, SMEM_BYTES = NST * STAGE_BYTES;
@@ -509,7 +509,8 @@ hipError_t launch_grad_W(const Problem& p, int v0, int width, hipStream_t st) {
     a.n_ht = (p.H_s + 255) / 256;
     a.n_vt = GradWFew::SLOTS / a.n_ht < 1 ? 1 : GradWFew::SLOTS / a.n_ht;
     if (a.n_vt > steps) a.n_vt = steps;
-    a.stream = (int64_t)width * p.H_s > (64 << 20);       // (128 MiB: half of the cache, which keeps dz and W_s for grad_h_s instead)
+    // (more than 128 MiB: half of the cache, which keeps dz and W_s for grad_h_s instead)
+    a.stream = !p.w_hv && !p.grad_f32 && !p.accumulate_grad_W && (int64_t)width * p.H_s * 2 > (128 << 20);
 #define KD_GF(HV, F32, ADD) launch_big<grad_w_few_kernel<HV, F32, ADD>>(a.n_vt * a.n_ht, 256, GradWFew::SMEM_BYTES, st, &a)
     if (p.accumulate_grad_W)
       return p.w_hv ? (p.grad_f32 ? KD_GF(true, true, true) : KD_GF(true, false, true))

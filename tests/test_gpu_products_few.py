@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
     (128, 128, 256, 1000, False, K.BF16, 0), (192, 192, 264, 520, False, K.F32, 256), (256, 256, 1032, 16392, False, K.BF16, 0),
     (256, 256, 2056, 4104, False, K.F32, 0), (256, 10, 1032, 16392, False, K.BF16, 8192), (200, 129, 520, 6152, False, K.F32, 2048),
     (64, 64, 64, 64, True, K.BF16, 0), (129, 129, 192, 1088, True, K.F32, 512), (256, 256, 1088, 16384, True, K.BF16, 0),
-    (250, 65, 320, 12352, True, K.F32, 0), (31, 31, 72, 328, True, K.BF16, 256)])
+    (250, 65, 320, 12352, True, K.F32, 0), (31, 31, 72, 328, True, K.BF16, 256),
+    # more than 128 MiB of bf16: stored past the last-level cache
+    (64, 64, 1024, 66000, False, K.BF16, 0), (200, 129, 1032, 65544, False, K.BF16, 0)])
 def test_grad_W_of_few_tokens(T, kept, H_s, V, hv, grad, chunk):
     cfg = I.scaled(I.workload("fkl_bf16"), batch=1, seq=T, H_t=128, H_s=H_s, V=V, w_t_std=0.1, mask="ones")
     data = I.generate(cfg)
