@@ -129,18 +129,19 @@ struct CallPlan {
 //    the skewed KLs) or 300 (AKL).
 //  - The gradient kernel walks whole tiles in rounds of n_cu workgroups; the passes before it even out over ranges of the
 //    vocabulary, down to a tile each.
-// The constants are from 1178 sizes on an earlier state of the strip loop, which has since become 6 % faster.  Steps of the present
-// state (eight waves against strips): T = 512, H_t = 8192, H_s = 512, V = 512 183 against 230 us; T = 4096, H = 256 / 128,
-// V = 151936 2.03 against 2.25 ms; T = 2048, H = 2048 / 1024, V = 4096 170 against 192 us and V = 100000 2.93 against 2.71 ms; T = 4096,
-// H = 4096 / 1024, V = 151936 12.5 against 11.8 ms.  Over 60 random sizes, T = 257 .. 16384, V = 256 .. 151936, every kind but AKL, 0.7 % is
-// lost against the faster loop of each, 6.5 % at most (one loop for all of them: 3.5 % and 3.8 %); over 24 with [H][V] heads
-// 0.3 %, 3.1 % at most.
+// The constants are from 1178 sizes on an earlier state of both loops.  Steps of the present state (eight waves against strips): T = 512,
+// H_t = 8192, H_s = 512, V = 512 183 against 230 us; T = 4096, H = 256 / 128, V = 151936 2.00 against 2.22 ms; T = 2048, H = 2048 / 1024,
+// V = 4096 168 against 200 us and V = 100000 2.91 against 2.71 ms; T = 4096, H = 4096 / 1024, V = 151936 12.6 against 11.8 ms.  Over 60
+// random sizes, T = 257 .. 16384, V = 256 .. 151936, every kind but AKL, 0.6 % is lost against the faster loop of each, 12 % at most (JSD,
+// T = 12361, H = 3648 / 832, V = 2304; one loop for all of them: 3.1 % and 4.5 %); over 24 with [H][V] heads 0.3 %, 2.6 % at most.
 // AKL's line lies too far to the eight-wave side: its 300 and its mean over seven passes are from when its search was four passes of
-// compares on both loops.  By bins (three passes then, two now) strips are ahead wherever V is large, down to H_t = 320: over 30 sizes the rule loses
-// 12 %, up to 33 % (T = 735, H = 2304 / 192, V = 151936 4.11 against 3.10 ms); strips for all of them would lose 1.2 %.
+// compares on both loops.  With two passes of bins strips are ahead at each of 30 sizes (T = 259 .. 11168, H_t from 320, V = 288 .. 151936),
+// and the rule loses 23 %, up to 48 % (T = 2182, H = 2112 / 320, V = 128256 9.35 against 6.33 ms).  It stands: the loops find the border
+// between head and tail on different grids, so that results change within AKL's tolerance with it, and tests/test_plan_host.py holds
+// two sizes to it.
 // One token tile: the heads stream through once, nothing is shared, and the smaller tiles spread better over the CUs
-// (T = 1, V = 151936, JSD 1.28 against 1.44 ms; 24 sizes: 10 % on average, strips never ahead by more than 2 %, at T = 256 1.10
-// against 1.08).
+// (T = 1, H = 4096 / 1024, V = 151936, JSD 1.09 against 1.37 ms; 24 sizes, T = 16 .. 256: 24 % on average, strips never ahead; at T = 256
+// FKL the same, 1.05 against 1.04).
 // `logit_k`: the contraction of one logit of all models, summed over the call's teachers.
 bool strips_ahead(const Problem& q, int n_teachers, int64_t logit_k) {
   if (q.n_tt < 2) return false;

@@ -17,7 +17,7 @@
 // accumulator stays in the register file it was given; the compiler's own choice copies them around inside the loop.
 // With the B ring and the fragments the 512 registers are full: what the statistics and the gradient kernels keep from tile to
 // tile lives in LDS (STATE_AT).  A spilled register costs more than its traffic: its reload waits for every load in flight.
-// (Left: 12 of RKL's and AKL's gradient kernels, 5 of the skewed FKL's row pass, up to 24 for [H][V] heads.)
+// (Left: 11 of RKL's and 15 of AKL's gradient kernel, 2 of the skewed FKL's row pass, up to 24 for [H][V] heads.)
 //
 // One wave per SIMD: whatever stands between two k-steps is idle matrix time.  The loads of a k-step go out one by one
 // between MFMAs, the cursor moves on in front of the last block, and the change to the next phase or tile is off the

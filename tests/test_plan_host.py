@@ -82,7 +82,8 @@ def test_few_tokens_need_few_rows(kw):
 
 
 # Which loop makes the logit tiles, at sizes where one of them measured at least 4 % ahead of the other.  (Three of them on an earlier
-# state: with AKL's search by bins the strip loop is 13 and 18 % ahead at its two sizes among EIGHT_WAVES, and 2 % at T = 256.)
+# state: the strip loop is 27 and 35 % ahead now at AKL's two sizes among EIGHT_WAVES, which only hold the line where it is, and 1 % at
+# T = 256.)
 EIGHT_WAVES = [   # T, H_t, H_s, V, kind
     (257, 2048, 1024, 512, 0), (512, 8192, 512, 512, 0), (4096, 8192, 512, 512, 0), (8192, 8192, 512, 256, 0),
     (1024, 2048, 1024, 4096, 0), (2048, 2048, 1024, 4096, 0), (4096, 2048, 1024, 2048, 0), (300, 4096, 1024, 32000, 0),
